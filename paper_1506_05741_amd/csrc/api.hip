@@ -92,7 +92,8 @@ Layout make_layout(const diam_config& c, const diam_target& tg) {
   L.V = take(dP * 8);
   L.lp = take(2 * P * 8);
   L.zq = take(2 * P * 8);
-  L.lpp_part = take((size_t)nrb * P * 8);
+  // the Gaussian target may write four partials per row block
+  L.lpp_part = take((size_t)(tg.kind == DIAM_TGT_GAUSS ? 4 : 1) * nrb * P * 8);
   L.zq_part = take(2 * (size_t)nch * P * 8);
   L.pq_part = take(2 * (size_t)nch * P * 8);
   L.nacc = take(P * 4);
@@ -668,6 +669,8 @@ extern "C" int diam_step_batch(diam_ctx* c, int32_t n, const double* W, const do
   a.Z = c->Z;
   a.V = c->V;
   a.nrb = c->nrb;
+  const int sub = (c->logreg || c->h2) ? 1 : dk::tgt_gauss_sub(d, P);
+  a.quarters = sub == 4;
   a.nacc = n_accepted ? n_accepted : c->nacc;
   a.wacc = c->wacc;
   a.win = c->win;
@@ -710,7 +713,7 @@ extern "C" int diam_step_batch(diam_ctx* c, int32_t n, const double* W, const do
     else if (c->h2)
       HIPCHK(dk::tgt_gauss_h2(c->R2, c->V2, c->rsc, d, P, c->Yp, fuse_h2 ? nullptr : c->lpp_part, s, c->tgt.twist));
     else
-      HIPCHK(dk::tgt_gauss(prec, c->tgt.R, c->V, d, P, c->lpp_part, s, c->tgt.twist));
+      HIPCHK(dk::tgt_gauss(prec, c->tgt.R, c->V, d, P, c->lpp_part, s, c->tgt.twist, sub));
     prof_end(c, ps);
     a.do_accept = 1;
     a.xi_cur = at(c->Xi, (long)t * dP, eb);

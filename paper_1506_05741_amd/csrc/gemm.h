@@ -981,4 +981,19 @@ DEV void h2_gemm(W32Frag<BM, BN, WGM, WGN>& f, const u16* __restrict__ A, long d
   }
 }
 
+// ---------------------------------------------------------------------------
+// Slices of 128 bytes of k per row in LDS: 16-byte chunk c of a row's eight at
+// position c ^ tswz(r), which puts the 16 rows of a fragment read on distinct
+// banks.
+// ---------------------------------------------------------------------------
+template <typename T> constexpr int tbk() { return 128 / (int)sizeof(T); }
+
+DEV int tswz(int r) { return (r >> 1) & 7; }
+// LDS index of element (r, k) of a slice
+template <typename T>
+DEV int t_index_kc(int r, int k) {
+  constexpr int VEC = 16 / (int)sizeof(T);
+  return r * tbk<T>() + (((k / VEC) ^ tswz(r)) * VEC) + k % VEC;
+}
+
 }  // namespace gemm

@@ -23,8 +23,15 @@ inline int step_chunks(int d) { return (d + STEP_RCH - 1) / STEP_RCH; }
 // Gaussian: part[p][rb] = -1/2 sum over rows of block rb of (R (x_p - mu))_i^2.
 // twist (optional, d FP64): the twisted Gaussians (Section 3.1): row 2k+1's
 // y gains twist[2k+1] * y_{2k}^2 before it is squared.
+// sub: partials per 64-row block, 1, or 4 (tgt_quarters(d) per chain, quarter
+// 2 h + g of a block holding its rows 32 h + {8 g .. 8 g + 7, 16 + 8 g .. 16 +
+// 8 g + 7}) where tgt_gauss_sub says so: few tiles then take a kernel that
+// spreads the contraction over the whole chip.  (q0 + q1) + (q2 + q3) is the
+// block's partial bit for bit in FP32.
+inline __host__ __device__ int tgt_quarters(int d) { return 2 * ((d + 31) / 32); }
+int tgt_gauss_sub(int d, int P);
 hipError_t tgt_gauss(Prec prec, const void* R, const void* V, int d, int P, double* part, hipStream_t s,
-                     const double* twist = nullptr);
+                     const double* twist = nullptr, int sub = 1);
 // Mixed form, Gaussian: the same partials from two-part half splits of
 // scaled R and V (FP32-equivalent products); needs tgt_h2_ok(d, P) and Yp
 // scratch of tgt_h2_scratch_bytes.  h2_scales computes the coordinate scales
@@ -129,6 +136,7 @@ struct StepArgs {
   const void* w_cur; const void* wlo_cur; // d x P
   const double* lpp_part;                 // P x nrb (chain-major)
   int nrb;
+  int quarters;                           // lpp_part holds four quarters per row block (P x tgt_quarters(d))
   const double* zq_part_cur;              // P x nch (chain-major)
   const double* lp_cur; const double* zq_cur;
   double* lp_nxt; double* zq_nxt;

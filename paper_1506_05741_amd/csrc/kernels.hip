@@ -70,6 +70,164 @@ __global__ __launch_bounds__(512) void k_tgt_gauss(const T* __restrict__ R, cons
   tgt_gauss_tile<T, BK, 64, 64, 2>(R, V, d, P, blockIdx.x, blockIdx.y, part, gridDim.x, twist);
 }
 
+// The same contraction where 64 x 64 tiles would leave most of the chip idle
+// (16 tiles at d = 1024, P = 64): one workgroup per 16 rows x 16 chains, K
+// split over its wavefronts, each with its own accumulator.  A unit of K is
+// 128 bytes per row: a wavefront loads it with eight lanes per row (fragments
+// straight from global memory would meet 16 rows per quarter-wavefront, four
+// times slower), turns it round in an LDS block of its own, so that the K loop
+// has no barrier, and multiplies while the next units are in flight.  FP32
+// keeps the two interleaved chains of 32-deep slices of the tile kernel (its
+// two k-groups) and the order of k inside them, so every product sum is
+// bitwise the tile kernel's; FP64 takes eight chains.  The 16 rows are 8 + 8
+// rows 16 apart, the rows whose squares the tile kernel adds up in one lane:
+// its row-block sum splits into such quarters exactly.  Loads are
+// bounds-checked buffer loads: rows, chains and units outside return zero, and
+// rows need no alignment.  The chain tiles of the same rows run on one XCD,
+// which keeps its part of R (1 MB of 8 at d = 1024 in FP64) in its L2 from
+// step to step.  d = 1024, P = 64: FP64 40.3 to 7.6 us, FP32 22.8 to 8.7 us;
+// P = 256: 39.6 to 18.6 and 22.8 to 12.3 us.
+template <typename T> struct TS {
+  static constexpr int KW = sizeof(T) == 8 ? 8 : 2;  // chains of K, one wavefront each
+  static constexpr int D = sizeof(T) == 8 ? 2 : 4;   // units in flight beside the one multiplied
+};
+template <typename T>
+struct TSUnit {
+  u32x4_t a[2], b[2];
+};
+
+template <typename T>
+__global__ __launch_bounds__(64 * TS<T>::KW) void k_tgt_split(const T* __restrict__ R, const T* __restrict__ V, int d,
+                                                              int P, double* __restrict__ part, int nh, int nct,
+                                                              const double* __restrict__ twist) {
+  constexpr int KW = TS<T>::KW, D = TS<T>::D, UK = tbk<T>(), VEC = 16 / (int)sizeof(T);
+  __shared__ __attribute__((aligned(16))) T stage[KW][2][16 * UK];
+  __shared__ T ys[KW][16][17];
+  const int xcd = blockIdx.x & 7, kb = blockIdx.x >> 3;
+  const int hb = (kb / nct) * 8 + xcd, ct = kb % nct;
+  if (hb >= nh) return;  // uniform per workgroup, before any barrier
+  const int lane = threadIdx.x & 63, g = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lr = lane & 15, lk = lane >> 4;
+  const int i0 = (hb >> 1) * 32 + (hb & 1) * 8, j0 = ct * 16;
+  const int mc = min(16, P - j0);
+  const T* A = R + (long)i0 * d;
+  const T* B = V + (long)j0 * d;
+  const __amdgpu_buffer_rsrc_t ra =
+      __builtin_amdgcn_make_buffer_rsrc((void*)A, 0, (int)(max(0, min(24, d - i0)) * (long)d * sizeof(T)), 0x00027000);
+  const __amdgpu_buffer_rsrc_t rb =
+      __builtin_amdgcn_make_buffer_rsrc((void*)B, 0, (int)((long)mc * d * sizeof(T)), 0x00027000);
+  // this lane's part of a unit: two 16-byte chunks of each operand (8 rows x
+  // 128 bytes per load), and where they go in the wavefront's LDS block
+  uint32_t oa[2], ob[2];
+  int sw[2];
+  const int ch = lane & 7;
+#pragma unroll
+  for (int v = 0; v < 2; ++v) {
+    const int t = v * 8 + (lane >> 3);
+    oa[v] = (uint32_t)((((t & 7) + 2 * (t & 8)) * (long)d + ch * VEC) * (long)sizeof(T));
+    ob[v] = (uint32_t)((t * (long)d + ch * VEC) * (long)sizeof(T));
+    sw[v] = t * UK + ((ch ^ tswz(t)) * VEC);
+  }
+  T* sa = stage[g][0];
+  T* sb = stage[g][1];
+  const int nfull = d / UK;
+  // whole units of this wavefront; past them loads lie outside and give zeros
+  const int cnt = nfull > g ? (nfull - g + KW - 1) / KW : 0;
+  auto load = [&](TSUnit<T>& u, int n) {
+    const uint32_t k = n < cnt ? (uint32_t)((g + KW * n) * UK * (int)sizeof(T)) : 0x80000000u;
+#pragma unroll
+    for (int v = 0; v < 2; ++v) {
+      u.a[v] = __builtin_amdgcn_raw_buffer_load_b128(ra, oa[v] + k, 0, 0);
+      u.b[v] = __builtin_amdgcn_raw_buffer_load_b128(rb, ob[v] + k, 0, 0);
+    }
+  };
+  typename EAcc<T>::V c = {T(0), T(0), T(0), T(0)};
+  // LDS instructions of a wavefront run in order, so its block needs no wait
+  // between the reads of one unit and the writes of the next
+  auto mma = [&](const TSUnit<T>& u) {
+#pragma unroll
+    for (int v = 0; v < 2; ++v) {
+      *(u32x4_t*)(sa + sw[v]) = u.a[v];
+      *(u32x4_t*)(sb + sw[v]) = u.b[v];
+    }
+    asm volatile("" ::: "memory");
+    if (sizeof(T) == 8) {
+      // a lane's two chunks of consecutive k feed four products
+#pragma unroll
+      for (int v = 0; v < 2; ++v) {
+        const int p = lr * UK + (((lk + 4 * v) ^ tswz(lr)) * VEC);
+        T av[VEC], bv[VEC];
+        *(u32x4_t*)av = *(const u32x4_t*)(sa + p);
+        *(u32x4_t*)bv = *(const u32x4_t*)(sb + p);
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) c = mfma_e<T>(av[e], bv[e], c);
+      }
+    } else {
+      T av[UK / 4], bv[UK / 4];
+#pragma unroll
+      for (int q = 0; q < UK / 4; ++q) {
+        const int p = t_index_kc<T>(lr, 4 * q + lk);
+        av[q] = sa[p];
+        bv[q] = sb[p];
+      }
+#pragma unroll
+      for (int q = 0; q < UK / 4; ++q) c = mfma_e<T>(av[q], bv[q], c);
+    }
+    asm volatile("" ::: "memory");
+  };
+  const bool has_tail = d % UK != 0 && nfull % KW == g;
+  TSUnit<T> tail;
+  if (has_tail) {
+#pragma unroll
+    for (int v = 0; v < 2; ++v) {
+      const int t = v * 8 + (lane >> 3), ar = (t & 7) + 2 * (t & 8), k0 = nfull * UK + ch * VEC;
+      T ta[VEC], tb[VEC];
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) {
+        ta[e] = (i0 + ar < d && k0 + e < d) ? A[(long)ar * d + k0 + e] : T(0);
+        tb[e] = (t < mc && k0 + e < d) ? B[(long)t * d + k0 + e] : T(0);
+      }
+      tail.a[v] = *(const u32x4_t*)ta;
+      tail.b[v] = *(const u32x4_t*)tb;
+    }
+  }
+  TSUnit<T> st[D];
+#pragma unroll
+  for (int x = 0; x < D; ++x) load(st[x], x);
+  for (int n = 0; n < cnt; n += D) {
+#pragma unroll
+    for (int x = 0; x < D; ++x) {
+      if (n + x < cnt) mma(st[x]);
+      load(st[x], n + x + D);
+    }
+  }
+  if (has_tail) mma(tail);
+#pragma unroll
+  for (int r = 0; r < 4; ++r) ys[g][sizeof(T) == 8 ? 4 * r + lk : 4 * lk + r][lr] = c[r];
+  __syncthreads();
+  if (g != 0) return;
+  // lane (lk, lr): rows 8 (hb % 2) + 4 (lk % 2) + r of both 16-row blocks of
+  // chain lr, in the tile kernel's order; a twisted row's partner is its own
+  double s = 0.0;
+#pragma unroll
+  for (int mm = 0; mm < 2; ++mm) {
+    double prev = 0.0;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int t = mm * 8 + 4 * (lk & 1) + r, i = i0 + (t & 7) + 2 * (t & 8);
+      T y0 = ys[0][t][lr];
+#pragma unroll
+      for (int q = 1; q < KW; ++q) y0 += ys[q][t][lr];
+      double y = (double)y0;
+      if (twist && (r & 1) && i < d) y = __fma_rn(twist[i], prev * prev, y);
+      prev = (double)y0;
+      s = __fma_rn(y, y, s);
+    }
+  }
+  s += lane_xor_f64<16>(s);
+  if (lane < mc) part[(long)(j0 + lane) * nh + hb] = -0.5 * s;
+}
+
 // ---- two-part half target (mixed form): Y = R V with both operands split
 // into two IEEE half parts (products with the accuracy of FP32, see h2_gemm).
 // Half precision needs operands in its range, so both are scaled by powers of
@@ -301,8 +459,24 @@ hipError_t tgt_gauss_h2(const uint16_t* R2, const uint16_t* V2, const double* rs
   return hipGetLastError();
 }
 
+// At most half as many 64 x 64 tiles as CUs: the tile kernel then takes its
+// time for one tile whatever their number (77 us in FP64 and 43 us in FP32 at
+// d = 2048), the split kernel about 0.5 and 0.33 us per tile there, so it
+// stays ahead up to about 130 (FP32) or 150 (FP64) tiles.
+int tgt_gauss_sub(int d, int P) { return (long)cdiv(d, TGT_BM) * cdiv(P, 64) <= 128 ? 4 : 1; }
+
 hipError_t tgt_gauss(Prec prec, const void* R, const void* V, int d, int P, double* part, hipStream_t s,
-                     const double* twist) {
+                     const double* twist, int sub) {
+  if (sub == 4) {
+    const int nh = tgt_quarters(d), nct = cdiv(P, 16), groups = (nh + 7) / 8;
+    if (prec == P64)
+      hipLaunchKernelGGL((k_tgt_split<double>), dim3(groups * 8 * nct), dim3(64 * TS<double>::KW), 0, s,
+                         (const double*)R, (const double*)V, d, P, part, nh, nct, twist);
+    else
+      hipLaunchKernelGGL((k_tgt_split<float>), dim3(groups * 8 * nct), dim3(64 * TS<float>::KW), 0, s,
+                         (const float*)R, (const float*)V, d, P, part, nh, nct, twist);
+    return hipGetLastError();
+  }
   dim3 grid(cdiv(d, TGT_BM), cdiv(P, 64));
   if (prec == P64)
     hipLaunchKernelGGL((k_tgt_gauss<double, 16>), grid, dim3(512), 0, s, (const double*)R, (const double*)V, d, P, part,
@@ -2142,6 +2316,17 @@ hipError_t moment_error(const double* S, const double* m, const double* Sigma, c
 }
 
 
+// Target partials of chain col, and row block q's term (the sum of its
+// quarters where the target kernel wrote those).
+DEV const double* chain_parts(const StepArgs& a, int col) {
+  return a.lpp_part + (long)col * (a.quarters ? tgt_quarters(a.d) : a.nrb);
+}
+DEV double row_block_part(const StepArgs& a, const double* parts, int q) {
+  if (!a.quarters) return parts[q];
+  const double* f = parts + 4 * q;
+  return (f[0] + f[1]) + (64 * q + 32 < a.d ? f[2] + f[3] : 0.0);
+}
+
 // Decision of chain p by one workgroup of 256 threads: the target partials
 // (thousands of row blocks for the logistic target) are summed by all
 // threads, then MH (or the second stage of delayed acceptance) decides.
@@ -2152,7 +2337,7 @@ DEV void decide_block(const StepArgs& a, int nch, int p) {
   const int col = a.da ? a.slot[p] : p;
   double s = 0.0;
   if (live)
-    for (int q = t; q < a.nrb; q += 256) s += a.lpp_part[(long)col * a.nrb + q];
+    for (int q = t; q < a.nrb; q += 256) s += row_block_part(a, chain_parts(a, col), q);
   s = block_sum_f64(s, red);
   if (a.prior_w > 0.0) {
     double pq = 0.0;
@@ -2220,7 +2405,7 @@ DEV DecIn decide_inputs(const StepArgs& a, int nch, int p) {
 
 DEV bool decide_wave(const StepArgs& a, int nch, int p, bool write, const double* parts, const DecIn& in) {
   const int lane = threadIdx.x & 63;
-  double s = lane < a.nrb ? 0.0 + parts[lane] : 0.0;
+  double s = lane < a.nrb ? 0.0 + row_block_part(a, parts, lane) : 0.0;
   s = wave_sum_f64(s);
   if (a.prior_w > 0.0) {
     const double pq = wave_sum_f64(in.pq);
@@ -2448,7 +2633,7 @@ DEV void step_update2(const StepArgs& a, int cb, int nch, int pq) {
   UpdRegs<PR, CPW> g;
   upd_load<PR, CPW>(a, p, cb, nch, g);
   const bool acc =
-      a.do_accept && (a.fuse_dec ? decide_wave(a, nch, p, cb == 0, a.lpp_part + (long)p * a.nrb) : a.acc_out[p] != 0);
+      a.do_accept && (a.fuse_dec ? decide_wave(a, nch, p, cb == 0, chain_parts(a, p)) : a.acc_out[p] != 0);
   upd_finish<PR, CPW>(a, p, cb, nch, acc, g);
 }
 
@@ -2904,7 +3089,7 @@ __global__ __launch_bounds__(PERSIST_THREADS) void gk_persist(const BProb* __res
       const int w = threadIdx.x >> 6;
       if (kind == 1) {
         for (int p = w; p < st.P; p += PERSIST_THREADS / 64)
-          decide_wave(a, b.nch, p, true, a.lpp_part + (long)p * a.nrb);
+          decide_wave(a, b.nch, p, true, chain_parts(a, p));
       } else {
         // eight waves: chains 8k .. 8k + 7 per pass (the bodies take chain 4 pq + wave)
         for (int pq = 0; pq * 4 < st.P; pq += PERSIST_THREADS / 256) {
