@@ -102,9 +102,12 @@ Tiles build_tiles(const std::vector<int>& dims, int P, int n) {
   T.step = T.add(v);
   v.clear();
   const long ncols = (long)P * n;
+  // eight column blocks at a time, one per XCD (tiles are dealt round-robin),
+  // each with its row blocks in turn, the longest K range first
   for (int g = 0; g < G; ++g)
-    for (int bx = 0; bx < cdivh(dims[g], 64); ++bx)
-      for (int by = 0; by < cdivh(ncols, 64); ++by) v.push_back({g, bx, by});
+    for (int by = 0; by < cdivh(ncols, 64); by += 8)
+      for (int bx = cdivh(dims[g], 64) - 1; bx >= 0; --bx)
+        for (int x = by; x < std::min(by + 8, cdivh(ncols, 64)); ++x) v.push_back({g, bx, x});
   T.trigemm = T.add(v);
   v.clear();
   for (int g = 0; g < G; ++g) {
@@ -212,7 +215,7 @@ BLay make_blay(const std::vector<int>& dims, int P, int n, long ntiles, long npi
   L.pstep = take(sizeof(int) * G);
   L.pctl = take(sizeof(int) * (G + 1));  // queue position, then the G counters
   for (int g = 0; g < G; ++g) {
-    const size_t d = dims[g], dP = d * P, dd = d * d, win = dP * n;
+    const size_t d = dims[g], dP = d * P, dd = d * d, win = (size_t)pad4(dims[g]) * P * n;
     const int nch = dk::step_chunks(dims[g]);
     PLay q;
     q.X = take(dP * 8);

@@ -996,4 +996,220 @@ DEV int t_index_kc(int r, int k) {
   return r * tbk<T>() + (((k / VEC) ^ tswz(r)) * VEC) + k % VEC;
 }
 
+// ---------------------------------------------------------------------------
+// FP64 / FP32 engine with direct-to-LDS copies: the element engine's product
+// (same MFMA, same order of k, so the sums are bitwise the same) without
+// staging registers.  A slice is 128 bytes of k per row (16 FP64, 32 FP32
+// values); both operands' slices go from global memory straight into an LDS
+// ring of ST stages by 16-byte global_load_lds copies, ST - 1 slices in
+// flight.  One copy fills 1 KB of LDS in lane order:
+//   KC operand (k contiguous): 8 rows x 8 chunks of 16 bytes; chunk c of row r
+//     sits at position c ^ tswz(r), which puts the 16 rows of a fragment read
+//     on distinct banks;
+//   else (rows contiguous): a run of rows at one k (or at 2 or 4 neighbouring
+//     k for narrow tiles); the chunks of row k are rotated by XOR so that the
+//     two (FP64) or four (FP32) k a fragment read meets in one LDS cycle lie
+//     in different 128- (64-) byte groups.
+// Rows outside the operand repeat its last ones (the caller drops their
+// results); the last, partial slice of K is copied from clamped addresses and
+// cleared in LDS beyond kend, so it adds exact zeros.  Needs 16-byte aligned
+// operands: base pointers, leading dimensions and, for KC operands, kbeg and
+// kend multiples of 16 bytes, row counts of non-KC operands too (t_gemm_ok).
+// FP64 products share the vector pipe with other vector instructions, so the
+// loop keeps those out: copy offsets and LDS positions are formed once, the
+// bases advance in scalar registers (proposal at d = 4096: 19.3 ms with the
+// addresses formed in the loop, 18.1 ms so).  The ring must be a kernel's only
+// shared array: with others the compiler tags LDS accesses with alias scopes
+// and then waits for every copy in flight before each LDS read (215 against
+// 152 us for the FP64 target at d = 4096, P = 256).
+// ---------------------------------------------------------------------------
+template <typename T, int ROWS> DEV int tkswz(int k) {
+  return (sizeof(T) == 8 ? (k & 1) * 8 : (k & 3) * 4) & (ROWS * (int)sizeof(T) / 16 - 1);
+}
+
+// Byte offset, from the first element of a slice of the tile, of what this
+// lane copies for its block blk (1 KB): nrows rows of the operand from the
+// tile's first, kv valid k (the rest repeats the first).
+template <typename T, int ROWS, bool KC>
+DEV uint32_t t_copy_offset(long ld, int nrows, int kv, int blk) {
+  constexpr int VEC = 16 / (int)sizeof(T);
+  const int lane = threadIdx.x & 63;
+  long e;
+  if (KC) {
+    const int r = blk * 8 + (lane >> 3);
+    const int k = ((lane & 7) ^ tswz(r)) * VEC;
+    e = (long)min(r, nrows - 1) * ld + (k < kv ? k : 0);
+  } else {
+    constexpr int LPK = ROWS / VEC;  // lanes per k
+    const int k = blk * (64 / LPK) + lane / LPK;
+    const int c = (lane % LPK) ^ tkswz<T, ROWS>(k);
+    e = min(c * VEC, nrows - VEC) + (long)(k < kv ? k : 0) * ld;
+  }
+  return (uint32_t)(e * (long)sizeof(T));
+}
+
+// LDS index of element (r, k) of an operand slice
+template <typename T, int ROWS, bool KC>
+DEV int t_index(int r, int k) {
+  constexpr int VEC = 16 / (int)sizeof(T);
+  return KC ? t_index_kc<T>(r, k)
+            : k * ROWS + (((r / VEC) ^ tkswz<T, ROWS>(k)) * VEC) + r % VEC;
+}
+
+// Accumulators of one wave: the workgroup tile BM x BN is split over WGM x WGN
+// waves, each holding FM x FN blocks of 16 x 16.
+template <typename T, int BM, int BN, int WGM, int WGN>
+struct TFrag {
+  static constexpr int FM = BM / (16 * WGM), FN = BN / (16 * WGN);
+  typename EAcc<T>::V c[FM][FN];
+  DEVM void zero() {
+#pragma unroll
+    for (int a = 0; a < FM; ++a)
+#pragma unroll
+      for (int b = 0; b < FN; ++b)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) c[a][b][r] = T(0);
+  }
+};
+
+// Tile coordinates of accumulator (m, n, r) of this lane.
+template <typename T, int BM, int BN, int WGM, int WGN>
+DEV void t_coords(int m, int n, int r, int& ti, int& tj) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int wm = w % WGM, wn = w / WGM;
+  ti = wm * (BM / WGM) + m * 16 + ((sizeof(T) == 8) ? (4 * r + (lane >> 4)) : (4 * (lane >> 4) + r));
+  tj = wn * (BN / WGN) + n * 16 + (lane & 15);
+}
+
+template <typename T, int BM, int BN, int ST>
+constexpr int t_lds_elems() { return ST * (BM + BN) * tbk<T>(); }
+
+template <typename T, bool AKC, bool BKC>
+__host__ __device__ inline bool t_gemm_ok(const void* A, long lda, int M, const void* B, long ldb, int N, long k) {
+  constexpr int VEC = 16 / (int)sizeof(T);
+  return (uintptr_t)A % 16 == 0 && (uintptr_t)B % 16 == 0 && lda % VEC == 0 && ldb % VEC == 0 &&
+         (AKC || M % VEC == 0) && (BKC || N % VEC == 0) && (!(AKC || BKC) || k % VEC == 0) &&
+         (lda > ldb ? lda : ldb) * 128 * (long)sizeof(T) < (1L << 31);  // 32-bit offsets in a tile's slice
+}
+
+// PAIR (both operands KC, FP64): a lane reads two consecutive k at a time (one
+// 16-byte read instead of two of 8 bytes) and the products take k in that
+// order, for sums whose order is free.
+template <typename T, int BM, int BN, int WGM, int WGN, int ST, bool AKC, bool BKC, bool PAIR = false>
+DEV void t_gemm(TFrag<T, BM, BN, WGM, WGN>& f, const T* __restrict__ A, long lda, int M, const T* __restrict__ B,
+                long ldb, int N, int i0, int j0, int kbeg, int kend, T* lds) {
+  typedef TFrag<T, BM, BN, WGM, WGN> F;
+  constexpr int NW = WGM * WGN, TBK = tbk<T>(), Q = TBK / 4;
+  constexpr int SA = BM * TBK, SS = (BM + BN) * TBK;
+  constexpr int BLK_A = BM / 8, BLK_B = BN / 8, NBLK = BLK_A + BLK_B;
+  static_assert(NBLK % NW == 0, "copy blocks must divide among the waves");
+  constexpr int LPW = NBLK / NW;
+  const int nk = (kend - kbeg) / TBK;  // whole slices
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  // Everything a lane needs is computed before the loop, whose bases advance
+  // in scalar registers: FP64 products and other vector instructions do not
+  // overlap, so the loop has as few of the latter as it can.
+  const T* Ab = AKC ? A + (long)i0 * lda + kbeg : A + i0 + (long)kbeg * lda;
+  const T* Bb = BKC ? B + (long)j0 * ldb + kbeg : B + j0 + (long)kbeg * ldb;
+  const long sa = (AKC ? 1 : lda) * TBK, sb = (BKC ? 1 : ldb) * TBK;
+  uint32_t voff[LPW];
+  auto offsets = [&](int kv) {
+#pragma unroll
+    for (int q = 0; q < LPW; ++q) {
+      const int blk = w * LPW + q;
+      voff[q] = blk < BLK_A ? t_copy_offset<T, BM, AKC>(lda, M - i0, kv, blk)
+                            : t_copy_offset<T, BN, BKC>(ldb, N - j0, kv, blk - BLK_A);
+    }
+  };
+  auto issue = [&](int kt, int slot) {
+    const char* pa = (const char*)(Ab + kt * sa);
+    const char* pb = (const char*)(Bb + kt * sb);
+    T* st = lds + slot * SS;
+#pragma unroll
+    for (int q = 0; q < LPW; ++q) {
+      const int blk = w * LPW + q;
+      const char* src = blk < BLK_A ? pa : pb;
+      __builtin_amdgcn_global_load_lds((const void*)(src + voff[q]),
+                                       (lds_ptr_t)(st + blk * (1024 / (int)sizeof(T))), 16, 0, 0);
+    }
+  };
+  const int wm = w % WGM, wn = w / WGM;
+  const int lr = lane & 15, lk = lane >> 4;
+  // LDS positions of this lane's fragments: per k quad or pair (KC) or per block row
+  static_assert(!PAIR || (AKC && BKC && sizeof(T) == 8), "pairs of k: FP64, both operands k-contiguous");
+  int ra[AKC ? Q : F::FM], rb[BKC ? Q : F::FN];
+#pragma unroll
+  for (int x = 0; x < (AKC ? Q : F::FM); ++x)
+    ra[x] = PAIR ? t_index<T, BM, AKC>(wm * (BM / WGM) + lr, 2 * lk + 8 * (x & 1))
+          : AKC ? t_index<T, BM, AKC>(wm * (BM / WGM) + lr, 4 * x + lk)
+                : t_index<T, BM, AKC>(wm * (BM / WGM) + x * 16 + lr, lk);
+#pragma unroll
+  for (int x = 0; x < (BKC ? Q : F::FN); ++x)
+    rb[x] = SA + (PAIR ? t_index<T, BN, BKC>(wn * (BN / WGN) + lr, 2 * lk + 8 * (x & 1))
+                  : BKC ? t_index<T, BN, BKC>(wn * (BN / WGN) + lr, 4 * x + lk)
+                      : t_index<T, BN, BKC>(wn * (BN / WGN) + x * 16 + lr, lk));
+  auto compute = [&](const T* st) {
+    if (PAIR) {
+#pragma unroll
+      for (int v = 0; v < 2; ++v) {
+        T a[F::FM][2], b[F::FN][2];
+#pragma unroll
+        for (int m = 0; m < F::FM; ++m) *(u32x4_t*)a[m] = *(const u32x4_t*)(st + ra[v] + m * 16 * TBK);
+#pragma unroll
+        for (int n = 0; n < F::FN; ++n) *(u32x4_t*)b[n] = *(const u32x4_t*)(st + rb[v] + n * 16 * TBK);
+#pragma unroll
+        for (int e = 0; e < 2; ++e)
+#pragma unroll
+          for (int m = 0; m < F::FM; ++m)
+#pragma unroll
+            for (int n = 0; n < F::FN; ++n) f.c[m][n] = mfma_e<T>(a[m][e], b[n][e], f.c[m][n]);
+      }
+      return;
+    }
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      T a[F::FM], b[F::FN];
+#pragma unroll
+      for (int m = 0; m < F::FM; ++m)
+        a[m] = AKC ? st[ra[AKC ? q : 0] + m * 16 * TBK] : st[ra[AKC ? 0 : m] + 4 * q * BM];
+#pragma unroll
+      for (int n = 0; n < F::FN; ++n)
+        b[n] = BKC ? st[rb[BKC ? q : 0] + n * 16 * TBK] : st[rb[BKC ? 0 : n] + 4 * q * BN];
+#pragma unroll
+      for (int m = 0; m < F::FM; ++m)
+#pragma unroll
+        for (int n = 0; n < F::FN; ++n) f.c[m][n] = mfma_e<T>(a[m], b[n], f.c[m][n]);
+    }
+  };
+  offsets(TBK);
+  // the ring may still be read by other waves from a previous call
+  asm volatile("s_barrier" ::: "memory");
+  for (int p = 0; p < ST - 1 && p < nk; ++p) issue(p, p);
+  int slot = 0;
+  for (int kt = 0; kt < nk; ++kt) {
+    // stage kt has landed once at most the later stages' copies are pending
+    if (kt + ST - 2 < nk) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LPW * (ST - 2)) : "memory");
+    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    asm volatile("s_barrier" ::: "memory");
+    // the ring slot refilled here was last read before this barrier
+    if (kt + ST - 1 < nk) issue(kt + ST - 1, slot == 0 ? ST - 1 : slot - 1);
+    compute(lds + slot * SS);
+    slot = slot == ST - 1 ? 0 : slot + 1;
+  }
+  const int kv = (kend - kbeg) - nk * TBK;
+  if (kv > 0) {  // the last, partial slice, cleared beyond kend
+    asm volatile("s_barrier" ::: "memory");
+    offsets(kv);
+    issue(nk, 0);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    for (int e = threadIdx.x; e < BM * (TBK - kv); e += 64 * NW)
+      lds[t_index<T, BM, AKC>(e % BM, kv + e / BM)] = T(0);
+    for (int e = threadIdx.x; e < BN * (TBK - kv); e += 64 * NW)
+      lds[SA + t_index<T, BN, BKC>(e % BN, kv + e / BN)] = T(0);
+    __syncthreads();
+    compute(lds);
+  }
+}
+
 }  // namespace gemm

@@ -170,6 +170,7 @@ struct StepArgs {
   const float* vsc;                       // d: power-of-two coordinate scales for vh
   int ldv;                                // leading dimension of V (0: d)
   int ldw;                                // leading dimension of Xi and W (0: d)
+  int ldwin;                              // leading dimension of the window store (0: d)
   int32_t* wacc;                          // P: accepted proposals since the last update (optional)
 };
 hipError_t step(const StepArgs& a, hipStream_t s);
@@ -219,7 +220,7 @@ struct BProb {
   double *X, *Z, *xr, *lp, *zq;     // d x P, d x P, d, 2 x P, 2 x P
   double *zq_part, *lpp_part, *la;  // 2 x P x nch, P x nrb, n x P
   uint8_t* acc;                     // n x P
-  float *V, *W, *Xi, *win;          // d x P; W and Xi ld x P n; win d x P n
+  float *V, *W, *Xi, *win;          // d x P; W, Xi and win ld x P n
   double *S, *m, *L, *C, *Linv, *G, *h;
   float* Llow;                      // d x d
   int *nacc, *info;

@@ -520,6 +520,67 @@ __global__ __launch_bounds__(256) void k_trigemm_e(const T* __restrict__ L, cons
   trigemm_tile<T, BK>(L, W, Xi, d, ncols, c, blockIdx.x, blockIdx.y);
 }
 
+// The same on the direct-to-LDS engine, Xi^T = W^T L^T so that lanes run along
+// the rows of Xi (128-byte stores); bitwise the tile above.  BJ columns of W by
+// BI rows of L per workgroup.  64 x 64 tiles, three stages, three workgroups
+// per CU measured best at middle sizes (d = 1024, 12800 columns: FP64 565 to
+// 306 us, FP32 276 to 179 us).  With many tiles FP64 runs at the chip's power
+// limit (about 1.95 GHz), where 128 x 64 tiles, which move less per product,
+// are ahead: d = 4096, 65536 columns 29.9 to 17.9 ms against 19.5 ms with 64 x
+// 64 (61 TFLOP/s; a large library product reaches 68 there), but 335 against
+// 314 us at d = 1024.  32 x 32 tiles where 64 x 64 would not give every CU two.
+template <typename T, int BJ, int BI, int ST>
+DEV void trigemm_tile_t(const T* __restrict__ L, const T* __restrict__ W, T* __restrict__ Xi, int d, int ncols, double c,
+                        int bi, int bj) {
+  typedef TFrag<T, BJ, BI, 2, 2> F;
+  __shared__ __attribute__((aligned(1024))) T lds[t_lds_elems<T, BJ, BI, ST>()];
+  const int i0 = bi * BI, j0 = bj * BJ;
+  F f;
+  f.zero();
+  t_gemm<T, BJ, BI, 2, 2, ST, true, false>(f, W, d, ncols, L, d, d, j0, i0, 0, min(d, i0 + BI), lds);
+#pragma unroll
+  for (int m = 0; m < F::FM; ++m)
+#pragma unroll
+    for (int n = 0; n < F::FN; ++n)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        int ti, tj;
+        t_coords<T, BJ, BI, 2, 2>(m, n, r, tj, ti);
+        const int i = i0 + ti, j = j0 + tj;
+        if (i < d && j < ncols) Xi[i + (long)j * d] = (T)(c * (double)f.c[m][n][r]);
+      }
+}
+
+// Workgroup ids are dealt round-robin to the 8 XCDs: ids xcd + 8 k on one XCD
+// take the row blocks of one column block of W, longest K range first, so that
+// slice of W is fetched into the XCD's L2 once.
+template <typename T, int BJ, int BI, int ST>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_trigemm_t(
+    const T* __restrict__ L, const T* __restrict__ W, T* __restrict__ Xi, int d, int ncols, double c, int nj, int ni) {
+  const int xcd = blockIdx.x & 7, k = blockIdx.x >> 3;
+  const int jb = (k / ni) * 8 + xcd;
+  if (jb >= nj) return;
+  trigemm_tile_t<T, BJ, BI, ST>(L, W, Xi, d, ncols, c, ni - 1 - k % ni, jb);
+}
+
+template <typename T, int BJ, int BI, int ST>
+static void trigemm_t_launch(const void* L, const void* W, void* Xi, int d, long ncols, double c, hipStream_t s) {
+  const int nj = cdiv(ncols, BJ), ni = cdiv(d, BI);
+  hipLaunchKernelGGL((k_trigemm_t<T, BJ, BI, ST>), dim3((unsigned)((nj + 7) / 8 * 8) * ni), dim3(256), 0, s,
+                     (const T*)L, (const T*)W, (T*)Xi, d, (int)ncols, c, nj, ni);
+}
+
+// false: operands not aligned for the engine
+template <typename T>
+static bool trigemm_t(const void* L, const void* W, void* Xi, int d, long ncols, double c, hipStream_t s) {
+  if (!t_gemm_ok<T, true, false>(W, d, (int)ncols, L, d, d, d)) return false;
+  const long tiles = (long)cdiv(d, 64) * cdiv(ncols, 64);
+  if (tiles < 512) trigemm_t_launch<T, 32, 32, 6>(L, W, Xi, d, ncols, c, s);
+  else if (sizeof(T) == 8 && tiles >= 8192) trigemm_t_launch<T, 128, 64, 3>(L, W, Xi, d, ncols, c, s);
+  else trigemm_t_launch<T, 64, 64, 3>(L, W, Xi, d, ncols, c, s);
+  return true;
+}
+
 // bf16: Xi^T = W~^T L~^T with the roles swapped so that lanes run along the
 // rows i of Xi (coalesced stores): A operand = W (rows = columns j of W,
 // k-contiguous), B operand = L~ (rows i, k-contiguous, row-major factor).
@@ -602,6 +663,8 @@ constexpr int TW_BM = 256, TW_BN = 128, TW_WGM = 4, TW_WGN = 2;
 hipError_t trigemm(Prec prec, const void* L, const void* W, const void* Wlo, void* Xi, int d, long ncols, double c,
                    hipStream_t s) {
   if (ncols <= 0) return hipSuccess;
+  if (prec == P64 && trigemm_t<double>(L, W, Xi, d, ncols, c, s)) return hipGetLastError();
+  if (prec == P32 && trigemm_t<float>(L, W, Xi, d, ncols, c, s)) return hipGetLastError();
   dim3 grid(cdiv(d, 64), cdiv(ncols, 64));
   if (prec == P64)
     hipLaunchKernelGGL((k_trigemm_e<double, 16>), grid, dim3(256), 0, s, (const double*)L, (const double*)W,
@@ -694,6 +757,74 @@ template <typename T, int BK>
 __global__ __launch_bounds__(256) void k_syrk_e(const T* __restrict__ Xs, int d, int K, int kchunk,
                                                 double* __restrict__ Gpart) {
   syrk_tile<T, BK>(Xs, d, K, kchunk, blockIdx.x, blockIdx.y, Gpart);
+}
+
+// The same on the direct-to-LDS engine (leading dimension ld), bitwise; lanes
+// run along j, so the stores are 128-byte runs of a column of G.
+template <typename T, int BT, int ST>
+DEV void syrk_tile_t(const T* __restrict__ Xs, int ld, int d, int K, int kchunk, int t, int ksp,
+                     double* __restrict__ Gpart) {
+  typedef TFrag<T, BT, BT, 2, 2> F;
+  __shared__ __attribute__((aligned(1024))) T lds[t_lds_elems<T, BT, BT, ST>()];
+  int bi, bj;
+  tile_pair(t, bi, bj);
+  const int i0 = bi * BT, j0 = bj * BT;
+  const int kb = ksp * kchunk, ke = min(K, kb + kchunk);
+  double acc[F::FM][F::FN][4];
+#pragma unroll
+  for (int m = 0; m < F::FM; ++m)
+#pragma unroll
+    for (int n = 0; n < F::FN; ++n)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) acc[m][n][r] = 0.0;
+  const int span = (sizeof(T) == 8) ? kchunk : FOLD_K;
+  for (int k0 = kb; k0 < ke; k0 += span) {
+    F f;
+    f.zero();
+    t_gemm<T, BT, BT, 2, 2, ST, false, false>(f, Xs, ld, ld, Xs, ld, ld, i0, j0, k0, min(ke, k0 + span), lds);
+#pragma unroll
+    for (int m = 0; m < F::FM; ++m)
+#pragma unroll
+      for (int n = 0; n < F::FN; ++n)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[m][n][r] += (double)f.c[m][n][r];
+  }
+  double* G = Gpart + (long)ksp * d * d;
+#pragma unroll
+  for (int m = 0; m < F::FM; ++m)
+#pragma unroll
+    for (int n = 0; n < F::FN; ++n)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        int ti, tj;
+        t_coords<T, BT, BT, 2, 2>(m, n, r, ti, tj);
+        const int i = i0 + ti, j = j0 + tj;
+        if (i < d && j < d) G[j + (long)i * d] = acc[m][n][r];  // G(i,j) at (row j, col i): upper
+      }
+}
+
+template <typename T, int BT, int ST>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_syrk_t(const T* __restrict__ Xs, int d,
+                                                                                       int K, int kchunk,
+                                                                                       double* __restrict__ Gpart) {
+  syrk_tile_t<T, BT, ST>(Xs, d, d, K, kchunk, blockIdx.x, blockIdx.y, Gpart);
+}
+
+// 64-row tiles (FP64 d = 4096, K = 65536: 22.5 to 21.1 ms, 2080 tiles being
+// 8.1 per CU; d = 1024, K = 12800: 415 to 320 us, FP32 195 to 168 us), 32-row
+// ones where those would not give every CU one (d = 100, K = 3200: 6 tiles).
+// false: operands not aligned for the engine.
+template <typename T>
+static bool syrk_t(const void* Xs, int d, long K, int ns, int kchunk, double* Gpart, hipStream_t s) {
+  if (!t_gemm_ok<T, false, false>(Xs, d, d, Xs, d, d, K)) return false;
+  const int n64 = cdiv(d, 64), n32 = cdiv(d, 32);
+  if ((long)n64 * (n64 + 1) / 2 * ns < 256)
+    hipLaunchKernelGGL((k_syrk_t<T, 32, 6>), dim3(n32 * (n32 + 1) / 2, ns), dim3(256), 0, s, (const T*)Xs, d, (int)K,
+                       kchunk, Gpart);
+  else
+    hipLaunchKernelGGL((k_syrk_t<T, 64, 3>), dim3(n64 * (n64 + 1) / 2, ns), dim3(256), 0, s, (const T*)Xs, d, (int)K,
+                       kchunk, Gpart);
+  return true;
 }
 
 // bf16: Xt is the transposed window (d x K row-major, ld = K).  Tiles are
@@ -811,16 +942,39 @@ __global__ __launch_bounds__(512) void k_syrk_pl(const u16* __restrict__ Xt, int
 
 // Row sums over K of the window.  COLMAJOR: element (i, k) at X[i + k d];
 // otherwise at X[i K + k] (bf16 transposed window).
+// Each of the four threads of a row adds its values in turn, ROWSUM_U loads in
+// flight at a time (one by one the chain took 133 us at d = 100, K = 3200).
+constexpr int ROWSUM_U = 32;
+
 template <typename T, bool COLMAJOR>
-DEV void rowsum_block(const T* __restrict__ X, int d, int K, int kchunk, int bx, int by, double* __restrict__ hpart) {
+DEV void rowsum_block(const T* __restrict__ X, int d, long ld, int K, int kchunk, int bx, int by,
+                      double* __restrict__ hpart) {
   __shared__ double red[4][64];
   const int kb = by * kchunk, ke = min(K, kb + kchunk);
   if (COLMAJOR) {
     const int r = threadIdx.x & 63, q = threadIdx.x >> 6;
     const int i = bx * 64 + r;
     double s = 0.0;
-    if (i < d)
-      for (int k = kb + q; k < ke; k += 4) s += (double)X[i + (long)k * d];
+    if (i < d) {
+      const T* p = X + i;
+      int k = kb + q;
+      if (k + 4 * (ROWSUM_U - 1) < ke) {
+        T v[ROWSUM_U], w[ROWSUM_U];
+#pragma unroll
+        for (int u = 0; u < ROWSUM_U; ++u) v[u] = p[(long)(k + 4 * u) * ld];
+        for (k += 4 * ROWSUM_U; k + 4 * (ROWSUM_U - 1) < ke; k += 4 * ROWSUM_U) {
+#pragma unroll
+          for (int u = 0; u < ROWSUM_U; ++u) w[u] = p[(long)(k + 4 * u) * ld];
+#pragma unroll
+          for (int u = 0; u < ROWSUM_U; ++u) s += (double)v[u];
+#pragma unroll
+          for (int u = 0; u < ROWSUM_U; ++u) v[u] = w[u];
+        }
+#pragma unroll
+        for (int u = 0; u < ROWSUM_U; ++u) s += (double)v[u];
+      }
+      for (; k < ke; k += 4) s += (double)p[(long)k * ld];
+    }
     red[q][r] = s;
     __syncthreads();
     if (threadIdx.x < 64 && i < d)
@@ -840,7 +994,7 @@ DEV void rowsum_block(const T* __restrict__ X, int d, int K, int kchunk, int bx,
 template <typename T, bool COLMAJOR>
 __global__ __launch_bounds__(256) void k_rowsum(const T* __restrict__ X, int d, int K, int kchunk,
                                                 double* __restrict__ hpart) {
-  rowsum_block<T, COLMAJOR>(X, d, K, kchunk, blockIdx.x, blockIdx.y, hpart);
+  rowsum_block<T, COLMAJOR>(X, d, d, K, kchunk, blockIdx.x, blockIdx.y, hpart);
 }
 
 // col-major d x K bf16 -> row-major d x K (ld K)
@@ -1012,7 +1166,9 @@ hipError_t syrk_window(Prec prec, const void* Xw, void* Xt, int d, long K, doubl
   }
   const int nt = syrk_tiles(prec, d, K);
   dim3 grid(nt, ns);
-  if (syrk_pl(prec, d, K) && (uintptr_t)Xs % 16 == 0)
+  if ((prec == P64 && syrk_t<double>(Xs, d, K, ns, kchunk, Gpart, s)) ||
+      (prec == P32 && syrk_t<float>(Xs, d, K, ns, kchunk, Gpart, s))) {
+  } else if (syrk_pl(prec, d, K) && (uintptr_t)Xs % 16 == 0)
     hipLaunchKernelGGL(k_syrk_pl, grid, dim3(512), 0, s, (const u16*)Xs, d, (int)K, kchunk, Gpart);
   else if (prec == P64)
     hipLaunchKernelGGL((k_syrk_e<double, 16>), grid, dim3(256), 0, s, (const double*)Xs, d, (int)K, kchunk, Gpart);
@@ -2206,7 +2362,7 @@ DEV void step_body(const StepArgs& a, int ch, int nch, int pq) {
         a.X[e] = xv;
         a.Z[e] = zv;
       }
-      store_win<PR>(a.win, i + (a.win_col0 + p) * (long)d, xv - xr[q]);
+      store_win<PR>(a.win, i + (a.win_col0 + p) * (long)(a.ldwin ? a.ldwin : d), xv - xr[q]);
       for (int k = 0; k < a.nproj; ++k) pacc[k] = __fma_rn(a.proj[i + (long)k * d], xv, pacc[k]);
     }
     if (a.do_propose) {
@@ -2577,7 +2733,7 @@ DEV void upd_finish(const StepArgs& a, int p, int cb, int nch, bool acc, const U
           *(double2*)(a.X + e) = make_double2(xa, xb);
           *(double2*)(a.Z + e) = make_double2(za, zb);
         }
-        store_win2<PR>(a.win, i + (a.win_col0 + p) * (long)d, xa - ra, xb - rb);
+        store_win2<PR>(a.win, i + (a.win_col0 + p) * (long)(a.ldwin ? a.ldwin : d), xa - ra, xb - rb);
         for (int k = 0; k < a.nproj; ++k) {
           const double2 pv = *(const double2*)(a.proj + i + (long)k * d);
           pacc[k] = __fma_rn(pv.y, xb, __fma_rn(pv.x, xa, pacc[k]));
@@ -2979,6 +3135,7 @@ DEV StepArgs g_step_args(const BProb& b, const BStep& st, int g) {
   a.lpp_part = b.lpp_part;
   a.nacc = b.nacc;
   a.win = b.win;
+  a.ldwin = b.ld;
   a.err = st.err;
   if (st.t >= 0) {
     a.do_accept = 1;
@@ -3120,11 +3277,11 @@ int g_persist_blocks_per_cu() {
   return nb > 0 ? nb : 1;
 }
 
-__global__ __launch_bounds__(256) void gk_trigemm(const BProb* __restrict__ pr, const BTile* __restrict__ tl, int ncols,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void gk_trigemm(const BProb* __restrict__ pr, const BTile* __restrict__ tl, int ncols,
                                                   double c) {
   const BTile t = tl[blockIdx.x];
   const BProb& b = pr[t.g];
-  trigemm_tile<float, 32>(b.Lp, b.W, b.Xi, b.ld, ncols, c, t.a, t.b);
+  trigemm_tile_t<float, 64, 64, 3>(b.Lp, b.W, b.Xi, b.ld, ncols, c, t.a, t.b);
 }
 
 hipError_t g_trigemm(const BProb* pr, const BTile* tl, int ntiles, int ncols, double c, hipStream_t s) {
@@ -3133,15 +3290,15 @@ hipError_t g_trigemm(const BProb* pr, const BTile* tl, int ntiles, int ncols, do
 }
 
 // window scatter (one K split) and row sums
-__global__ __launch_bounds__(256) void gk_syrk(const BProb* __restrict__ pr, const BTile* __restrict__ tl, int K) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void gk_syrk(const BProb* __restrict__ pr, const BTile* __restrict__ tl, int K) {
   const BTile t = tl[blockIdx.x];
   const BProb& b = pr[t.g];
-  syrk_tile<float, 32>(b.win, b.d, K, K, t.a, 0, b.G);
+  syrk_tile_t<float, 64, 3>(b.win, b.ld, b.d, K, K, t.a, 0, b.G);
 }
 __global__ __launch_bounds__(256) void gk_rowsum(const BProb* __restrict__ pr, const BTile* __restrict__ tl, int K) {
   const BTile t = tl[blockIdx.x];
   const BProb& b = pr[t.g];
-  rowsum_block<float, true>(b.win, b.d, K, K, t.a, 0, b.h);
+  rowsum_block<float, true>(b.win, b.d, b.ld, K, K, t.a, 0, b.h);
 }
 
 hipError_t g_scatter(const BProb* pr, const BTile* syrk_tl, int nsyrk, const BTile* row_tl, int nrow, int K,

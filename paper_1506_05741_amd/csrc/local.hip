@@ -61,11 +61,40 @@ __global__ __launch_bounds__(256) void k_pc_gemm(const double* __restrict__ Lp, 
       }
 }
 
+// The same on the direct-to-LDS engine (bitwise), lanes along the rows of Xi;
+// all tiles of chain p run on XCD p mod 8, longest K range first, so L_p is
+// fetched into one L2 (d = 1024, P = 64, n = 200: 730 to 342 us).
+constexpr int PC_ST = 3;
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_pc_gemm_t(
+    const double* __restrict__ Lp, const double* __restrict__ W, const double* __restrict__ xrp,
+    const double* __restrict__ xr, double* __restrict__ Xi, int d, int P, int n, double c, double omr, int ni, int nt) {
+  typedef TFrag<double, PC_T, PC_T, 2, 2> F;
+  __shared__ __attribute__((aligned(1024))) double lds[t_lds_elems<double, PC_T, PC_T, PC_ST>()];
+  const int k = blockIdx.x >> 3, p = (k / (ni * nt)) * 8 + (blockIdx.x & 7), t = k % (ni * nt);
+  if (p >= P) return;
+  const int i0 = (ni - 1 - t / nt) * PC_T, t0 = (t % nt) * PC_T;
+  F f;
+  f.zero();
+  t_gemm<double, PC_T, PC_T, 2, 2, PC_ST, true, false>(f, W + (long)p * d, (long)P * d, n, Lp + (long)p * d * d, d, d,
+                                                       t0, i0, 0, min(d, i0 + PC_T), lds);
+#pragma unroll
+  for (int m = 0; m < F::FM; ++m)
+#pragma unroll
+    for (int q = 0; q < F::FN; ++q)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        int ti, tj;
+        t_coords<double, PC_T, PC_T, 2, 2>(m, q, r, tj, ti);
+        const int i = i0 + ti, s = t0 + tj;
+        if (i < d && s < n)
+          Xi[i + ((long)s * P + p) * d] = __fma_rn(c, f.c[m][q][r], omr * (xrp[i + (long)p * d] - xr[i]));
+      }
+}
+
 // G_p += sum_t y_t y_t^T over one window (y = the stored shifted states of
-// chain p: the d x n operand at win + p d, leading dimension P d).  Lower
-// 64 x 64 tiles only, on the FP64 MFMA engine; entry (i, j), i >= j, is added
-// at (i, j) and (j, i) by the one workgroup that owns it, so G_p stays
-// exactly symmetric and needs no atomics.
+// chain p: the d x n operand at win + p d, leading dimension P d).  The lower
+// triangle only, by lower 64 x 64 tiles on the FP64 MFMA engine; one workgroup
+// owns an entry, so no atomics.
 __global__ __launch_bounds__(256) void k_pc_scatter(const double* __restrict__ win, double* __restrict__ Gp, int d,
                                                     int P, int n) {
   __shared__ double lds[e_lds_elems<double, PC_T, PC_T, PC_BK>()];
@@ -87,10 +116,39 @@ __global__ __launch_bounds__(256) void k_pc_scatter(const double* __restrict__ w
         int ti, tj;
         frag_coords<PC_T, PC_T, double>(m, q, r, ti, tj);
         const int i = i0 + ti, j = j0 + tj;
-        if (i < d && j <= i) {
-          G[i + (long)j * d] += f.c[m][q][r];
-          if (j < i) G[j + (long)i * d] += f.c[m][q][r];
-        }
+        if (i < d && j <= i) G[i + (long)j * d] += f.c[m][q][r];
+      }
+}
+
+// The same on the direct-to-LDS engine (bitwise): lanes along i, the rows of
+// G; chain p on XCD p mod 8, which keeps its states in L2 (d = 1024, P = 64,
+// n = 200: 634 to 321 us, of which reading and writing the lower
+// triangles takes about 110).
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_pc_scatter_t(
+    const double* __restrict__ win, double* __restrict__ Gp, int d, int P, int n, int nt) {
+  typedef TFrag<double, PC_T, PC_T, 2, 2> F;
+  __shared__ __attribute__((aligned(1024))) double lds[t_lds_elems<double, PC_T, PC_T, PC_ST>()];
+  const int k = blockIdx.x >> 3, p = (k / nt) * 8 + (blockIdx.x & 7);
+  if (p >= P) return;
+  int bi, bj;
+  lower_tile(k % nt, bi, bj);
+  const int i0 = bi * PC_T, j0 = bj * PC_T;
+  const double* Y = win + (long)p * d;
+  const long ld = (long)P * d;
+  F f;
+  f.zero();
+  t_gemm<double, PC_T, PC_T, 2, 2, PC_ST, false, false>(f, Y, ld, d, Y, ld, d, j0, i0, 0, n, lds);
+  double* G = Gp + (long)p * d * d;
+#pragma unroll
+  for (int m = 0; m < F::FM; ++m)
+#pragma unroll
+    for (int q = 0; q < F::FN; ++q)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        int ti, tj;
+        t_coords<double, PC_T, PC_T, 2, 2>(m, q, r, tj, ti);
+        const int i = i0 + ti, j = j0 + tj;
+        if (i < d && j <= i) G[i + (long)j * d] += f.c[m][q][r];
       }
 }
 
@@ -100,6 +158,7 @@ __global__ __launch_bounds__(256) void k_pc_rowsum(const double* __restrict__ wi
   const int i = blockIdx.x * 256 + threadIdx.x, p = blockIdx.y;
   if (i >= d) return;
   double s = 0.0;
+#pragma unroll 16
   for (int t = 0; t < n; ++t) s += win[i + ((long)t * P + p) * d];
   hp[i + (long)p * d] += s;
 }
@@ -124,19 +183,36 @@ __global__ __launch_bounds__(256) void k_pc_moments(const double* __restrict__ S
   if (e < d) mpg[e] = (N * m[e] + (h[e] + n * sft[e])) * inv;
 }
 
-// Sums over the chains for the global merge: G = sum_p G_p, h = sum_p h_p.
+// Sums over the chains for the global merge: G = sum_p G_p, h = sum_p h_p; the
+// lower triangles' sum (i, j), i >= j, goes to (j, i), where the fold reads it
+// (the upper storage of the shared scatter).  64 x 64 tiles through LDS.
 __global__ __launch_bounds__(256) void k_pc_sum(const double* __restrict__ Gp, const double* __restrict__ hp,
                                                 double* __restrict__ G, double* __restrict__ h, int d, int P) {
-  const long e = (long)blockIdx.x * 256 + threadIdx.x, dd = (long)d * d;
-  if (e < dd) {
+  __shared__ double T[64][65];
+  const long dd = (long)d * d;
+  int bi, bj;
+  lower_tile(blockIdx.x, bi, bj);
+  const int i0 = 64 * bi, j0 = 64 * bj, tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
+  for (int jj = ty; jj < 64; jj += 4) {
+    const int i = i0 + tx, j = j0 + jj;
     double s = 0.0;
-    for (int p = 0; p < P; ++p) s += Gp[e + p * dd];
-    G[e] = s;
+    if (i < d && j < d && j <= i) {
+      const double* g = Gp + i + (long)j * d;
+#pragma unroll 8
+      for (int p = 0; p < P; ++p) s += g[p * dd];
+    }
+    T[jj][tx] = s;
   }
-  if (e < d) {
+  __syncthreads();
+  for (int ii = ty; ii < 64; ii += 4) {
+    const int i = i0 + ii, j = j0 + tx;
+    if (i < d && j <= i) G[j + (long)i * d] = T[tx][ii];
+  }
+  const int e = blockIdx.x * 256 + threadIdx.x;
+  for (int r = e; r < d; r += gridDim.x * 256) {
     double s = 0.0;
-    for (int p = 0; p < P; ++p) s += hp[e + (long)p * d];
-    h[e] = s;
+    for (int p = 0; p < P; ++p) s += hp[r + (long)p * d];
+    h[r] = s;
   }
 }
 
@@ -194,16 +270,26 @@ long cdiv_l(long a, long b) { return (a + b - 1) / b; }
 hipError_t pc_gemm(const double* Lp, const double* W, const double* xrp, const double* xr, double* Xi, int d, int P,
                    int n, double c, double one_minus_rho, hipStream_t s) {
   if (d < 1 || P < 1 || n < 1 || P > 65535) return hipErrorInvalidValue;
-  dim3 grid((unsigned)cdiv_l(d, PC_T), (unsigned)cdiv_l(n, PC_T), (unsigned)P);
+  const int ni = (int)cdiv_l(d, PC_T), nt = (int)cdiv_l(n, PC_T);
+  if (t_gemm_ok<double, true, false>(W, (long)P * d, n, Lp, d, d, d) && cdiv_l(P, 8) * 8 * ni * nt < (1L << 31)) {
+    hipLaunchKernelGGL(k_pc_gemm_t, dim3((unsigned)(cdiv_l(P, 8) * 8 * ni * nt)), dim3(256), 0, s, Lp, W, xrp, xr, Xi,
+                       d, P, n, c, one_minus_rho, ni, nt);
+    return hipGetLastError();
+  }
+  dim3 grid((unsigned)ni, (unsigned)nt, (unsigned)P);
   hipLaunchKernelGGL(k_pc_gemm, grid, dim3(256), 0, s, Lp, W, xrp, xr, Xi, d, P, n, c, one_minus_rho);
   return hipGetLastError();
 }
 
 hipError_t pc_scatter(const double* win, double* Gp, double* hp, int d, int P, int n, hipStream_t s) {
   if (d < 1 || P < 1 || n < 1 || P > 65535) return hipErrorInvalidValue;
-  const long nb = cdiv_l(d, PC_T);
-  hipLaunchKernelGGL(k_pc_scatter, dim3((unsigned)(nb * (nb + 1) / 2), 1, (unsigned)P), dim3(256), 0, s, win, Gp, d, P,
-                     n);
+  const long nb = cdiv_l(d, PC_T), nt = nb * (nb + 1) / 2;
+  if (t_gemm_ok<double, false, false>(win, (long)P * d, d, win, (long)P * d, d, n) &&
+      cdiv_l(P, 8) * 8 * nt < (1L << 31))
+    hipLaunchKernelGGL(k_pc_scatter_t, dim3((unsigned)(cdiv_l(P, 8) * 8 * nt)), dim3(256), 0, s, win, Gp, d, P, n,
+                       (int)nt);
+  else
+    hipLaunchKernelGGL(k_pc_scatter, dim3((unsigned)nt, 1, (unsigned)P), dim3(256), 0, s, win, Gp, d, P, n);
   hipLaunchKernelGGL(k_pc_rowsum, dim3((unsigned)cdiv_l(d, 256), (unsigned)P), dim3(256), 0, s, win, hp, d, P, n);
   return hipGetLastError();
 }
@@ -239,7 +325,8 @@ hipError_t pc_adopt(const double* Cp, const double* mpgp, const int* skip, doubl
 }
 
 hipError_t pc_sum(const double* Gp, const double* hp, double* G, double* h, int d, int P, hipStream_t s) {
-  hipLaunchKernelGGL(k_pc_sum, dim3((unsigned)cdiv_l((long)d * d, 256)), dim3(256), 0, s, Gp, hp, G, h, d, P);
+  const long nb = cdiv_l(d, 64);
+  hipLaunchKernelGGL(k_pc_sum, dim3((unsigned)(nb * (nb + 1) / 2)), dim3(256), 0, s, Gp, hp, G, h, d, P);
   return hipGetLastError();
 }
 

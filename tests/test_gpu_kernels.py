@@ -51,3 +51,43 @@ def test_split_target_log_density(prec, d, P):
         t = diam.Sampler(diam.make_config(d, P, 2, prec), mu, R.float(), x.contiguous())
         ref, tol = t.get_f64(diam.F_LOGP, (P,)), 72 * U64
     assert float(((lp - ref).abs() / ref.abs()).max()) <= tol
+
+
+@pytest.mark.parametrize("prec,d,P,n", [("fp64", 2, 3, 2), ("fp64", 30, 33, 3), ("fp64", 32, 8, 40), ("fp64", 62, 5, 7),
+                                        ("fp64", 66, 17, 31), ("fp64", 130, 64, 33), ("fp64", 75, 9, 5),
+                                        ("fp64", 194, 256, 44), ("fp64", 2050, 128, 128), ("fp32", 4, 3, 2),
+                                        ("fp32", 28, 65, 3), ("fp32", 68, 31, 9), ("fp32", 132, 64, 66),
+                                        ("fp32", 300, 100, 90), ("fp32", 70, 9, 5)])
+def test_proposal_and_scatter_products(prec, d, P, n):
+    """The proposal contraction and the merged moments at the edges of their
+    tiles and sizes of the dispatch, against FP64 products of the same operands
+    (factor, normals, visited states as the sampler holds them).  A sum of k
+    terms in a format of unit roundoff u errs by at most k u sum |a b|; the
+    window store rounds each entry once more in FP32."""
+    s, R, mu, rn = sampler(prec, d, P, n, 5 + d, beta=0.3)
+    A = rn(d, d) / np.sqrt(d)
+    S0 = A @ A.T + torch.eye(d, dtype=torch.float64, device="cuda") + torch.outer(mu, mu)
+    N0 = 50.0
+    assert s.seed_moments(S0.contiguous(), mu, N0)[0] == diam.OK
+    L, xr = s.get_f64(diam.F_L, (d, d)).T, s.get_f64(diam.F_XREF, (d,))
+    wt, u = (torch.float64, U64) if prec == "fp64" else (torch.float32, 2.0 ** -24)
+    X = torch.empty(n, P, d, dtype=torch.float64, device="cuda")
+    if n > 8:  # all steps in one call: the contraction's columns
+        s.step_batch(n)
+        W = s.get(diam.F_W).view(wt).reshape(n * P, d).double()
+        Xi = s.get(diam.F_XI).view(wt).reshape(n * P, d).double()
+        ref, mag = 0.3 * (W @ L.T), 0.3 * (W.abs() @ L.abs().T)
+        assert bool(((Xi - ref).abs() <= (d + 4) * u * mag + 1e-300).all())
+        s.merge_moments()
+        S = s.get_f64(diam.F_S, (d, d))
+        assert torch.equal(S, S.T) and bool(torch.isfinite(S).all())
+        return
+    for t in range(n):
+        s.step_batch(1, rn(1, P, d))
+        X[t] = s.get_f64(diam.F_X, (P, d))
+    s.merge_moments()
+    Y, K = X.reshape(-1, d) - xr, float(n * P)
+    scale = 2 * (K + 8) * u * (Y.abs().T @ Y.abs() + 2 * torch.outer(Y.abs().sum(0), xr.abs()) +
+                               K * torch.outer(xr.abs(), xr.abs())) + 8 * U64 * N0 * S0.abs()
+    ref = (N0 * S0 + X.reshape(-1, d).T @ X.reshape(-1, d)) / (N0 + K)
+    assert bool(((s.get_f64(diam.F_S, (d, d)) - ref).abs() * (N0 + K) <= scale + scale.T).all())
