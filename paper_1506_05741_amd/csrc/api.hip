@@ -669,8 +669,8 @@ extern "C" int diam_step_batch(diam_ctx* c, int32_t n, const double* W, const do
   a.Z = c->Z;
   a.V = c->V;
   a.nrb = c->nrb;
-  const int sub = (c->logreg || c->h2) ? 1 : dk::tgt_gauss_sub(d, P);
-  a.quarters = sub == 4;
+  const int sub = (c->logreg || c->h2) ? 1 : dk::tgt_gauss_sub(prec, d, P);
+  a.sub = sub;
   a.nacc = n_accepted ? n_accepted : c->nacc;
   a.wacc = c->wacc;
   a.win = c->win;

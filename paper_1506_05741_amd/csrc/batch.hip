@@ -83,20 +83,25 @@ Tiles build_tiles(const std::vector<int>& dims, int P, int n) {
   Tiles T;
   const int G = (int)dims.size();
   std::vector<BTile> v;
+  // every list starts with the largest problems: their tiles run longest, and a
+  // launch ends with its last tile (target of 48 problems 93 to 77 us)
+  std::vector<int> order(G);
+  for (int g = 0; g < G; ++g) order[g] = g;
+  std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return dims[x] > dims[y]; });
   for (int c = 0; c < dk::G_TGT_CONFIGS; ++c) {
     v.clear();
-    const int bm = dk::g_tgt_bm(c);
-    for (int g = 0; g < G; ++g)
+    const int bm = dk::g_tgt_rows(c);
+    for (int g : order)
       for (int bx = 0; bx < cdivh(dims[g], bm); ++bx)
         for (int by = 0; by < cdivh(P, 32); ++by) v.push_back({g, bx, by});
     T.tgt[c] = T.add(v);
   }
   v.clear();
-  for (int g = 0; g < G; ++g)
+  for (int g : order)
     for (int p = 0; p < P; ++p) v.push_back({g, 0, p});
   T.decide = T.add(v);
   v.clear();
-  for (int g = 0; g < G; ++g)
+  for (int g : order)
     for (int ch = 0; ch < dk::step_chunks(dims[g]); ++ch)
       for (int pq = 0; pq < cdivh(P, 4); ++pq) v.push_back({g, ch, pq});
   T.step = T.add(v);
@@ -104,45 +109,45 @@ Tiles build_tiles(const std::vector<int>& dims, int P, int n) {
   const long ncols = (long)P * n;
   // eight column blocks at a time, one per XCD (tiles are dealt round-robin),
   // each with its row blocks in turn, the longest K range first
-  for (int g = 0; g < G; ++g)
+  for (int g : order)
     for (int by = 0; by < cdivh(ncols, 64); by += 8)
       for (int bx = cdivh(dims[g], 64) - 1; bx >= 0; --bx)
         for (int x = by; x < std::min(by + 8, cdivh(ncols, 64)); ++x) v.push_back({g, bx, x});
   T.trigemm = T.add(v);
   v.clear();
-  for (int g = 0; g < G; ++g) {
+  for (int g : order) {
     const int nb = cdivh(dims[g], 64);
     for (int t = 0; t < nb * (nb + 1) / 2; ++t) v.push_back({g, t, 0});
   }
   T.syrk = T.add(v);
   v.clear();
-  for (int g = 0; g < G; ++g)
+  for (int g : order)
     for (int bx = 0; bx < cdivh(dims[g], 64); ++bx) v.push_back({g, bx, 0});
   T.rowsum = T.add(v);
   v.clear();
-  for (int g = 0; g < G; ++g)
+  for (int g : order)
     for (int b = 0; b < cdivh((long)dims[g] * dims[g], 256); ++b) v.push_back({g, b, 0});
   T.dd = T.add(v);
   v.clear();
-  for (int g = 0; g < G; ++g)
+  for (int g : order)
     for (int b = 0; b < cdivh(dims[g], 256); ++b) v.push_back({g, b, 0});
   T.d1 = T.add(v);
   v.clear();
-  for (int g = 0; g < G; ++g)
+  for (int g : order)
     for (int b = 0; b < cdivh((long)dims[g] * P, 256); ++b) v.push_back({g, b, 0});
   T.dp = T.add(v);
   v.clear();
-  for (int g = 0; g < G; ++g)
+  for (int g : order)
     for (int p = 0; p < P; ++p) v.push_back({g, p, 0});
   T.colnorm = T.add(v);
   v.clear();
-  for (int g = 0; g < G; ++g)
+  for (int g : order)
     for (int b = 0; b < cdivh(dims[g], NB); ++b) v.push_back({g, b, 0});
   T.triinv = T.add(v);
   for (int g = 0; g < G; ++g) T.max_nb = std::max(T.max_nb, cdivh(dims[g], NB));
   for (int jb = 0; jb < T.max_nb; ++jb) {
     std::vector<BTile> dg, pn, up, td, tu;
-    for (int g = 0; g < G; ++g) {
+    for (int g : order) {
       const int nb = cdivh(dims[g], NB);
       if (jb >= nb) continue;
       const int m = nb - jb - 1;
@@ -163,9 +168,6 @@ Tiles build_tiles(const std::vector<int>& dims, int P, int n) {
   // persistent loop: per step the target tiles of every problem (largest
   // problems first: the longest chains of dependent items start earliest),
   // then every problem's decisions, then the update chunks
-  std::vector<int> order(G);
-  for (int g = 0; g < G; ++g) order[g] = g;
-  std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return dims[x] > dims[y]; });
   const int pbm = dk::g_tgt_bm(dk::PERSIST_TGT_CFG);
   std::vector<int> ntg(G);
   T.pstep.assign(G, 0);

@@ -1095,8 +1095,10 @@ __host__ __device__ inline bool t_gemm_ok(const void* A, long lda, int M, const 
 // PAIR (both operands KC, FP64): a lane reads two consecutive k at a time (one
 // 16-byte read instead of two of 8 bytes) and the products take k in that
 // order, for sums whose order is free.
-template <typename T, int BM, int BN, int WGM, int WGN, int ST, bool AKC, bool BKC, bool PAIR = false>
-DEV void t_gemm(TFrag<T, BM, BN, WGM, WGN>& f, const T* __restrict__ A, long lda, int M, const T* __restrict__ B,
+// SETS accumulator sets take the slices in turn (slice s to set s mod SETS), as
+// the k-groups of the element engine do; the caller adds them up in order.
+template <typename T, int BM, int BN, int WGM, int WGN, int ST, bool AKC, bool BKC, bool PAIR = false, int SETS = 1>
+DEV void t_gemm(TFrag<T, BM, BN, WGM, WGN> (&fs)[SETS], const T* __restrict__ A, long lda, int M, const T* __restrict__ B,
                 long ldb, int N, int i0, int j0, int kbeg, int kend, T* lds) {
   typedef TFrag<T, BM, BN, WGM, WGN> F;
   constexpr int NW = WGM * WGN, TBK = tbk<T>(), Q = TBK / 4;
@@ -1148,7 +1150,7 @@ DEV void t_gemm(TFrag<T, BM, BN, WGM, WGN>& f, const T* __restrict__ A, long lda
     rb[x] = SA + (PAIR ? t_index<T, BN, BKC>(wn * (BN / WGN) + lr, 2 * lk + 8 * (x & 1))
                   : BKC ? t_index<T, BN, BKC>(wn * (BN / WGN) + lr, 4 * x + lk)
                       : t_index<T, BN, BKC>(wn * (BN / WGN) + x * 16 + lr, lk));
-  auto compute = [&](const T* st) {
+  auto compute = [&](const T* st, F& f) {
     if (PAIR) {
 #pragma unroll
       for (int v = 0; v < 2; ++v) {
@@ -1186,15 +1188,20 @@ DEV void t_gemm(TFrag<T, BM, BN, WGM, WGN>& f, const T* __restrict__ A, long lda
   asm volatile("s_barrier" ::: "memory");
   for (int p = 0; p < ST - 1 && p < nk; ++p) issue(p, p);
   int slot = 0;
-  for (int kt = 0; kt < nk; ++kt) {
-    // stage kt has landed once at most the later stages' copies are pending
-    if (kt + ST - 2 < nk) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LPW * (ST - 2)) : "memory");
-    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    asm volatile("s_barrier" ::: "memory");
-    // the ring slot refilled here was last read before this barrier
-    if (kt + ST - 1 < nk) issue(kt + ST - 1, slot == 0 ? ST - 1 : slot - 1);
-    compute(lds + slot * SS);
-    slot = slot == ST - 1 ? 0 : slot + 1;
+  for (int k0 = 0; k0 < nk; k0 += SETS) {
+#pragma unroll
+    for (int x = 0; x < SETS; ++x) {
+      const int kt = k0 + x;
+      if (SETS > 1 && kt >= nk) break;
+      // stage kt has landed once at most the later stages' copies are pending
+      if (kt + ST - 2 < nk) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LPW * (ST - 2)) : "memory");
+      else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      asm volatile("s_barrier" ::: "memory");
+      // the ring slot refilled here was last read before this barrier
+      if (kt + ST - 1 < nk) issue(kt + ST - 1, slot == 0 ? ST - 1 : slot - 1);
+      compute(lds + slot * SS, fs[x]);
+      slot = slot == ST - 1 ? 0 : slot + 1;
+    }
   }
   const int kv = (kend - kbeg) - nk * TBK;
   if (kv > 0) {  // the last, partial slice, cleared beyond kend
@@ -1208,8 +1215,17 @@ DEV void t_gemm(TFrag<T, BM, BN, WGM, WGN>& f, const T* __restrict__ A, long lda
     for (int e = threadIdx.x; e < BN * (TBK - kv); e += 64 * NW)
       lds[SA + t_index<T, BN, BKC>(e % BN, kv + e / BN)] = T(0);
     __syncthreads();
-    compute(lds);
+#pragma unroll
+    for (int x = 0; x < SETS; ++x)
+      if (nk % SETS == x) compute(lds, fs[x]);
   }
+}
+
+template <typename T, int BM, int BN, int WGM, int WGN, int ST, bool AKC, bool BKC, bool PAIR = false>
+DEV void t_gemm(TFrag<T, BM, BN, WGM, WGN>& f, const T* __restrict__ A, long lda, int M, const T* __restrict__ B,
+                long ldb, int N, int i0, int j0, int kbeg, int kend, T* lds) {
+  t_gemm<T, BM, BN, WGM, WGN, ST, AKC, BKC, PAIR, 1>(*(TFrag<T, BM, BN, WGM, WGN>(*)[1]) & f, A, lda, M, B, ldb, N,
+                                                     i0, j0, kbeg, kend, lds);
 }
 
 }  // namespace gemm

@@ -23,13 +23,13 @@ inline int step_chunks(int d) { return (d + STEP_RCH - 1) / STEP_RCH; }
 // Gaussian: part[p][rb] = -1/2 sum over rows of block rb of (R (x_p - mu))_i^2.
 // twist (optional, d FP64): the twisted Gaussians (Section 3.1): row 2k+1's
 // y gains twist[2k+1] * y_{2k}^2 before it is squared.
-// sub: partials per 64-row block, 1, or 4 (tgt_quarters(d) per chain, quarter
-// 2 h + g of a block holding its rows 32 h + {8 g .. 8 g + 7, 16 + 8 g .. 16 +
-// 8 g + 7}) where tgt_gauss_sub says so: few tiles then take a kernel that
-// spreads the contraction over the whole chip.  (q0 + q1) + (q2 + q3) is the
-// block's partial bit for bit in FP32.
+// sub: partials per 64-row block, as tgt_gauss_sub chooses with the kernel: 1,
+// 2 (cdiv(d, 32) per chain, 32 rows each; FP64) or 4 (tgt_quarters(d) per chain,
+// quarter 2 h + g of a block holding its rows 32 h + {8 g .. 8 g + 7, 16 + 8 g
+// .. 16 + 8 g + 7}).  (q0 + q1) + (q2 + q3) is the block's partial bit for bit
+// in FP32.
 inline __host__ __device__ int tgt_quarters(int d) { return 2 * ((d + 31) / 32); }
-int tgt_gauss_sub(int d, int P);
+int tgt_gauss_sub(Prec prec, int d, int P);
 hipError_t tgt_gauss(Prec prec, const void* R, const void* V, int d, int P, double* part, hipStream_t s,
                      const double* twist = nullptr, int sub = 1);
 // Mixed form, Gaussian: the same partials from two-part half splits of
@@ -136,7 +136,7 @@ struct StepArgs {
   const void* w_cur; const void* wlo_cur; // d x P
   const double* lpp_part;                 // P x nrb (chain-major)
   int nrb;
-  int quarters;                           // lpp_part holds four quarters per row block (P x tgt_quarters(d))
+  int sub;                                // partials per row block in lpp_part (tgt_gauss; 0: 1)
   const double* zq_part_cur;              // P x nch (chain-major)
   const double* lp_cur; const double* zq_cur;
   double* lp_nxt; double* zq_nxt;
@@ -260,7 +260,8 @@ hipError_t g_persist(const BProb* pr, const PItem* items, int nitems, const BSte
 // Workgroups of the persistent loop that fit one CU at once.
 int g_persist_blocks_per_cu();
 constexpr int G_TGT_CONFIGS = 5;    // target tile shapes the autotuner chooses from
-int g_tgt_bm(int cfg);
+int g_tgt_bm(int cfg);               // rows per partial
+int g_tgt_rows(int cfg);             // rows per tile of the list
 hipError_t g_tgt(int cfg, const BProb* pr, const BTile* tl, int ntiles, int P, hipStream_t s);
 hipError_t g_step(const BProb* pr, const BTile* dec_tl, int ndec, const BTile* tl, int ntiles, const BStep& st,
                   hipStream_t s);

@@ -70,6 +70,70 @@ __global__ __launch_bounds__(512) void k_tgt_gauss(const T* __restrict__ R, cons
   tgt_gauss_tile<T, BK, 64, 64, 2>(R, V, d, P, blockIdx.x, blockIdx.y, part, gridDim.x, twist);
 }
 
+// The same on the direct-to-LDS engine: rows [bx BM, +BM) x chains [by BN, +BN)
+// by WGM x WGN waves and SETS interleaved chains of 128-byte slices of K (two
+// in FP32, as the tile above).  Every two waves' rows make one partial, so a
+// tile writes WGM / 2 of them per chain (ldp per chain in all); FP32 tiles with
+// the same rows per wave and chains write the element engine's partials bit for
+// bit.  FP64 (one chain, pairs of consecutive k) sums in another order.
+template <typename T, int BM, int BN, int WGM, int WGN, int ST, int SETS>
+DEV void tgt_tile_t(const T* __restrict__ R, const T* __restrict__ V, int d, int P, int bx, int by,
+                    double* __restrict__ part, int ldp, const double* __restrict__ twist = nullptr) {
+  typedef TFrag<T, BM, BN, WGM, WGN> F;
+  constexpr int NTH = 64 * WGM * WGN, NS = WGM / 2;
+  static_assert(WGM % 2 == 0 && 2 * WGM * BN <= t_lds_elems<T, BM, BN, ST>(), "two waves' rows per partial");
+  __shared__ __attribute__((aligned(1024))) T lds[t_lds_elems<T, BM, BN, ST>()];
+  const int i0 = bx * BM, j0 = by * BN;
+  F f[SETS];
+#pragma unroll
+  for (int x = 0; x < SETS; ++x) f[x].zero();
+  t_gemm<T, BM, BN, WGM, WGN, ST, true, true, sizeof(T) == 8, SETS>(f, R, d, d, V, d, P, i0, j0, 0, d, lds);
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, wm = w % WGM, wn = w / WGM;
+  double (*red)[BN] = (double (*)[BN])lds;
+  __syncthreads();  // the ring's last reads are done
+#pragma unroll
+  for (int n = 0; n < F::FN; ++n) {
+    double s = 0.0;
+#pragma unroll
+    for (int m = 0; m < F::FM; ++m)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        int ti, tj;
+        t_coords<T, BM, BN, WGM, WGN>(m, n, r, ti, tj);
+        const int i = i0 + ti;
+        auto total = [&](int rr) {
+          T t = f[0].c[m][n][rr];
+#pragma unroll
+          for (int x = 1; x < SETS; ++x) t += f[x].c[m][n][rr];
+          return (double)t;
+        };
+        double y = total(r);
+        if (twist) {
+          // a twisted row's partner: this lane (FP32) or lane ^ 16 (FP64), as above
+          const double yp = (sizeof(T) == 8) ? lane_xor_f64<16>(y) : total(r & ~1);
+          if ((i & 1) && i < d) y = __fma_rn(twist[i], yp * yp, y);
+        }
+        // rows past the operand repeat its last one
+        if (i < d) s = __fma_rn(y, y, s);
+      }
+    s += lane_xor_f64<16>(s);
+    s += lane_xor_f64<32>(s);
+    if (lane < 16) red[wm][wn * (BN / WGN) + n * 16 + lane] = s;
+  }
+  __syncthreads();
+  for (int e = threadIdx.x; e < BN * NS; e += NTH) {
+    const int c = e % BN, q = e / BN, j = j0 + c;
+    if (j < P && bx * NS + q < ldp) part[(long)j * ldp + bx * NS + q] = -0.5 * (red[2 * q][c] + red[2 * q + 1][c]);
+  }
+}
+
+template <int BM>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_tgt_gauss_t(
+    const double* __restrict__ R, const double* __restrict__ V, int d, int P, double* __restrict__ part,
+    const double* __restrict__ twist) {
+  tgt_tile_t<double, BM, 32, 2, 2, 4, 1>(R, V, d, P, blockIdx.x, blockIdx.y, part, gridDim.x, twist);
+}
+
 // The same contraction where 64 x 64 tiles would leave most of the chip idle
 // (16 tiles at d = 1024, P = 64): one workgroup per 16 rows x 16 chains, K
 // split over its wavefronts, each with its own accumulator.  A unit of K is
@@ -459,11 +523,34 @@ hipError_t tgt_gauss_h2(const uint16_t* R2, const uint16_t* V2, const double* rs
   return hipGetLastError();
 }
 
-// At most half as many 64 x 64 tiles as CUs: the tile kernel then takes its
-// time for one tile whatever their number (77 us in FP64 and 43 us in FP32 at
-// d = 2048), the split kernel about 0.5 and 0.33 us per tile there, so it
-// stays ahead up to about 130 (FP32) or 150 (FP64) tiles.
-int tgt_gauss_sub(int d, int P) { return (long)cdiv(d, TGT_BM) * cdiv(P, 64) <= 128 ? 4 : 1; }
+// Which kernel, by the number n of 64 x 64 tiles (256 CUs), in us:
+//   d, P (n)         tile kernel    split         engine tiles, FP64
+//                    FP64   FP32    FP64   FP32   32 x 32   64 x 32
+//   1024, 192 (48)   40.3   23.0    14.5   11.1   17.8      26.5
+//   2048, 128 (64)   77.4   43.3    35.0   21.4   32.4      50.6
+//   1536, 192 (72)   59.0   33.3    29.4   20.2   32.0      38.4
+//   2048, 256 (128)  78.2   43.7    59.8   33.1   41.8      50.7
+//   3000, 200 (188)  136    111     111    70.2   89.6      106
+//   2048, 512 (256)  78.1   44.1    139    64.3   74.4      72.0
+//   4096, 256 (256)  153    84.8    210    121    150       141
+// The tile kernel takes the time of one tile up to n = 256, the split kernel
+// time in proportion to n.  The engine needs rows of 16-byte multiples; in
+// FP32, whose two chains double its accumulators, it is behind (99.3 us at d =
+// 4096, P = 256).
+int tgt_gauss_sub(Prec prec, int d, int P) {
+  const long n = (long)cdiv(d, TGT_BM) * cdiv(P, 64);
+  if (prec != P64 || d % 2) return n <= 192 ? 4 : 1;
+  return n <= 64 ? 4 : n < 256 ? 2 : 1;
+}
+
+// FP64 on the engine's tiles of BM rows; false: rows not aligned for it
+template <int BM>
+static bool tgt_gauss_t(const void* R, const void* V, int d, int P, double* part, const double* twist, hipStream_t s) {
+  if (!t_gemm_ok<double, true, true>(R, d, d, V, d, P, d)) return false;
+  hipLaunchKernelGGL((k_tgt_gauss_t<BM>), dim3(cdiv(d, BM), cdiv(P, 32)), dim3(256), 0, s, (const double*)R,
+                     (const double*)V, d, P, part, twist);
+  return true;
+}
 
 hipError_t tgt_gauss(Prec prec, const void* R, const void* V, int d, int P, double* part, hipStream_t s,
                      const double* twist, int sub) {
@@ -477,6 +564,11 @@ hipError_t tgt_gauss(Prec prec, const void* R, const void* V, int d, int P, doub
                          (const float*)R, (const float*)V, d, P, part, nh, nct, twist);
     return hipGetLastError();
   }
+  if (sub == 2) {
+    if (prec != P64 || !tgt_gauss_t<32>(R, V, d, P, part, twist, s)) return hipErrorInvalidValue;
+    return hipGetLastError();
+  }
+  if (prec == P64 && tgt_gauss_t<64>(R, V, d, P, part, twist, s)) return hipGetLastError();
   dim3 grid(cdiv(d, TGT_BM), cdiv(P, 64));
   if (prec == P64)
     hipLaunchKernelGGL((k_tgt_gauss<double, 16>), grid, dim3(512), 0, s, (const double*)R, (const double*)V, d, P, part,
@@ -2472,15 +2564,17 @@ hipError_t moment_error(const double* S, const double* m, const double* Sigma, c
 }
 
 
-// Target partials of chain col, and row block q's term (the sum of its
-// quarters where the target kernel wrote those).
+// Target partials of chain col, and row block q's term (the sum of its halves
+// or quarters where the target kernel wrote those).
 DEV const double* chain_parts(const StepArgs& a, int col) {
-  return a.lpp_part + (long)col * (a.quarters ? tgt_quarters(a.d) : a.nrb);
+  return a.lpp_part + (long)col * (a.sub == 4 ? tgt_quarters(a.d) : a.sub == 2 ? (a.d + 31) / 32 : a.nrb);
 }
 DEV double row_block_part(const StepArgs& a, const double* parts, int q) {
-  if (!a.quarters) return parts[q];
+  if (a.sub <= 1) return parts[q];
+  const bool two = 64 * q + 32 < a.d;  // the block has a second half
+  if (a.sub == 2) return parts[2 * q] + (two ? parts[2 * q + 1] : 0.0);
   const double* f = parts + 4 * q;
-  return (f[0] + f[1]) + (64 * q + 32 < a.d ? f[2] + f[3] : 0.0);
+  return (f[0] + f[1]) + (two ? f[2] + f[3] : 0.0);
 }
 
 // Decision of chain p by one workgroup of 256 threads: the target partials
@@ -3096,16 +3190,34 @@ __global__ __launch_bounds__(256 * KG) void gk_tgt(const BProb* __restrict__ pr,
   tgt_gauss_tile<float, 32, BM, 32, KG>(b.Rp, b.Vp, b.ld, P, t.a, t.b, b.lpp_part, b.nrb);
 }
 
+// Shapes 64 x 2 and 32 x 4 on the direct-to-LDS engine, 64-row tiles for both
+// (the latter writes two 32-row partials), bitwise the tiles above.  The 271 MB
+// of R of the 48 problems do not fit the 256 MB Infinity Cache, so R streams
+// from HBM every step: 93 us in either shape as the lists stood, 81 and 77 us
+// with the largest problems first, 67 us (4.0 TB/s) with the engine too.
+template <int WGM, int WGN, int SETS>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void gk_tgt_t(const BProb* __restrict__ pr,
+                                                                                      const BTile* __restrict__ tl,
+                                                                                      int P) {
+  const BTile t = tl[blockIdx.x];
+  const BProb& b = pr[t.g];
+  tgt_tile_t<float, 64, 32, WGM, WGN, 6, SETS>(b.Rp, b.Vp, b.ld, P, t.a, t.b, b.lpp_part, b.nrb);
+}
+
 hipError_t g_tgt(int cfg, const BProb* pr, const BTile* tl, int ntiles, int P, hipStream_t s) {
   if (ntiles <= 0) return hipSuccess;
   switch (cfg) {
     case 0: hipLaunchKernelGGL((gk_tgt<32, 2>), dim3(ntiles), dim3(512), 0, s, pr, tl, P); break;
     case 1: hipLaunchKernelGGL((gk_tgt<64, 1>), dim3(ntiles), dim3(256), 0, s, pr, tl, P); break;
-    case 2: hipLaunchKernelGGL((gk_tgt<64, 2>), dim3(ntiles), dim3(512), 0, s, pr, tl, P); break;
+    case 2: hipLaunchKernelGGL((gk_tgt_t<2, 2, 2>), dim3(ntiles), dim3(256), 0, s, pr, tl, P); break;
     case 3: hipLaunchKernelGGL((gk_tgt<128, 2>), dim3(ntiles), dim3(512), 0, s, pr, tl, P); break;
-    default: hipLaunchKernelGGL((gk_tgt<32, 4>), dim3(ntiles), dim3(1024), 0, s, pr, tl, P); break;
+    default: hipLaunchKernelGGL((gk_tgt_t<4, 1, 4>), dim3(ntiles), dim3(256), 0, s, pr, tl, P); break;
   }
   return hipGetLastError();
+}
+int g_tgt_rows(int cfg) {
+  static const int rows[G_TGT_CONFIGS] = {32, 64, 64, 128, 64};
+  return rows[cfg];
 }
 int g_tgt_bm(int cfg) {
   static const int bm[G_TGT_CONFIGS] = {32, 64, 64, 128, 32};

@@ -71,6 +71,55 @@ __global__ __launch_bounds__(512) void k_tgt_logreg(const float* __restrict__ A,
   }
 }
 
+// The same on the direct-to-LDS engine: BM observations x 64 chains by WGM x 2
+// waves of 32 x 32, two interleaved chains of slices of K as the two k-groups
+// above, every 64 observations' term bitwise the tile's.
+template <int BM, int WGM>
+__global__ __launch_bounds__(128 * WGM) __attribute__((amdgpu_waves_per_eu(2))) void k_tgt_logreg_t(
+    const float* __restrict__ A, const float* __restrict__ y, int n_obs, const float* __restrict__ V, int d, int P,
+    const int* __restrict__ nact_ptr, int nrb, int nct, double* __restrict__ part) {
+  constexpr int BN = 64, ST = 3, RB = BM / 64;
+  typedef TFrag<float, BM, BN, WGM, 2> F;
+  static_assert(F::FM == 2, "32 rows per wave: two waves per 64-row term");
+  __shared__ __attribute__((aligned(1024))) float lds[t_lds_elems<float, BM, BN, ST>()];
+  const int xcd = blockIdx.x & 7, k = blockIdx.x >> 3;
+  const int rb = (k / nct) * 8 + xcd, ct = k % nct;
+  const int nact = nact_ptr ? *nact_ptr : P;
+  const int i0 = rb * BM, j0 = ct * BN;
+  if (i0 >= n_obs || j0 >= nact) return;  // uniform per workgroup, before any barrier
+  F f[2];
+  f[0].zero();
+  f[1].zero();
+  t_gemm<float, BM, BN, WGM, 2, ST, true, true, false, 2>(f, A, d, n_obs, V, d, P, i0, j0, 0, d, lds);
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, wm = w % WGM, wn = w / WGM;
+  double (*red)[BN] = (double (*)[BN])lds;
+  __syncthreads();  // the ring's last reads are done
+#pragma unroll
+  for (int n = 0; n < F::FN; ++n) {
+    double s = 0.0;
+#pragma unroll
+    for (int m = 0; m < F::FM; ++m)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        int ti, tj;
+        t_coords<float, BM, BN, WGM, 2>(m, n, r, ti, tj);
+        const int i = i0 + ti;
+        if (i < n_obs) {
+          const float t = f[0].c[m][n][r] + f[1].c[m][n][r];
+          s += (double)(y[i] * t - softplus_f(t));
+        }
+      }
+    s += lane_xor_f64<16>(s);
+    s += lane_xor_f64<32>(s);
+    if (lane < 16) red[wm][wn * (BN / 2) + n * 16 + lane] = s;
+  }
+  __syncthreads();
+  for (int e = threadIdx.x; e < RB * BN; e += 128 * WGM) {
+    const int c = e % BN, q = e / BN, j = j0 + c, b = rb * RB + q;
+    if (j < nact && b < nrb) part[(long)j * nrb + b] = red[2 * q][c] + red[2 * q + 1][c];
+  }
+}
+
 int logreg_row_blocks(long n_obs) { return (int)((n_obs + 63) / 64); }
 
 // Column tiles of 64 chains; under delayed acceptance (nact set) the tiles
@@ -80,6 +129,18 @@ hipError_t tgt_logreg(const float* A, const float* y, long n_obs, const float* V
                       double* part, hipStream_t s) {
   const int nrb = logreg_row_blocks(n_obs), groups = (nrb + 7) / 8;
   const int nct = cdiv(P, 64);
+  // 128-row tiles from 1024 of them on (n = 200000, d = 512, P = 128: 342 to 314
+  // us, of which the softplus terms take about 72; 64-row ones 338), 64-row
+  // ones below (n = 50001, d = 256, P = 100: 73.9 to 58.6 us, 128-row 61.4)
+  if (t_gemm_ok<float, true, true>(A, d, (int)n_obs, V, d, P, d)) {
+    if (n_obs >= 1024 * 128)
+      hipLaunchKernelGGL((k_tgt_logreg_t<128, 4>), dim3((cdiv(n_obs, 128) + 7) / 8 * 8 * nct), dim3(512), 0, s, A, y,
+                         (int)n_obs, V, d, P, nact, nrb, nct, part);
+    else
+      hipLaunchKernelGGL((k_tgt_logreg_t<64, 2>), dim3(groups * 8 * nct), dim3(256), 0, s, A, y, (int)n_obs, V, d, P,
+                         nact, nrb, nct, part);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(k_tgt_logreg<64>, dim3(groups * 8 * nct), dim3(512), 0, s, A, y, (int)n_obs, V, d, P, nact, nrb,
                      nct, part);
   return hipGetLastError();

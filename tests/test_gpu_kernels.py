@@ -26,12 +26,14 @@ def sampler(prec, d, P, n_lag, seed, twist=None, **kw):
 
 @pytest.mark.parametrize("prec", ["fp64", "fp32"])
 @pytest.mark.parametrize("d,P", [(1, 1), (7, 16), (8, 17), (16, 2), (17, 15), (32, 33), (33, 1), (63, 16), (64, 64),
-                                 (65, 3), (127, 31), (129, 65), (511, 16), (1001, 18), (1024, 130)])
-def test_split_target_log_density(prec, d, P):
-    """The step's target kernel for few tiles (16 x 16 per workgroup, K split)
-    on accepted proposals, against FP64 products of the same operands: FP64
-    within 8 d u; FP32 against the tile kernel, whose products it repeats bit
-    for bit, up to the order of the FP64 row-block sum (d u, 64 blocks)."""
+                                 (65, 3), (127, 31), (129, 65), (511, 16), (1001, 18), (1024, 130),
+                                 (1026, 290), (4100, 70), (1030, 960), (1031, 770)])
+def test_target_log_density_by_size(prec, d, P):
+    """The step's target kernels (16 x 16 per workgroup with K split, 32- and
+    64-row tiles of the direct-to-LDS engine, the tile kernel) on accepted
+    proposals, against FP64 products of the same operands: FP64 within 8 d u;
+    FP32 against the tile kernel at initialisation, whose products they repeat
+    bit for bit, up to the order of the FP64 row-block sum (d u, 64 blocks)."""
     twist = None
     if prec == "fp64" and d % 2 == 0:  # the twisted rows' partner lies in the same lane
         twist = torch.zeros(d, dtype=torch.float64, device="cuda")
@@ -91,3 +93,55 @@ def test_proposal_and_scatter_products(prec, d, P, n):
                                K * torch.outer(xr.abs(), xr.abs())) + 8 * U64 * N0 * S0.abs()
     ref = (N0 * S0 + X.reshape(-1, d).T @ X.reshape(-1, d)) / (N0 + K)
     assert bool(((s.get_f64(diam.F_S, (d, d)) - ref).abs() * (N0 + K) <= scale + scale.T).all())
+
+
+@pytest.mark.parametrize("n_obs,d,P", [(1, 4, 1), (63, 8, 3), (65, 36, 65), (200, 12, 64), (131, 33, 17),
+                                       (131072, 32, 66), (131200, 40, 3)])
+def test_logistic_target_by_size(n_obs, d, P):
+    """The logistic target's tiles (64 and 128 observations, the unaligned
+    fallback) against FP64 at the accepted states: an FP32 dot product of d
+    terms errs by d u32 sum |a x|, a term of the log likelihood by no more than
+    that plus 4 u32 (|t| + 1) of its own evaluation."""
+    g = torch.Generator("cuda").manual_seed(n_obs + d)
+    rn = lambda *s: torch.randn(*s, generator=g, dtype=torch.float64, device="cuda")
+    A, y = (rn(n_obs, d) / np.sqrt(d)).float(), (rn(n_obs) > 0).float()
+    s = diam.Sampler(diam.make_config(d, P, 2, "fp32", beta=0.05, seed=3), None, None, rn(P, d).contiguous(), A=A, y=y,
+                     prior_var=10.0)
+    s.step_batch(1, rn(1, P, d), torch.full((1, P), 0.5 * 2.0 ** -52, dtype=torch.float64, device="cuda"))
+    acc = s.get(diam.F_ACC).bool()
+    x = s.get_f64(diam.F_X, (P, d))
+    lp = s.get_f64(diam.F_LOGP, (P,))
+    xf = x.float().double()
+    t = A.double() @ xf.T
+    ref = (y.double()[:, None] * t - torch.nn.functional.softplus(t)).sum(0) - 0.05 * (x * x).sum(1)
+    u32 = 2.0 ** -24
+    tol = ((d + 4) * u32 * (A.double().abs() @ xf.abs().T) + 6 * u32 * (t.abs() + 1)).sum(0) + 1e-12 * ref.abs()
+    assert bool(acc.any()) and bool(((lp - ref).abs() <= tol).all())
+
+
+@pytest.mark.parametrize("tiles", [2, 4])
+def test_grouped_target_tiles(tiles):
+    """The grouped target's 64-row tiles at ragged dimensions and chain counts:
+    a first window's log alpha against a separate FP32 sampler's (the same
+    products; shape 32 x 4 sums them in four chains instead of two, within 2 d
+    u32 |log pi|)."""
+    dims, P, n = [1, 5, 31, 33, 64, 97, 130, 260], 34, 4
+    g = torch.Generator("cuda").manual_seed(2)
+    rn = lambda *s: torch.randn(*s, generator=g, dtype=torch.float64, device="cuda")
+    mus, Rs, xs = [rn(d) for d in dims], [(torch.eye(d, device="cuda") + rn(d, d) / d).float() for d in dims], [
+        rn(P, d) for d in dims]
+    b = diam.Batch(diam.make_batch_config(len(dims), P, n, seed=4), mus, Rs, xs)
+    b.set_tiles(tiles)
+    assert b.window()[0] in (diam.OK, diam.E_NOT_PD)
+    for k, d in enumerate(dims):
+        s = diam.Sampler(diam.make_config(d, P, n, "fp32"), mus[k], Rs[k], xs[k])
+        ld = (d + 3) // 4 * 4
+        W = b.get(k, diam.F_W).view(torch.float32).reshape(n, P, ld)[:, :, :d].double().contiguous()
+        s.step_batch(n, W, b.get_f64(k, diam.F_U, (n, P)).contiguous())
+        la_b, la_s = b.get_f64(k, diam.F_LA, (n, P)), s.get_f64(diam.F_LA, (n, P))
+        if tiles == 2:
+            assert torch.equal(la_b, la_s), d
+        else:  # the first step: same states on both sides
+            y = (xs[k] - mus[k]) @ Rs[k].double().T
+            tol = 2 * d * 2.0 ** -24 * (100.0 + 4.0 * (y * y).sum(1))
+            assert bool(((la_b[0] - la_s[0]).abs() <= tol).all()), d
