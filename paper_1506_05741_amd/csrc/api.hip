@@ -608,6 +608,16 @@ extern "C" int diam_init(diam_ctx** out, const diam_config* cfg, const diam_targ
   return DIAM_OK;
 }
 
+// host state after n steps of a call
+static void finish_steps(diam_ctx* c, int n, int stages, bool tracing) {
+  if (tracing) c->trace_pos += n;
+  c->siw += n;
+  c->win_steps += n;
+  c->steps += n;
+  c->last_call_steps = n;
+  c->last_call_stages = stages;
+}
+
 extern "C" int diam_step_batch(diam_ctx* c, int32_t n, const double* W, const double* U, int32_t* n_accepted) {
   if (!c) return fail(DIAM_E_ARG, "null context");
   if (n < 0) return fail(DIAM_E_ARG, "n_steps < 0");
@@ -655,11 +665,50 @@ extern "C" int diam_step_batch(diam_ctx* c, int32_t n, const double* W, const do
   const bool tracing = c->trace && c->trace_pos + n <= c->trace_cap;
   const int nfun = 1 + c->nproj;
 
+  const bool walk = walk_proposal(c->cfg);
+  if (prec == dk::P64 && !c->logreg && !c->da_on && dk::steps_resident_ok(d, P)) {
+    dk::ResidentArgs r{};
+    r.d = d;
+    r.P = P;
+    r.n = n;
+    r.rho = walk ? 1.0 : sqrt(1.0 - beta * beta);
+    r.c = cc;
+    r.inv2a2 = walk ? 0.0 : 1.0 / (2.0 * alpha * alpha);
+    r.R = (const double*)c->tgt.R;
+    r.mu = c->tgt.mu;
+    r.twist = c->tgt.twist;
+    r.xr = c->xr;
+    r.X = c->X;
+    r.Z = c->Z;
+    r.xi = (const double*)c->Xi;
+    r.w = (const double*)Wp;
+    r.u = Up;
+    const int last = c->cur ^ (n & 1);
+    r.lp = c->lp + (long)c->cur * P;
+    r.zq = c->zq + (long)c->cur * P;
+    r.lp_out = c->lp + (long)last * P;
+    r.zq_out = c->zq + (long)last * P;
+    r.nacc = n_accepted ? n_accepted : c->nacc;
+    r.wacc = c->wacc;
+    r.la = c->la;
+    r.acc = c->acc;
+    r.win = (double*)c->win + (long)c->siw * dP;
+    r.trace = tracing ? c->trace + c->trace_pos * nfun * P : nullptr;
+    r.nfun = nfun;
+    r.proj = c->proj;
+    r.err = &c->status->err;
+    ps = prof_begin(c, DIAM_ST_STEP);
+    HIPCHK(dk::steps_resident(r, s));
+    prof_end(c, ps);
+    c->cur = last;
+    finish_steps(c, n, stages, tracing);
+    return DIAM_OK;
+  }
+
   dk::StepArgs a{};
   a.d = d;
   a.P = P;
   a.prec = prec;
-  const bool walk = walk_proposal(c->cfg);
   a.rho = walk ? 1.0 : sqrt(1.0 - beta * beta);
   a.c = cc;
   a.inv2a2 = walk ? 0.0 : 1.0 / (2.0 * alpha * alpha);
@@ -757,12 +806,7 @@ extern "C" int diam_step_batch(diam_ctx* c, int32_t n, const double* W, const do
   }
   if (tracing && c->nproj > 0)
     HIPCHK(dk::proj_reduce(c->proj_part, n, c->nch, c->nproj, P, c->trace + c->trace_pos * nfun * P, nfun, s));
-  if (tracing) c->trace_pos += n;
-  c->siw += n;
-  c->win_steps += n;
-  c->steps += n;
-  c->last_call_steps = n;
-  c->last_call_stages = stages;
+  finish_steps(c, n, stages, tracing);
   return DIAM_OK;
 }
 

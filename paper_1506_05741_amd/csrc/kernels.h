@@ -181,6 +181,29 @@ hipError_t step(const StepArgs& a, hipStream_t s);
 bool step_h2_ok(int d, int P, int nrb);
 hipError_t step_h2(const StepArgs& a, const float* Yp, const double* rsc, double* part, const double* twist,
                    hipStream_t s);
+// All n steps of a call in one launch, one workgroup per chain with the FP64
+// matrix of the Gaussian target in its registers.
+bool steps_resident_ok(int d, int P);
+struct ResidentArgs {
+  int d, P, n;
+  double rho, c, inv2a2;         // as StepArgs
+  const double *R, *mu, *twist;  // twist may be null
+  const double* xr;              // d
+  double *X, *Z;                 // d x P
+  const double *xi, *w;          // d x P per step
+  const double* u;               // P per step
+  const double *lp, *zq;         // P: at the current states
+  double *lp_out, *zq_out;       // P: after the call (may be the same)
+  int *nacc, *wacc;              // P, accumulated (wacc may be null)
+  double* la;                    // n x P
+  uint8_t* acc;                  // n x P
+  double* win;                   // d x (P n): the window's columns of this call
+  double* trace;                 // null, or per step nfun x P: log pi, then the projections
+  int nfun;                      // 1 + projections
+  const double* proj;            // d x (nfun - 1)
+  int* err;
+};
+hipError_t steps_resident(const ResidentArgs& a, hipStream_t s);
 // PSRF accumulators (Section 2.4.2, M = 1): merge the nw stored states of
 // each chain of the window (store shifted by xr, column p + P t) into the
 // running per-chain means and sums of squared deviations (d x P each) that

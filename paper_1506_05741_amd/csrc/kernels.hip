@@ -3060,6 +3060,203 @@ hipError_t step_h2(const StepArgs& a, const float* Yp, const double* rsc, double
   return hipGetLastError();
 }
 
+// ---- the steps of a call with the target matrix in registers --------------------
+// Between merges the chains do not meet, so one workgroup runs all n steps of
+// one chain.  Waves 1 .. KS hold R in registers (wave q columns (q - 1) KPT ..
+// of all rows, lane l rows l, l + 64, ..), wave 0 the chain's state; a step is
+// two barriers: wave 0 proposes and writes x' - mu to LDS, the others form
+// their columns' part of y = R (x' - mu), wave 0 adds the parts, sums the
+// squares, decides and proposes again.  The steps' search directions and
+// normals are loaded RES_PF steps ahead (more spills at d = 192), log u for 64
+// steps at a time and the traced projections are formed by the other waves
+// while wave 0 decides.  Bound by that chain: LDS round trip, KPT dependent
+// products, LDS round trip, the wave sum.  One launch replaces 2 or 3 per step,
+// whose dispatch and round trips cost 9 to 13 us a step at d <= 128 whatever
+// the work; the loop takes 0.55, 0.82 and 1.13 us a step at d = 32, 100 and
+// 192 (one chain per CU).
+constexpr int RES_PF = 2;
+
+template <int RPT, int KS, int KPT>
+__global__ __launch_bounds__(64 * (KS + 1)) void k_steps_resident(ResidentArgs a) {
+  constexpr int DR = 64 * RPT;
+  static_assert(KS * KPT >= DR && KPT % 2 == 0, "every column has a wave");
+  __shared__ __attribute__((aligned(16))) double vs[KS * KPT];
+  __shared__ double ys[KS][DR], xs[2][DR], lu[2][64], pj[MAXPROJ][DR];
+  const int lane = threadIdx.x & 63, q = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int p = blockIdx.x, d = a.d, P = a.P, n = a.n;
+  const long dP = (long)d * P;
+  const int nproj = a.trace ? a.nfun - 1 : 0;
+  for (int e = threadIdx.x; e < nproj * DR; e += 64 * (KS + 1))
+    pj[e / DR][e % DR] = e % DR < d ? a.proj[(long)(e / DR) * d + e % DR] : 0.0;
+  for (int e = threadIdx.x; e < KS * KPT; e += 64 * (KS + 1)) vs[e] = 0.0;  // columns past d
+  if (q != 0) {
+    double rk[RPT][KPT];
+#pragma unroll
+    for (int j = 0; j < KPT; ++j) {
+      const int k = (q - 1) * KPT + j;
+      const double* col = a.R + (k < d ? k : d - 1);
+#pragma unroll
+      for (int r = 0; r < RPT; ++r) {
+        const int i = lane + 64 * r;
+        const double v = col[(unsigned)((i < d ? i : d - 1) * d)];
+        rk[r][j] = (i < d && k < d) ? v : 0.0;
+      }
+    }
+    auto log_uniforms = [&](int t0) {
+      if (t0 + lane < n) lu[(t0 >> 6) & 1][lane] = log(a.u[(long)(t0 + lane) * P + p]);
+    };
+    // projections of the state after step t (xs[t & 1] is written again two
+    // decisions later)
+    auto project = [&](int t) {
+      for (int k = q - 1; k < nproj; k += KS) {
+        double s = 0.0;
+#pragma unroll
+        for (int r = 0; r < RPT; ++r) s = __fma_rn(pj[k][lane + 64 * r], xs[t & 1][lane + 64 * r], s);
+        s = wave_sum_f64(s);
+        if (lane == 0) a.trace[((long)t * a.nfun + 1 + k) * P + p] = s;
+      }
+    };
+    if (q == 1) log_uniforms(0);
+    __syncthreads();  // vs cleared, pj and lu written
+    for (int t = 0; t < n; ++t) {
+      if (q == 1 && (t & 63) == 32) log_uniforms((t & ~63) + 64);
+      __syncthreads();  // x' - mu
+      double y0[RPT], y1[RPT];
+#pragma unroll
+      for (int r = 0; r < RPT; ++r) y0[r] = y1[r] = 0.0;
+#pragma unroll
+      for (int j = 0; j < KPT; j += 2) {
+        const double2 v = *(const double2*)&vs[(q - 1) * KPT + j];
+#pragma unroll
+        for (int r = 0; r < RPT; ++r) {
+          y0[r] = __fma_rn(rk[r][j], v.x, y0[r]);
+          y1[r] = __fma_rn(rk[r][j + 1], v.y, y1[r]);
+        }
+      }
+#pragma unroll
+      for (int r = 0; r < RPT; ++r) ys[q - 1][lane + 64 * r] = y0[r] + y1[r];
+      __syncthreads();  // parts of y
+      if (t > 0) project(t - 1);
+    }
+    __syncthreads();  // the last state
+    project(n - 1);
+    return;
+  }
+  double x[RPT], z[RPT], xr[RPT], mu[RPT], tw[RPT];
+  double fx[RES_PF][RPT], fw[RES_PF][RPT];
+  bool in[RPT];
+  const long e0 = (long)p * d + lane;
+  auto fetch = [&](int t, double* bx, double* bw) {
+#pragma unroll
+    for (int r = 0; r < RPT; ++r) {
+      bx[r] = bw[r] = 0.0;
+      if (in[r] && t < n) {
+        bx[r] = a.xi[t * dP + e0 + 64 * r];
+        bw[r] = a.w[t * dP + e0 + 64 * r];
+      }
+    }
+  };
+#pragma unroll
+  for (int r = 0; r < RPT; ++r) {
+    const int i = lane + 64 * r;
+    in[r] = i < d;
+    x[r] = in[r] ? a.X[e0 + 64 * r] : 0.0;
+    z[r] = in[r] ? a.Z[e0 + 64 * r] : 0.0;
+    xr[r] = in[r] ? a.xr[i] : 0.0;
+    mu[r] = in[r] ? a.mu[i] : 0.0;
+    tw[r] = (a.twist && (i & 1) && in[r]) ? a.twist[i] : 0.0;
+  }
+  double lp = a.lp[p], zq = a.zq[p];
+  int nacc = 0;
+#pragma unroll
+  for (int b = 0; b < RES_PF; ++b) fetch(b, fx[b], fw[b]);
+  __syncthreads();  // vs cleared, pj and lu written
+  auto step = [&](int t, double* bx, double* bw) {
+    double xp[RPT], zp[RPT], zacc = 0.0;
+#pragma unroll
+    for (int r = 0; r < RPT; ++r) {
+      xp[r] = propose1(xr[r], x[r], a.rho, bx[r]);
+      zp[r] = __fma_rn(a.c, bw[r], a.rho * z[r]);
+      if (in[r]) vs[lane + 64 * r] = xp[r] - mu[r];
+    }
+    __syncthreads();  // x' - mu
+    fetch(t + RES_PF, bx, bw);
+#pragma unroll
+    for (int r = 0; r < RPT; ++r) zacc = __fma_rn(zp[r], zp[r], zacc);
+    const double zs = wave_sum_f64(zacc);
+    const double logu = lu[(t >> 6) & 1][t & 63];
+    __syncthreads();  // parts of y
+    double s = 0.0;
+#pragma unroll
+    for (int r = 0; r < RPT; ++r) {
+      double v = ys[0][lane + 64 * r];
+#pragma unroll
+      for (int g = 1; g < KS; ++g) v += ys[g][lane + 64 * r];
+      if (a.twist) {
+        const double e = lane_xor_f64<1>(v);  // row 2k of a twisted row 2k + 1
+        if (lane & 1) v = __fma_rn(tw[r], e * e, v);
+      }
+      s = in[r] ? __fma_rn(v, v, s) : s;  // not 0 x infinity of the rows past d
+    }
+    const double lpp = -0.5 * wave_sum_f64(s);
+    const double la = (lpp + zs * a.inv2a2) - (lp + zq * a.inv2a2);
+    const bool acc = logu < la;  // NaN compares false: rejected
+    if (acc) {
+      lp = lpp;
+      zq = zs;
+      ++nacc;
+    }
+#pragma unroll
+    for (int r = 0; r < RPT; ++r) {
+      x[r] = acc ? xp[r] : x[r];
+      z[r] = acc ? zp[r] : z[r];
+      if (in[r]) a.win[t * dP + e0 + 64 * r] = x[r] - xr[r];
+      if (nproj) xs[t & 1][lane + 64 * r] = x[r];
+    }
+    if (lane == 0) {
+      a.la[(long)t * P + p] = la;
+      a.acc[(long)t * P + p] = acc ? 1 : 0;
+      if (a.trace) a.trace[(long)t * a.nfun * P + p] = lp;
+      if (isinf(lpp) && lpp > 0.0) atomicOr(a.err, 1);
+    }
+  };
+  for (int t = 0; t < n; t += RES_PF) {
+#pragma unroll
+    for (int b = 0; b < RES_PF; ++b)
+      if (t + b < n) step(t + b, fx[b], fw[b]);
+  }
+  __syncthreads();  // the last state
+#pragma unroll
+  for (int r = 0; r < RPT; ++r)
+    if (in[r]) {
+      a.X[e0 + 64 * r] = x[r];
+      a.Z[e0 + 64 * r] = z[r];
+    }
+  if (lane == 0) {
+    a.lp_out[p] = lp;
+    a.zq_out[p] = zq;
+    a.nacc[p] += nacc;
+    if (a.wacc) a.wacc[p] += nacc;
+  }
+}
+
+// Above d = 192 the columns pass a lane's 256 registers.  Every chain reads R
+// from its own CU's registers, so the CUs' rounds over many chains lose to the
+// tiled target in the end: us a step, proposals included, this loop / the
+// launches per step: 10.8 / 23.3 at d = 64 and 8192 chains, 31.7 / 34.9 at d =
+// 128 and 8192, 10.7 / 18.6 at d = 192 and 1024, 20.9 / 22.6 at 2048, 41.5 /
+// 29.7 at 4096.
+bool steps_resident_ok(int d, int P) { return d <= 64 || (d <= 128 && P <= 8192) || (d <= 192 && P <= 1024); }
+
+hipError_t steps_resident(const ResidentArgs& a, hipStream_t s) {
+  if (a.d < 1 || !steps_resident_ok(a.d, a.P) || a.P < 1 || a.n < 1 || a.nfun - 1 > MAXPROJ)
+    return hipErrorInvalidValue;
+  if (a.d <= 64) hipLaunchKernelGGL((k_steps_resident<1, 3, 22>), dim3(a.P), dim3(256), 0, s, a);
+  else if (a.d <= 128) hipLaunchKernelGGL((k_steps_resident<2, 7, 20>), dim3(a.P), dim3(512), 0, s, a);
+  else hipLaunchKernelGGL((k_steps_resident<3, 7, 28>), dim3(a.P), dim3(512), 0, s, a);
+  return hipGetLastError();
+}
+
 DEV void init_eval_elem(int v64, const double* __restrict__ X, const double* __restrict__ mu, void* __restrict__ V,
                         double* __restrict__ Z, int d, long e) {
   const double x = X[e];

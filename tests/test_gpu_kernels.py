@@ -55,6 +55,72 @@ def test_target_log_density_by_size(prec, d, P):
     assert float(((lp - ref).abs() / ref.abs()).max()) <= tol
 
 
+@pytest.mark.parametrize("d,P,n,nproj,proposal", [(1, 1, 3, 1, "diam"), (2, 5, 65, 4, "diam"), (31, 3, 130, 0, "am"),
+                                                  (32, 16, 64, 2, "diam"), (63, 2, 33, 4, "diam"),
+                                                  (64, 4, 66, 4, "diam"), (65, 3, 1, 1, "diam"),
+                                                  (100, 20, 70, 4, "diam"), (128, 5, 34, 3, "pcn"),
+                                                  (129, 2, 35, 4, "diam"), (191, 3, 7, 1, "am"),
+                                                  (192, 300, 36, 4, "diam"), (193, 3, 9, 2, "diam"),
+                                                  (130, 1025, 3, 1, "diam"), (66, 8193, 2, 1, "diam")])
+def test_steps_of_a_call_in_one_launch(d, P, n, nproj, proposal):
+    """The loop with R in registers and the launches per step past its range: states, log densities, log ratios, traced projections and decisions of
+    two calls against the recursion in FP64 on the directions the call drew.
+    The recursion contracts (rho <= 1), so t steps err by at most t times one
+    step's 4 u, and log pi by 8 (d + n) u of the sum of its absolute terms."""
+    twist = None
+    if d % 2 == 0:
+        twist = torch.zeros(d, dtype=torch.float64, device="cuda")
+        twist[1::2] = 0.2
+    s, R, mu, rn = sampler("fp64", d, P, n + 2, 77 + d, twist=twist, beta=0.25, proposal=proposal)
+    walk = proposal == "am"
+    rho, c = (1.0 if walk else np.sqrt(1 - 0.25 ** 2)), 0.25
+    proj = rn(nproj, d) if nproj else None
+    trace = torch.zeros(n + 2, 1 + nproj, P, dtype=torch.float64, device="cuda")
+    s.set_trace(proj, trace)
+    scale = 0.4 / np.sqrt(d)
+    done, tot = 0, 0.0
+    for m in (2, n):
+        x, z = s.get_f64(diam.F_X, (P, d)), s.get_f64(diam.F_Z, (P, d))
+        lp, xr = s.get_f64(diam.F_LOGP, (P,)), s.get_f64(diam.F_XREF, (d,))
+        W = (scale * rn(m, P, d)).contiguous()
+        U = torch.rand(m, P, dtype=torch.float64, device="cuda").clamp_(1e-12)
+        cnt = torch.full((P,), 7, dtype=torch.int32, device="cuda")
+        s.step_batch(m, W, U, cnt)
+        Xi = s.get(diam.F_XI).view(torch.float64)[:m * P * d].reshape(m, P, d)
+        La = s.get(diam.F_LA).view(torch.float64)[:m * P].reshape(m, P)
+        Acc = s.get(diam.F_ACC)[:m * P].reshape(m, P).bool()
+        assert torch.equal(cnt, 7 + Acc.sum(0, dtype=torch.int32))
+        mag = torch.maximum(x.abs(), z.abs()).amax() + Xi.abs().amax() * m + mu.abs().amax()
+        for t in range(m):
+            xp, zp = xr + rho * (x - xr) + Xi[t], rho * z + c * W[t]
+            y = (xp - mu) @ R.T
+            ya = (xp - mu).abs() @ R.abs().T
+            if twist is not None:
+                ya[:, 1::2] += 3 * twist[1::2] * ya[:, 0::2] ** 2
+                y[:, 1::2] += twist[1::2] * y[:, 0::2] ** 2
+            lpp = -0.5 * (y * y).sum(1)
+            tol = 8 * (d + m + 8) * U64 * ((y.abs() * ya).sum(1) + (y.abs() + ya) @ R.abs().sum(1) * mag)
+            q = 0.0 if walk else 0.5 * ((zp * zp).sum(1) - (z * z).sum(1))
+            la = lpp - lp + q
+            assert bool(((La[t] - la).abs() <= 2 * tol + 8 * (d + m) * U64 * (1 + (zp * zp).sum(1))).all())
+            assert torch.equal(Acc[t], torch.log(U[t]) < La[t])
+            a = Acc[t][:, None]
+            x, z, lp = torch.where(a, xp, x), torch.where(a, zp, z), torch.where(Acc[t], lpp, lp)
+            tot = tot + x.sum(0)
+            assert bool(((trace[done + t, 0] - lp).abs() <= 2 * tol + 8 * (d + m) * U64 * lp.abs()).all())
+            for k in range(nproj):
+                bound = 4 * (d + m) * U64 * proj[k].abs().sum() * mag
+                assert bool(((trace[done + t, 1 + k] - x @ proj[k]).abs() <= bound).all())
+        assert 0 < int(Acc.sum()) or m * P < 8
+        assert bool(((s.get_f64(diam.F_X, (P, d)) - x).abs() <= 4 * m * U64 * mag).all())
+        assert bool(((s.get_f64(diam.F_Z, (P, d)) - z).abs() <= 4 * m * U64 * mag).all())
+        assert bool(((s.get_f64(diam.F_LOGP, (P,)) - lp).abs() <= 2 * tol + 8 * (d + m) * U64 * lp.abs()).all())
+        done += m
+    s.merge_moments()  # the window store of both calls
+    K = (n + 2) * P
+    assert bool(((s.get_f64(diam.F_M, (d,)) - tot / K).abs() <= 4 * (K + n) * U64 * mag).all())
+
+
 @pytest.mark.parametrize("prec,d,P,n", [("fp64", 2, 3, 2), ("fp64", 30, 33, 3), ("fp64", 32, 8, 40), ("fp64", 62, 5, 7),
                                         ("fp64", 66, 17, 31), ("fp64", 130, 64, 33), ("fp64", 75, 9, 5),
                                         ("fp64", 194, 256, 44), ("fp64", 2050, 128, 128), ("fp32", 4, 3, 2),
