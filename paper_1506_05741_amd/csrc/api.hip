@@ -834,10 +834,13 @@ extern "C" int diam_surrogate_train(diam_ctx* c, const double* X, const double* 
   if (c->cfg.surrogate == 2) {
     // residual form: the network learns log pi(x) + |z(x)|^2 / (2 alpha^2)
     // with z under the current factor and pivot
-    const int d = c->cfg.d, chunk = nmax;
+    const int d = c->cfg.d;
+    HIPCHK(dk::trsm_inverses(c->L, c->linv, d, s));
+    const bool whole = dk::whiten_rows(d) >= d;  // z itself is then not stored
+    const long chunk = whole ? 1L << 20 : nmax;
     for (long k0 = 0; k0 < n; k0 += chunk) {
       const int nc = (int)(n - k0 < chunk ? n - k0 : chunk);
-      HIPCHK(dk::trsm_whiten(c->L, X + k0 * d, c->xr, c->Zs, c->t64 + k0, c->linv, d, nc, s));
+      HIPCHK(dk::trsm_whiten(c->L, X + k0 * d, c->xr, whole ? nullptr : c->Zs, c->t64 + k0, c->linv, d, nc, s));
     }
     HIPCHK(dk::axpy_f64(lp, c->t64, 1.0 / (2.0 * c->cfg.alpha * c->cfg.alpha), n, c->t64, s));
     target = c->t64;
@@ -1101,6 +1104,7 @@ static int update_local(diam_ctx* c, int32_t* jitter_used) {
       continue;
     }
     HIPCHK(hipMemcpyAsync(c->Cp + p * dd, c->Lnew, dd * sizeof(double), hipMemcpyDeviceToDevice, s));
+    HIPCHK(hipMemcpyAsync(c->linvb + p * sL, c->linv, sL * sizeof(double), hipMemcpyDeviceToDevice, s));
     HIPCHK(hipMemcpyAsync(c->mpgp + (long)p * d, c->mpg, d * sizeof(double), hipMemcpyDeviceToDevice, s));
     HIPCHK(hipMemsetAsync(c->pinfo + p, 0, sizeof(int32_t), s));
   }
@@ -1161,6 +1165,8 @@ static int update_impl(diam_ctx* c, int32_t* jitter_used, bool refactor) {
   const int ps = prof_begin(c, DIAM_ST_WHITEN);
   HIPCHK(dk::round_factor(c->prec, c->L, c->Llow, d, s));
   HIPCHK(hipMemcpyAsync(c->xr, c->m, d * sizeof(double), hipMemcpyDeviceToDevice, s));
+  // the factorisation left the inverses of the unrounded diagonal blocks
+  if (c->prec != dk::P64) HIPCHK(dk::trsm_inverses(c->L, c->linv, d, s));
   HIPCHK(dk::trsm_whiten(c->L, c->X, c->xr, c->Z, c->zq + (long)c->cur * P, c->linv, d, P, s));
   const int r2 = refresh_h2(c);
   prof_end(c, ps);

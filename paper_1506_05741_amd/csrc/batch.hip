@@ -65,8 +65,8 @@ struct BLay {
 // Tile lists of every phase (host side, uploaded once).
 struct Tiles {
   std::vector<BTile> all;
-  Seg tgt[dk::G_TGT_CONFIGS], decide, step, trigemm, syrk, rowsum, dd, d1, dp, colnorm, triinv;
-  std::vector<Seg> cdiag, cpanel, cupd, tdiag, tupd;
+  Seg tgt[dk::G_TGT_CONFIGS], decide, step, trigemm, syrk, rowsum, dd, d1, colnorm, triinv;
+  std::vector<Seg> cdiag, cpanel, cupd, whiten, wupd;
   std::vector<dk::PItem> pitems;  // one step of the persistent loop
   std::vector<int> pstep;         // items of problem g per step
   int max_nb = 0;
@@ -134,11 +134,7 @@ Tiles build_tiles(const std::vector<int>& dims, int P, int n) {
   T.d1 = T.add(v);
   v.clear();
   for (int g : order)
-    for (int b = 0; b < cdivh((long)dims[g] * P, 256); ++b) v.push_back({g, b, 0});
-  T.dp = T.add(v);
-  v.clear();
-  for (int g : order)
-    for (int p = 0; p < P; ++p) v.push_back({g, p, 0});
+    for (int p = 0; p < P && dk::whiten_rows(dims[g]) < dims[g]; ++p) v.push_back({g, p, 0});
   T.colnorm = T.add(v);
   v.clear();
   for (int g : order)
@@ -146,7 +142,7 @@ Tiles build_tiles(const std::vector<int>& dims, int P, int n) {
   T.triinv = T.add(v);
   for (int g = 0; g < G; ++g) T.max_nb = std::max(T.max_nb, cdivh(dims[g], NB));
   for (int jb = 0; jb < T.max_nb; ++jb) {
-    std::vector<BTile> dg, pn, up, td, tu;
+    std::vector<BTile> dg, pn, up;
     for (int g : order) {
       const int nb = cdivh(dims[g], NB);
       if (jb >= nb) continue;
@@ -154,16 +150,23 @@ Tiles build_tiles(const std::vector<int>& dims, int P, int n) {
       dg.push_back({g, 0, 0});
       for (int i = 0; i < m; ++i) pn.push_back({g, i, 0});
       for (int t = 0; t < m * (m + 1) / 2; ++t) up.push_back({g, t, 0});
-      for (int b = 0; b < cdivh(P, 64); ++b) td.push_back({g, b, 0});
-      const int rem = dims[g] - std::min(dims[g], (jb + 1) * NB);
-      for (int bx = 0; bx < cdivh(rem, 64); ++bx)
-        for (int by = 0; by < cdivh(P, 64); ++by) tu.push_back({g, bx, by});
     }
     T.cdiag.push_back(T.add(dg));
     T.cpanel.push_back(T.add(pn));
     T.cupd.push_back(T.add(up));
-    T.tdiag.push_back(T.add(td));
-    T.tupd.push_back(T.add(tu));
+  }
+  for (int k = 0;; ++k) {
+    std::vector<BTile> wt, wu;
+    for (int g : order) {
+      const int rows = dk::whiten_rows(dims[g]), r0 = k * rows;
+      if (r0 >= dims[g]) continue;
+      for (int b = 0; b < cdivh(P, 16); ++b) wt.push_back({g, b, k});
+      for (int bx = 0; bx < cdivh(std::max(dims[g] - (r0 + rows), 0), 64); ++bx)
+        for (int by = 0; by < cdivh(P, 64); ++by) wu.push_back({g, bx, by});
+    }
+    if (wt.empty()) break;
+    T.whiten.push_back(T.add(wt));
+    T.wupd.push_back(T.add(wu));
   }
   // persistent loop: per step the target tiles of every problem (largest
   // problems first: the longest chains of dependent items start earliest),
@@ -544,6 +547,7 @@ static int retry_failed(diam_batch* b, int32_t* jitter, int* any_fail) {
                            (long)p.ld, p.ld, p.Lp, 1);
         BCHK(hipGetLastError());
         BCHK(hipMemcpyAsync(p.xr, p.m, (size_t)d * 8, hipMemcpyDeviceToDevice, s));
+        BCHK(dk::trsm_inverses(p.L, p.Linv, d, s));
         BCHK(dk::trsm_whiten(p.L, p.X, p.xr, p.Z, p.zq, p.Linv, d, b->P, s));
       } else {
         *any_fail = 1;
@@ -605,10 +609,9 @@ static int enqueue_window(diam_batch* b, hipStream_t s) {
     BCHK(dk::g_chol_step(b->dp, tl(T.cdiag[jb]), T.cdiag[jb].n, tl(T.cpanel[jb]), T.cpanel[jb].n, tl(T.cupd[jb]),
                          T.cupd[jb].n, jb, s));
   BCHK(dk::g_adopt(b->dp, tl(T.dd), T.dd.n, s));
-  BCHK(dk::g_sub_ref(b->dp, tl(T.dp), T.dp.n, P, s));
   BCHK(dk::g_tri_inv(b->dp, tl(T.triinv), T.triinv.n, s));
-  for (int jb = 0; jb < T.max_nb; ++jb)
-    BCHK(dk::g_trsm_step(b->dp, tl(T.tdiag[jb]), T.tdiag[jb].n, tl(T.tupd[jb]), T.tupd[jb].n, jb, P, s));
+  for (int k = 0; k < (int)T.whiten.size(); ++k)
+    BCHK(dk::g_whiten(b->dp, tl(T.whiten[k]), T.whiten[k].n, tl(T.wupd[k]), T.wupd[k].n, k, P, s));
   BCHK(dk::g_colnorm(b->dp, tl(T.colnorm), T.colnorm.n, s));
   return DIAM_OK;
 }
@@ -701,10 +704,9 @@ extern "C" int diam_batch_seed_moments(diam_batch* b, const double* const* S0, c
     BCHK(dk::g_chol_step(b->dp, tl(T.cdiag[jb]), T.cdiag[jb].n, tl(T.cpanel[jb]), T.cpanel[jb].n, tl(T.cupd[jb]),
                          T.cupd[jb].n, jb, s));
   BCHK(dk::g_adopt(b->dp, tl(T.dd), T.dd.n, s));
-  BCHK(dk::g_sub_ref(b->dp, tl(T.dp), T.dp.n, b->P, s));
   BCHK(dk::g_tri_inv(b->dp, tl(T.triinv), T.triinv.n, s));
-  for (int jb = 0; jb < T.max_nb; ++jb)
-    BCHK(dk::g_trsm_step(b->dp, tl(T.tdiag[jb]), T.tdiag[jb].n, tl(T.tupd[jb]), T.tupd[jb].n, jb, b->P, s));
+  for (int k = 0; k < (int)T.whiten.size(); ++k)
+    BCHK(dk::g_whiten(b->dp, tl(T.whiten[k]), T.whiten[k].n, tl(T.wupd[k]), T.wupd[k].n, k, b->P, s));
   BCHK(dk::g_colnorm(b->dp, tl(T.colnorm), T.colnorm.n, s));
   int any = 0;
   int r = retry_failed(b, jitter, &any);

@@ -111,9 +111,14 @@ hipError_t potrf(double* A, int d, int* info, double* Linv, hipStream_t s);
 // copy (f32 column-major, or bf16 hi and lo row-major: L~ = hi + lo); no-op
 // for P64.
 hipError_t round_factor(Prec prec, double* L, void* Llow, int d, hipStream_t s);
-// Z = L^-1 (X - xr) in place of Z (d x P); then zq[p] = ||z_p||^2.
-hipError_t trsm_whiten(const double* L, const double* X, const double* xr, double* Z, double* zq, double* Linv, int d,
-                       int P, hipStream_t s);
+// Linv = the inverses of the diagonal blocks of L.
+hipError_t trsm_inverses(const double* L, double* Linv, int d, hipStream_t s);
+// Rows the whitening solves per launch: all of them for moderate d.
+__host__ __device__ int whiten_rows(int d);
+// Z = L^-1 (X - xr) (d x P), zq[p] = ||z_p||^2 (either may be null; Z only if
+// whiten_rows(d) >= d).
+hipError_t trsm_whiten(const double* L, const double* X, const double* xr, double* Z, double* zq, const double* Linv,
+                       int d, int P, hipStream_t s);
 
 // Normals for steps [s0, s0 + n) of P chains; layout per step d x P column-major.
 hipError_t normals(Prec prec, uint64_t seed, long s0, int n, int d, int P, void* W, void* Wlo, hipStream_t s);
@@ -297,10 +302,11 @@ hipError_t g_cov(const BProb* pr, const BTile* dd_tl, int ndd, hipStream_t s);
 hipError_t g_chol_step(const BProb* pr, const BTile* diag, int ndiag, const BTile* panel, int npanel,
                        const BTile* upd, int nupd, int jb, hipStream_t s);
 hipError_t g_adopt(const BProb* pr, const BTile* dd_tl, int ndd, hipStream_t s);
-hipError_t g_sub_ref(const BProb* pr, const BTile* dp_tl, int ndp, int P, hipStream_t s);
 hipError_t g_tri_inv(const BProb* pr, const BTile* tl, int n, hipStream_t s);
-hipError_t g_trsm_step(const BProb* pr, const BTile* diag, int ndiag, const BTile* upd, int nupd, int jb, int P,
-                       hipStream_t s);
+// piece `piece` of the whitenings (tl: problem, 16-column tile, piece) and its
+// product for the rows below (upd: problem, 64-row tile, 64-column tile)
+hipError_t g_whiten(const BProb* pr, const BTile* tl, int n, const BTile* upd, int nupd, int piece, int P,
+                    hipStream_t s);
 hipError_t g_colnorm(const BProb* pr, const BTile* tl, int n, hipStream_t s);
 hipError_t g_rng(uint64_t seed, const long* win, long nW, long nU, int P, float* W, double* U, hipStream_t s);
 hipError_t g_bump(long* win, double* N, double K, hipStream_t s);
@@ -330,7 +336,7 @@ hipError_t pc_adopt(const double* Cp, const double* mpgp, const int* skip, doubl
 // for the chains with skip[p] == 0), bitwise the one-problem calls.
 hipError_t potrf_batched(double* A, long sA, int d, int* info, double* Linv, long sL, int nprob, hipStream_t s);
 hipError_t trsm_whiten_batched(const double* L, long sA, const double* X, const double* xrp, double* Z, double* zq,
-                               double* Linv, long sL, int d, int P, const int* skip, hipStream_t s);
+                               const double* Linv, long sL, int d, int P, const int* skip, hipStream_t s);
 // G = sum_p Gp[p], h = sum_p hp[:, p].
 hipError_t pc_sum(const double* Gp, const double* hp, double* G, double* h, int d, int P, hipStream_t s);
 

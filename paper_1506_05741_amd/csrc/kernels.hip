@@ -1395,21 +1395,6 @@ hipError_t cov_assemble(const double* S, const double* m, double eps, double* C,
 //                 updated it.
 // ============================================================================
 
-// Inverse of the lower-triangular 64 x 64 block held in Ls (row-major, LDS):
-// lane c forms column c of L^-1 by forward substitution; x[] stays in
-// registers (the loops are fully unrolled), Ls reads are broadcasts.
-// rdiag[q] = 1 / Ls[q][q]; four partial sums break the dependency chain of
-// each substitution step.
-DEV void tri_inverse_col(const double (*Ls)[CHOL_NB + 1], const double* rdiag, double* x, int c) {
-#pragma unroll
-  for (int rr = 0; rr < CHOL_NB; ++rr) {
-    double s[4] = {(rr == c) ? 1.0 : 0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-    for (int q = 0; q < rr; ++q) s[q & 3] = __fma_rn(-Ls[rr][q], x[q], s[q & 3]);
-    x[rr] = ((s[0] + s[1]) + (s[2] + s[3])) * rdiag[rr];
-  }
-}
-
 // lane's value v broadcast from lane `src` (a compile-time lane after unrolling)
 DEV double readlane_f64(double v, int src) {
   const unsigned long long u = (unsigned long long)__double_as_longlong(v);
@@ -1473,99 +1458,15 @@ DEV void tri_inverse_col16(const double (*Ls)[CHOL_NB + 1], const double* rdiag,
   }
 }
 
-DEV void chol_diag_core(double* __restrict__ A, int d, int j0, int jn, double* __restrict__ Linv,
-                        int* __restrict__ info, double* sh) {
-  constexpr int H = CHOL_NB / 4;  // columns per wavefront
-  double (*colp)[CHOL_CB][CHOL_NB] = (double (*)[CHOL_CB][CHOL_NB])sh;  // [parity][column of block][row]
-  double (*Ls)[CHOL_NB + 1] = (double (*)[CHOL_NB + 1])(sh + 2 * CHOL_CB * CHOL_NB);
-  double* rdiag = sh + 2 * CHOL_CB * CHOL_NB + CHOL_NB * (CHOL_NB + 1);
-  double (*Ai)[33] = (double (*)[33])(rdiag + CHOL_NB);
+// The inverse of the lower-triangular block Ls (zeros above the diagonal,
+// which are overwritten; identity past the matrix edge; rdiag its reciprocal
+// diagonal) by four wavefronts; AC: 2 x 32 x 33 + 4 x 16 x 17 doubles of LDS.
+DEV void tri_inverse_core(double (*Ls)[CHOL_NB + 1], const double* rdiag, double* AC, double* __restrict__ Linv) {
+  double (*Ai)[33] = (double (*)[33])AC;
   double (*Ci)[33] = Ai + 32;
   double (*Di)[16][17] = (double (*)[16][17])(Ai + 64);
   const int t = threadIdx.x, r = t & 63;
   const int w = __builtin_amdgcn_readfirstlane(t >> 6);
-  double a[H];
-#pragma unroll
-  for (int k = 0; k < H; ++k) {
-    const int c = w * H + k;
-    double v = 0.0;
-    if (r < jn && c < jn) {
-      if (c <= r) v = A[(j0 + r) + (long)(j0 + c) * d];
-    } else if (c == r) {
-      v = 1.0;  // identity padding beyond the matrix edge
-    }
-    a[k] = v;
-  }
-  // pivot step of column c by the wavefront holding it (its local column kc)
-  auto pivot = [&](int c, int kc, double* dst) {
-    const double piv = readlane_f64(a[kc], c);
-    const double y = rsqrt_nr(piv);
-    const double l = (r == c) ? piv * y : a[kc] * y;
-    a[kc] = l;
-    dst[r] = (r >= c) ? l : 0.0;
-  };
-  // the owner of block (n .. n + CB - 1) factors its columns in turn, each
-  // updating the later ones of the block from its own registers and the
-  // pivot row's value (readlane), and publishes them
-  auto own_block = [&](int n, int buf) {
-    const int k0 = n % H;
-#pragma unroll
-    for (int t = 0; t < CHOL_CB; ++t) {
-      pivot(n + t, k0 + t, colp[buf][t]);
-      const double lt = (r >= n + t) ? a[k0 + t] : 0.0;
-#pragma unroll
-      for (int u = t + 1; u < CHOL_CB; ++u) a[k0 + u] = __fma_rn(-lt, readlane_f64(a[k0 + t], n + u), a[k0 + u]);
-    }
-  };
-  if (w == 0) own_block(0, 0);
-#pragma unroll
-  for (int q = 0; q < CHOL_NB / CHOL_CB; ++q) {
-    const int c0 = CHOL_CB * q, wc = c0 / H, n0 = c0 + CHOL_CB, wn = n0 / H;
-    const int buf = q & 1;
-    __syncthreads();
-    if (n0 < CHOL_NB && w == wn) {
-      // owner of the next block: the published block applied to its columns,
-      // that block factored and published, then the rest of its columns
-      double lb[CHOL_CB];
-#pragma unroll
-      for (int t = 0; t < CHOL_CB; ++t) lb[t] = colp[buf][t][r];
-      const int k0 = n0 % H;
-#pragma unroll
-      for (int u = 0; u < CHOL_CB; ++u)
-#pragma unroll
-        for (int t = 0; t < CHOL_CB; ++t) a[k0 + u] = __fma_rn(-lb[t], colp[buf][t][n0 + u], a[k0 + u]);
-      own_block(n0, buf ^ 1);
-#pragma unroll
-      for (int k = (wn == wc) ? k0 + CHOL_CB : CHOL_CB; k < H; ++k)
-#pragma unroll
-        for (int t = 0; t < CHOL_CB; ++t) a[k] = __fma_rn(-lb[t], colp[buf][t][w * H + k], a[k]);
-    } else if (w > wc) {
-      double lb[CHOL_CB];
-#pragma unroll
-      for (int t = 0; t < CHOL_CB; ++t) lb[t] = colp[buf][t][r];
-#pragma unroll
-      for (int k = 0; k < H; ++k)
-#pragma unroll
-        for (int t = 0; t < CHOL_CB; ++t) a[k] = __fma_rn(-lb[t], colp[buf][t][w * H + k], a[k]);
-    }
-  }
-#pragma unroll
-  for (int k = 0; k < H; ++k) {
-    const int c = w * H + k;
-    if (r < jn && c < jn) A[(j0 + r) + (long)(j0 + c) * d] = (c <= r) ? a[k] : 0.0;
-    Ls[r][c] = (c <= r) ? a[k] : 0.0;
-  }
-  __syncthreads();
-  if (w == 0) {
-    // a pivot that is not > 0 (or NaN) leaves a diagonal root that is not > 0,
-    // and every later pivot inherits the failure: the first bad column is the
-    // lowest such lane
-    const double diag = Ls[r][r];
-    const unsigned long long bad = __ballot(r < jn && !(diag > 0.0));
-    if (r == 0 && bad && *info == 0) *info = j0 + __ffsll((long long)bad);
-    rdiag[r] = 1.0 / diag;
-  }
-  __syncthreads();
   // the inverses of the four 16 x 16 diagonal blocks, one per wavefront
   // (lane c < 16: column c, by substitution; zeros above the diagonal)
   if (r < 16) {
@@ -1657,6 +1558,99 @@ DEV void chol_diag_core(double* __restrict__ A, int d, int j0, int jn, double* _
   }
 }
 
+DEV void chol_diag_core(double* __restrict__ A, int d, int j0, int jn, double* __restrict__ Linv,
+                        int* __restrict__ info, double* sh) {
+  constexpr int H = CHOL_NB / 4;  // columns per wavefront
+  double (*colp)[CHOL_CB][CHOL_NB] = (double (*)[CHOL_CB][CHOL_NB])sh;  // [parity][column of block][row]
+  double (*Ls)[CHOL_NB + 1] = (double (*)[CHOL_NB + 1])(sh + 2 * CHOL_CB * CHOL_NB);
+  double* rdiag = sh + 2 * CHOL_CB * CHOL_NB + CHOL_NB * (CHOL_NB + 1);
+  const int t = threadIdx.x, r = t & 63;
+  const int w = __builtin_amdgcn_readfirstlane(t >> 6);
+  double a[H];
+#pragma unroll
+  for (int k = 0; k < H; ++k) {
+    const int c = w * H + k;
+    double v = 0.0;
+    if (r < jn && c < jn) {
+      if (c <= r) v = A[(j0 + r) + (long)(j0 + c) * d];
+    } else if (c == r) {
+      v = 1.0;  // identity padding beyond the matrix edge
+    }
+    a[k] = v;
+  }
+  // pivot step of column c by the wavefront holding it (its local column kc)
+  auto pivot = [&](int c, int kc, double* dst) {
+    const double piv = readlane_f64(a[kc], c);
+    const double y = rsqrt_nr(piv);
+    const double l = (r == c) ? piv * y : a[kc] * y;
+    a[kc] = l;
+    dst[r] = (r >= c) ? l : 0.0;
+  };
+  // the owner of block (n .. n + CB - 1) factors its columns in turn, each
+  // updating the later ones of the block from its own registers and the
+  // pivot row's value (readlane), and publishes them
+  auto own_block = [&](int n, int buf) {
+    const int k0 = n % H;
+#pragma unroll
+    for (int t = 0; t < CHOL_CB; ++t) {
+      pivot(n + t, k0 + t, colp[buf][t]);
+      const double lt = (r >= n + t) ? a[k0 + t] : 0.0;
+#pragma unroll
+      for (int u = t + 1; u < CHOL_CB; ++u) a[k0 + u] = __fma_rn(-lt, readlane_f64(a[k0 + t], n + u), a[k0 + u]);
+    }
+  };
+  if (w == 0) own_block(0, 0);
+#pragma unroll
+  for (int q = 0; q < CHOL_NB / CHOL_CB; ++q) {
+    const int c0 = CHOL_CB * q, wc = c0 / H, n0 = c0 + CHOL_CB, wn = n0 / H;
+    const int buf = q & 1;
+    __syncthreads();
+    if (n0 < CHOL_NB && w == wn) {
+      // owner of the next block: the published block applied to its columns,
+      // that block factored and published, then the rest of its columns
+      double lb[CHOL_CB];
+#pragma unroll
+      for (int t = 0; t < CHOL_CB; ++t) lb[t] = colp[buf][t][r];
+      const int k0 = n0 % H;
+#pragma unroll
+      for (int u = 0; u < CHOL_CB; ++u)
+#pragma unroll
+        for (int t = 0; t < CHOL_CB; ++t) a[k0 + u] = __fma_rn(-lb[t], colp[buf][t][n0 + u], a[k0 + u]);
+      own_block(n0, buf ^ 1);
+#pragma unroll
+      for (int k = (wn == wc) ? k0 + CHOL_CB : CHOL_CB; k < H; ++k)
+#pragma unroll
+        for (int t = 0; t < CHOL_CB; ++t) a[k] = __fma_rn(-lb[t], colp[buf][t][w * H + k], a[k]);
+    } else if (w > wc) {
+      double lb[CHOL_CB];
+#pragma unroll
+      for (int t = 0; t < CHOL_CB; ++t) lb[t] = colp[buf][t][r];
+#pragma unroll
+      for (int k = 0; k < H; ++k)
+#pragma unroll
+        for (int t = 0; t < CHOL_CB; ++t) a[k] = __fma_rn(-lb[t], colp[buf][t][w * H + k], a[k]);
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < H; ++k) {
+    const int c = w * H + k;
+    if (r < jn && c < jn) A[(j0 + r) + (long)(j0 + c) * d] = (c <= r) ? a[k] : 0.0;
+    Ls[r][c] = (c <= r) ? a[k] : 0.0;
+  }
+  __syncthreads();
+  if (w == 0) {
+    // a pivot that is not > 0 (or NaN) leaves a diagonal root that is not > 0,
+    // and every later pivot inherits the failure: the first bad column is the
+    // lowest such lane
+    const double diag = Ls[r][r];
+    const unsigned long long bad = __ballot(r < jn && !(diag > 0.0));
+    if (r == 0 && bad && *info == 0) *info = j0 + __ffsll((long long)bad);
+    rdiag[r] = 1.0 / diag;
+  }
+  __syncthreads();
+  tri_inverse_core(Ls, rdiag, rdiag + CHOL_NB, Linv);
+}
+
 DEV void chol_diag_block(double* __restrict__ A, int d, int j0, int jn, double* __restrict__ Linv,
                          int* __restrict__ info) {
   __shared__ double sh[CHOL_DIAG_LDS];
@@ -1668,28 +1662,29 @@ __global__ __launch_bounds__(CHOL_DIAG_THREADS) void k_chol_diag(double* __restr
   chol_diag_block(A, d, j0, jn, Linv, info);
 }
 
-// Inverses of all (already factored) diagonal blocks of L, one wave per block.
+// Inverses of all (already factored) diagonal blocks of L, one workgroup per
+// block: the block is read once and inverted as in the factorisation (16 us,
+// a serial chain in code that is cold once a window; 20 to 34 us when each
+// lane of one wavefront substituted for a whole column).  Only for a factor
+// rounded since; the factorisation leaves the unrounded blocks' inverses.
 DEV void tri_inv_block(const double* __restrict__ L, int d, double* __restrict__ Linv, int bx) {
-  __shared__ double Ls[CHOL_NB][CHOL_NB + 1];
-  __shared__ double rdiag[CHOL_NB];
-  const int r = threadIdx.x, j0 = bx * CHOL_NB, jn = min(CHOL_NB, d - j0);
+  __shared__ double sh[CHOL_NB * (CHOL_NB + 1) + CHOL_NB + 2 * 32 * 33 + 4 * 16 * 17];
+  double (*Ls)[CHOL_NB + 1] = (double (*)[CHOL_NB + 1])sh;
+  double* rdiag = sh + CHOL_NB * (CHOL_NB + 1);
+  const int r = threadIdx.x & 63, w = threadIdx.x >> 6, j0 = bx * CHOL_NB, jn = min(CHOL_NB, d - j0);
 #pragma unroll
-  for (int c = 0; c < CHOL_NB; ++c) {
+  for (int k = 0; k < CHOL_NB / 4; ++k) {
+    const int c = w * (CHOL_NB / 4) + k;
     double v = (c == r) ? 1.0 : 0.0;
     if (r < jn && c < jn) v = (c <= r) ? L[(j0 + r) + (long)(j0 + c) * d] : 0.0;
     Ls[r][c] = v;
+    if (c == r) rdiag[r] = 1.0 / v;
   }
   __syncthreads();
-  rdiag[r] = 1.0 / Ls[r][r];
-  __syncthreads();
-  double x[CHOL_NB];
-  tri_inverse_col(Ls, rdiag, x, r);
-  double* out = Linv + (long)bx * CHOL_NB * CHOL_NB;
-#pragma unroll
-  for (int q = 0; q < CHOL_NB; ++q) out[q + r * CHOL_NB] = x[q];
+  tri_inverse_core(Ls, rdiag, rdiag + CHOL_NB, Linv + (long)bx * CHOL_NB * CHOL_NB);
 }
 
-__global__ __launch_bounds__(64) void k_tri_inv(const double* __restrict__ L, int d, double* __restrict__ Linv) {
+__global__ __launch_bounds__(256) void k_tri_inv(const double* __restrict__ L, int d, double* __restrict__ Linv) {
   tri_inv_block(L, d, Linv, blockIdx.x);
 }
 
@@ -1982,47 +1977,153 @@ hipError_t psrf_finalize(const double* mean, const double* m2, int d, int P, dou
 }
 
 // ---- whitening Z = L^-1 (X - xr) ------------------------------------------
-DEV void sub_ref_elem(const double* __restrict__ X, const double* __restrict__ xr, double* __restrict__ Z, int d,
-                      long e) {
-  Z[e] = X[e] - xr[e % d];
+// Rows r0 .. r0 + rows - 1 of Z for 16 columns on one workgroup, with those
+// rows of all 16 columns in LDS: per 64-row block j, four wavefronts form z_j =
+// Linv_j r_j, then all eight subtract L_ij z_j from the rows below, a 16-row
+// tile of L at a time straight from memory (column-major: a quarter wavefront
+// reads 128 contiguous bytes) with the next tile's loads in flight.  The solve
+// is a chain of rows / 64 dependent blocks; a launch per block made a link of
+// it 14 us, in LDS it is 5 to 8 us, the latency of the L tiles (rows^2 / 2 per
+// workgroup, mostly from L2): 39 us at 512 rows and 122 at 1024, where the
+// launches took 150 and 260; 20000 columns of 512 rows 5.5 ms to 0.16.  X
+// null: the rows already hold the right-hand side in Z.  zq (whole columns
+// only): column norms.
+constexpr int WHITEN_MAX = 1024;  // rows whose 16 columns fit the LDS: 128 KB
+
+// Above that, equal pieces of at most 512 rows with one product per piece for
+// the rows below it.
+__host__ __device__ int whiten_rows(int d) {
+  const int nb = (d + CHOL_NB - 1) / CHOL_NB;
+  if (nb * CHOL_NB <= WHITEN_MAX) return nb * CHOL_NB;
+  const int pieces = (nb + 7) / 8;
+  return (nb + pieces - 1) / pieces * CHOL_NB;
 }
 
-__global__ __launch_bounds__(256) void k_sub_ref(const double* __restrict__ X, const double* __restrict__ xr,
-                                                 double* __restrict__ Z, int d, int P) {
-  const long e = (long)blockIdx.x * 256 + threadIdx.x;
-  if (e < (long)d * P) sub_ref_elem(X, xr, Z, d, e);
-}
-
-// Z_j <- Linv_jj Z_j (in place: each workgroup reads its 64 x 64 column
-// block completely before writing it back)
-DEV void trsm_diag_tile(const double* __restrict__ Linv, double* __restrict__ Z, int d, int P, int j0, int jn, int bx) {
-  constexpr int BM = 64, BN = 64, BK = 16;
-  __shared__ double lds[e_lds_elems<double, BM, BN, BK>()];
-  const int p0 = bx * BN;
-  EFrag<double, BM, BN> f;
-  f.zero();
-  e_gemm<double, BM, BN, BK, false, true>(f, Linv, CHOL_NB, jn, Z + j0, d, P, 0, p0, 0, jn, lds);
+DEV void whiten_tile(const double* __restrict__ L, const double* __restrict__ Linv, const double* __restrict__ X,
+                     const double* __restrict__ xr, double* __restrict__ Z, double* __restrict__ zq, int d, int P,
+                     int r0, int rows, int bx) {
+  __shared__ double sh[(WHITEN_MAX + CHOL_NB) * 16];
+  // row i, column c at zs[16 i + (c + i) % 16]: a row is one 128-byte line for
+  // the products, 64 rows of a column cover the banks for the copies
+  double* zs = sh;
+  double (*zj)[16] = (double (*)[16])(sh + WHITEN_MAX * 16);
+  const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lk = lane >> 4;
+  const int q = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int c0 = bx * 16, m = min(rows, d - r0);  // rows that exist
+  const int nb = (m + CHOL_NB - 1) / CHOL_NB;
+  for (int e = tid; e < nb * CHOL_NB * 16; e += 512) {
+    const int i = (e & 63) | ((e >> 10) << 6), c = (e >> 6) & 15;
+    double v = 0.0;
+    if (i < m && c0 + c < P) {
+      const long g = r0 + i + (long)(c0 + c) * d;
+      v = X ? X[g] - xr[r0 + i] : Z[g];
+    }
+    zs[16 * i + ((c + i) & 15)] = v;
+  }
+  const double* Lb = L + (long)r0 * d + r0;  // the diagonal piece
+  const int ntile = (m + 15) / 16;
+  const int off = lk * d + lr;
+  // 16 rows from 16 t, the 64 columns of block j
+  auto load = [&](double* a, int j, int t) {
+    const double* b = Lb + (long)(CHOL_NB * j) * d + 16 * t;
+    if (16 * t + 16 <= m) {
 #pragma unroll
-  for (int m = 0; m < 2; ++m)
+      for (int s = 0; s < 16; ++s) a[s] = (b + (long)(4 * s) * d)[off];
+    } else {
+      const bool in = 16 * t + lr < m;
+      const int o = in ? off : lk * d;
 #pragma unroll
-    for (int n = 0; n < 2; ++n)
+      for (int s = 0; s < 16; ++s) {
+        const double v = (b + (long)(4 * s) * d)[o];
+        a[s] = in ? v : 0.0;
+      }
+    }
+  };
+  double ad[16], a0[16], a1[16], b[16];
+  auto load_diag = [&](int j) {
+    const double* p = Linv + (long)(r0 / CHOL_NB + j) * CHOL_NB * CHOL_NB + 16 * q;
+#pragma unroll
+    for (int s = 0; s < 16; ++s) ad[s] = p[(4 * s + lk) * CHOL_NB + lr];
+  };
+  auto first = [&](int j) { return 4 * (j + 1) + q; };  // this wavefront's first tile below block j
+  auto update = [&](const double* a, int t) {
+    d4_t acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int s = 0; s < 16; ++s) acc = mfma_f64(a[s], b[s], acc);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      double* p = &zs[16 * (16 * t + 4 * r + lk) + ((lr + 4 * r + lk) & 15)];
+      *p -= acc[r];
+    }
+  };
+  if (q < 4) load_diag(0);
+  if (first(0) < ntile) load(a0, 0, first(0));
+  __syncthreads();
+  for (int j = 0; j < nb; ++j) {
+    d4_t z = {0.0, 0.0, 0.0, 0.0};
+    if (q < 4) {
+#pragma unroll
+      for (int s = 0; s < 16; ++s) {
+        const int k = 4 * s + lk;
+        z = mfma_f64(ad[s], zs[16 * (CHOL_NB * j + k) + ((lr + k) & 15)], z);
+      }
+#pragma unroll
+      for (int r = 0; r < 4; ++r) zj[16 * q + 4 * r + lk][lr] = z[r];
+      if (j + 1 < nb) load_diag(j + 1);
+    }
+    __syncthreads();  // z_j formed from all of r_j
+    if (q < 4) {
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        int ti, tj;
-        frag_coords<BM, BN, double>(m, n, r, ti, tj);
-        const int p = p0 + tj;
-        if (ti < jn && p < P) Z[(j0 + ti) + (long)p * d] = f.c[m][n][r];
+        const int i = CHOL_NB * j + 16 * q + 4 * r + lk;
+        zs[16 * i + ((lr + i) & 15)] = z[r];
       }
+    }
+    if (first(j) < ntile) {
+#pragma unroll
+      for (int s = 0; s < 16; ++s) b[s] = zj[4 * s + lk][lr];
+      for (int t = first(j); t < ntile; t += 16) {
+        if (t + 8 < ntile) load(a1, j, t + 8);
+        update(a0, t);
+        if (t + 16 < ntile) load(a0, j, t + 16);
+        else if (first(j + 1) < ntile) load(a0, j + 1, first(j + 1));
+        if (t + 8 < ntile) update(a1, t + 8);
+      }
+    }
+    __syncthreads();  // r_(j+1); z_j's copy read
+  }
+  if (Z)
+    for (int e = tid; e < nb * CHOL_NB * 16; e += 512) {
+      const int i = (e & 63) | ((e >> 10) << 6), c = (e >> 6) & 15;
+      if (i < m && c0 + c < P) Z[r0 + i + (long)(c0 + c) * d] = zs[16 * i + ((c + i) & 15)];
+    }
+  if (zq)
+    for (int c = q; c < 16 && c0 + c < P; c += 8) {
+      // rows 256 apart per partial sum, then their tree: the order of colnorm_block
+      double p[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        p[u] = 0.0;
+        for (int i = lane + 64 * u; i < m; i += 256) {
+          const double v = zs[16 * i + ((c + i) & 15)];
+          p[u] = __fma_rn(v, v, p[u]);
+        }
+      }
+      const double n2 = wave_sum_f64((p[0] + p[2]) + (p[1] + p[3]));
+      if (lane == 0) zq[c0 + c] = n2;
+    }
 }
 
-__global__ __launch_bounds__(256) void k_trsm_diag(const double* __restrict__ Linv, double* __restrict__ Z, int d, int P,
-                                                   int j0, int jn) {
-  trsm_diag_tile(Linv, Z, d, P, j0, jn, blockIdx.x);
+__global__ __launch_bounds__(512) void k_whiten(const double* __restrict__ L, const double* __restrict__ Linv,
+                                                const double* __restrict__ X, const double* __restrict__ xr,
+                                                double* __restrict__ Z, double* __restrict__ zq, int d, int P, int r0,
+                                                int rows) {
+  whiten_tile(L, Linv, X, xr, Z, zq, d, P, r0, rows, blockIdx.x);
 }
 
-// Z_i -= L_ij Z_j for row blocks below j
-DEV void trsm_update_tile(const double* __restrict__ L, double* __restrict__ Z, int d, int P, int j0, int jn, int bx,
-                          int by) {
+// Rows below a piece: Z_i <- (X_i - xr_i, or Z_i where X is null) - L_i,piece Z_piece
+DEV void whiten_update_tile(const double* __restrict__ L, const double* __restrict__ X, const double* __restrict__ xr,
+                            double* __restrict__ Z, int d, int P, int j0, int jn, int bx, int by) {
   constexpr int BM = 64, BN = 64, BK = 16;
   __shared__ double lds[e_lds_elems<double, BM, BN, BK>()];
   const int i0 = j0 + jn + bx * BM, p0 = by * BN;
@@ -2038,23 +2139,16 @@ DEV void trsm_update_tile(const double* __restrict__ L, double* __restrict__ Z, 
         int ti, tj;
         frag_coords<BM, BN, double>(m, n, r, ti, tj);
         const int i = i0 + ti, p = p0 + tj;
-        if (i < d && p < P) Z[i + (long)p * d] -= f.c[m][n][r];
+        if (i >= d || p >= P) continue;
+        const long e = i + (long)p * d;
+        Z[e] = (X ? X[e] - xr[i] : Z[e]) - f.c[m][n][r];
       }
 }
 
-// The update of block column j fused with the diagonal solve of block j + 1:
-// the first row tile of the update is that block, so the workgroup that
-// finishes it applies Linv_{j+1} to its own column tile at once (the barrier
-// orders the tile's stores before the solve's loads in one workgroup; no
-// other workgroup touches that tile before the next launch).
-__global__ __launch_bounds__(256) void k_trsm_update_diag(const double* __restrict__ L, double* __restrict__ Z, int d,
-                                                          int P, int j0, int jn, const double* __restrict__ Linv_next) {
-  trsm_update_tile(L, Z, d, P, j0, jn, blockIdx.x, blockIdx.y);
-  if (blockIdx.x == 0) {
-    __syncthreads();
-    const int j1 = j0 + jn;
-    trsm_diag_tile(Linv_next, Z, d, P, j1, min(CHOL_NB, d - j1), blockIdx.y);
-  }
+__global__ __launch_bounds__(256) void k_whiten_update(const double* __restrict__ L, const double* __restrict__ X,
+                                                       const double* __restrict__ xr, double* __restrict__ Z, int d,
+                                                       int P, int j0, int jn) {
+  whiten_update_tile(L, X, xr, Z, d, P, j0, jn, blockIdx.x, blockIdx.y);
 }
 
 DEV void colnorm_block(const double* __restrict__ Z, int d, double* __restrict__ zq, int p) {
@@ -2077,22 +2171,25 @@ __global__ __launch_bounds__(256) void k_colnorm(const double* __restrict__ Z, i
   colnorm_block(Z, d, zq, blockIdx.x);
 }
 
-hipError_t trsm_whiten(const double* L, const double* X, const double* xr, double* Z, double* zq, double* Linv, int d,
-                       int P, hipStream_t s) {
-  hipLaunchKernelGGL(k_sub_ref, dim3(cdiv((long)d * P, 256)), dim3(256), 0, s, X, xr, Z, d, P);
-  const int nb = cdiv(d, CHOL_NB);
-  hipLaunchKernelGGL(k_tri_inv, dim3(nb), dim3(64), 0, s, L, d, Linv);
-  // block 0's solve, then per block column the update fused with the next block's solve
-  hipLaunchKernelGGL(k_trsm_diag, dim3(cdiv(P, 64)), dim3(256), 0, s, (const double*)Linv, Z, d, P, 0,
-                     min(CHOL_NB, d));
-  for (int jb = 0; jb < nb; ++jb) {
-    const int j0 = jb * CHOL_NB, jn = min(CHOL_NB, d - j0);
-    const int rem = d - (j0 + jn);
+hipError_t trsm_inverses(const double* L, double* Linv, int d, hipStream_t s) {
+  hipLaunchKernelGGL(k_tri_inv, dim3(cdiv(d, CHOL_NB)), dim3(256), 0, s, L, d, Linv);
+  return hipGetLastError();
+}
+
+hipError_t trsm_whiten(const double* L, const double* X, const double* xr, double* Z, double* zq, const double* Linv,
+                       int d, int P, hipStream_t s) {
+  const int rows = whiten_rows(d);
+  const bool whole = rows >= d;
+  for (int r0 = 0; r0 < d; r0 += rows) {
+    const double* x = r0 ? nullptr : X;
+    hipLaunchKernelGGL(k_whiten, dim3(cdiv(P, 16)), dim3(512), 0, s, L, Linv, x, xr, Z, whole ? zq : (double*)nullptr, d, P, r0,
+                  rows);
+    const int rem = d - (r0 + rows);
     if (rem > 0)
-      hipLaunchKernelGGL(k_trsm_update_diag, dim3(cdiv(rem, 64), cdiv(P, 64)), dim3(256), 0, s, L, Z, d, P, j0, jn,
-                         (const double*)(Linv + (long)(jb + 1) * CHOL_NB * CHOL_NB));
+      hipLaunchKernelGGL(k_whiten_update, dim3(cdiv(rem, 64), cdiv(P, 64)), dim3(256), 0, s, L, x, xr, Z, d, P, r0,
+                         rows);
   }
-  if (zq) hipLaunchKernelGGL(k_colnorm, dim3(P), dim3(256), 0, s, Z, d, zq);
+  if (zq && !whole) hipLaunchKernelGGL(k_colnorm, dim3(P), dim3(256), 0, s, Z, d, zq);
   return hipGetLastError();
 }
 
@@ -2145,31 +2242,26 @@ hipError_t potrf_batched(double* A, long sA, int d, int* info, double* Linv, lon
   return hipGetLastError();
 }
 
-__global__ __launch_bounds__(256) void kb_sub_ref(const double* __restrict__ X, const double* __restrict__ xrp,
-                                                  double* __restrict__ Z, int d, int P, const int* __restrict__ skip) {
-  const long e = (long)blockIdx.x * 256 + threadIdx.x;
-  if (e < (long)d * P && !skip[e / d]) Z[e] = X[e] - xrp[e];
-}
-
-__global__ __launch_bounds__(64) void kb_tri_inv(const double* __restrict__ L, long sA, int d,
-                                                 double* __restrict__ Linv, long sL, const int* __restrict__ skip) {
+__global__ __launch_bounds__(512) void kb_whiten(const double* __restrict__ L, long sA, const double* __restrict__ Linv,
+                                                 long sL, const double* __restrict__ X,
+                                                 const double* __restrict__ xrp, double* __restrict__ Z,
+                                                 double* __restrict__ zq, int d, int r0, int rows,
+                                                 const int* __restrict__ skip) {
   const int z = blockIdx.z;
   if (skip[z]) return;
-  tri_inv_block(L + z * sA, d, Linv + z * sL, blockIdx.x);
+  const long o = (long)z * d;
+  whiten_tile(L + z * sA, Linv + z * sL, X ? X + o : nullptr, xrp + o, Z + o, zq ? zq + z : nullptr, d, 1, r0,
+                    rows, 0);
 }
 
-__global__ __launch_bounds__(256) void kb_trsm_diag(const double* __restrict__ Linv, long sL, double* __restrict__ Z,
-                                                    int d, int j0, int jn, const int* __restrict__ skip) {
+__global__ __launch_bounds__(256) void kb_whiten_update(const double* __restrict__ L, long sA,
+                                                        const double* __restrict__ X, const double* __restrict__ xrp,
+                                                        double* __restrict__ Z, int d, int j0, int jn,
+                                                        const int* __restrict__ skip) {
   const int z = blockIdx.z;
   if (skip[z]) return;
-  trsm_diag_tile(Linv + z * sL, Z + (long)z * d, d, 1, j0, jn, 0);
-}
-
-__global__ __launch_bounds__(256) void kb_trsm_update(const double* __restrict__ L, long sA, double* __restrict__ Z,
-                                                      int d, int j0, int jn, const int* __restrict__ skip) {
-  const int z = blockIdx.z;
-  if (skip[z]) return;
-  trsm_update_tile(L + z * sA, Z + (long)z * d, d, 1, j0, jn, blockIdx.x, 0);
+  const long o = (long)z * d;
+  whiten_update_tile(L + z * sA, X ? X + o : nullptr, xrp + o, Z + o, d, 1, j0, jn, blockIdx.x, 0);
 }
 
 __global__ __launch_bounds__(256) void kb_colnorm(const double* __restrict__ Z, int d, double* __restrict__ zq,
@@ -2179,19 +2271,20 @@ __global__ __launch_bounds__(256) void kb_colnorm(const double* __restrict__ Z, 
 }
 
 hipError_t trsm_whiten_batched(const double* L, long sA, const double* X, const double* xrp, double* Z, double* zq,
-                               double* Linv, long sL, int d, int P, const int* skip, hipStream_t s) {
+                               const double* Linv, long sL, int d, int P, const int* skip, hipStream_t s) {
   if (P < 1 || P > 65535) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(kb_sub_ref, dim3(cdiv((long)d * P, 256)), dim3(256), 0, s, X, xrp, Z, d, P, skip);
-  const int nb = cdiv(d, CHOL_NB);
-  hipLaunchKernelGGL(kb_tri_inv, dim3(nb, 1, P), dim3(64), 0, s, L, sA, d, Linv, sL, skip);
-  for (int jb = 0; jb < nb; ++jb) {
-    const int j0 = jb * CHOL_NB, jn = min(CHOL_NB, d - j0);
-    hipLaunchKernelGGL(kb_trsm_diag, dim3(1, 1, P), dim3(256), 0, s,
-                       (const double*)(Linv + (long)jb * CHOL_NB * CHOL_NB), sL, Z, d, j0, jn, skip);
-    const int rem = d - (j0 + jn);
-    if (rem > 0) hipLaunchKernelGGL(kb_trsm_update, dim3(cdiv(rem, 64), 1, P), dim3(256), 0, s, L, sA, Z, d, j0, jn, skip);
+  const int rows = whiten_rows(d);
+  const bool whole = rows >= d;
+  for (int r0 = 0; r0 < d; r0 += rows) {
+    const double* x = r0 ? nullptr : X;
+    hipLaunchKernelGGL(kb_whiten, dim3(1, 1, P), dim3(512), 0, s, L, sA, Linv, sL, x, xrp, Z,
+                  whole ? zq : (double*)nullptr, d, r0, rows, skip);
+    const int rem = d - (r0 + rows);
+    if (rem > 0)
+      hipLaunchKernelGGL(kb_whiten_update, dim3(cdiv(rem, 64), 1, P), dim3(256), 0, s, L, sA, x, xrp, Z, d, r0, rows,
+                         skip);
   }
-  hipLaunchKernelGGL(kb_colnorm, dim3(P), dim3(256), 0, s, Z, d, zq, skip);
+  if (!whole) hipLaunchKernelGGL(kb_colnorm, dim3(P), dim3(256), 0, s, Z, d, zq, skip);
   return hipGetLastError();
 }
 
@@ -3706,30 +3799,24 @@ hipError_t g_adopt(const BProb* pr, const BTile* dd_tl, int ndd, hipStream_t s) 
 }
 
 // whitening z = L^-1 (x - x_ref) of every problem
-__global__ __launch_bounds__(256) void gk_sub_ref(const BProb* __restrict__ pr, const BTile* __restrict__ dp_tl, int P) {
-  const BTile t = dp_tl[blockIdx.x];
-  const BProb& b = pr[t.g];
-  const long e = (long)t.a * 256 + threadIdx.x;
-  if (e < (long)b.d * P) sub_ref_elem(b.X, b.xr, b.Z, b.d, e);
-}
-__global__ __launch_bounds__(64) void gk_tri_inv(const BProb* __restrict__ pr, const BTile* __restrict__ tl) {
+__global__ __launch_bounds__(256) void gk_tri_inv(const BProb* __restrict__ pr, const BTile* __restrict__ tl) {
   const BTile t = tl[blockIdx.x];
   const BProb& b = pr[t.g];
   tri_inv_block(b.L, b.d, b.Linv, t.a);
 }
-__global__ __launch_bounds__(256) void gk_trsm_diag(const BProb* __restrict__ pr, const BTile* __restrict__ tl, int jb,
-                                                    int P) {
+// piece t.b of 16 columns t.a
+__global__ __launch_bounds__(512) void gk_whiten(const BProb* __restrict__ pr, const BTile* __restrict__ tl, int P) {
   const BTile t = tl[blockIdx.x];
   const BProb& b = pr[t.g];
-  const int j0 = jb * CHOL_NB, jn = min(CHOL_NB, b.d - j0);
-  trsm_diag_tile(b.Linv + (long)jb * CHOL_NB * CHOL_NB, b.Z, b.d, P, j0, jn, t.a);
+  const int rows = whiten_rows(b.d), r0 = t.b * rows;
+  whiten_tile(b.L, b.Linv, t.b ? nullptr : b.X, b.xr, b.Z, rows >= b.d ? b.zq : nullptr, b.d, P, r0, rows, t.a);
 }
-__global__ __launch_bounds__(256) void gk_trsm_update(const BProb* __restrict__ pr, const BTile* __restrict__ tl, int jb,
-                                                      int P) {
+__global__ __launch_bounds__(256) void gk_whiten_update(const BProb* __restrict__ pr, const BTile* __restrict__ tl,
+                                                        int piece, int P) {
   const BTile t = tl[blockIdx.x];
   const BProb& b = pr[t.g];
-  const int j0 = jb * CHOL_NB, jn = min(CHOL_NB, b.d - j0);
-  trsm_update_tile(b.L, b.Z, b.d, P, j0, jn, t.a, t.b);
+  const int rows = whiten_rows(b.d);
+  whiten_update_tile(b.L, piece ? nullptr : b.X, b.xr, b.Z, b.d, P, piece * rows, rows, t.a, t.b);
 }
 __global__ __launch_bounds__(256) void gk_colnorm(const BProb* __restrict__ pr, const BTile* __restrict__ tl) {
   const BTile t = tl[blockIdx.x];
@@ -3737,21 +3824,18 @@ __global__ __launch_bounds__(256) void gk_colnorm(const BProb* __restrict__ pr, 
   colnorm_block(b.Z, b.d, b.zq, t.a);  // parity 0 at a window boundary
 }
 
-hipError_t g_sub_ref(const BProb* pr, const BTile* dp_tl, int ndp, int P, hipStream_t s) {
-  hipLaunchKernelGGL(gk_sub_ref, dim3(ndp), dim3(256), 0, s, pr, dp_tl, P);
-  return hipGetLastError();
-}
 hipError_t g_tri_inv(const BProb* pr, const BTile* tl, int n, hipStream_t s) {
-  hipLaunchKernelGGL(gk_tri_inv, dim3(n), dim3(64), 0, s, pr, tl);
+  hipLaunchKernelGGL(gk_tri_inv, dim3(n), dim3(256), 0, s, pr, tl);
   return hipGetLastError();
 }
-hipError_t g_trsm_step(const BProb* pr, const BTile* diag, int ndiag, const BTile* upd, int nupd, int jb, int P,
-                       hipStream_t s) {
-  if (ndiag) hipLaunchKernelGGL(gk_trsm_diag, dim3(ndiag), dim3(256), 0, s, pr, diag, jb, P);
-  if (nupd) hipLaunchKernelGGL(gk_trsm_update, dim3(nupd), dim3(256), 0, s, pr, upd, jb, P);
+hipError_t g_whiten(const BProb* pr, const BTile* tl, int n, const BTile* upd, int nupd, int piece, int P,
+                    hipStream_t s) {
+  hipLaunchKernelGGL(gk_whiten, dim3(n), dim3(512), 0, s, pr, tl, P);
+  if (nupd) hipLaunchKernelGGL(gk_whiten_update, dim3(nupd), dim3(256), 0, s, pr, upd, piece, P);
   return hipGetLastError();
 }
 hipError_t g_colnorm(const BProb* pr, const BTile* tl, int n, hipStream_t s) {
+  if (!n) return hipSuccess;
   hipLaunchKernelGGL(gk_colnorm, dim3(n), dim3(256), 0, s, pr, tl);
   return hipGetLastError();
 }

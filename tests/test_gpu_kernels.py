@@ -161,6 +161,41 @@ def test_proposal_and_scatter_products(prec, d, P, n):
     assert bool(((s.get_f64(diam.F_S, (d, d)) - ref).abs() * (N0 + K) <= scale + scale.T).all())
 
 
+@pytest.mark.parametrize("prec,d,P", [("fp64", 1, 1), ("fp64", 15, 17), ("fp64", 64, 16), ("fp64", 65, 15),
+                                      ("fp64", 130, 33), ("fp32", 511, 20), ("fp64", 512, 64), ("fp64", 577, 3),
+                                      ("fp64", 1023, 18), ("fp64", 1024, 31), ("fp64", 1025, 17), ("fp32", 2051, 5)])
+def test_whitening_by_size(prec, d, P):
+    """Z = L^-1 (x - x_ref) and its column norms after a refactorisation, all
+    rows in one launch up to d = 1024 and in pieces above: the solve's backward
+    error is bounded by d u |L| |Z| per entry (block inverses: times the
+    blocks' condition, here below 8)."""
+    s, R, mu, rn = sampler(prec, d, P, 2, 3 + d, beta=0.3)
+    A = 0.3 * rn(d, d) / np.sqrt(d)
+    S0 = A @ A.T + torch.eye(d, dtype=torch.float64, device="cuda") + torch.outer(mu, mu)
+    assert s.seed_moments(S0.contiguous(), mu, 50.0)[0] == diam.OK
+    L, xr = s.get_f64(diam.F_L, (d, d)).T, s.get_f64(diam.F_XREF, (d,))
+    X, Z, zq = s.get_f64(diam.F_X, (P, d)), s.get_f64(diam.F_Z, (P, d)), s.get_f64(diam.F_ZQ, (P,))
+    assert bool(((Z @ L.T - (X - xr)).abs() <= 8 * (d + 8) * U64 * (Z.abs() @ L.abs().T + X.abs() + xr.abs())).all())
+    assert bool(((zq - (Z * Z).sum(1)).abs() <= (d + 8) * U64 * zq).all())
+
+
+@pytest.mark.parametrize("d,P,M", [(65, 3, 2), (130, 17, 2), (1100, 4, 2)])
+def test_per_chain_whitening(d, P, M):
+    """Every chain's Z after a local update against its own pair, as above."""
+    s, R, mu, rn = sampler("fp64", d, P, 4, 9 + d, beta=0.3, M=M)
+    S0 = torch.eye(d, dtype=torch.float64, device="cuda") + torch.outer(mu, mu)
+    assert s.seed_moments(S0.contiguous(), mu, 50.0)[0] == diam.OK
+    s.step_batch(4)
+    s.merge_moments()
+    assert s.update_proposal()[0] == diam.OK
+    Lp, xrp = s.get_f64(diam.F_LP, (P, d, d)), s.get_f64(diam.F_XREFP, (P, d))
+    X, Z = s.get_f64(diam.F_X, (P, d)), s.get_f64(diam.F_Z, (P, d))
+    for p in range(P):
+        L = torch.tril(Lp[p].T)
+        y, m = L @ Z[p] - (X[p] - xrp[p]), L.abs() @ Z[p].abs() + X[p].abs() + xrp[p].abs()
+        assert bool((y.abs() <= 8 * (d + 8) * U64 * m).all())
+
+
 @pytest.mark.parametrize("n_obs,d,P", [(1, 4, 1), (63, 8, 3), (65, 36, 65), (200, 12, 64), (131, 33, 17),
                                        (131072, 32, 66), (131200, 40, 3)])
 def test_logistic_target_by_size(n_obs, d, P):
