@@ -849,7 +849,7 @@ extern "C" int diam_surrogate_train(diam_ctx* c, const double* X, const double* 
   dk::MlpBufs b = c->mlp;
   for (int t = 0; t < steps; ++t) {
     b.loss = c->mlp.loss + (t % LOSS_HIST);
-    HIPCHK(dk::mlp_train_step(b, n, batch, t, seed, (float)lr, s));
+    HIPCHK(dk::mlp_train_step(b, n, batch, t, steps, nmax, seed, (float)lr, s));
   }
   prof_end(c, ps);
   c->trained = 1;

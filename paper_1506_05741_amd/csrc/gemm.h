@@ -1097,16 +1097,21 @@ __host__ __device__ inline bool t_gemm_ok(const void* A, long lda, int M, const 
 // order, for sums whose order is free.
 // SETS accumulator sets take the slices in turn (slice s to set s mod SETS), as
 // the k-groups of the element engine do; the caller adds them up in order.
-template <typename T, int BM, int BN, int WGM, int WGN, int ST, bool AKC, bool BKC, bool PAIR = false, int SETS = 1>
+// GRP slices per stage of the ring and per barrier, for one tile per CU, where
+// a barrier and an LDS round trip per slice would stretch the chain of
+// products (kend - kbeg then a multiple of GRP slices).
+template <typename T, int BM, int BN, int WGM, int WGN, int ST, bool AKC, bool BKC, bool PAIR = false, int SETS = 1,
+          int GRP = 1>
 DEV void t_gemm(TFrag<T, BM, BN, WGM, WGN> (&fs)[SETS], const T* __restrict__ A, long lda, int M, const T* __restrict__ B,
                 long ldb, int N, int i0, int j0, int kbeg, int kend, T* lds) {
   typedef TFrag<T, BM, BN, WGM, WGN> F;
   constexpr int NW = WGM * WGN, TBK = tbk<T>(), Q = TBK / 4;
   constexpr int SA = BM * TBK, SS = (BM + BN) * TBK;
   constexpr int BLK_A = BM / 8, BLK_B = BN / 8, NBLK = BLK_A + BLK_B;
+  static_assert(GRP == 1 || SETS == 1, "grouped slices: one accumulator set");
   static_assert(NBLK % NW == 0, "copy blocks must divide among the waves");
   constexpr int LPW = NBLK / NW;
-  const int nk = (kend - kbeg) / TBK;  // whole slices
+  const int nk = (kend - kbeg) / (GRP * TBK);  // whole stages
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   // Everything a lane needs is computed before the loop, whose bases advance
   // in scalar registers: FP64 products and other vector instructions do not
@@ -1124,15 +1129,18 @@ DEV void t_gemm(TFrag<T, BM, BN, WGM, WGN> (&fs)[SETS], const T* __restrict__ A,
     }
   };
   auto issue = [&](int kt, int slot) {
-    const char* pa = (const char*)(Ab + kt * sa);
-    const char* pb = (const char*)(Bb + kt * sb);
-    T* st = lds + slot * SS;
 #pragma unroll
-    for (int q = 0; q < LPW; ++q) {
-      const int blk = w * LPW + q;
-      const char* src = blk < BLK_A ? pa : pb;
-      __builtin_amdgcn_global_load_lds((const void*)(src + voff[q]),
-                                       (lds_ptr_t)(st + blk * (1024 / (int)sizeof(T))), 16, 0, 0);
+    for (int g = 0; g < GRP; ++g) {
+      const char* pa = (const char*)(Ab + (kt * GRP + g) * sa);
+      const char* pb = (const char*)(Bb + (kt * GRP + g) * sb);
+      T* st = lds + (slot * GRP + g) * SS;
+#pragma unroll
+      for (int q = 0; q < LPW; ++q) {
+        const int blk = w * LPW + q;
+        const char* src = blk < BLK_A ? pa : pb;
+        __builtin_amdgcn_global_load_lds((const void*)(src + voff[q]),
+                                         (lds_ptr_t)(st + blk * (1024 / (int)sizeof(T))), 16, 0, 0);
+      }
     }
   };
   const int wm = w % WGM, wn = w / WGM;
@@ -1194,17 +1202,18 @@ DEV void t_gemm(TFrag<T, BM, BN, WGM, WGN> (&fs)[SETS], const T* __restrict__ A,
       const int kt = k0 + x;
       if (SETS > 1 && kt >= nk) break;
       // stage kt has landed once at most the later stages' copies are pending
-      if (kt + ST - 2 < nk) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LPW * (ST - 2)) : "memory");
+      if (kt + ST - 2 < nk) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LPW * GRP * (ST - 2)) : "memory");
       else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       asm volatile("s_barrier" ::: "memory");
       // the ring slot refilled here was last read before this barrier
       if (kt + ST - 1 < nk) issue(kt + ST - 1, slot == 0 ? ST - 1 : slot - 1);
-      compute(lds + slot * SS, fs[x]);
+#pragma unroll
+      for (int g = 0; g < GRP; ++g) compute(lds + (slot * GRP + g) * SS, fs[x]);
       slot = slot == ST - 1 ? 0 : slot + 1;
     }
   }
   const int kv = (kend - kbeg) - nk * TBK;
-  if (kv > 0) {  // the last, partial slice, cleared beyond kend
+  if (GRP == 1 && kv > 0) {  // the last, partial slice, cleared beyond kend
     asm volatile("s_barrier" ::: "memory");
     offsets(kv);
     issue(nk, 0);

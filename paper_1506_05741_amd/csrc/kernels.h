@@ -71,7 +71,8 @@ struct MlpBufs {
 };
 size_t mlp_nparam(int D, int H);
 hipError_t mlp_prepare(const MlpBufs& b, const double* X, const double* lp, long n, uint64_t seed, hipStream_t s);
-hipError_t mlp_train_step(const MlpBufs& b, long n, int nb, long tau, uint64_t seed, float lr, hipStream_t s);
+hipError_t mlp_train_step(const MlpBufs& b, long n, int nb, long tau, long steps, int room, uint64_t seed, float lr,
+                          hipStream_t s);
 hipError_t mlp_forward(const MlpBufs& b, const float* xs, int n, hipStream_t s);
 // s_out[j] = surrogate log density of column j of X64 (FP64) or X32 (FP32), d x n
 hipError_t mlp_eval(const MlpBufs& b, const double* X64, const float* X32, int n, double* s_out, hipStream_t s);

@@ -158,43 +158,99 @@ DEV float gelu_grad_f(float a) {
   return 0.5f * (1.f + erff(a * 0.70710678118654752f)) + a * 0.39894228040143268f * expf(-0.5f * a * a);
 }
 
-// C(m, n) = sum_k A(m, k) B(n, k) with the engine's (row, k) operand
-// description, then one of three epilogues:
-//   EPI 0: out[m * ldc + n] = C                       (weight gradients, row-major)
-//   EPI 1: a[m + n * ldc] = C + bias[m]; h = gelu(a)    (forward layer)
-//   EPI 2: out[m + n * ldc] = C * gelu'(aux[m + n*ldc]) (back through GELU)
-template <bool AKC, bool BKC, int EPI>
-__global__ __launch_bounds__(256) void k_mlp_gemm(const float* __restrict__ A, int lda, int M, const float* __restrict__ B,
-                                                  int ldb, int N, int K, float* __restrict__ out, int ldc,
-                                                  const float* __restrict__ bias, const float* __restrict__ aux,
-                                                  float* __restrict__ out2) {
-  constexpr int BM = 64, BN = 64, BK = 32;
-  __shared__ float lds[e_lds_elems<float, BM, BN, BK>()];
-  const int i0 = blockIdx.x * BM, j0 = blockIdx.y * BN;
-  EFrag<float, BM, BN> f;
-  f.zero();
-  e_gemm<float, BM, BN, BK, AKC, BKC>(f, A, lda, M, B, ldb, N, i0, j0, 0, K, lds);
+// Products of the network: C(p, q) = sum_k A(p, k) B(q, k), epi(p, q, C) per
+// element (lanes of a quarter wavefront along q).  The layers are small (256 x
+// 256 outputs, K = 256 or 512, at the default minibatch), so a product is one
+// chain of K / 4 matrix instructions and the time to fill it.  MLP_T32: 32 x 32
+// tiles of the direct-to-LDS engine, one 16 x 16 block and one chain per
+// wavefront; MLP_CHAIN: the same with four slices of K per barrier and 128 KB
+// in flight, where no CU gets a second tile and K is whole stages (a forward
+// layer 6.6 us against 7.9); MLP_T64: its 64 x 64 tiles, where those give every
+// CU two; MLP_E: the element engine for unaligned operands.  All take k in the
+// same order, so the results are bitwise the same (64 x 64 tiles of the element
+// engine, 16 workgroups: 17.4 us a forward layer of 256 samples).
+enum { MLP_CHAIN, MLP_T32, MLP_T64, MLP_E };
+constexpr int mlp_tile(int cfg) { return cfg == MLP_CHAIN || cfg == MLP_T32 ? 32 : 64; }
+constexpr int MLP_GRP = 4, MLP_CHAIN_ST = 4;
+constexpr int mlp_lds(int cfg) {
+  return cfg == MLP_CHAIN ? t_lds_elems<float, 32, 32, MLP_GRP * MLP_CHAIN_ST>()
+       : cfg == MLP_T32   ? t_lds_elems<float, 32, 32, 6>()
+       : cfg == MLP_T64   ? t_lds_elems<float, 64, 64, 3>()
+                          : e_lds_elems<float, 64, 64, 32>();
+}
+
+template <int CFG, bool AKC, bool BKC, typename E>
+DEV void mlp_product(const float* __restrict__ A, int lda, int M, const float* __restrict__ B, int ldb, int N, int K,
+                     int bx, int by, float* lds, E epi) {
+  if constexpr (CFG == MLP_E) {
+    constexpr int BM = 64, BN = 64;
+    EFrag<float, BM, BN> f;
+    f.zero();
+    e_gemm<float, BM, BN, 32, AKC, BKC>(f, A, lda, M, B, ldb, N, bx * BM, by * BN, 0, K, lds);
 #pragma unroll
-  for (int m = 0; m < 2; ++m)
+    for (int m = 0; m < 2; ++m)
 #pragma unroll
-    for (int n = 0; n < 2; ++n)
+      for (int n = 0; n < 2; ++n)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        int ti, tj;
-        frag_coords<BM, BN>(m, n, r, ti, tj);
-        const int i = i0 + ti, j = j0 + tj;
-        if (i >= M || j >= N) continue;
-        const float c = f.c[m][n][r];
-        if (EPI == 0) {
-          out[(long)i * ldc + j] = c;
-        } else if (EPI == 1) {
-          const float a = c + bias[i];
-          out[i + (long)j * ldc] = a;
-          out2[i + (long)j * ldc] = gelu_f(a);
-        } else {
-          out[i + (long)j * ldc] = c * gelu_grad_f(aux[i + (long)j * ldc]);
+        for (int r = 0; r < 4; ++r) {
+          int tp, tq;
+          frag_coords<BM, BN>(m, n, r, tp, tq);
+          if (bx * BM + tp < M && by * BN + tq < N) epi(bx * BM + tp, by * BN + tq, f.c[m][n][r]);
         }
-      }
+  } else {
+    constexpr int BM = mlp_tile(CFG), ST = CFG == MLP_CHAIN ? MLP_CHAIN_ST : CFG == MLP_T32 ? 6 : 3;
+    constexpr int GRP = CFG == MLP_CHAIN ? MLP_GRP : 1;
+    typedef TFrag<float, BM, BM, 2, 2> F;
+    F f;
+    f.zero();
+    t_gemm<float, BM, BM, 2, 2, ST, AKC, BKC, false, 1, GRP>(*(F(*)[1]) & f, A, lda, M, B, ldb, N, bx * BM, by * BM, 0,
+                                                             K, lds);
+#pragma unroll
+    for (int m = 0; m < F::FM; ++m)
+#pragma unroll
+      for (int n = 0; n < F::FN; ++n)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          int tp, tq;
+          t_coords<float, BM, BM, 2, 2>(m, n, r, tp, tq);
+          if (bx * BM + tp < M && by * BM + tq < N) epi(bx * BM + tp, by * BM + tq, f.c[m][n][r]);
+        }
+  }
+}
+
+// blocks of a product of M x N outputs
+static int mlp_blocks(int cfg, int M, int N) { return cdiv(M, mlp_tile(cfg)) * cdiv(N, mlp_tile(cfg)); }
+template <bool AKC, bool BKC>
+static int mlp_cfg(const float* A, int lda, int M, const float* B, int ldb, int N, int K) {
+  if (!t_gemm_ok<float, AKC, BKC>(A, lda, M, B, ldb, N, K)) return MLP_E;
+  if ((long)cdiv(M, 64) * cdiv(N, 64) >= 512) return MLP_T64;
+  return K % (MLP_GRP * tbk<float>()) == 0 && (long)cdiv(M, 32) * cdiv(N, 32) <= 256 ? MLP_CHAIN : MLP_T32;
+}
+
+// Forward layer of n samples: a = W x + bias, h = gelu(a) (O outputs, I inputs)
+template <int CFG>
+__global__ __launch_bounds__(256) void k_mlp_layer(const float* __restrict__ x, int I, int n,
+                                                   const float* __restrict__ W, int O, const float* __restrict__ bias,
+                                                   float* __restrict__ a, float* __restrict__ h) {
+  __shared__ __attribute__((aligned(1024))) float lds[mlp_lds(CFG)];
+  constexpr int T = mlp_tile(CFG);
+  const int nq = (O + T - 1) / T;
+  mlp_product<CFG, true, true>(x, I, n, W, I, O, I, blockIdx.x / nq, blockIdx.x % nq, lds,
+                               [&](int s, int o, float c) {
+                                 const float v = c + bias[o];
+                                 a[o + (long)s * O] = v;
+                                 h[o + (long)s * O] = gelu_f(v);
+                               });
+}
+
+static void mlp_layer(const float* x, int I, int n, const float* W, int O, const float* bias, float* a, float* h,
+                      hipStream_t s) {
+  const int cfg = mlp_cfg<true, true>(x, I, n, W, I, O, I);
+  const dim3 grid(mlp_blocks(cfg, n, O));
+  if (cfg == MLP_CHAIN) hipLaunchKernelGGL(k_mlp_layer<MLP_CHAIN>, grid, dim3(256), 0, s, x, I, n, W, O, bias, a, h);
+  else if (cfg == MLP_T32) hipLaunchKernelGGL(k_mlp_layer<MLP_T32>, grid, dim3(256), 0, s, x, I, n, W, O, bias, a, h);
+  else if (cfg == MLP_T64) hipLaunchKernelGGL(k_mlp_layer<MLP_T64>, grid, dim3(256), 0, s, x, I, n, W, O, bias, a, h);
+  else hipLaunchKernelGGL(k_mlp_layer<MLP_E>, grid, dim3(256), 0, s, x, I, n, W, O, bias, a, h);
 }
 
 // out[s] = sum_o w3[o] h2[o, s] + b3 (one wavefront per sample)
@@ -307,99 +363,182 @@ __global__ __launch_bounds__(256) void k_mlp_init(uint32_t k0, uint32_t k1, int 
   eff[e] = bf16_bits_to_f32(f32_to_bf16_bits(v));
 }
 
-// gather a minibatch: indices from Philox (with replacement), step tau
-__global__ __launch_bounds__(256) void k_mlp_batch(uint32_t k0, uint32_t k1, long tau, const float* __restrict__ Xs,
-                                                   const float* __restrict__ ts, int D, long n, int nb,
-                                                   float* __restrict__ xb, float* __restrict__ tb,
-                                                   int* __restrict__ idx) {
-  const int j = blockIdx.x;
-  __shared__ long src;
+// Minibatches: indices from Philox (with replacement), step tau; one block of
+// 256 threads per pair.
+struct BatchArgs {
+  uint32_t k0, k1;
+  const float *Xs, *ts;
+  int D, nb;
+  long n;
+  float *xb, *tb;
+  int* idx;
+};
+DEV void mlp_batch_pair(const BatchArgs& a, long tau, int j) {
+  // every thread draws the index: no trip through LDS
+  const u4_t r = philox4x32_10({(uint32_t)tau, (uint32_t)(tau >> 32), 8u, (uint32_t)j}, a.k0, a.k1);
+  const uint64_t bits = ((uint64_t)r.x << 32) | r.y;
+  const long src = (long)(bits % (uint64_t)a.n);
   if (threadIdx.x == 0) {
-    const u4_t r = philox4x32_10({(uint32_t)tau, (uint32_t)(tau >> 32), 8u, (uint32_t)j}, k0, k1);
-    const uint64_t bits = ((uint64_t)r.x << 32) | r.y;
-    src = (long)(bits % (uint64_t)n);
-    idx[j] = (int)src;
-    tb[j] = ts[src];
+    a.idx[j] = (int)src;
+    a.tb[j] = a.ts[src];
   }
-  __syncthreads();
-  for (int i = threadIdx.x; i < D; i += 256) xb[i + (long)j * D] = Xs[i + src * D];
+  for (int i = threadIdx.x; i < a.D; i += 256) a.xb[i + (long)j * a.D] = a.Xs[i + src * a.D];
 }
+__global__ __launch_bounds__(256) void k_mlp_batch(BatchArgs a, long tau) { mlp_batch_pair(a, tau, blockIdx.x); }
 
-// dL/dout for L = mean (out - t)^2, and the minibatch loss (one block)
-__global__ __launch_bounds__(256) void k_mlp_loss(const float* __restrict__ out, const float* __restrict__ tb, int nb,
-                                                  float* __restrict__ gout, float* __restrict__ loss) {
-  __shared__ float red[256];
-  float s = 0.f;
-  for (int j = threadIdx.x; j < nb; j += 256) {
-    const float r = out[j] - tb[j];
-    gout[j] = 2.f * r / nb;
-    s = fmaf(r, r, s);
-  }
-  red[threadIdx.x] = s;
+// Sums over the samples of four units' values by 256 threads: thread t holds
+// unit t % 4's partial sum over samples t / 4 + 64 i; combined in the order of
+// a wavefront's butterfly.  Threads 0 to 3 return the totals.
+DEV float unit_sum4(float v, float (*red)[4]) {
+  const int l = threadIdx.x >> 2, u = threadIdx.x & 3;
   __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if (threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
+  red[l][u] = v;
+  for (int o = 32; o > 0; o >>= 1) {
     __syncthreads();
+    if (l < o) red[l][u] += red[l + o][u];
   }
-  if (threadIdx.x == 0) *loss = red[0] / nb;
+  return red[0][u];
 }
 
-// output layer backward: gW3[o] = sum_s gout[s] h2[o,s] (one wave per o),
-// gb3 = sum gout; ga2[o,s] = w3[o] gout[s] gelu'(a2[o,s])
-__global__ __launch_bounds__(256) void k_mlp_out_bwd(const float* __restrict__ w3, const float* __restrict__ gout,
-                                                     const float* __restrict__ h2, const float* __restrict__ a2, int H,
-                                                     int nb, float* __restrict__ gW3, float* __restrict__ gb3,
-                                                     float* __restrict__ ga2) {
-  const int lane = threadIdx.x & 63, o = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (o < H) {
-    float acc = 0.f;
-    for (int s = lane; s < nb; s += 64) acc = fmaf(gout[s], h2[o + (long)s * H], acc);
-    acc = wave_sum_f32(acc);
-    if (lane == 0) gW3[o] = acc;
-    for (int s = lane; s < nb; s += 64) ga2[o + (long)s * H] = w3[o] * gout[s] * gelu_grad_f(a2[o + (long)s * H]);
+// Output layer backward for L = mean (out - t)^2, g[s] = dL/dout[s]: gW3[o] =
+// sum_s g[s] h2[o,s], ga2[o,s] = w3[o] g[s] gelu'(a2[o,s]) and gb2[o] = sum_s
+// ga2[o,s] per block of four units, the loss and gb3 = sum g on the last block.
+// Bound by the special functions (more units a block leave CUs idle: 14 us with
+// 16) and by one trip to memory.
+__global__ __launch_bounds__(256) void k_mlp_out_bwd(const float* __restrict__ w3, const float* __restrict__ out,
+                                                     const float* __restrict__ tb, const float* __restrict__ h2,
+                                                     const float* __restrict__ a2, int H, int nb,
+                                                     float* __restrict__ gW3, float* __restrict__ gb3,
+                                                     float* __restrict__ ga2, float* __restrict__ gb2,
+                                                     float* __restrict__ loss) {
+  const int t = threadIdx.x;
+  if (blockIdx.x == gridDim.x - 1) {
+    __shared__ float red[256];
+    float s = 0.f;
+    for (int j = t; j < nb; j += 256) {
+      const float r = out[j] - tb[j];
+      s = fmaf(r, r, s);
+    }
+    red[t] = s;
+    __syncthreads();
+    for (int o = 128; o > 0; o >>= 1) {
+      if (t < o) red[t] += red[t + o];
+      __syncthreads();
+    }
+    if (t == 0) *loss = red[0] / nb;
+    if (t < 64) {
+      float b = 0.f;
+      for (int j = t; j < nb; j += 64) b += 2.f * (out[j] - tb[j]) / nb;
+      b = wave_sum_f32(b);
+      if (t == 0) gb3[0] = b;
+    }
+    return;
   }
-  if (blockIdx.x == 0 && threadIdx.x < 64) {
-    float b = 0.f;
-    for (int s = lane; s < nb; s += 64) b += gout[s];
-    b = wave_sum_f32(b);
-    if (lane == 0) gb3[0] = b;
+  __shared__ float red[64][4];
+  const int o = blockIdx.x * 4 + (t & 3);
+  const bool in = o < H;
+  const float w = in ? w3[o] : 0.f;
+  float vw = 0.f, vb = 0.f;
+#pragma unroll 4
+  for (int s = t >> 2; s < nb; s += 64) {
+    const long e = (in ? o : 0) + (long)s * H;
+    const float g = 2.f * (out[s] - tb[s]) / nb;
+    const float ga = w * g * gelu_grad_f(a2[e]);
+    if (in) ga2[e] = ga;
+    vw = fmaf(g, h2[e], vw);
+    vb += ga;
+  }
+  const float sw = unit_sum4(vw, red), sb = unit_sum4(vb, red);
+  if (t < 4 && in) {
+    gW3[o] = sw;
+    gb2[o] = sb;
   }
 }
 
-// bias gradient: gb[o] = sum_s g[o + s*H] (one wave per o)
-__global__ __launch_bounds__(256) void k_mlp_bias_grad(const float* __restrict__ g, int H, int nb,
-                                                       float* __restrict__ gb) {
-  const int lane = threadIdx.x & 63, o = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (o >= H) return;
-  float acc = 0.f;
-  for (int s = lane; s < nb; s += 64) acc += g[o + (long)s * H];
-  acc = wave_sum_f32(acc);
-  if (lane == 0) gb[o] = acc;
+// The two products on ga2: gW2 = ga2 h1^T (the first blocks) and ga1 = (W2^T
+// ga2) * gelu'(a1).  Neither fills the chip; one launch runs both.
+template <int CW, int CG>
+__global__ __launch_bounds__(256) void k_mlp_hidden_bwd(const float* __restrict__ ga2, const float* __restrict__ h1,
+                                                        const float* __restrict__ W2, const float* __restrict__ a1,
+                                                        int H, int nb, float* __restrict__ gW2,
+                                                        float* __restrict__ ga1) {
+  constexpr int NW = mlp_lds(CW), NG = mlp_lds(CG), TW = mlp_tile(CW), TG = mlp_tile(CG);
+  __shared__ __attribute__((aligned(1024))) float lds[NW > NG ? NW : NG];
+  const int nw = (H + TW - 1) / TW, ng = (H + TG - 1) / TG, b = blockIdx.x;
+  if (b < nw * nw) {
+    mlp_product<CW, false, false>(ga2, H, H, h1, H, H, nb, b / nw, b % nw, lds,
+                                  [&](int o, int i, float c) { gW2[(long)o * H + i] = c; });
+  } else {
+    const int k = b - nw * nw;
+    mlp_product<CG, true, false>(ga2, H, nb, W2, H, H, H, k / ng, k % ng, lds, [&](int s, int i, float c) {
+      const long e = i + (long)s * H;
+      ga1[e] = c * gelu_grad_f(a1[e]);
+    });
+  }
 }
 
 // Adam (Kingma & Ba 2015), bias-corrected; eff = bf16 rounding of the master
-__global__ __launch_bounds__(256) void k_mlp_adam(float* __restrict__ master, float* __restrict__ eff,
-                                                  const float* __restrict__ g, float* __restrict__ m,
-                                                  float* __restrict__ v, long nparam, float lr, float b1, float b2,
-                                                  float eps, float c1, float c2) {
-  const long e = (long)blockIdx.x * 256 + threadIdx.x;
-  if (e >= nparam) return;
-  const float gg = g[e];
-  const float mm = b1 * m[e] + (1.f - b1) * gg;
-  const float vv = b2 * v[e] + (1.f - b2) * gg * gg;
-  m[e] = mm;
-  v[e] = vv;
-  const float w = master[e] - lr * (mm / c1) / (sqrtf(vv / c2) + eps);
-  master[e] = w;
-  eff[e] = bf16_bits_to_f32(f32_to_bf16_bits(w));
+struct AdamArgs {
+  float *master, *eff, *g, *m, *v;
+  float lr, b1, b2, eps, c1, c2;
+};
+DEV void adam_elem(const AdamArgs& a, long e, float gg) {
+  const float mm = a.b1 * a.m[e] + (1.f - a.b1) * gg;
+  const float vv = a.b2 * a.v[e] + (1.f - a.b2) * gg * gg;
+  a.m[e] = mm;
+  a.v[e] = vv;
+  const float w = a.master[e] - a.lr * (mm / a.c1) / (sqrtf(vv / a.c2) + a.eps);
+  a.master[e] = w;
+  a.eff[e] = bf16_bits_to_f32(f32_to_bf16_bits(w));
+}
+
+// The step's last launch: gW1 = ga1 xb^T with Adam on each element as it is
+// formed, then blocks of four units for gb1 = rowsum(ga1) and its step, then
+// the other parameters' steps (nothing reads them until the next minibatch),
+// then the next minibatch's pairs (next.nb = 0: none) into another buffer.
+template <int CFG>
+__global__ __launch_bounds__(256) void k_mlp_input_bwd(const float* __restrict__ ga1, const float* __restrict__ xb,
+                                                       int D, int H, int nb, AdamArgs a, BatchArgs next,
+                                                       long tau) {
+  __shared__ __attribute__((aligned(1024))) float lds[mlp_lds(CFG)];
+  constexpr int T = mlp_tile(CFG);
+  const int nq = (D + T - 1) / T, np = (H + T - 1) / T, t = threadIdx.x;
+  int b = blockIdx.x;
+  if (b < np * nq) {
+    mlp_product<CFG, false, false>(ga1, H, H, xb, D, D, nb, b / nq, b % nq, lds, [&](int o, int i, float c) {
+      const long e = (long)o * D + i;
+      a.g[e] = c;
+      adam_elem(a, e, c);
+    });
+    return;
+  }
+  b -= np * nq;
+  const long bias1 = (long)H * D, rest = bias1 + H, end = rest + (long)H * H + 2 * H + 1;
+  if (b < (H + 3) / 4) {
+    const int o = b * 4 + (t & 3);
+    float v = 0.f;
+#pragma unroll 4
+    for (int s = t >> 2; s < nb; s += 64) v += o < H ? ga1[o + (long)s * H] : 0.f;
+    const float sum = unit_sum4(v, (float (*)[4])lds);
+    if (t < 4 && o < H) {
+      a.g[bias1 + o] = sum;
+      adam_elem(a, bias1 + o, sum);
+    }
+    return;
+  }
+  b -= (H + 3) / 4;
+  if (b < (end - rest + 255) / 256) {
+    const long e = rest + (long)b * 256 + t;
+    if (e < end) adam_elem(a, e, a.g[e]);
+    return;
+  }
+  mlp_batch_pair(next, tau + 1, b - (int)((end - rest + 255) / 256));
 }
 
 __global__ void k_fill_f32(float* p, long n) {
   const long e = (long)blockIdx.x * 256 + threadIdx.x;
   if (e < n) p[e] = 0.f;
 }
-
-static dim3 g2(int M, int N) { return dim3(cdiv(M, 64), cdiv(N, 64)); }
 
 size_t mlp_nparam(int D, int H) { return (size_t)H * D + H + (size_t)H * H + H + H + 1; }
 
@@ -412,10 +551,8 @@ hipError_t mlp_forward(const MlpBufs& b, const float* xs, int n, hipStream_t s) 
   const float* b2 = W2 + (long)H * H;
   const float* W3 = b2 + H;
   const float* b3 = W3 + H;
-  hipLaunchKernelGGL((k_mlp_gemm<true, true, 1>), g2(H, n), dim3(256), 0, s, W1, D, H, xs, D, n, D, b.a1, H, b1,
-                     (const float*)nullptr, b.h1);
-  hipLaunchKernelGGL((k_mlp_gemm<true, true, 1>), g2(H, n), dim3(256), 0, s, W2, H, H, (const float*)b.h1, H, n, H,
-                     b.a2, H, b2, (const float*)nullptr, b.h2);
+  mlp_layer(xs, D, n, W1, H, b1, b.a1, b.h1, s);
+  mlp_layer(b.h1, H, n, W2, H, b2, b.a2, b.h2, s);
   hipLaunchKernelGGL(k_mlp_out, dim3(cdiv(n, 4)), dim3(256), 0, s, W3, b3, (const float*)b.h2, H, n, b.out);
   return hipGetLastError();
 }
@@ -445,42 +582,55 @@ hipError_t mlp_prepare(const MlpBufs& b, const double* X, const double* lp, long
   return hipGetLastError();
 }
 
-// One Adam step on a Philox-drawn minibatch of nb training pairs.
-hipError_t mlp_train_step(const MlpBufs& b, long n, int nb, long tau, uint64_t seed, float lr, hipStream_t s) {
+// One Adam step on a Philox-drawn minibatch of nb training pairs, step tau of
+// `steps`.  Where two minibatches fit xb (room columns), they take its halves
+// in turn and a step's last launch gathers the next step's (3 us a step as a
+// launch of its own).
+hipError_t mlp_train_step(const MlpBufs& b, long n, int nb, long tau, long steps, int room, uint64_t seed, float lr,
+                          hipStream_t s) {
   const int D = b.D, H = b.H;
   const long np = (long)mlp_nparam(D, H);
-  float* gW1 = b.grad;
-  float* gb1 = gW1 + (long)H * D;
-  float* gW2 = gb1 + H;
+  float* gW2 = b.grad + (long)H * D + H;
   float* gb2 = gW2 + (long)H * H;
   float* gW3 = gb2 + H;
-  float* gb3 = gW3 + H;
   const float* W2 = b.eff + (long)H * D + H;
   const float* W3 = W2 + (long)H * H + H;
-  hipLaunchKernelGGL(k_mlp_batch, dim3(nb), dim3(256), 0, s, (uint32_t)seed, (uint32_t)(seed >> 32), tau,
-                     (const float*)b.Xs, (const float*)b.ts, D, n, nb, b.xb, b.tb, b.bidx);
-  hipError_t e = mlp_forward(b, b.xb, nb, s);
+  const float* ga1 = b.ga1;
+  const bool ahead = 2L * nb <= room;
+  float* half[2] = {b.xb, ahead ? b.xb + (long)nb * D : b.xb};
+  BatchArgs ba{(uint32_t)seed, (uint32_t)(seed >> 32), b.Xs, b.ts, D, nb, n, half[tau & 1], b.tb, b.bidx};
+  const float* xb = ba.xb;
+  if (tau == 0 || !ahead) hipLaunchKernelGGL(k_mlp_batch, dim3(nb), dim3(256), 0, s, ba, tau);
+  ba.xb = half[(tau + 1) & 1];
+  if (!ahead || tau + 1 >= steps) ba.nb = 0;
+  hipError_t e = mlp_forward(b, xb, nb, s);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_mlp_loss, dim3(1), dim3(256), 0, s, (const float*)b.out, (const float*)b.tb, nb, b.gout, b.loss);
-  hipLaunchKernelGGL(k_mlp_out_bwd, dim3(cdiv(H, 4)), dim3(256), 0, s, W3, (const float*)b.gout, (const float*)b.h2,
-                     (const float*)b.a2, H, nb, gW3, gb3, b.ga2);
-  // gW2 = ga2 h1^T ; gb2 = rowsum(ga2)
-  hipLaunchKernelGGL((k_mlp_gemm<false, false, 0>), g2(H, H), dim3(256), 0, s, (const float*)b.ga2, H, H,
-                     (const float*)b.h1, H, H, nb, gW2, H, (const float*)nullptr, (const float*)nullptr,
-                     (float*)nullptr);
-  hipLaunchKernelGGL(k_mlp_bias_grad, dim3(cdiv(H, 4)), dim3(256), 0, s, (const float*)b.ga2, H, nb, gb2);
-  // ga1 = (W2^T ga2) * gelu'(a1)
-  hipLaunchKernelGGL((k_mlp_gemm<false, true, 2>), g2(H, nb), dim3(256), 0, s, W2, H, H, (const float*)b.ga2, H, nb, H,
-                     b.ga1, H, (const float*)nullptr, (const float*)b.a1, (float*)nullptr);
-  // gW1 = ga1 xb^T ; gb1 = rowsum(ga1)
-  hipLaunchKernelGGL((k_mlp_gemm<false, false, 0>), g2(H, D), dim3(256), 0, s, (const float*)b.ga1, H, H,
-                     (const float*)b.xb, D, D, nb, gW1, D, (const float*)nullptr, (const float*)nullptr,
-                     (float*)nullptr);
-  hipLaunchKernelGGL(k_mlp_bias_grad, dim3(cdiv(H, 4)), dim3(256), 0, s, (const float*)b.ga1, H, nb, gb1);
-  const float b1 = 0.9f, b2 = 0.999f;
-  const float c1 = 1.f - powf(b1, (float)(tau + 1)), c2 = 1.f - powf(b2, (float)(tau + 1));
-  hipLaunchKernelGGL(k_mlp_adam, dim3((unsigned)((np + 255) / 256)), dim3(256), 0, s, b.master, b.eff,
-                     (const float*)b.grad, b.m, b.m + np, np, lr, b1, b2, 1e-8f, c1, c2);
+  hipLaunchKernelGGL(k_mlp_out_bwd, dim3(cdiv(H, 4) + 1), dim3(256), 0, s, W3, (const float*)b.out,
+                     (const float*)b.tb, (const float*)b.h2, (const float*)b.a2, H, nb, gW3, gW3 + H, b.ga2, gb2,
+                     b.loss);
+  const float *ga2 = b.ga2, *h1 = b.h1, *a1 = b.a1;
+  const int cw = mlp_cfg<false, false>(ga2, H, H, h1, H, H, nb), cg = mlp_cfg<true, false>(ga2, H, nb, W2, H, H, H);
+  const auto blocks2 = [&](int w, int g) { return dim3(mlp_blocks(w, H, H) + mlp_blocks(g, nb, H)); };
+  if (cw > MLP_T32 || cg > MLP_T64) return hipErrorInvalidValue;  // H = 256: aligned, few tiles
+  if (cw == MLP_CHAIN && cg == MLP_CHAIN)
+    hipLaunchKernelGGL((k_mlp_hidden_bwd<MLP_CHAIN, MLP_CHAIN>), blocks2(cw, cg), dim3(256), 0, s, ga2, h1, W2, a1, H,
+                       nb, gW2, b.ga1);
+  else if (cg == MLP_T64)
+    hipLaunchKernelGGL((k_mlp_hidden_bwd<MLP_T32, MLP_T64>), blocks2(MLP_T32, cg), dim3(256), 0, s, ga2, h1, W2, a1,
+                       H, nb, gW2, b.ga1);
+  else
+    hipLaunchKernelGGL((k_mlp_hidden_bwd<MLP_T32, MLP_T32>), blocks2(MLP_T32, MLP_T32), dim3(256), 0, s, ga2, h1, W2,
+                       a1, H, nb, gW2, b.ga1);
+  AdamArgs ad{b.master, b.eff, b.grad, b.m, b.m + np, lr, 0.9f, 0.999f, 1e-8f, 0.f, 0.f};
+  ad.c1 = 1.f - powf(ad.b1, (float)(tau + 1));
+  ad.c2 = 1.f - powf(ad.b2, (float)(tau + 1));
+  // not one tile per CU: the other blocks of this launch share the CUs
+  const int cfg1 = std::max(mlp_cfg<false, false>(ga1, H, H, xb, D, D, nb), (int)MLP_T32);
+  const dim3 grid1(mlp_blocks(cfg1, H, D) + cdiv(H, 4) + cdiv((long)H * H + 2 * H + 1, 256) + ba.nb);
+  if (cfg1 == MLP_T32) hipLaunchKernelGGL(k_mlp_input_bwd<MLP_T32>, grid1, dim3(256), 0, s, ga1, xb, D, H, nb, ad, ba, tau);
+  else if (cfg1 == MLP_T64)
+    hipLaunchKernelGGL(k_mlp_input_bwd<MLP_T64>, grid1, dim3(256), 0, s, ga1, xb, D, H, nb, ad, ba, tau);
+  else hipLaunchKernelGGL(k_mlp_input_bwd<MLP_E>, grid1, dim3(256), 0, s, ga1, xb, D, H, nb, ad, ba, tau);
   return hipGetLastError();
 }
 
@@ -574,10 +724,8 @@ hipError_t da_screen(const MlpBufs& b, const float* V, int d, int P, int nch, co
   const float* b2 = W2 + (long)H * H;
   const float* W3 = b2 + H;
   const float* b3 = W3 + H;
-  hipLaunchKernelGGL((k_mlp_gemm<true, true, 1>), g2(H, P), dim3(256), 0, s, W1, b.D, H, (const float*)b.xb, b.D, P,
-                     b.D, b.a1, H, b1, (const float*)nullptr, b.h1);
-  hipLaunchKernelGGL((k_mlp_gemm<true, true, 1>), g2(H, P), dim3(256), 0, s, W2, H, H, (const float*)b.h1, H, P, H,
-                     b.a2, H, b2, (const float*)nullptr, b.h2);
+  mlp_layer(b.xb, b.D, P, W1, H, b1, b.a1, b.h1, s);
+  mlp_layer(b.h1, H, P, W2, H, b2, b.a2, b.h2, s);
   hipLaunchKernelGGL(k_da_screen, dim3(1), dim3(1024), 0, s, W3, b3, (const float*)b.h2, H, (const float*)b.stats, P,
                      nch, s_cur, zq_part, zq, u1, inv2a2, resid, s_new, pass, slot, idx, nsurv, npass);
   hipLaunchKernelGGL(k_da_gather, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, s, V, (const int*)idx,

@@ -196,6 +196,54 @@ def test_per_chain_whitening(d, P, M):
         assert bool((y.abs() <= 8 * (d + 8) * U64 * m).all())
 
 
+@pytest.mark.parametrize("D,nb", [(1, 1), (4, 33), (30, 64), (64, 256), (101, 65), (512, 300), (520, 512)])
+def test_training_step_by_size(D, nb):
+    """Gradient and Adam step of one minibatch at the sizes of the network's
+    product kernels (unaligned inputs on the element engine), against FP64
+    products of the same rounded weights.  A gradient entry is a chain of at
+    most three products of D, 256 and nb terms in FP32: (D + 512 + nb) u of the
+    gradient with every factor taken positive, doubled for the activations'
+    own rounding; Adam's first step is lr g / (|g| + eps) up to 8 u."""
+    H, n = 256, 700
+    s, R, mu, rn = sampler("fp32", D, 4, 2, 31 + D, surrogate=1, train_max=n)
+    X = rn(n, D)
+    lp = -0.5 * (X * X).sum(1) + X.sin().sum(1)
+    shapes = [(H, D), (H,), (H, H), (H,), (1, H), (1,)]
+    cut = lambda f: [t.reshape(sh) for t, sh in zip(torch.split(s.get(f).view(torch.float32).double(),
+                                                                [int(np.prod(sh)) for sh in shapes]), shapes)]
+    dg = lambda a: 0.5 * (1 + torch.erf(a / np.sqrt(2))) + a * torch.exp(-a * a / 2) / np.sqrt(2 * np.pi)
+    for steps in (1, 2):  # the second step's minibatch is gathered by the first
+        s.surrogate_train(X, lp, steps=steps - 1, batch=nb, lr=1e-3, seed=7)
+        p0, st = cut(diam.F_MLP_PARAMS), s.get(diam.F_MLP_STATS).view(torch.float32)
+        s.surrogate_train(X, lp, steps=steps, batch=nb, lr=1e-3, seed=7)
+        g, p1, idx = cut(diam.F_MLP_GRAD), cut(diam.F_MLP_PARAMS), s.get(diam.F_MLP_BATCH).view(torch.int32).long()
+        W1, b1, W2, b2, W3, b3 = [p.bfloat16().double() for p in p0]
+        x = ((X[idx].float() - st[:D]) * st[D:2 * D]).double()
+        t = ((lp[idx] - lp.mean()) / lp.std(correction=0)).float().double()
+        a1 = x @ W1.T + b1
+        h1 = torch.nn.functional.gelu(a1)
+        a2 = h1 @ W2.T + b2
+        h2 = torch.nn.functional.gelu(a2)
+        r = 2 * ((h2 @ W3.T + b3)[:, 0] - t) / nb
+        ga2 = r[:, None] * W3 * dg(a2)
+        ga1 = (ga2 @ W2) * dg(a1)
+        ref = [ga1.T @ x, ga1.sum(0), ga2.T @ h1, ga2.sum(0), (r @ h2)[None], r.sum()[None]]
+        # every factor positive, residuals with the size of their terms
+        ra = (2 * (h2.abs() @ W3.abs().T + b3.abs())[:, 0] + 2 * t.abs()) / nb
+        m2 = ra[:, None] * W3.abs() * 1.2
+        m1 = (m2 @ W2.abs()) * 1.2
+        xa, ha1 = x.abs() + 1e-3, x.abs() @ W1.abs().T + b1.abs() + 1e-3
+        ha2 = ha1 @ W2.abs().T + b2.abs()
+        mag = [m1.T @ xa, m1.sum(0), m2.T @ ha1, m2.sum(0), (ra @ ha2)[None], ra.sum()[None]]
+        # the activations' rounding, relative to their own terms, moves gelu and gelu'
+        amp = 1 + float(ha2.max())
+        for got, want, m, q0, q1 in zip(g, ref, mag, p0, p1):
+            assert bool(((got - want).abs() <= 2 * (D + 512 + nb) * 2.0 ** -24 * amp * m).all())
+            if steps == 1:
+                step = 1e-3 * got / (got.abs() + 1e-8)
+                assert bool(((q0 - q1 - step).abs() <= 1e-3 * 32 * 2.0 ** -24 + 2.0 ** -24 * q0.abs()).all())
+
+
 @pytest.mark.parametrize("n_obs,d,P", [(1, 4, 1), (63, 8, 3), (65, 36, 65), (200, 12, 64), (131, 33, 17),
                                        (131072, 32, 66), (131200, 40, 3)])
 def test_logistic_target_by_size(n_obs, d, P):
