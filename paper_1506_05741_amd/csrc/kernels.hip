@@ -1414,25 +1414,27 @@ DEV double readlane_f64(double v, int src) {
 // columns in turn (each updating the later ones of the block from its own
 // registers and the pivot row's value by readlane) and publishes them before
 // its other updates, so one barrier per CB columns separates consecutive
-// blocks (per column in the earlier design: 20 to 9 us per 64 x 64 core,
-// the factor bitwise unchanged).  The pivot step forms
-// y ~ 1/sqrt(pivot) by the hardware reciprocal square root refined with two
-// Newton-Raphson steps, then L(c, c) = pivot y and L(r, c) = a(r, c) y; a
-// pivot that is not > 0 (or NaN) gives a diagonal that is not > 0.  Each
-// entry of the lower triangle sees the updates in the same order as a
-// right-looking factorisation.  The block inverse is formed as
-// [[A, 0], [B, C]]^-1 = [[A^-1, 0], [-C^-1 B A^-1, C^-1]] twice: each
-// wavefront inverts one 16 x 16 diagonal block by substitution (lane c a
-// column), two wavefronts per 32 x 32 half combine two of them with two
-// 16 x 16 products, then all four combine the halves (32 x 32 products).
-// LDS: two buffers of CB columns, the factored block (whose zero upper
-// triangle then holds the products' intermediate terms), the reciprocal
-// diagonal, A^-1 and C^-1 of the 32 x 32 halves, the four 16 x 16 inverses.
+// blocks.  The pivot step forms y ~ 1/sqrt(pivot) by the hardware reciprocal
+// square root refined with two Newton-Raphson steps, then L(c, c) = pivot y and
+// L(r, c) = a(r, c) y; a pivot that is not > 0 (or NaN) gives a diagonal that
+// is not > 0.  Each entry of the lower triangle sees the updates in the same
+// order as a right-looking factorisation.  The block inverse is formed as [[A,
+// 0], [B, C]]^-1 = [[A^-1, 0], [-C^-1 B A^-1, C^-1]] twice: each wavefront
+// inverts one 16 x 16 diagonal block by substitution, then the 16 x 16 and 32 x
+// 32 products run on the matrix cores, whose FP64 product is the chain of fused
+// multiply-adds over k, bit for bit.
+// All of it is latency, in clock cycles: loads 1000 (2400 one at a time), the
+// 64 pivot steps 19000 (all of a wavefront's 16 columns by readlane, without
+// LDS: 30000), substitution 2800 (4400 with a column per lane), the products
+// 2300 (11000 on the vector unit), stores.
+// LDS: two buffers of CB columns, the factored block, the four 16 x 16
+// inverses, the lower-left blocks of the two 32 x 32 inverses, the 32 x 32
+// product.
 constexpr int CHOL_DIAG_THREADS = 256;
-constexpr int CHOL_CB = 4;  // columns factored per workgroup barrier
+constexpr int CHOL_CB = 4;  // columns published per workgroup barrier
 static_assert((CHOL_NB / 4) % CHOL_CB == 0, "a column block lies within one wavefront's columns");
-constexpr int CHOL_DIAG_LDS =
-    2 * CHOL_CB * CHOL_NB + CHOL_NB * (CHOL_NB + 1) + CHOL_NB + 2 * 32 * 33 + 4 * 16 * 17;  // doubles
+constexpr int TRI_INV_LDS = 4 * 16 * 17 + 2 * 16 * 17 + 32 * 33;                               // doubles
+constexpr int CHOL_DIAG_LDS = 2 * CHOL_CB * CHOL_NB + CHOL_NB * (CHOL_NB + 1) + TRI_INV_LDS;  // doubles
 
 // 1/sqrt(x): hardware estimate, then two Newton-Raphson steps
 // y <- y + y (1 - x y^2) / 2 (NaN for x < 0 or NaN, +inf for x = 0)
@@ -1446,115 +1448,107 @@ DEV double rsqrt_nr(double x) {
   return y;
 }
 
-// Column c (0 .. 15) of the inverse of the lower-triangular 16 x 16 block of
-// Ls starting at (o, o), by forward substitution (four partial sums).
-DEV void tri_inverse_col16(const double (*Ls)[CHOL_NB + 1], const double* rdiag, int o, double* x, int c) {
+// The inverse of a lower-triangular 16 x 16 block by forward substitution on
+// one wavefront, Ls its first entry in LDS, rd the reciprocal of the diagonal
+// of row o + r in lane o + r.  Each entry is a sum in four parts (column q in
+// part q mod 4): lane 4 c + g forms part g of column c, the parts meet by quad
+// permutations, so a row is one dependent product, two sums and the scaling.
+DEV void tri_inverse16(const double (*Ls)[CHOL_NB + 1], double rd, int o, double (*Di)[17]) {
+  const int lane = threadIdx.x & 63, c = lane >> 2, g = lane & 3;
+  double l[16][4], x[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int rr = 1; rr < 16; ++rr)
+#pragma unroll
+    for (int m = 0; 4 * m < rr; ++m) l[rr][m] = Ls[rr][4 * m + g];
 #pragma unroll
   for (int rr = 0; rr < 16; ++rr) {
-    double s[4] = {(rr == c) ? 1.0 : 0.0, 0.0, 0.0, 0.0};
+    double s = (g == 0 && rr == c) ? 1.0 : 0.0;
 #pragma unroll
-    for (int q = 0; q < rr; ++q) s[q & 3] = __fma_rn(-Ls[o + rr][o + q], x[q], s[q & 3]);
-    x[rr] = ((s[0] + s[1]) + (s[2] + s[3])) * rdiag[o + rr];
+    for (int m = 0; 4 * m < rr; ++m) {
+      // the parts' last columns differ; an entry past them meets x = 0
+      const double v = (4 * m + 3 < rr || 4 * m + g < rr) ? l[rr][m] : 0.0;
+      s = __fma_rn(-v, x[m], s);
+    }
+    s += lane_xor_f64<1>(s);
+    s += lane_xor_f64<2>(s);
+    s *= readlane_f64(rd, o + rr);
+    x[rr >> 2] = (g == (rr & 3)) ? s : x[rr >> 2];
   }
+#pragma unroll
+  for (int m = 0; m < 4; ++m) Di[4 * m + g][c] = x[m];
 }
 
-// The inverse of the lower-triangular block Ls (zeros above the diagonal,
-// which are overwritten; identity past the matrix edge; rdiag its reciprocal
-// diagonal) by four wavefronts; AC: 2 x 32 x 33 + 4 x 16 x 17 doubles of LDS.
-DEV void tri_inverse_core(double (*Ls)[CHOL_NB + 1], const double* rdiag, double* AC, double* __restrict__ Linv) {
-  double (*Ai)[33] = (double (*)[33])AC;
-  double (*Ci)[33] = Ai + 32;
-  double (*Di)[16][17] = (double (*)[16][17])(Ai + 64);
-  const int t = threadIdx.x, r = t & 63;
+// The inverse of the lower-triangular block Ls (identity past the matrix
+// edge) by four wavefronts from Di, the inverses of its 16 x 16 diagonal
+// blocks (rows x columns, zeros above the diagonal) at the start of sh
+// (TRI_INV_LDS); Ls and Di are published here.
+DEV void tri_inverse_core(const double (*Ls)[CHOL_NB + 1], double* sh, double* __restrict__ Linv) {
+  double (*Di)[16][17] = (double (*)[16][17])sh;
+  double (*Xh)[16][17] = Di + 4;
+  double (*T)[33] = (double (*)[33])(sh + 6 * 16 * 17);
+  const int t = threadIdx.x, lane = t & 63, lr = lane & 15, lk = lane >> 4;
   const int w = __builtin_amdgcn_readfirstlane(t >> 6);
-  // the inverses of the four 16 x 16 diagonal blocks, one per wavefront
-  // (lane c < 16: column c, by substitution; zeros above the diagonal)
-  if (r < 16) {
-    double x[16];
-    tri_inverse_col16(Ls, rdiag, 16 * w, x, r);
-#pragma unroll
-    for (int q = 0; q < 16; ++q) Di[w][q][r] = x[q];
-  }
   __syncthreads();
   // the two 32 x 32 halves, [[D0, 0], [E, D1]]^-1 = [[D0^-1, 0], [-D1^-1 E
-  // D0^-1, D1^-1]], half hh on wavefronts 2 hh and 2 hh + 1: thread u forms
-  // row u / 8, columns 2 (u % 8) .. + 1 of T = E D0^-1 into the factor's zero
-  // block Ls[o + i][o + 16 + j], then of -D1^-1 T, and copies its share of
-  // the diagonal blocks and the zero block into A^-1 (hh = 0) or C^-1
-  {
-    const int hh = w >> 1, u = t & 127, o = 32 * hh;
-    const int ui = u >> 3, uj = (u & 7) * 2;
-    double (*Dst)[33] = hh ? Ci : Ai;
-    double s0 = 0.0, s1 = 0.0;
+  // D0^-1, D1^-1]]: a product's result registers are the next one's operand
+  if ((w & 1) == 0) {
+    const int hh = w >> 1, o = 32 * hh;
+    d4_t e = {0.0, 0.0, 0.0, 0.0}, x = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {
-      const double e = Ls[o + 16 + ui][o + k];
-      s0 = __fma_rn(e, Di[2 * hh][k][uj], s0);
-      s1 = __fma_rn(e, Di[2 * hh][k][uj + 1], s1);
-    }
-    Ls[o + ui][o + 16 + uj] = s0;
-    Ls[o + ui][o + 16 + uj + 1] = s1;
+    for (int s = 0; s < 4; ++s) e = mfma_f64(Ls[o + 16 + lr][o + 4 * s + lk], Di[2 * hh][4 * s + lk][lr], e);
 #pragma unroll
-    for (int e = 0; e < 2; ++e) {
-      Dst[ui][uj + e] = Di[2 * hh][ui][uj + e];
-      Dst[16 + ui][16 + uj + e] = Di[2 * hh + 1][ui][uj + e];
-      Dst[ui][16 + uj + e] = 0.0;
-    }
+    for (int s = 0; s < 4; ++s) x = mfma_f64(-Di[2 * hh + 1][lr][4 * s + lk], e[s], x);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) Xh[hh][4 * r + lk][lr] = x[r];
   }
   __syncthreads();
+  // T = B A^-1 (B = rows 32 .. 63, columns 0 .. 31 of L), then -C^-1 T: one 16
+  // x 16 block (bi, bj) per wavefront
+  const int bi = w >> 1, bj = w & 1;
   {
-    const int hh = w >> 1, u = t & 127, o = 32 * hh;
-    const int ui = u >> 3, uj = (u & 7) * 2;
-    double (*Dst)[33] = hh ? Ci : Ai;
-    double s0 = 0.0, s1 = 0.0;
+    d4_t c = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {
-      const double g = Di[2 * hh + 1][ui][k];
-      s0 = __fma_rn(-g, Ls[o + k][o + 16 + uj], s0);
-      s1 = __fma_rn(-g, Ls[o + k][o + 16 + uj + 1], s1);
-    }
-    Dst[16 + ui][uj] = s0;
-    Dst[16 + ui][uj + 1] = s1;
-  }
-  __syncthreads();
-  // T = B A^-1 (B = rows 32 .. 63, columns 0 .. 31 of L; A^-1 lower) into
-  // Ls[i][32 + j] (rows 0 .. 31 of the factor's zero columns 32 .. 63):
-  // thread t forms row t / 8, columns 4 (t % 8) .. 4 (t % 8) + 3
-  const int ti = t >> 3, tj = (t & 7) * 4;
-  {
-    double acc[4] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-    for (int q = 0; q < 32; ++q) {
-      const double bq = Ls[32 + ti][q];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) acc[e] = __fma_rn(bq, Ai[q][tj + e], acc[e]);
+    for (int s = 0; s < 8; ++s) {
+      const int q = 4 * s + lk, qq = q & 15;
+      const double inv = s < 4 ? (bj == 0 ? Di[0][qq][lr] : 0.0) : (bj == 0 ? Xh[0][qq][lr] : Di[1][qq][lr]);
+      c = mfma_f64(Ls[32 + 16 * bi + lr][q], inv, c);
     }
 #pragma unroll
-    for (int e = 0; e < 4; ++e) Ls[ti][32 + tj + e] = acc[e];
+    for (int r = 0; r < 4; ++r) T[16 * bi + 4 * r + lk][16 * bj + lr] = c[r];
   }
   __syncthreads();
-  // lower-left block of the inverse: -C^-1 T (C^-1 lower)
-  double xl[4] = {0.0, 0.0, 0.0, 0.0};
+  d4_t xl = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-  for (int q = 0; q < 32; ++q) {
-    const double cq = Ci[ti][q];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) xl[e] = __fma_rn(-cq, Ls[q][32 + tj + e], xl[e]);
+  for (int s = 0; s < 8; ++s) {
+    const int q = 4 * s + lk, qq = q & 15;
+    const double inv = s < 4 ? (bi == 0 ? Di[2][lr][qq] : Xh[1][lr][qq]) : (bi == 0 ? 0.0 : Di[3][lr][qq]);
+    xl = mfma_f64(-inv, T[q][16 * bj + lr], xl);
   }
-  // inverse out, column-major: Linv[q + c 64] = (L^-1)(q, c).  Thread t
-  // writes its lower-left entries from registers, then the other three blocks
-  // (A^-1, the zero block, C^-1) from LDS in coalesced column runs
+  // inverse out, column-major: Linv[q + c 64] = (L^-1)(q, c): the lower-left
+  // block from registers, the rest from LDS in column runs
 #pragma unroll
-  for (int e = 0; e < 4; ++e) Linv[(32 + ti) + (tj + e) * CHOL_NB] = xl[e];
+  for (int r = 0; r < 4; ++r) Linv[(32 + 16 * bi + 4 * r + lk) + (16 * bj + lr) * CHOL_NB] = xl[r];
 #pragma unroll
   for (int k = 0; k < CHOL_NB * CHOL_NB / CHOL_DIAG_THREADS; ++k) {
     const int e = t + k * CHOL_DIAG_THREADS;
-    const int q = e & (CHOL_NB - 1), c = e >> 6;
-    if (c < 32) {
-      if (q < 32) Linv[e] = Ai[q][c];
-    } else {
-      Linv[e] = (q < 32) ? 0.0 : Ci[q - 32][c - 32];
-    }
+    const int q = e & (CHOL_NB - 1), c = e >> 6, bq = q >> 4, bc = c >> 4;
+    if (bq >= 2 && bc < 2) continue;
+    Linv[e] = bq < bc ? 0.0 : (bq == bc ? Di[bq] : Xh[bq >> 1])[q & 15][c & 15];
+  }
+}
+
+// Row r of columns 16 w .. 16 w + 15 of a lower-triangular 64 x 64 block of
+// which jn rows and columns exist: zeros right of the diagonal, identity past
+// the edge.  Clamped addresses, so that all 16 loads are in flight.
+DEV void load_block_columns(const double* __restrict__ A, int d, int jn, int w, int r, double* a) {
+  constexpr int H = CHOL_NB / 4;
+  const int i = min(r, jn - 1);
+#pragma unroll
+  for (int k = 0; k < H; ++k) a[k] = A[i + (long)min(w * H + k, jn - 1) * d];
+#pragma unroll
+  for (int k = 0; k < H; ++k) {
+    const int c = w * H + k;
+    a[k] = (c <= r && r < jn) ? a[k] : (c == r) ? 1.0 : 0.0;
   }
 }
 
@@ -1563,21 +1557,11 @@ DEV void chol_diag_core(double* __restrict__ A, int d, int j0, int jn, double* _
   constexpr int H = CHOL_NB / 4;  // columns per wavefront
   double (*colp)[CHOL_CB][CHOL_NB] = (double (*)[CHOL_CB][CHOL_NB])sh;  // [parity][column of block][row]
   double (*Ls)[CHOL_NB + 1] = (double (*)[CHOL_NB + 1])(sh + 2 * CHOL_CB * CHOL_NB);
-  double* rdiag = sh + 2 * CHOL_CB * CHOL_NB + CHOL_NB * (CHOL_NB + 1);
+  double* inv = sh + 2 * CHOL_CB * CHOL_NB + CHOL_NB * (CHOL_NB + 1);
   const int t = threadIdx.x, r = t & 63;
   const int w = __builtin_amdgcn_readfirstlane(t >> 6);
   double a[H];
-#pragma unroll
-  for (int k = 0; k < H; ++k) {
-    const int c = w * H + k;
-    double v = 0.0;
-    if (r < jn && c < jn) {
-      if (c <= r) v = A[(j0 + r) + (long)(j0 + c) * d];
-    } else if (c == r) {
-      v = 1.0;  // identity padding beyond the matrix edge
-    }
-    a[k] = v;
-  }
+  load_block_columns(A + j0 + (long)j0 * d, d, jn, w, r, a);
   // pivot step of column c by the wavefront holding it (its local column kc)
   auto pivot = [&](int c, int kc, double* dst) {
     const double piv = readlane_f64(a[kc], c);
@@ -1631,24 +1615,29 @@ DEV void chol_diag_core(double* __restrict__ A, int d, int j0, int jn, double* _
         for (int t = 0; t < CHOL_CB; ++t) a[k] = __fma_rn(-lb[t], colp[buf][t][w * H + k], a[k]);
     }
   }
+  double diag = 1.0;
+#pragma unroll
+  for (int k = 0; k < H; ++k) {
+    const int c = w * H + k;
+    Ls[r][c] = (c <= r) ? a[k] : 0.0;
+    diag = (r == c) ? a[k] : diag;
+  }
+  // the inverses of the four 16 x 16 diagonal blocks, one per wavefront
+  tri_inverse16((const double (*)[CHOL_NB + 1]) & Ls[w * H][w * H], 1.0 / diag, w * H, ((double (*)[16][17])inv)[w]);
+  tri_inverse_core(Ls, inv, Linv);
+  // the factor last: a barrier waits for the stores before it
 #pragma unroll
   for (int k = 0; k < H; ++k) {
     const int c = w * H + k;
     if (r < jn && c < jn) A[(j0 + r) + (long)(j0 + c) * d] = (c <= r) ? a[k] : 0.0;
-    Ls[r][c] = (c <= r) ? a[k] : 0.0;
   }
-  __syncthreads();
   if (w == 0) {
     // a pivot that is not > 0 (or NaN) leaves a diagonal root that is not > 0,
     // and every later pivot inherits the failure: the first bad column is the
     // lowest such lane
-    const double diag = Ls[r][r];
-    const unsigned long long bad = __ballot(r < jn && !(diag > 0.0));
+    const unsigned long long bad = __ballot(r < jn && !(Ls[r][r] > 0.0));
     if (r == 0 && bad && *info == 0) *info = j0 + __ffsll((long long)bad);
-    rdiag[r] = 1.0 / diag;
   }
-  __syncthreads();
-  tri_inverse_core(Ls, rdiag, rdiag + CHOL_NB, Linv);
 }
 
 DEV void chol_diag_block(double* __restrict__ A, int d, int j0, int jn, double* __restrict__ Linv,
@@ -1668,20 +1657,21 @@ __global__ __launch_bounds__(CHOL_DIAG_THREADS) void k_chol_diag(double* __restr
 // lane of one wavefront substituted for a whole column).  Only for a factor
 // rounded since; the factorisation leaves the unrounded blocks' inverses.
 DEV void tri_inv_block(const double* __restrict__ L, int d, double* __restrict__ Linv, int bx) {
-  __shared__ double sh[CHOL_NB * (CHOL_NB + 1) + CHOL_NB + 2 * 32 * 33 + 4 * 16 * 17];
+  __shared__ double sh[CHOL_NB * (CHOL_NB + 1) + TRI_INV_LDS];
   double (*Ls)[CHOL_NB + 1] = (double (*)[CHOL_NB + 1])sh;
-  double* rdiag = sh + CHOL_NB * (CHOL_NB + 1);
-  const int r = threadIdx.x & 63, w = threadIdx.x >> 6, j0 = bx * CHOL_NB, jn = min(CHOL_NB, d - j0);
+  double* inv = sh + CHOL_NB * (CHOL_NB + 1);
+  constexpr int H = CHOL_NB / 4;
+  const int r = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int j0 = bx * CHOL_NB, jn = min(CHOL_NB, d - j0);
+  double a[H], diag = 1.0;
+  load_block_columns(L + j0 + (long)j0 * d, d, jn, w, r, a);
 #pragma unroll
-  for (int k = 0; k < CHOL_NB / 4; ++k) {
-    const int c = w * (CHOL_NB / 4) + k;
-    double v = (c == r) ? 1.0 : 0.0;
-    if (r < jn && c < jn) v = (c <= r) ? L[(j0 + r) + (long)(j0 + c) * d] : 0.0;
-    Ls[r][c] = v;
-    if (c == r) rdiag[r] = 1.0 / v;
+  for (int k = 0; k < H; ++k) {
+    Ls[r][w * H + k] = a[k];
+    diag = (r == w * H + k) ? a[k] : diag;
   }
-  __syncthreads();
-  tri_inverse_core(Ls, rdiag, rdiag + CHOL_NB, Linv + (long)bx * CHOL_NB * CHOL_NB);
+  tri_inverse16((const double (*)[CHOL_NB + 1]) & Ls[w * H][w * H], 1.0 / diag, w * H, ((double (*)[16][17])inv)[w]);
+  tri_inverse_core(Ls, inv, Linv + (long)bx * CHOL_NB * CHOL_NB);
 }
 
 __global__ __launch_bounds__(256) void k_tri_inv(const double* __restrict__ L, int d, double* __restrict__ Linv) {

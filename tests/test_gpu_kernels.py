@@ -161,6 +161,24 @@ def test_proposal_and_scatter_products(prec, d, P, n):
     assert bool(((s.get_f64(diam.F_S, (d, d)) - ref).abs() * (N0 + K) <= scale + scale.T).all())
 
 
+@pytest.mark.parametrize("prec,d", [("fp64", 1), ("fp64", 15), ("fp64", 17), ("fp64", 48), ("fp64", 63), ("fp64", 64),
+                                    ("fp64", 66), ("fp64", 127), ("fp64", 129), ("fp64", 320), ("fp64", 451),
+                                    ("fp32", 200), ("fp64", 1030)])
+def test_refactorisation_by_size(prec, d):
+    """L L^T against the covariance it factors, entry by entry: (d + 8) u of
+    |L| |L^T| (block inverses: times their condition, here below 8), and once
+    more the FP32 rounding of L where it is rounded."""
+    s, R, mu, rn = sampler(prec, d, 3, 2, 13 + d, beta=0.3)
+    A = 0.3 * rn(d, d) / np.sqrt(d)
+    C = A @ A.T + torch.eye(d, dtype=torch.float64, device="cuda")
+    S0 = C + torch.outer(mu, mu)
+    assert s.seed_moments(S0.contiguous(), mu, 50.0)[0] == diam.OK
+    L = s.get_f64(diam.F_L, (d, d)).T
+    assert torch.equal(L, torch.tril(L))
+    u = 8 * (d + 8) * U64 + (0 if prec == "fp64" else 4 * 2.0 ** -24)
+    assert bool(((L @ L.T - (S0 - torch.outer(mu, mu))).abs() <= u * (L.abs() @ L.abs().T) + 8 * U64 * S0.abs()).all())
+
+
 @pytest.mark.parametrize("prec,d,P", [("fp64", 1, 1), ("fp64", 15, 17), ("fp64", 64, 16), ("fp64", 65, 15),
                                       ("fp64", 130, 33), ("fp32", 511, 20), ("fp64", 512, 64), ("fp64", 577, 3),
                                       ("fp64", 1023, 18), ("fp64", 1024, 31), ("fp64", 1025, 17), ("fp32", 2051, 5)])
