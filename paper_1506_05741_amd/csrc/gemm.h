@@ -1097,20 +1097,23 @@ __host__ __device__ inline bool t_gemm_ok(const void* A, long lda, int M, const 
 // order, for sums whose order is free.
 // SETS accumulator sets take the slices in turn (slice s to set s mod SETS), as
 // the k-groups of the element engine do; the caller adds them up in order.
-// GRP slices per stage of the ring and per barrier, for one tile per CU, where
+// SPLIT: the sets take consecutive parts of the slices instead, in order (nk a
+// multiple of SETS).
+// GRP slices per stage of the ring and per barrier: for one tile per CU, where
 // a barrier and an LDS round trip per slice would stretch the chain of
-// products (kend - kbeg then a multiple of GRP slices).
+// products, and for GRP = SETS, whose slices are then free to overlap.
 template <typename T, int BM, int BN, int WGM, int WGN, int ST, bool AKC, bool BKC, bool PAIR = false, int SETS = 1,
-          int GRP = 1>
+          int GRP = 1, bool SPLIT = false>
 DEV void t_gemm(TFrag<T, BM, BN, WGM, WGN> (&fs)[SETS], const T* __restrict__ A, long lda, int M, const T* __restrict__ B,
                 long ldb, int N, int i0, int j0, int kbeg, int kend, T* lds) {
   typedef TFrag<T, BM, BN, WGM, WGN> F;
   constexpr int NW = WGM * WGN, TBK = tbk<T>(), Q = TBK / 4;
   constexpr int SA = BM * TBK, SS = (BM + BN) * TBK;
   constexpr int BLK_A = BM / 8, BLK_B = BN / 8, NBLK = BLK_A + BLK_B;
-  static_assert(GRP == 1 || SETS == 1, "grouped slices: one accumulator set");
+  static_assert(GRP == 1 || SETS == 1 || (SETS == GRP && !SPLIT), "grouped slices: one set, or one per slice");
   static_assert(NBLK % NW == 0, "copy blocks must divide among the waves");
   constexpr int LPW = NBLK / NW;
+  constexpr bool UNROLLED = SPLIT || (SETS > 2 && GRP == 1);  // steps without a loop's end between them
   const int nk = (kend - kbeg) / (GRP * TBK);  // whole stages
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   // Everything a lane needs is computed before the loop, whose bases advance
@@ -1128,20 +1131,21 @@ DEV void t_gemm(TFrag<T, BM, BN, WGM, WGN> (&fs)[SETS], const T* __restrict__ A,
                             : t_copy_offset<T, BN, BKC>(ldb, N - j0, kv, blk - BLK_A);
     }
   };
+  auto issue_slice = [&](int sl, int pos) {
+    const char* pa = (const char*)(Ab + sl * sa);
+    const char* pb = (const char*)(Bb + sl * sb);
+    T* st = lds + pos * SS;
+#pragma unroll
+    for (int q = 0; q < LPW; ++q) {
+      const int blk = w * LPW + q;
+      const char* src = blk < BLK_A ? pa : pb;
+      __builtin_amdgcn_global_load_lds((const void*)(src + voff[q]),
+                                       (lds_ptr_t)(st + blk * (1024 / (int)sizeof(T))), 16, 0, 0);
+    }
+  };
   auto issue = [&](int kt, int slot) {
 #pragma unroll
-    for (int g = 0; g < GRP; ++g) {
-      const char* pa = (const char*)(Ab + (kt * GRP + g) * sa);
-      const char* pb = (const char*)(Bb + (kt * GRP + g) * sb);
-      T* st = lds + (slot * GRP + g) * SS;
-#pragma unroll
-      for (int q = 0; q < LPW; ++q) {
-        const int blk = w * LPW + q;
-        const char* src = blk < BLK_A ? pa : pb;
-        __builtin_amdgcn_global_load_lds((const void*)(src + voff[q]),
-                                         (lds_ptr_t)(st + blk * (1024 / (int)sizeof(T))), 16, 0, 0);
-      }
-    }
+    for (int g = 0; g < GRP; ++g) issue_slice(kt * GRP + g, slot * GRP + g);
   };
   const int wm = w % WGM, wn = w / WGM;
   const int lr = lane & 15, lk = lane >> 4;
@@ -1176,6 +1180,38 @@ DEV void t_gemm(TFrag<T, BM, BN, WGM, WGN> (&fs)[SETS], const T* __restrict__ A,
       }
       return;
     }
+    if (UNROLLED) {
+      // a quarter of the slice's reads ahead of the products, so that none is
+      // pending at the next barrier, which the last products may pass
+      constexpr int G = Q / 4;
+      T a[4][G][F::FM], b[4][G][F::FN];
+      auto read = [&](int h) {
+#pragma unroll
+        for (int e = 0; e < G; ++e) {
+          const int q = h * G + e;
+#pragma unroll
+          for (int m = 0; m < F::FM; ++m)
+            a[h][e][m] = AKC ? st[ra[AKC ? q : 0] + m * 16 * TBK] : st[ra[AKC ? 0 : m] + 4 * q * BM];
+#pragma unroll
+          for (int n = 0; n < F::FN; ++n)
+            b[h][e][n] = BKC ? st[rb[BKC ? q : 0] + n * 16 * TBK] : st[rb[BKC ? 0 : n] + 4 * q * BN];
+        }
+      };
+      read(0);
+      read(1);
+#pragma unroll
+      for (int h = 0; h < 4; ++h) {
+        if (h < 3) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int e = 0; e < G; ++e)
+#pragma unroll
+          for (int m = 0; m < F::FM; ++m)
+#pragma unroll
+            for (int n = 0; n < F::FN; ++n) f.c[m][n] = mfma_e<T>(a[h][e][m], b[h][e][n], f.c[m][n]);
+        if (h + 2 < 4) read(h + 2);
+      }
+      return;
+    }
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
       T a[F::FM], b[F::FN];
@@ -1196,37 +1232,71 @@ DEV void t_gemm(TFrag<T, BM, BN, WGM, WGN> (&fs)[SETS], const T* __restrict__ A,
   asm volatile("s_barrier" ::: "memory");
   for (int p = 0; p < ST - 1 && p < nk; ++p) issue(p, p);
   int slot = 0;
-  for (int k0 = 0; k0 < nk; k0 += SETS) {
+  auto step = [&](int kt, F& f) {
+    // Stage kt has landed once at most the later stages' copies are pending.
+    // Without a loop's end between steps the compiler moves products, and with
+    // them the waits for their operands, behind the next barrier, after which
+    // the slot they read is refilled: there the reads are waited for here.
+    if (UNROLLED) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    if (kt + ST - 2 < nk) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LPW * GRP * (ST - 2)) : "memory");
+    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    asm volatile("s_barrier" ::: "memory");
+    // the ring slot refilled here was last read before this barrier
+    if (kt + ST - 1 < nk) issue(kt + ST - 1, slot == 0 ? ST - 1 : slot - 1);
 #pragma unroll
-    for (int x = 0; x < SETS; ++x) {
-      const int kt = k0 + x;
-      if (SETS > 1 && kt >= nk) break;
-      // stage kt has landed once at most the later stages' copies are pending
-      if (kt + ST - 2 < nk) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LPW * GRP * (ST - 2)) : "memory");
-      else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-      asm volatile("s_barrier" ::: "memory");
-      // the ring slot refilled here was last read before this barrier
-      if (kt + ST - 1 < nk) issue(kt + ST - 1, slot == 0 ? ST - 1 : slot - 1);
+    for (int g = 0; g < GRP; ++g) compute(lds + (slot * GRP + g) * SS, SETS == GRP ? fs[SETS == GRP ? g : 0] : f);
+    slot = slot == ST - 1 ? 0 : slot + 1;
+  };
+  if (SPLIT) {
 #pragma unroll
-      for (int g = 0; g < GRP; ++g) compute(lds + (slot * GRP + g) * SS, fs[x]);
-      slot = slot == ST - 1 ? 0 : slot + 1;
+    for (int x = 0; x < SETS; ++x)
+      for (int kt = x * (nk / SETS); kt < (x + 1) * (nk / SETS); ++kt) step(kt, fs[x]);
+  } else if (GRP > 1) {
+    for (int kt = 0; kt < nk; ++kt) step(kt, fs[0]);
+  } else if (SETS == 2) {
+    // one step per trip, the sets changing places (the logistic target 399 us
+    // with two steps per trip and the wait above, 344 so)
+#pragma unroll 1
+    for (int kt = 0; kt < nk; ++kt) {
+      step(kt, fs[0]);
+      const F t = fs[0];
+      fs[0] = fs[SETS - 1];
+      fs[SETS - 1] = t;
+    }
+    if (nk & 1) {
+      const F t = fs[0];
+      fs[0] = fs[SETS - 1];
+      fs[SETS - 1] = t;
+    }
+  } else {
+    for (int k0 = 0; k0 < nk; k0 += SETS) {
+#pragma unroll
+      for (int x = 0; x < SETS; ++x) {
+        if (SETS > 1 && k0 + x >= nk) break;
+        step(k0 + x, fs[x]);
+      }
     }
   }
-  const int kv = (kend - kbeg) - nk * TBK;
-  if (GRP == 1 && kv > 0) {  // the last, partial slice, cleared beyond kend
-    asm volatile("s_barrier" ::: "memory");
-    offsets(kv);
-    issue(nk, 0);
+  const int kv = (kend - kbeg) - nk * GRP * TBK;
+  if (SPLIT || kv <= 0) return;
+#pragma unroll
+  for (int g = 0; g < GRP; ++g) {  // the last slices, the partial one cleared beyond kend
+    const int kg = min(kv - g * TBK, TBK);
+    if (kg <= 0) break;
+    asm volatile("s_waitcnt lgkmcnt(0)\n s_barrier" ::: "memory");
+    offsets(kg);
+    issue_slice(nk * GRP + g, 0);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
-    for (int e = threadIdx.x; e < BM * (TBK - kv); e += 64 * NW)
-      lds[t_index<T, BM, AKC>(e % BM, kv + e / BM)] = T(0);
-    for (int e = threadIdx.x; e < BN * (TBK - kv); e += 64 * NW)
-      lds[SA + t_index<T, BN, BKC>(e % BN, kv + e / BN)] = T(0);
+    for (int e = threadIdx.x; e < BM * (TBK - kg); e += 64 * NW)
+      lds[t_index<T, BM, AKC>(e % BM, kg + e / BM)] = T(0);
+    for (int e = threadIdx.x; e < BN * (TBK - kg); e += 64 * NW)
+      lds[SA + t_index<T, BN, BKC>(e % BN, kg + e / BN)] = T(0);
     __syncthreads();
 #pragma unroll
     for (int x = 0; x < SETS; ++x)
-      if (nk % SETS == x) compute(lds, fs[x]);
+      if ((GRP > 1 ? g % SETS : nk % SETS) == x) compute(lds, fs[x]);
+    if (GRP > 1) __syncthreads();
   }
 }
 

@@ -71,14 +71,16 @@ __global__ __launch_bounds__(512) void k_tgt_logreg(const float* __restrict__ A,
   }
 }
 
-// The same on the direct-to-LDS engine: BM observations x 64 chains by WGM x 2
+// The same on the direct-to-LDS engine, 64 observations x 64 chains by 2 x 2
 // waves of 32 x 32, two interleaved chains of slices of K as the two k-groups
-// above, every 64 observations' term bitwise the tile's.
-template <int BM, int WGM>
-__global__ __launch_bounds__(128 * WGM) __attribute__((amdgpu_waves_per_eu(2))) void k_tgt_logreg_t(
+// above, the term bitwise the tile's.  Two stages of LDS: five workgroups a CU
+// overlap one's softplus terms (72 us of n = 200000, d = 512, P = 128) with
+// the others' products; 342 us in the tile above, 333 so, 348 with three
+// stages, 341 with 128 x 64 tiles.
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_tgt_logreg_t(
     const float* __restrict__ A, const float* __restrict__ y, int n_obs, const float* __restrict__ V, int d, int P,
     const int* __restrict__ nact_ptr, int nrb, int nct, double* __restrict__ part) {
-  constexpr int BN = 64, ST = 3, RB = BM / 64;
+  constexpr int BM = 64, BN = 64, WGM = 2, ST = 2;
   typedef TFrag<float, BM, BN, WGM, 2> F;
   static_assert(F::FM == 2, "32 rows per wave: two waves per 64-row term");
   __shared__ __attribute__((aligned(1024))) float lds[t_lds_elems<float, BM, BN, ST>()];
@@ -114,9 +116,9 @@ __global__ __launch_bounds__(128 * WGM) __attribute__((amdgpu_waves_per_eu(2))) 
     if (lane < 16) red[wm][wn * (BN / 2) + n * 16 + lane] = s;
   }
   __syncthreads();
-  for (int e = threadIdx.x; e < RB * BN; e += 128 * WGM) {
-    const int c = e % BN, q = e / BN, j = j0 + c, b = rb * RB + q;
-    if (j < nact && b < nrb) part[(long)j * nrb + b] = red[2 * q][c] + red[2 * q + 1][c];
+  if (threadIdx.x < BN) {
+    const int j = j0 + threadIdx.x;
+    if (j < nact) part[(long)j * nrb + rb] = red[0][threadIdx.x] + red[1][threadIdx.x];
   }
 }
 
@@ -129,16 +131,9 @@ hipError_t tgt_logreg(const float* A, const float* y, long n_obs, const float* V
                       double* part, hipStream_t s) {
   const int nrb = logreg_row_blocks(n_obs), groups = (nrb + 7) / 8;
   const int nct = cdiv(P, 64);
-  // 128-row tiles from 1024 of them on (n = 200000, d = 512, P = 128: 342 to 314
-  // us, of which the softplus terms take about 72; 64-row ones 338), 64-row
-  // ones below (n = 50001, d = 256, P = 100: 73.9 to 58.6 us, 128-row 61.4)
   if (t_gemm_ok<float, true, true>(A, d, (int)n_obs, V, d, P, d)) {
-    if (n_obs >= 1024 * 128)
-      hipLaunchKernelGGL((k_tgt_logreg_t<128, 4>), dim3((cdiv(n_obs, 128) + 7) / 8 * 8 * nct), dim3(512), 0, s, A, y,
-                         (int)n_obs, V, d, P, nact, nrb, nct, part);
-    else
-      hipLaunchKernelGGL((k_tgt_logreg_t<64, 2>), dim3(groups * 8 * nct), dim3(256), 0, s, A, y, (int)n_obs, V, d, P,
-                         nact, nrb, nct, part);
+    hipLaunchKernelGGL(k_tgt_logreg_t, dim3(groups * 8 * nct), dim3(256), 0, s, A, y, (int)n_obs, V, d, P, nact, nrb,
+                       nct, part);
     return hipGetLastError();
   }
   hipLaunchKernelGGL(k_tgt_logreg<64>, dim3(groups * 8 * nct), dim3(512), 0, s, A, y, (int)n_obs, V, d, P, nact, nrb,
