@@ -66,7 +66,8 @@ struct BLay {
 struct Tiles {
   std::vector<BTile> all;
   Seg tgt[dk::G_TGT_CONFIGS], decide, step, trigemm, syrk, rowsum, dd, d1, colnorm, triinv;
-  std::vector<Seg> cdiag, cpanel, cupd, whiten, wupd;
+  Seg cdiag;
+  std::vector<Seg> cpanel, cupd, whiten, wupd;
   std::vector<dk::PItem> pitems;  // one step of the persistent loop
   std::vector<int> pstep;         // items of problem g per step
   int max_nb = 0;
@@ -140,18 +141,21 @@ Tiles build_tiles(const std::vector<int>& dims, int P, int n) {
   for (int g : order)
     for (int b = 0; b < cdivh(dims[g], NB); ++b) v.push_back({g, b, 0});
   T.triinv = T.add(v);
+  v.clear();
+  for (int g : order) v.push_back({g, 0, 0});
+  T.cdiag = T.add(v);
   for (int g = 0; g < G; ++g) T.max_nb = std::max(T.max_nb, cdivh(dims[g], NB));
   for (int jb = 0; jb < T.max_nb; ++jb) {
-    std::vector<BTile> dg, pn, up;
+    std::vector<BTile> pn, up;
     for (int g : order) {
-      const int nb = cdivh(dims[g], NB);
-      if (jb >= nb) continue;
-      const int m = nb - jb - 1;
-      dg.push_back({g, 0, 0});
-      for (int i = 0; i < m; ++i) pn.push_back({g, i, 0});
-      for (int t = 0; t < m * (m + 1) / 2; ++t) up.push_back({g, t, 0});
+      const int m = cdivh(dims[g], NB) - jb - 1;
+      if (m <= 0) continue;
+      for (int i = 0; i < m * (NB / dk::CHOL_PANEL_ROWS); ++i) pn.push_back({g, i, 0});
+      up.push_back({g, 0, 0});  // first: the next diagonal blocks are factored there
     }
-    T.cdiag.push_back(T.add(dg));
+    for (int g : order)
+      for (int t = 1; t < (jb + 1 < cdivh(dims[g], NB) ? dk::chol_update_tiles(cdivh(dims[g], NB), jb) : 0); ++t)
+        up.push_back({g, t, 0});
     T.cpanel.push_back(T.add(pn));
     T.cupd.push_back(T.add(up));
   }
@@ -605,9 +609,9 @@ static int enqueue_window(diam_batch* b, hipStream_t s) {
   BCHK(dk::g_fold(b->dp, tl(T.dd), T.dd.n, tl(T.d1), T.d1.n, b->Nd, (double)K, s));
   BCHK(dk::g_bump(b->win_ctr, b->Nd, (double)K, s));
   BCHK(dk::g_cov(b->dp, tl(T.dd), T.dd.n, s));
+  BCHK(dk::g_chol_diag(b->dp, tl(T.cdiag), T.cdiag.n, s));
   for (int jb = 0; jb < T.max_nb; ++jb)
-    BCHK(dk::g_chol_step(b->dp, tl(T.cdiag[jb]), T.cdiag[jb].n, tl(T.cpanel[jb]), T.cpanel[jb].n, tl(T.cupd[jb]),
-                         T.cupd[jb].n, jb, s));
+    BCHK(dk::g_chol_step(b->dp, tl(T.cpanel[jb]), T.cpanel[jb].n, tl(T.cupd[jb]), T.cupd[jb].n, jb, s));
   BCHK(dk::g_adopt(b->dp, tl(T.dd), T.dd.n, s));
   BCHK(dk::g_tri_inv(b->dp, tl(T.triinv), T.triinv.n, s));
   for (int k = 0; k < (int)T.whiten.size(); ++k)
@@ -700,9 +704,9 @@ extern "C" int diam_batch_seed_moments(diam_batch* b, const double* const* S0, c
   const Tiles& T = b->T;
   auto tl = [&](const Seg& g) { return (const BTile*)(b->dt + g.off); };
   BCHK(dk::g_cov(b->dp, tl(T.dd), T.dd.n, s));
+  BCHK(dk::g_chol_diag(b->dp, tl(T.cdiag), T.cdiag.n, s));
   for (int jb = 0; jb < T.max_nb; ++jb)
-    BCHK(dk::g_chol_step(b->dp, tl(T.cdiag[jb]), T.cdiag[jb].n, tl(T.cpanel[jb]), T.cpanel[jb].n, tl(T.cupd[jb]),
-                         T.cupd[jb].n, jb, s));
+    BCHK(dk::g_chol_step(b->dp, tl(T.cpanel[jb]), T.cpanel[jb].n, tl(T.cupd[jb]), T.cupd[jb].n, jb, s));
   BCHK(dk::g_adopt(b->dp, tl(T.dd), T.dd.n, s));
   BCHK(dk::g_tri_inv(b->dp, tl(T.triinv), T.triinv.n, s));
   for (int k = 0; k < (int)T.whiten.size(); ++k)

@@ -107,6 +107,10 @@ hipError_t cov_assemble(const double* S, const double* m, double eps, double* C,
 // In-place lower Cholesky; *info = 0 on success, else 1 + first failing column.
 // Linv: chol_scratch_bytes(d) of scratch (inverses of the diagonal blocks).
 size_t chol_scratch_bytes(int d);
+// tiles of the update after block column jb of nb
+int chol_update_tiles(int nb, int jb);
+// rows of a panel tile
+constexpr int CHOL_PANEL_ROWS = 32;
 hipError_t potrf(double* A, int d, int* info, double* Linv, hipStream_t s);
 // Round the factor to the working precision in place and emit the low-precision
 // copy (f32 column-major, or bf16 hi and lo row-major: L~ = hi + lo); no-op
@@ -300,8 +304,9 @@ hipError_t g_scatter(const BProb* pr, const BTile* syrk_tl, int nsyrk, const BTi
 hipError_t g_fold(const BProb* pr, const BTile* dd_tl, int ndd, const BTile* d_tl, int nd, const double* N, double K,
                   hipStream_t s);
 hipError_t g_cov(const BProb* pr, const BTile* dd_tl, int ndd, hipStream_t s);
-hipError_t g_chol_step(const BProb* pr, const BTile* diag, int ndiag, const BTile* panel, int npanel,
-                       const BTile* upd, int nupd, int jb, hipStream_t s);
+hipError_t g_chol_diag(const BProb* pr, const BTile* tl, int n, hipStream_t s);
+hipError_t g_chol_step(const BProb* pr, const BTile* panel, int npanel, const BTile* upd, int nupd, int jb,
+                       hipStream_t s);
 hipError_t g_adopt(const BProb* pr, const BTile* dd_tl, int ndd, hipStream_t s);
 hipError_t g_tri_inv(const BProb* pr, const BTile* tl, int n, hipStream_t s);
 // piece `piece` of the whitenings (tl: problem, 16-column tile, piece) and its

@@ -1678,14 +1678,46 @@ __global__ __launch_bounds__(256) void k_tri_inv(const double* __restrict__ L, i
   tri_inv_block(L, d, Linv, blockIdx.x);
 }
 
-// Panel rows below the diagonal block: A(i, j0 + c) <- sum_q A(i, j0 + q) Linv(c, q)
+// Panel rows below the diagonal block: A(i, j0 + c) <- sum_q A(i, j0 + q)
+// Linv(c, q), 32 rows per workgroup (few rows, so latency counts) on the
+// direct-to-LDS engine with all of K in flight, transposed so that lanes run
+// along the columns of memory: 7.3 us on the element engine, which unaligned d
+// keeps, now 4.8.
+constexpr int CHOL_ST = 5;  // four slices of 16 in flight: a block column
+constexpr int CHOL_PANEL_LDS = t_lds_elems<double, CHOL_NB, CHOL_PANEL_ROWS, CHOL_ST>();
+static_assert(CHOL_PANEL_LDS >= e_lds_elems<double, 64, 64, 16>(), "one buffer for both engines");
+
+DEV bool chol_aligned(const double* A, int d) { return d % 2 == 0 && (uintptr_t)A % 16 == 0; }
+
 DEV void chol_panel_tile(double* __restrict__ A, int d, int j0, int jn, const double* __restrict__ Linv, int bx) {
+  __shared__ __attribute__((aligned(1024))) double lds[CHOL_PANEL_LDS];
+  const int i0 = j0 + jn + bx * CHOL_PANEL_ROWS;
+  if (i0 >= d) return;  // uniform: the second half of a block of at most 32 rows
+  double* Pc = A + (long)j0 * d;
+  if (chol_aligned(A, d)) {
+    constexpr int BN = CHOL_PANEL_ROWS;
+    typedef TFrag<double, CHOL_NB, BN, 2, 2> F;
+    F f;
+    f.zero();
+    t_gemm<double, CHOL_NB, BN, 2, 2, CHOL_ST, false, false>(f, Linv, CHOL_NB, CHOL_NB, Pc, d, d, 0, i0, 0, CHOL_NB,
+                                                             lds);
+#pragma unroll
+    for (int m = 0; m < F::FM; ++m)
+#pragma unroll
+      for (int n = 0; n < F::FN; ++n)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          int c, ti;
+          t_coords<double, CHOL_NB, BN, 2, 2>(m, n, r, c, ti);
+          if (i0 + ti < d) Pc[i0 + ti + (long)c * d] = f.c[m][n][r];
+        }
+    return;
+  }
+  if (bx & 1) return;  // 64 rows per tile
   constexpr int BM = 64, BN = 64, BK = 16;
-  __shared__ double lds[e_lds_elems<double, BM, BN, BK>()];
-  const int i0 = j0 + jn + bx * BM;
   EFrag<double, BM, BN> f;
   f.zero();
-  e_gemm<double, BM, BN, BK, false, false>(f, A + (long)j0 * d, d, d, Linv, CHOL_NB, jn, i0, 0, 0, jn, lds);
+  e_gemm<double, BM, BN, BK, false, false>(f, Pc, d, d, Linv, CHOL_NB, jn, i0, 0, 0, jn, lds);
 #pragma unroll
   for (int m = 0; m < 2; ++m)
 #pragma unroll
@@ -1694,8 +1726,7 @@ DEV void chol_panel_tile(double* __restrict__ A, int d, int j0, int jn, const do
       for (int r = 0; r < 4; ++r) {
         int ti, tj;
         frag_coords<BM, BN, double>(m, n, r, ti, tj);
-        const int i = i0 + ti;
-        if (i < d && tj < jn) A[i + (long)(j0 + tj) * d] = f.c[m][n][r];
+        if (i0 + ti < d) Pc[i0 + ti + (long)tj * d] = f.c[m][n][r];
       }
 }
 
@@ -1704,54 +1735,112 @@ __global__ __launch_bounds__(256) void k_chol_panel(double* __restrict__ A, int 
   chol_panel_tile(A, d, j0, jn, Linv, blockIdx.x);
 }
 
-// Trailing update A(i, k) -= sum_c A(i, c) A(k, c) over the panel columns,
-// for the lower tiles of block rows/cols >= t0.
-constexpr int CHOL_UPD_LDS = e_lds_elems<double, 64, 64, 16>();  // doubles
+// Updates of the trailing lower tiles, A(i, k) -= sum_c A(i, c) A(k, c), two
+// block columns at a time: after an even block column jb only block column jb
+// + 1, which is factored next, and the diagonal tile after it are updated;
+// after an odd one the whole trailing part takes both columns' products, one
+// after the other, in one trip through memory.  Every entry sees the same
+// operations in the same order as with an update per block column, whose
+// trips bound the factorisation of many or large matrices: per block column of
+// 64 of 1024 x 1024 95 us, now 60, of one of 4096 x 4096 33 and 24 (22 and 20
+// at 1024 x 1024, where the diagonal core bounds it).
+int chol_update_tiles(int nb, int jb) {
+  const int m = nb - jb - 1;
+  return jb % 2 == 0 ? m + (m >= 2) : m * (m + 1) / 2;
+}
+constexpr int CHOL_UPD_LDS = t_lds_elems<double, 64, 64, CHOL_ST>();  // doubles
+static_assert(CHOL_UPD_LDS >= e_lds_elems<double, 64, 64, 16>(), "one buffer for both engines");
 
-DEV void chol_update_core(double* __restrict__ A, int d, int j0, int jn, int t0, int t, double* lds) {
+// block columns [c0, c0 + 64 NC) on tile (i0, k0)
+template <int NC>
+DEV void chol_update_part(double* __restrict__ A, int d, int c0, int i0, int k0, double* lds) {
+  const double* Pc = A + (long)c0 * d;
+  if (chol_aligned(A, d)) {
+    typedef TFrag<double, 64, 64, 2, 2> F;
+    // the tile itself, on its way during the products
+    double c[F::FM][F::FN][4];
+#pragma unroll
+    for (int m = 0; m < F::FM; ++m)
+#pragma unroll
+      for (int n = 0; n < F::FN; ++n)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          int tk, ti;
+          t_coords<double, 64, 64, 2, 2>(m, n, r, tk, ti);
+          c[m][n][r] = A[min(i0 + ti, d - 1) + (long)min(k0 + tk, d - 1) * d];
+        }
+    F f[NC];
+#pragma unroll
+    for (int x = 0; x < NC; ++x) f[x].zero();
+    t_gemm<double, 64, 64, 2, 2, CHOL_ST, false, false, false, NC, 1, true>(f, Pc, d, d, Pc, d, d, k0, i0, 0,
+                                                                            CHOL_NB * NC, lds);
+#pragma unroll
+    for (int m = 0; m < F::FM; ++m)
+#pragma unroll
+      for (int n = 0; n < F::FN; ++n)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          int tk, ti;
+          t_coords<double, 64, 64, 2, 2>(m, n, r, tk, ti);
+          double v = c[m][n][r];
+#pragma unroll
+          for (int x = 0; x < NC; ++x) v -= f[x].c[m][n][r];
+          if (i0 + ti < d && k0 + tk < d) A[i0 + ti + (long)(k0 + tk) * d] = v;
+        }
+    return;
+  }
   constexpr int BM = 64, BN = 64, BK = 16;
-  int bi, bk;
-  tile_pair(t, bi, bk);
-  const int i0 = (t0 + bi) * BM, k0 = (t0 + bk) * BN;
-  const double* Pc = A + (long)j0 * d;
-  EFrag<double, BM, BN> f;
-  f.zero();
-  e_gemm<double, BM, BN, BK, false, false>(f, Pc, d, d, Pc, d, d, i0, k0, 0, jn, lds);
+#pragma unroll 1
+  for (int x = 0; x < NC; ++x) {
+    EFrag<double, BM, BN> f;
+    f.zero();
+    e_gemm<double, BM, BN, BK, false, false>(f, Pc, d, d, Pc, d, d, i0, k0, CHOL_NB * x, CHOL_NB * (x + 1), lds);
 #pragma unroll
-  for (int m = 0; m < 2; ++m)
+    for (int m = 0; m < 2; ++m)
 #pragma unroll
-    for (int n = 0; n < 2; ++n)
+      for (int n = 0; n < 2; ++n)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        int ti, tj;
-        frag_coords<BM, BN, double>(m, n, r, ti, tj);
-        const int i = i0 + ti, k = k0 + tj;
-        if (i < d && k < d) A[i + (long)k * d] -= f.c[m][n][r];
-      }
+        for (int r = 0; r < 4; ++r) {
+          int ti, tj;
+          frag_coords<BM, BN, double>(m, n, r, ti, tj);
+          const int i = i0 + ti, k = k0 + tj;
+          if (i < d && k < d) A[i + (long)k * d] -= f.c[m][n][r];
+        }
+    __syncthreads();
+  }
 }
 
-DEV void chol_update_tile(double* __restrict__ A, int d, int j0, int jn, int t0, int t) {
-  __shared__ double lds[CHOL_UPD_LDS];
-  chol_update_core(A, d, j0, jn, t0, t, lds);
+// tile t of the update after block column jb
+DEV void chol_update_core(double* __restrict__ A, int d, int jb, int t, double* lds) {
+  const int nb = (d + CHOL_NB - 1) / CHOL_NB, t0 = jb + 1;
+  if (jb % 2 == 0) {
+    const int bi = t < nb - t0 ? t : 1, bk = t < nb - t0 ? 0 : 1;
+    chol_update_part<1>(A, d, jb * CHOL_NB, (t0 + bi) * CHOL_NB, (t0 + bk) * CHOL_NB, lds);
+  } else if (t == 0) {  // the next diagonal block: the first column's part is done
+    chol_update_part<1>(A, d, jb * CHOL_NB, t0 * CHOL_NB, t0 * CHOL_NB, lds);
+  } else {
+    int bi, bk;
+    tile_pair(t, bi, bk);
+    chol_update_part<2>(A, d, (jb - 1) * CHOL_NB, (t0 + bi) * CHOL_NB, (t0 + bk) * CHOL_NB, lds);
+  }
 }
 
 size_t chol_scratch_bytes(int d) { return (size_t)cdiv(d, CHOL_NB) * CHOL_NB * CHOL_NB * sizeof(double); }
 
-// Trailing update of block column j0 fused with the factorisation of the
-// next diagonal block: workgroup 0 updates tile (t0, t0), the first of the
-// row-by-row enumeration, which is that diagonal block, and then factors it
-// while the other workgroups finish the update.  The barrier at the start of
+// The update after block column jb fused with the factorisation of the next
+// diagonal block: workgroup 0 updates that block, the first tile, and then
+// factors it while the other workgroups finish the update.  The barrier at the start of
 // the factorisation orders the tile's stores before its loads (one
 // workgroup); nothing else reads the block before the next launch.
 // Both phases use the same LDS buffer.
-__global__ __launch_bounds__(256) void k_chol_update_diag(double* __restrict__ A, int d, int j0, int jn, int t0,
+__global__ __launch_bounds__(256) void k_chol_update_diag(double* __restrict__ A, int d, int jb,
                                                           double* __restrict__ Linv_next, int* __restrict__ info) {
   constexpr int NLDS = CHOL_UPD_LDS > CHOL_DIAG_LDS ? CHOL_UPD_LDS : CHOL_DIAG_LDS;
-  __shared__ double lds[NLDS];
-  chol_update_core(A, d, j0, jn, t0, blockIdx.x, lds);
+  __shared__ __attribute__((aligned(1024))) double lds[NLDS];
+  chol_update_core(A, d, jb, blockIdx.x, lds);
   if (blockIdx.x == 0) {
     __syncthreads();
-    const int j1 = t0 * CHOL_NB;
+    const int j1 = (jb + 1) * CHOL_NB;
     chol_diag_core(A, d, j1, min(CHOL_NB, d - j1), Linv_next, info, lds);
   }
 }
@@ -1763,8 +1852,8 @@ hipError_t potrf(double* A, int d, int* info, double* Linv, hipStream_t s) {
     const int j0 = jb * CHOL_NB, jn = CHOL_NB;
     const double* Li = Linv + (long)jb * CHOL_NB * CHOL_NB;
     const int m = nb - jb - 1;
-    hipLaunchKernelGGL(k_chol_panel, dim3(m), dim3(256), 0, s, A, d, j0, jn, Li);
-    hipLaunchKernelGGL(k_chol_update_diag, dim3(m * (m + 1) / 2), dim3(256), 0, s, A, d, j0, jn, jb + 1,
+    hipLaunchKernelGGL(k_chol_panel, dim3(m * (CHOL_NB / CHOL_PANEL_ROWS)), dim3(256), 0, s, A, d, j0, jn, Li);
+    hipLaunchKernelGGL(k_chol_update_diag, dim3(chol_update_tiles(nb, jb)), dim3(256), 0, s, A, d, jb,
                        Linv + (long)(jb + 1) * CHOL_NB * CHOL_NB, info);
   }
   return hipGetLastError();
@@ -2201,17 +2290,17 @@ __global__ __launch_bounds__(256) void kb_chol_panel(double* __restrict__ A, lon
   chol_panel_tile(A + z * sA, d, j0, jn, Linv + z * sL, blockIdx.x);
 }
 
-__global__ __launch_bounds__(256) void kb_chol_update_diag(double* __restrict__ A, long sA, int d, int j0, int jn,
-                                                           int t0, double* __restrict__ Linv_next, long sL,
+__global__ __launch_bounds__(256) void kb_chol_update_diag(double* __restrict__ A, long sA, int d, int jb,
+                                                           double* __restrict__ Linv_next, long sL,
                                                            int* __restrict__ info) {
   constexpr int NLDS = CHOL_UPD_LDS > CHOL_DIAG_LDS ? CHOL_UPD_LDS : CHOL_DIAG_LDS;
-  __shared__ double lds[NLDS];
+  __shared__ __attribute__((aligned(1024))) double lds[NLDS];
   const int z = blockIdx.z;
   double* Az = A + z * sA;
-  chol_update_core(Az, d, j0, jn, t0, blockIdx.x, lds);
+  chol_update_core(Az, d, jb, blockIdx.x, lds);
   if (blockIdx.x == 0) {
     __syncthreads();
-    const int j1 = t0 * CHOL_NB;
+    const int j1 = (jb + 1) * CHOL_NB;
     chol_diag_core(Az, d, j1, min(CHOL_NB, d - j1), Linv_next + z * sL, info + z, lds);
   }
 }
@@ -2224,10 +2313,10 @@ hipError_t potrf_batched(double* A, long sA, int d, int* info, double* Linv, lon
   for (int jb = 0; jb + 1 < nb; ++jb) {
     const int j0 = jb * CHOL_NB, jn = CHOL_NB;
     const int m = nb - jb - 1;
-    hipLaunchKernelGGL(kb_chol_panel, dim3(m, 1, nprob), dim3(256), 0, s, A, sA, d, j0, jn,
-                       (const double*)(Linv + (long)jb * CHOL_NB * CHOL_NB), sL);
-    hipLaunchKernelGGL(kb_chol_update_diag, dim3(m * (m + 1) / 2, 1, nprob), dim3(256), 0, s, A, sA, d, j0, jn,
-                       jb + 1, Linv + (long)(jb + 1) * CHOL_NB * CHOL_NB, sL, info);
+    hipLaunchKernelGGL(kb_chol_panel, dim3(m * (CHOL_NB / CHOL_PANEL_ROWS), 1, nprob), dim3(256), 0, s, A, sA, d, j0,
+                       jn, (const double*)(Linv + (long)jb * CHOL_NB * CHOL_NB), sL);
+    hipLaunchKernelGGL(kb_chol_update_diag, dim3(chol_update_tiles(nb, jb), 1, nprob), dim3(256), 0, s, A, sA, d, jb,
+                       Linv + (long)(jb + 1) * CHOL_NB * CHOL_NB, sL, info);
   }
   return hipGetLastError();
 }
@@ -3739,12 +3828,12 @@ hipError_t g_cov(const BProb* pr, const BTile* dd_tl, int ndd, hipStream_t s) {
   return hipGetLastError();
 }
 
-// blocked Cholesky, block column jb of every problem with more than jb blocks
-__global__ __launch_bounds__(CHOL_DIAG_THREADS) void gk_chol_diag(const BProb* __restrict__ pr, const BTile* __restrict__ tl, int jb) {
-  const BTile t = tl[blockIdx.x];
-  const BProb& b = pr[t.g];
-  const int j0 = jb * CHOL_NB, jn = min(CHOL_NB, b.d - j0);
-  chol_diag_block(b.C, b.d, j0, jn, b.Linv + (long)jb * CHOL_NB * CHOL_NB, b.info);
+// blocked Cholesky: every problem's first diagonal block, then per block column
+// jb the panel and the update of the problems with more blocks
+__global__ __launch_bounds__(CHOL_DIAG_THREADS) void gk_chol_diag(const BProb* __restrict__ pr,
+                                                                  const BTile* __restrict__ tl) {
+  const BProb& b = pr[tl[blockIdx.x].g];
+  chol_diag_block(b.C, b.d, 0, min(CHOL_NB, b.d), b.Linv, b.info);
 }
 __global__ __launch_bounds__(256) void gk_chol_panel(const BProb* __restrict__ pr, const BTile* __restrict__ tl, int jb) {
   const BTile t = tl[blockIdx.x];
@@ -3752,19 +3841,30 @@ __global__ __launch_bounds__(256) void gk_chol_panel(const BProb* __restrict__ p
   const int j0 = jb * CHOL_NB, jn = min(CHOL_NB, b.d - j0);
   chol_panel_tile(b.C, b.d, j0, jn, b.Linv + (long)jb * CHOL_NB * CHOL_NB, t.a);
 }
-__global__ __launch_bounds__(256) void gk_chol_update(const BProb* __restrict__ pr, const BTile* __restrict__ tl,
-                                                      int jb) {
+// tile t.a of the update after block column jb; tile 0 is the problem's next
+// diagonal block, factored at once
+__global__ __launch_bounds__(256) void gk_chol_update_diag(const BProb* __restrict__ pr,
+                                                           const BTile* __restrict__ tl, int jb) {
+  constexpr int NLDS = CHOL_UPD_LDS > CHOL_DIAG_LDS ? CHOL_UPD_LDS : CHOL_DIAG_LDS;
+  __shared__ __attribute__((aligned(1024))) double lds[NLDS];
   const BTile t = tl[blockIdx.x];
   const BProb& b = pr[t.g];
-  const int j0 = jb * CHOL_NB, jn = min(CHOL_NB, b.d - j0);
-  chol_update_tile(b.C, b.d, j0, jn, jb + 1, t.a);
+  chol_update_core(b.C, b.d, jb, t.a, lds);
+  if (t.a == 0) {
+    __syncthreads();
+    const int j1 = (jb + 1) * CHOL_NB;
+    chol_diag_core(b.C, b.d, j1, min(CHOL_NB, b.d - j1), b.Linv + (long)(jb + 1) * CHOL_NB * CHOL_NB, b.info, lds);
+  }
 }
 
-hipError_t g_chol_step(const BProb* pr, const BTile* diag, int ndiag, const BTile* panel, int npanel,
-                       const BTile* upd, int nupd, int jb, hipStream_t s) {
-  if (ndiag) hipLaunchKernelGGL(gk_chol_diag, dim3(ndiag), dim3(CHOL_DIAG_THREADS), 0, s, pr, diag, jb);
+hipError_t g_chol_diag(const BProb* pr, const BTile* tl, int n, hipStream_t s) {
+  hipLaunchKernelGGL(gk_chol_diag, dim3(n), dim3(CHOL_DIAG_THREADS), 0, s, pr, tl);
+  return hipGetLastError();
+}
+hipError_t g_chol_step(const BProb* pr, const BTile* panel, int npanel, const BTile* upd, int nupd, int jb,
+                       hipStream_t s) {
   if (npanel) hipLaunchKernelGGL(gk_chol_panel, dim3(npanel), dim3(256), 0, s, pr, panel, jb);
-  if (nupd) hipLaunchKernelGGL(gk_chol_update, dim3(nupd), dim3(256), 0, s, pr, upd, jb);
+  if (nupd) hipLaunchKernelGGL(gk_chol_update_diag, dim3(nupd), dim3(256), 0, s, pr, upd, jb);
   return hipGetLastError();
 }
 
