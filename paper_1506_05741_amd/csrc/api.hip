@@ -639,15 +639,10 @@ extern "C" int diam_step_batch(diam_ctx* c, int32_t n, const double* W, const do
   if (W) {
     if (prec == dk::P64) Wp = W;
     else HIPCHK(dk::convert_normals(prec, W, (long)n * dP, c->W, c->Wlo, s));
-  } else {
-    HIPCHK(dk::normals(prec, c->cfg.seed, c->steps, n, d, P, c->W, c->Wlo, s));
   }
   const int stages = c->da_on ? 2 : 1;
-  const double* Up = U;
-  if (!Up) {
-    HIPCHK(dk::uniforms(c->cfg.seed, c->steps, n, P, stages, c->U, s));
-    Up = c->U;
-  }
+  const double* Up = U ? U : c->U;
+  HIPCHK(dk::draws(prec, c->cfg.seed, c->steps, n, d, P, stages, W ? nullptr : c->W, c->Wlo, U ? nullptr : c->U, s));
   prof_end(c, ps);
   const double beta = c->cfg.beta, alpha = c->cfg.alpha;
   const double cc = beta * alpha;
@@ -840,7 +835,7 @@ extern "C" int diam_surrogate_train(diam_ctx* c, const double* X, const double* 
     const long chunk = whole ? 1L << 20 : nmax;
     for (long k0 = 0; k0 < n; k0 += chunk) {
       const int nc = (int)(n - k0 < chunk ? n - k0 : chunk);
-      HIPCHK(dk::trsm_whiten(c->L, X + k0 * d, c->xr, whole ? nullptr : c->Zs, c->t64 + k0, c->linv, d, nc, s));
+      HIPCHK(dk::trsm_whiten(c->L, X + k0 * d, c->xr, whole ? nullptr : c->Zs, c->t64 + k0, c->linv, d, nc, nullptr, s));
     }
     HIPCHK(dk::axpy_f64(lp, c->t64, 1.0 / (2.0 * c->cfg.alpha * c->cfg.alpha), n, c->t64, s));
     target = c->t64;
@@ -906,6 +901,7 @@ extern "C" int diam_merge_moments(diam_ctx* c) {
   const int ps = prof_begin(c, DIAM_ST_MERGE);
   double* G = c->Lnew;  // scratch until the next factorisation
   bool global = true;
+  dk::Scatter sc{G, c->h, 1, 1};
   long Kg = K;
   if (c->cfg.M > 1) {
     // chain-local sums of the batch (eqs. mom2p, mom1p); every M-th interval
@@ -919,9 +915,9 @@ extern "C" int diam_merge_moments(diam_ctx* c) {
       Kg = (long)llround(c->loc_n) * P;
     }
   } else {
-    HIPCHK(dk::syrk_window(c->prec, c->win, c->wint, d, K, G, c->h, c->syrk, s));
+    HIPCHK(dk::syrk_window(c->prec, c->win, c->wint, d, K, c->syrk, &sc, s));
   }
-  if (global) HIPCHK(dk::fold_moments(G, c->h, c->xr, c->N, Kg, c->S, c->m, d, s));
+  if (global) HIPCHK(dk::fold_moments(sc, c->xr, c->N, Kg, c->S, c->m, d, s));
   prof_end(c, ps);
   if (c->psrf_on) {
     // the store still holds the window's states and xr its pivot
@@ -1027,13 +1023,13 @@ static int refresh_h2(diam_ctx* c) {
 // retrying on C + eps_j I, eps_j = 10^j jitter0 tr(C)/d (1 if not > 0), when a
 // pivot is not positive.  *j: -1, the level used, or jitter_tries when every
 // try failed.  Also reports a target error flagged by the steps before.
-static int factor_jitter(diam_ctx* c, const double* S, const double* m, int* j) {
+// cnt, unless null: P counters to clear on the way.
+static int factor_jitter(diam_ctx* c, const double* S, const double* m, int* j, int* cnt) {
   const int d = c->cfg.d;
   hipStream_t s = c->stream;
   Status st;
   int ps = prof_begin(c, DIAM_ST_CHOL);
-  hipLaunchKernelGGL(k_clear_status, dim3(1), dim3(64), 0, s, c->status, 0);
-  HIPCHK(dk::cov_assemble(S, m, 0.0, c->Lnew, &c->status->trace, d, s));
+  HIPCHK(dk::cov_assemble(S, m, 0.0, c->Lnew, &c->status->trace, &c->status->info, cnt, c->cfg.P, d, s));
   HIPCHK(dk::potrf(c->Lnew, d, &c->status->info, c->linv, s));
   prof_end(c, ps);
   int r = read_status(c, &st);
@@ -1049,8 +1045,7 @@ static int factor_jitter(diam_ctx* c, const double* S, const double* m, int* j) 
     for (int q = 0; q < c->cfg.jitter_tries; ++q) {
       const double eps = pow(10.0, q) * c->cfg.jitter0 * sc;
       ps = prof_begin(c, DIAM_ST_CHOL);
-      hipLaunchKernelGGL(k_clear_status, dim3(1), dim3(64), 0, s, c->status, 0);
-      HIPCHK(dk::cov_assemble(S, m, eps, c->Lnew, nullptr, d, s));
+      HIPCHK(dk::cov_assemble(S, m, eps, c->Lnew, nullptr, &c->status->info, nullptr, 0, d, s));
       HIPCHK(dk::potrf(c->Lnew, d, &c->status->info, c->linv, s));
       prof_end(c, ps);
       r = read_status(c, &st);
@@ -1096,7 +1091,7 @@ static int update_local(diam_ctx* c, int32_t* jitter_used) {
     HIPCHK(dk::pc_moments(c->S, c->m, c->N, c->Gp + p * dd, c->hp + (long)p * d, c->xr, c->loc_n, c->Spg, c->mpg,
                           d, s));
     int j = -1;
-    r = factor_jitter(c, c->Spg, c->mpg, &j);
+    r = factor_jitter(c, c->Spg, c->mpg, &j, nullptr);
     if (r) return r;
     jmax = std::max(jmax, j);
     if (j == c->cfg.jitter_tries) {
@@ -1139,7 +1134,9 @@ static int update_impl(diam_ctx* c, int32_t* jitter_used, bool refactor) {
     if (rate > c->acc_max) c->cfg.beta = std::min(c->cfg.beta * c->adapt_factor, c->beta_max);
     else if (rate < c->acc_min) c->cfg.beta = c->cfg.beta / c->adapt_factor;
   }
-  hipLaunchKernelGGL(k_fill_i32, dim3(nblk(P)), dim3(256), 0, s, c->wacc, (long)P);
+  const bool local = refactor && c->cfg.M > 1 && c->m_int > 0;
+  if (!refactor || local)  // a refactorisation clears them on its way
+    hipLaunchKernelGGL(k_fill_i32, dim3(nblk(P)), dim3(256), 0, s, c->wacc, (long)P);
   c->win_steps = 0;
   if (!refactor) {  // fixed factor: beta only; still report a target error of the past steps
     if (jitter_used) *jitter_used = -1;
@@ -1150,9 +1147,9 @@ static int update_impl(diam_ctx* c, int32_t* jitter_used, bool refactor) {
     if (st.err) return status_error(c, st.err);
     return refresh_h2(c);
   }
-  if (c->cfg.M > 1 && c->m_int > 0) return update_local(c, jitter_used);
+  if (local) return update_local(c, jitter_used);
   int j = -1;
-  int r = factor_jitter(c, c->S, c->m, &j);
+  int r = factor_jitter(c, c->S, c->m, &j, c->wacc);
   if (r) return r;
   c->last_jitter = j;
   if (jitter_used) *jitter_used = j;
@@ -1164,10 +1161,9 @@ static int update_impl(diam_ctx* c, int32_t* jitter_used, bool refactor) {
   c->pc_on = 0;  // every chain shares the new pair again
   const int ps = prof_begin(c, DIAM_ST_WHITEN);
   HIPCHK(dk::round_factor(c->prec, c->L, c->Llow, d, s));
-  HIPCHK(hipMemcpyAsync(c->xr, c->m, d * sizeof(double), hipMemcpyDeviceToDevice, s));
   // the factorisation left the inverses of the unrounded diagonal blocks
   if (c->prec != dk::P64) HIPCHK(dk::trsm_inverses(c->L, c->linv, d, s));
-  HIPCHK(dk::trsm_whiten(c->L, c->X, c->xr, c->Z, c->zq + (long)c->cur * P, c->linv, d, P, s));
+  HIPCHK(dk::trsm_whiten(c->L, c->X, c->m, c->Z, c->zq + (long)c->cur * P, c->linv, d, P, c->xr, s));
   const int r2 = refresh_h2(c);
   prof_end(c, ps);
   return r2;

@@ -523,7 +523,7 @@ static int retry_failed(diam_batch* b, int32_t* jitter, int* any_fail) {
       const BProb& p = b->hp[g];
       const int d = p.d;
       tr_dev = p.h;
-      BCHK(dk::cov_assemble(p.S, p.m, 0.0, p.C, tr_dev, d, s));
+      BCHK(dk::cov_assemble(p.S, p.m, 0.0, p.C, tr_dev, nullptr, nullptr, 0, d, s));
       double tr = 0.0;
       BCHK(hipMemcpyAsync(&tr, tr_dev, 8, hipMemcpyDeviceToHost, s));
       BCHK(hipStreamSynchronize(s));
@@ -534,7 +534,7 @@ static int retry_failed(diam_batch* b, int32_t* jitter, int* any_fail) {
         const double eps = pow(10.0, q) * b->cfg.jitter0 * sc;
         int zero = 0;
         BCHK(hipMemcpyAsync(p.info, &zero, sizeof(int), hipMemcpyHostToDevice, s));
-        BCHK(dk::cov_assemble(p.S, p.m, eps, p.C, nullptr, d, s));
+        BCHK(dk::cov_assemble(p.S, p.m, eps, p.C, nullptr, nullptr, nullptr, 0, d, s));
         BCHK(dk::potrf(p.C, d, p.info, p.Linv, s));
         int st = 0;
         BCHK(hipMemcpyAsync(&st, p.info, sizeof(int), hipMemcpyDeviceToHost, s));
@@ -552,7 +552,7 @@ static int retry_failed(diam_batch* b, int32_t* jitter, int* any_fail) {
         BCHK(hipGetLastError());
         BCHK(hipMemcpyAsync(p.xr, p.m, (size_t)d * 8, hipMemcpyDeviceToDevice, s));
         BCHK(dk::trsm_inverses(p.L, p.Linv, d, s));
-        BCHK(dk::trsm_whiten(p.L, p.X, p.xr, p.Z, p.zq, p.Linv, d, b->P, s));
+        BCHK(dk::trsm_whiten(p.L, p.X, p.xr, p.Z, p.zq, p.Linv, d, b->P, nullptr, s));
       } else {
         *any_fail = 1;
       }

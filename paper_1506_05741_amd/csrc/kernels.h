@@ -92,18 +92,26 @@ hipError_t trigemm(Prec prec, const void* L, const void* W, const void* Wlo, voi
                    hipStream_t s);
 
 // Scatter of the shifted window Xs (d x K): FP64 result G stored in the upper
-// triangle (G(i,j), i >= j, at row j, column i), plus row sums h.
+// triangle (G(i,j), i >= j, at row j, column i), plus row sums h; both as
+// partial sums over ns and nh parts of K, each part d x d and d.
+struct Scatter {
+  const double *G, *h;
+  int ns, nh;
+};
 // f64/f32: column-major Xs (ld = d); bf16: row-major transposed window (ld = K).
 size_t syrk_scratch_bytes(int prec, int d, long K);
-// Xw: the window (col-major d x K); Xt: room for its row-major copy (bf16 only)
-hipError_t syrk_window(Prec prec, const void* Xw, void* Xt, int d, long K, double* G, double* h, void* scratch,
+// Xw: the window (col-major d x K); Xt: room for its row-major copy (bf16
+// only); the parts lie in scratch
+hipError_t syrk_window(Prec prec, const void* Xw, void* Xt, int d, long K, void* scratch, Scatter* out,
                        hipStream_t s);
 
 // Fold the window into the global moments (counts N -> N + K).
-hipError_t fold_moments(const double* G, const double* h, const double* sft, double N, long K, double* S, double* m,
+hipError_t fold_moments(const Scatter& g, const double* sft, double N, long K, double* S, double* m, int d,
+                        hipStream_t s);
+// Cov = S - m m^T + eps I into the lower triangle of C (upper zeroed); unless
+// null: trace -> *tr, *info and the P counters cnt cleared.
+hipError_t cov_assemble(const double* S, const double* m, double eps, double* C, double* tr, int* info, int* cnt, int P,
                         int d, hipStream_t s);
-// Cov = S - m m^T + eps I into the lower triangle of C (upper zeroed); trace -> *tr.
-hipError_t cov_assemble(const double* S, const double* m, double eps, double* C, double* tr, int d, hipStream_t s);
 // In-place lower Cholesky; *info = 0 on success, else 1 + first failing column.
 // Linv: chol_scratch_bytes(d) of scratch (inverses of the diagonal blocks).
 size_t chol_scratch_bytes(int d);
@@ -121,14 +129,14 @@ hipError_t trsm_inverses(const double* L, double* Linv, int d, hipStream_t s);
 // Rows the whitening solves per launch: all of them for moderate d.
 __host__ __device__ int whiten_rows(int d);
 // Z = L^-1 (X - xr) (d x P), zq[p] = ||z_p||^2 (either may be null; Z only if
-// whiten_rows(d) >= d).
+// whiten_rows(d) >= d); xr also into xr_copy unless null.
 hipError_t trsm_whiten(const double* L, const double* X, const double* xr, double* Z, double* zq, const double* Linv,
-                       int d, int P, hipStream_t s);
+                       int d, int P, double* xr_copy, hipStream_t s);
 
-// Normals for steps [s0, s0 + n) of P chains; layout per step d x P column-major.
-hipError_t normals(Prec prec, uint64_t seed, long s0, int n, int d, int P, void* W, void* Wlo, hipStream_t s);
-// Uniforms for steps [s0, s0 + n), `stages` per step: U[t][g][p].
-hipError_t uniforms(uint64_t seed, long s0, int n, int P, int stages, double* U, hipStream_t s);
+// Normals (W, Wlo; layout per step d x P column-major) and uniforms (U[t][g][p],
+// `stages` per step) for steps [s0, s0 + n) of P chains; W or U null: not drawn.
+hipError_t draws(Prec prec, uint64_t seed, long s0, int n, int d, int P, int stages, void* W, void* Wlo, double* U,
+                 hipStream_t s);
 // Caller FP64 normals -> working format (f32, or bf16 hi/lo).
 hipError_t convert_normals(Prec prec, const double* W64, long count, void* W, void* Wlo, hipStream_t s);
 

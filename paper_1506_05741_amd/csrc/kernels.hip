@@ -2,6 +2,8 @@
 // dense contractions run on MFMA through the tile engines of gemm.h.
 #include <math.h>
 
+#include <algorithm>
+
 #include "gemm.h"
 #include "kernels.h"
 
@@ -855,9 +857,8 @@ __global__ __launch_bounds__(256) void k_syrk_e(const T* __restrict__ Xs, int d,
 // run along j, so the stores are 128-byte runs of a column of G.
 template <typename T, int BT, int ST>
 DEV void syrk_tile_t(const T* __restrict__ Xs, int ld, int d, int K, int kchunk, int t, int ksp,
-                     double* __restrict__ Gpart) {
+                     double* __restrict__ Gpart, T* lds) {
   typedef TFrag<T, BT, BT, 2, 2> F;
-  __shared__ __attribute__((aligned(1024))) T lds[t_lds_elems<T, BT, BT, ST>()];
   int bi, bj;
   tile_pair(t, bi, bj);
   const int i0 = bi * BT, j0 = bj * BT;
@@ -895,11 +896,72 @@ DEV void syrk_tile_t(const T* __restrict__ Xs, int ld, int d, int K, int kchunk,
       }
 }
 
+// Row sums over K of the window.  COLMAJOR: element (i, k) at X[i + k d];
+// otherwise at X[i K + k] (bf16 transposed window).
+// Each of the four threads of a row adds its values in turn, ROWSUM_U loads in
+// flight at a time (one by one the chain took 133 us at d = 100, K = 3200).
+constexpr int ROWSUM_U = 32;
+
+template <typename T, bool COLMAJOR>
+DEV void rowsum_block(const T* __restrict__ X, int d, long ld, int K, int kchunk, int bx, int by,
+                      double* __restrict__ hpart, double (*red)[64]) {
+  const int kb = by * kchunk, ke = min(K, kb + kchunk);
+  if (COLMAJOR) {
+    const int r = threadIdx.x & 63, q = threadIdx.x >> 6;
+    const int i = bx * 64 + r;
+    double s = 0.0;
+    if (i < d) {
+      const T* p = X + i;
+      int k = kb + q;
+      if (k + 4 * (ROWSUM_U - 1) < ke) {
+        T v[ROWSUM_U], w[ROWSUM_U];
+#pragma unroll
+        for (int u = 0; u < ROWSUM_U; ++u) v[u] = p[(long)(k + 4 * u) * ld];
+        for (k += 4 * ROWSUM_U; k + 4 * (ROWSUM_U - 1) < ke; k += 4 * ROWSUM_U) {
+#pragma unroll
+          for (int u = 0; u < ROWSUM_U; ++u) w[u] = p[(long)(k + 4 * u) * ld];
+#pragma unroll
+          for (int u = 0; u < ROWSUM_U; ++u) s += (double)v[u];
+#pragma unroll
+          for (int u = 0; u < ROWSUM_U; ++u) v[u] = w[u];
+        }
+#pragma unroll
+        for (int u = 0; u < ROWSUM_U; ++u) s += (double)v[u];
+      }
+      for (; k < ke; k += 4) s += (double)p[(long)k * ld];
+    }
+    red[q][r] = s;
+    __syncthreads();
+    if (threadIdx.x < 64 && i < d)
+      hpart[(long)by * d + i] = (red[0][r] + red[1][r]) + (red[2][r] + red[3][r]);
+  } else {
+    // one row per wavefront, 4 rows per block
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int i = bx * 4 + w;
+    if (i >= d) return;
+    double s = 0.0;
+    for (int k = kb + lane; k < ke; k += 64) s += (double)bf16_bits_to_f32(((const u16*)X)[(long)i * K + k]);
+    s = wave_sum_f64(s);
+    if (lane == 0) hpart[(long)by * d + i] = s;
+  }
+}
+
+// The window's scatter and, in FP64, on the first nrb nh workgroups of split 0
+// its row sums: a chain of loads of its own (26 us at d = 1024), beside the
+// products.  The loads in flight take registers, which FP32 products need for
+// their occupancy (173 + 21 us apart, 231 together, at d = 1024, K = 12800).
 template <typename T, int BT, int ST>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_syrk_t(const T* __restrict__ Xs, int d,
-                                                                                       int K, int kchunk,
-                                                                                       double* __restrict__ Gpart) {
-  syrk_tile_t<T, BT, ST>(Xs, d, d, K, kchunk, blockIdx.x, blockIdx.y, Gpart);
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_syrk_t(
+    const T* __restrict__ Xs, int d, int K, int kchunk, double* __restrict__ Gpart, int nrb, int nh, int hchunk,
+    double* __restrict__ hpart) {
+  __shared__ __attribute__((aligned(1024))) T lds[t_lds_elems<T, BT, BT, ST>()];
+  const int b = blockIdx.x;
+  if constexpr (sizeof(T) == 8)
+    if (b < nrb * nh) {
+      if (blockIdx.y == 0) rowsum_block<T, true>(Xs, d, d, K, hchunk, b % nrb, b / nrb, hpart, (double (*)[64])lds);
+      return;
+    }
+  syrk_tile_t<T, BT, ST>(Xs, d, d, K, kchunk, b - nrb * nh, blockIdx.y, Gpart, lds);
 }
 
 // 64-row tiles (FP64 d = 4096, K = 65536: 22.5 to 21.1 ms, 2080 tiles being
@@ -907,15 +969,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
 // ones where those would not give every CU one (d = 100, K = 3200: 6 tiles).
 // false: operands not aligned for the engine.
 template <typename T>
-static bool syrk_t(const void* Xs, int d, long K, int ns, int kchunk, double* Gpart, hipStream_t s) {
+static bool syrk_t(const void* Xs, int d, long K, int ns, int kchunk, double* Gpart, int nh, int hchunk,
+                   double* hpart, hipStream_t s) {
   if (!t_gemm_ok<T, false, false>(Xs, d, d, Xs, d, d, K)) return false;
   const int n64 = cdiv(d, 64), n32 = cdiv(d, 32);
+  if (sizeof(T) != 8) nh = 0;
   if ((long)n64 * (n64 + 1) / 2 * ns < 256)
-    hipLaunchKernelGGL((k_syrk_t<T, 32, 6>), dim3(n32 * (n32 + 1) / 2, ns), dim3(256), 0, s, (const T*)Xs, d, (int)K,
-                       kchunk, Gpart);
+    hipLaunchKernelGGL((k_syrk_t<T, 32, 6>), dim3(n64 * nh + n32 * (n32 + 1) / 2, ns), dim3(256), 0, s, (const T*)Xs,
+                       d, (int)K, kchunk, Gpart, n64, nh, hchunk, hpart);
   else
-    hipLaunchKernelGGL((k_syrk_t<T, 64, 3>), dim3(n64 * (n64 + 1) / 2, ns), dim3(256), 0, s, (const T*)Xs, d, (int)K,
-                       kchunk, Gpart);
+    hipLaunchKernelGGL((k_syrk_t<T, 64, 3>), dim3(n64 * nh + n64 * (n64 + 1) / 2, ns), dim3(256), 0, s, (const T*)Xs,
+                       d, (int)K, kchunk, Gpart, n64, nh, hchunk, hpart);
   return true;
 }
 
@@ -1032,61 +1096,11 @@ __global__ __launch_bounds__(512) void k_syrk_pl(const u16* __restrict__ Xt, int
       }
 }
 
-// Row sums over K of the window.  COLMAJOR: element (i, k) at X[i + k d];
-// otherwise at X[i K + k] (bf16 transposed window).
-// Each of the four threads of a row adds its values in turn, ROWSUM_U loads in
-// flight at a time (one by one the chain took 133 us at d = 100, K = 3200).
-constexpr int ROWSUM_U = 32;
-
-template <typename T, bool COLMAJOR>
-DEV void rowsum_block(const T* __restrict__ X, int d, long ld, int K, int kchunk, int bx, int by,
-                      double* __restrict__ hpart) {
-  __shared__ double red[4][64];
-  const int kb = by * kchunk, ke = min(K, kb + kchunk);
-  if (COLMAJOR) {
-    const int r = threadIdx.x & 63, q = threadIdx.x >> 6;
-    const int i = bx * 64 + r;
-    double s = 0.0;
-    if (i < d) {
-      const T* p = X + i;
-      int k = kb + q;
-      if (k + 4 * (ROWSUM_U - 1) < ke) {
-        T v[ROWSUM_U], w[ROWSUM_U];
-#pragma unroll
-        for (int u = 0; u < ROWSUM_U; ++u) v[u] = p[(long)(k + 4 * u) * ld];
-        for (k += 4 * ROWSUM_U; k + 4 * (ROWSUM_U - 1) < ke; k += 4 * ROWSUM_U) {
-#pragma unroll
-          for (int u = 0; u < ROWSUM_U; ++u) w[u] = p[(long)(k + 4 * u) * ld];
-#pragma unroll
-          for (int u = 0; u < ROWSUM_U; ++u) s += (double)v[u];
-#pragma unroll
-          for (int u = 0; u < ROWSUM_U; ++u) v[u] = w[u];
-        }
-#pragma unroll
-        for (int u = 0; u < ROWSUM_U; ++u) s += (double)v[u];
-      }
-      for (; k < ke; k += 4) s += (double)p[(long)k * ld];
-    }
-    red[q][r] = s;
-    __syncthreads();
-    if (threadIdx.x < 64 && i < d)
-      hpart[(long)by * d + i] = (red[0][r] + red[1][r]) + (red[2][r] + red[3][r]);
-  } else {
-    // one row per wavefront, 4 rows per block
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int i = bx * 4 + w;
-    if (i >= d) return;
-    double s = 0.0;
-    for (int k = kb + lane; k < ke; k += 64) s += (double)bf16_bits_to_f32(((const u16*)X)[(long)i * K + k]);
-    s = wave_sum_f64(s);
-    if (lane == 0) hpart[(long)by * d + i] = s;
-  }
-}
-
 template <typename T, bool COLMAJOR>
 __global__ __launch_bounds__(256) void k_rowsum(const T* __restrict__ X, int d, int K, int kchunk,
                                                 double* __restrict__ hpart) {
-  rowsum_block<T, COLMAJOR>(X, d, d, K, kchunk, blockIdx.x, blockIdx.y, hpart);
+  __shared__ double red[4][64];
+  rowsum_block<T, COLMAJOR>(X, d, d, K, kchunk, blockIdx.x, blockIdx.y, hpart, red);
 }
 
 // col-major d x K bf16 -> row-major d x K (ld K)
@@ -1169,26 +1183,6 @@ __global__ __launch_bounds__(256) void k_transpose_rowsum_bf16(const u16* __rest
   }
 }
 
-__global__ __launch_bounds__(256) void k_reduce_splits(const double* __restrict__ Gpart, int ns,
-                                                       const double* __restrict__ hpart, int nh, int d,
-                                                       double* __restrict__ G, double* __restrict__ h) {
-  const long e = (long)blockIdx.x * 256 + threadIdx.x;
-  const long dd = (long)d * d;
-  if (e < dd) {
-    const int r = (int)(e % d), c = (int)(e / d);
-    if (r <= c) {  // the scatter is stored in the upper triangle
-      double g = 0.0;
-      for (int q = 0; q < ns; ++q) g += Gpart[q * dd + e];
-      G[e] = g;
-    }
-  }
-  if (e < d) {
-    double s = 0.0;
-    for (int q = 0; q < nh; ++q) s += hpart[(long)q * d + e];
-    h[e] = s;
-  }
-}
-
 // Output tiles of the scatter: 64 x 64 lower pairs (f64/f32) or 128 x 64
 // lower-covering tiles (bf16).
 // bf16 windows whose tiles are whole take the direct-to-LDS kernel
@@ -1229,7 +1223,7 @@ size_t syrk_scratch_bytes(int prec, int d, long K) {
   return (size_t)ns * d * d * sizeof(double) + (size_t)64 * d * sizeof(double);
 }
 
-hipError_t syrk_window(Prec prec, const void* Xw, void* Xt, int d, long K, double* G, double* h, void* scratch,
+hipError_t syrk_window(Prec prec, const void* Xw, void* Xt, int d, long K, void* scratch, Scatter* out,
                        hipStream_t s) {
   const int ns = syrk_splits(prec, d, K);
   const int kchunk = (int)syrk_kchunk(prec, d, K);
@@ -1258,8 +1252,9 @@ hipError_t syrk_window(Prec prec, const void* Xw, void* Xt, int d, long K, doubl
   }
   const int nt = syrk_tiles(prec, d, K);
   dim3 grid(nt, ns);
-  if ((prec == P64 && syrk_t<double>(Xs, d, K, ns, kchunk, Gpart, s)) ||
-      (prec == P32 && syrk_t<float>(Xs, d, K, ns, kchunk, Gpart, s))) {
+  if ((prec == P64 && syrk_t<double>(Xs, d, K, ns, kchunk, Gpart, nh, hchunk, hpart, s)) ||
+      (prec == P32 && syrk_t<float>(Xs, d, K, ns, kchunk, Gpart, nh, hchunk, hpart, s))) {
+    h_done = prec == P64;
   } else if (syrk_pl(prec, d, K) && (uintptr_t)Xs % 16 == 0)
     hipLaunchKernelGGL(k_syrk_pl, grid, dim3(512), 0, s, (const u16*)Xs, d, (int)K, kchunk, Gpart);
   else if (prec == P64)
@@ -1270,19 +1265,17 @@ hipError_t syrk_window(Prec prec, const void* Xw, void* Xt, int d, long K, doubl
     const int vec_ok = (K % 8 == 0) && ((uintptr_t)Xs % 16 == 0);
     hipLaunchKernelGGL(k_syrk_bf16, grid, dim3(256), 0, s, (const u16*)Xs, d, (int)K, kchunk, vec_ok, Gpart);
   }
-  if (prec == P64)
+  if (h_done) {
+  } else if (prec == P64)
     hipLaunchKernelGGL((k_rowsum<double, true>), dim3(cdiv(d, 64), nh), dim3(256), 0, s, (const double*)Xs, d, (int)K,
                        hchunk, hpart);
   else if (prec == P32)
     hipLaunchKernelGGL((k_rowsum<float, true>), dim3(cdiv(d, 64), nh), dim3(256), 0, s, (const float*)Xs, d, (int)K,
                        hchunk, hpart);
-  else if (!h_done)
+  else
     hipLaunchKernelGGL((k_rowsum<u16, false>), dim3(cdiv(d, 4), nh), dim3(256), 0, s, (const u16*)Xs, d, (int)K,
                        hchunk, hpart);
-  // reduce the splits in order into G (lower) and h
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_reduce_splits, dim3(cdiv((long)d * d, 256)), dim3(256), 0, s, Gpart, ns, hpart, nh, d, G, h);
+  *out = {Gpart, hpart, ns, nh};
   return hipGetLastError();
 }
 
@@ -1303,44 +1296,61 @@ DEV void fold_S_elem(const double* __restrict__ G, const double* __restrict__ h,
   S[e] = (N * S[e] + sxx) / (N + n);
 }
 
-__global__ __launch_bounds__(256) void k_fold_mean(const double* __restrict__ h, const double* __restrict__ sft, double N,
-                                                   double n, double* __restrict__ m, int d) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i < d) fold_mean_elem(h, sft, N, n, m, i);
-}
-
-// fold_S_elem by 64 x 64 tiles of S: the scatter's upper-storage tile that
-// holds the tile's values, G(min(i, j), max(i, j)), is read along its columns
-// into LDS first, so the tiles below the diagonal do not read G at a stride
-// of d (each element's arithmetic is fold_S_elem's).
-__global__ __launch_bounds__(256) void k_fold_S(const double* __restrict__ G, const double* __restrict__ h,
-                                                const double* __restrict__ sft, double N, double n,
-                                                double* __restrict__ S, int d) {
-  __shared__ double T[64][65];
-  const int bx = blockIdx.x, by = blockIdx.y;
-  const int r0 = 64 * min(bx, by), c0 = 64 * max(bx, by);
+// The merge: the scatter's splits added up in order and folded into S and m,
+// one workgroup per pair of 64 x 64 tiles of S (tile (bi, bj), bi >= bj, and
+// its mirror image).  The scatter's upper-storage tile is read along its
+// columns into LDS, so the tile below the diagonal does not read it at a
+// stride of d; each element's arithmetic is fold_S_elem's.  One launch and one
+// trip through the splits in place of three (d = 1024: 20 + 10 + 3 us, now 16).
+constexpr int MERGE_TY = 16;
+__global__ __launch_bounds__(64 * MERGE_TY) void k_merge(Scatter g, const double* __restrict__ sft, double N, double n,
+                                                         double* __restrict__ S, double* __restrict__ m, int d) {
+  __shared__ double T[64][65], hs[2][64];
+  int bi, bj;
+  tile_pair(blockIdx.x, bi, bj);
+  const int r0 = 64 * bj, c0 = 64 * bi;
   const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-  for (int c = ty; c < 64; c += 4) {
+  const long dd = (long)d * d;
+  if (ty < 2) {
+    const int i = (ty ? c0 : r0) + tx;
+    double s = 0.0;
+    if (i < d)
+      for (int q = 0; q < g.nh; ++q) s += g.h[(long)q * d + i];
+    hs[ty][tx] = s;
+    if (ty == 0 && bi == bj && i < d) m[i] = (N * m[i] + (s + n * sft[i])) / (N + n);
+  }
+#pragma unroll
+  for (int c = ty; c < 64; c += MERGE_TY) {
     const int r = r0 + tx, cc = c0 + c;
-    T[tx][c] = (r < d && cc < d) ? G[r + (long)cc * d] : 0.0;
+    double v = 0.0;
+    if (r < d && cc < d)
+      for (int q = 0; q < g.ns; ++q) v += g.G[q * dd + r + (long)cc * d];
+    T[tx][c] = v;
   }
   __syncthreads();
-  for (int jj = ty; jj < 64; jj += 4) {
-    const int i = 64 * bx + tx, j = 64 * by + jj;
+  auto fold = [&](int i, int j, double v, int a, double ha, int b, double hb) {
+    const long e = i + (long)j * d;
+    const double sxx = v + sft[a] * hb + ha * sft[b] + n * sft[a] * sft[b];
+    S[e] = (N * S[e] + sxx) / (N + n);
+  };
+#pragma unroll
+  for (int jj = ty; jj < 64; jj += MERGE_TY) {
+    const int i = c0 + tx, j = r0 + jj;
     if (i < d && j < d) {
-      const int a = i > j ? i : j, b = i > j ? j : i;
-      const double g = T[b - r0][a - c0];
-      const long e = i + (long)j * d;
-      const double sxx = g + sft[a] * h[b] + h[a] * sft[b] + n * sft[a] * sft[b];
-      S[e] = (N * S[e] + sxx) / (N + n);
+      if (i >= j) fold(i, j, T[jj][tx], i, hs[1][tx], j, hs[0][jj]);
+      else fold(i, j, T[tx][jj], j, hs[0][jj], i, hs[1][tx]);  // diagonal tile, upper part
+    }
+    if (bi != bj) {
+      const int iu = r0 + tx, ju = c0 + jj;
+      if (iu < d && ju < d) fold(iu, ju, T[tx][jj], ju, hs[1][jj], iu, hs[0][tx]);
     }
   }
 }
 
-hipError_t fold_moments(const double* G, const double* h, const double* sft, double N, long K, double* S, double* m,
-                        int d, hipStream_t s) {
-  hipLaunchKernelGGL(k_fold_S, dim3(cdiv(d, 64), cdiv(d, 64)), dim3(256), 0, s, G, h, sft, N, (double)K, S, d);
-  hipLaunchKernelGGL(k_fold_mean, dim3(cdiv(d, 256)), dim3(256), 0, s, h, sft, N, (double)K, m, d);
+hipError_t fold_moments(const Scatter& g, const double* sft, double N, long K, double* S, double* m, int d,
+                        hipStream_t s) {
+  const int nt = cdiv(d, 64);
+  hipLaunchKernelGGL(k_merge, dim3(nt * (nt + 1) / 2), dim3(64 * MERGE_TY), 0, s, g, sft, N, (double)K, S, m, d);
   return hipGetLastError();
 }
 
@@ -1353,12 +1363,6 @@ DEV void cov_elem(const double* __restrict__ S, const double* __restrict__ m, do
     if (i == j) v += eps;
   }
   C[e] = v;
-}
-
-__global__ __launch_bounds__(256) void k_cov(const double* __restrict__ S, const double* __restrict__ m, double eps,
-                                             double* __restrict__ C, int d) {
-  const long e = (long)blockIdx.x * 256 + threadIdx.x;
-  if (e < (long)d * d) cov_elem(S, m, eps, C, d, e);
 }
 
 DEV void trace_block(const double* __restrict__ S, const double* __restrict__ m, int d, double* __restrict__ tr) {
@@ -1374,14 +1378,24 @@ DEV void trace_block(const double* __restrict__ S, const double* __restrict__ m,
   if (threadIdx.x == 0) *tr = red[0];
 }
 
-__global__ __launch_bounds__(256) void k_trace(const double* __restrict__ S, const double* __restrict__ m, int d,
-                                               double* __restrict__ tr) {
-  trace_block(S, m, d, tr);
+// The last workgroup forms the trace and clears the factorisation's words.
+__global__ __launch_bounds__(256) void k_cov(const double* __restrict__ S, const double* __restrict__ m, double eps,
+                                             double* __restrict__ C, int d, double* __restrict__ tr,
+                                             int* __restrict__ info, int* __restrict__ cnt, int P) {
+  if (blockIdx.x == gridDim.x - 1) {
+    if (tr) trace_block(S, m, d, tr);
+    if (info && threadIdx.x == 0) *info = 0;
+    if (cnt)
+      for (int p = threadIdx.x; p < P; p += 256) cnt[p] = 0;
+    return;
+  }
+  const long e = (long)blockIdx.x * 256 + threadIdx.x;
+  if (e < (long)d * d) cov_elem(S, m, eps, C, d, e);
 }
 
-hipError_t cov_assemble(const double* S, const double* m, double eps, double* C, double* tr, int d, hipStream_t s) {
-  hipLaunchKernelGGL(k_cov, dim3(cdiv((long)d * d, 256)), dim3(256), 0, s, S, m, eps, C, d);
-  if (tr) hipLaunchKernelGGL(k_trace, dim3(1), dim3(256), 0, s, S, m, d, tr);
+hipError_t cov_assemble(const double* S, const double* m, double eps, double* C, double* tr, int* info, int* cnt, int P,
+                        int d, hipStream_t s) {
+  hipLaunchKernelGGL(k_cov, dim3(cdiv((long)d * d, 256) + 1), dim3(256), 0, s, S, m, eps, C, d, tr, info, cnt, P);
   return hipGetLastError();
 }
 
@@ -1588,6 +1602,7 @@ DEV void chol_diag_core(double* __restrict__ A, int d, int j0, int jn, double* _
   for (int q = 0; q < CHOL_NB / CHOL_CB; ++q) {
     const int c0 = CHOL_CB * q, wc = c0 / H, n0 = c0 + CHOL_CB, wn = n0 / H;
     const int buf = q & 1;
+    if (c0 >= jn) break;  // uniform: identity from here on, its own factor
     __syncthreads();
     if (n0 < CHOL_NB && w == wn) {
       // owner of the next block: the published block applied to its columns,
@@ -2196,7 +2211,9 @@ DEV void whiten_tile(const double* __restrict__ L, const double* __restrict__ Li
 __global__ __launch_bounds__(512) void k_whiten(const double* __restrict__ L, const double* __restrict__ Linv,
                                                 const double* __restrict__ X, const double* __restrict__ xr,
                                                 double* __restrict__ Z, double* __restrict__ zq, int d, int P, int r0,
-                                                int rows) {
+                                                int rows, double* __restrict__ xr_copy) {
+  if (xr_copy && blockIdx.x == 0)
+    for (int i = threadIdx.x; i < d; i += 512) xr_copy[i] = xr[i];
   whiten_tile(L, Linv, X, xr, Z, zq, d, P, r0, rows, blockIdx.x);
 }
 
@@ -2256,13 +2273,13 @@ hipError_t trsm_inverses(const double* L, double* Linv, int d, hipStream_t s) {
 }
 
 hipError_t trsm_whiten(const double* L, const double* X, const double* xr, double* Z, double* zq, const double* Linv,
-                       int d, int P, hipStream_t s) {
+                       int d, int P, double* xr_copy, hipStream_t s) {
   const int rows = whiten_rows(d);
   const bool whole = rows >= d;
   for (int r0 = 0; r0 < d; r0 += rows) {
     const double* x = r0 ? nullptr : X;
-    hipLaunchKernelGGL(k_whiten, dim3(cdiv(P, 16)), dim3(512), 0, s, L, Linv, x, xr, Z, whole ? zq : (double*)nullptr, d, P, r0,
-                  rows);
+    hipLaunchKernelGGL(k_whiten, dim3(cdiv(P, 16)), dim3(512), 0, s, L, Linv, x, xr, Z, whole ? zq : (double*)nullptr,
+                       d, P, r0, rows, r0 ? (double*)nullptr : xr_copy);
     const int rem = d - (r0 + rows);
     if (rem > 0)
       hipLaunchKernelGGL(k_whiten_update, dim3(cdiv(rem, 64), cdiv(P, 64)), dim3(256), 0, s, L, x, xr, Z, d, P, r0,
@@ -2385,9 +2402,25 @@ DEV void normals4_f32(uint32_t k0, uint32_t k1, uint64_t ctr, float* v) {
   v[3] = rc * s2;
 }
 
+DEV void uniform_elem(uint32_t k0, uint32_t k1, long s0, int P, int stages, double* __restrict__ U, long e) {
+  const int p = (int)(e % P);
+  const long tg = e / P;
+  const int g = (int)(tg % stages);
+  const uint64_t st = (uint64_t)(s0 + tg / stages);
+  const u4_t r = philox4x32_10({(uint32_t)st, (uint32_t)(st >> 32), 1u + (uint32_t)g, (uint32_t)(p >> 1)}, k0, k1);
+  U[e] = (p & 1) ? u01_f64(r.z, r.w) : u01_f64(r.x, r.y);
+}
+
+// The workgroups from nblk on draw the call's nu uniforms.
 __global__ __launch_bounds__(256) void k_normals(int prec, uint32_t k0, uint32_t k1, long g0, long total,
-                                                 void* __restrict__ W, void* __restrict__ Wlo) {
-  const long stride = (long)gridDim.x * 256;
+                                                 void* __restrict__ W, void* __restrict__ Wlo, int nblk, long s0, int P,
+                                                 int stages, long nu, double* __restrict__ U) {
+  if ((int)blockIdx.x >= nblk) {
+    const long e = (long)(blockIdx.x - nblk) * 256 + threadIdx.x;
+    if (e < nu) uniform_elem(k0, k1, s0, P, stages, U, e);
+    return;
+  }
+  const long stride = (long)nblk * 256;
   const long gid = (long)blockIdx.x * 256 + threadIdx.x;
   if (prec == P64) {
     for (long q = gid; 2 * q < total; q += stride) {
@@ -2437,37 +2470,15 @@ __global__ __launch_bounds__(256) void k_normals(int prec, uint32_t k0, uint32_t
   }
 }
 
-hipError_t normals(Prec prec, uint64_t seed, long s0, int n, int d, int P, void* W, void* Wlo, hipStream_t s) {
-  const long total = (long)n * P * d;
-  if (total <= 0) return hipSuccess;
+hipError_t draws(Prec prec, uint64_t seed, long s0, int n, int d, int P, int stages, void* W, void* Wlo, double* U,
+                 hipStream_t s) {
+  const long total = W ? (long)n * P * d : 0, nu = U ? (long)n * stages * P : 0;
+  if (total + nu <= 0) return hipSuccess;
   const long per = (prec == P64) ? 2 : 4;
-  long nq = (total + per - 1) / per;
-  int blocks = (int)((nq + 255) / 256);
-  if (blocks > 4096) blocks = 4096;
-  hipLaunchKernelGGL(k_normals, dim3(blocks), dim3(256), 0, s, (int)prec, (uint32_t)seed, (uint32_t)(seed >> 32),
-                     s0 * (long)P * d, total, W, Wlo);
-  return hipGetLastError();
-}
-
-__global__ __launch_bounds__(256) void k_uniforms(uint32_t k0, uint32_t k1, long s0, int n, int P, int stages,
-                                                  double* __restrict__ U) {
-  const long e = (long)blockIdx.x * 256 + threadIdx.x;
-  const long total = (long)n * stages * P;
-  if (e >= total) return;
-  const int p = (int)(e % P);
-  const long tg = e / P;
-  const int g = (int)(tg % stages);
-  const long t = tg / stages;
-  const uint64_t st = (uint64_t)(s0 + t);
-  const u4_t r = philox4x32_10({(uint32_t)st, (uint32_t)(st >> 32), 1u + (uint32_t)g, (uint32_t)(p >> 1)}, k0, k1);
-  U[e] = (p & 1) ? u01_f64(r.z, r.w) : u01_f64(r.x, r.y);
-}
-
-hipError_t uniforms(uint64_t seed, long s0, int n, int P, int stages, double* U, hipStream_t s) {
-  const long total = (long)n * stages * P;
-  if (total <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_uniforms, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, (uint32_t)seed,
-                     (uint32_t)(seed >> 32), s0, n, P, stages, U);
+  const long nq = (total + per - 1) / per;
+  const int nb = (int)std::min((nq + 255) / 256, 4096L);
+  hipLaunchKernelGGL(k_normals, dim3((unsigned)(nb + (nu + 255) / 256)), dim3(256), 0, s, (int)prec, (uint32_t)seed,
+                     (uint32_t)(seed >> 32), s0 * (long)P * d, total, W, Wlo, nb, s0, P, stages, nu, U);
   return hipGetLastError();
 }
 
@@ -3774,12 +3785,14 @@ hipError_t g_trigemm(const BProb* pr, const BTile* tl, int ntiles, int ncols, do
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void gk_syrk(const BProb* __restrict__ pr, const BTile* __restrict__ tl, int K) {
   const BTile t = tl[blockIdx.x];
   const BProb& b = pr[t.g];
-  syrk_tile_t<float, 64, 3>(b.win, b.ld, b.d, K, K, t.a, 0, b.G);
+  __shared__ __attribute__((aligned(1024))) float lds[t_lds_elems<float, 64, 64, 3>()];
+  syrk_tile_t<float, 64, 3>(b.win, b.ld, b.d, K, K, t.a, 0, b.G, lds);
 }
 __global__ __launch_bounds__(256) void gk_rowsum(const BProb* __restrict__ pr, const BTile* __restrict__ tl, int K) {
   const BTile t = tl[blockIdx.x];
   const BProb& b = pr[t.g];
-  rowsum_block<float, true>(b.win, b.d, b.ld, K, K, t.a, 0, b.h);
+  __shared__ double red[4][64];
+  rowsum_block<float, true>(b.win, b.d, b.ld, K, K, t.a, 0, b.h, red);
 }
 
 hipError_t g_scatter(const BProb* pr, const BTile* syrk_tl, int nsyrk, const BTile* row_tl, int nrow, int K,

@@ -161,6 +161,36 @@ def test_proposal_and_scatter_products(prec, d, P, n):
     assert bool(((s.get_f64(diam.F_S, (d, d)) - ref).abs() * (N0 + K) <= scale + scale.T).all())
 
 
+@pytest.mark.parametrize("prec,d,P,n", [("fp64", 1, 1, 2), ("fp64", 63, 3, 2), ("fp64", 66, 130, 65),
+                                        ("fp64", 129, 2, 4100), ("fp32", 200, 100, 90), ("mixed", 128, 64, 130)])
+def test_merge_by_size(prec, d, P, n):
+    """S and m after a merge from the kernel's own splits, tiles and both
+    triangles, against FP64 sums over the visited states: (K + 8) u of the sums
+    of absolute values in the window's format, the mean's likewise."""
+    s, R, mu, rn = sampler(prec, d, P, n, 17 + d, beta=0.3)
+    S0 = torch.eye(d, dtype=torch.float64, device="cuda") + torch.outer(mu, mu)
+    assert s.seed_moments(S0.contiguous(), mu, 40.0)[0] == diam.OK
+    proj = torch.eye(d, dtype=torch.float64, device="cuda")[:, :min(d, 4)].T.contiguous()
+    trace = torch.zeros(n, 1 + proj.shape[0], P, dtype=torch.float64, device="cuda")
+    s.set_trace(proj, trace)
+    m0 = s.get_f64(diam.F_M, (d,)).clone()
+    s.step_batch(n)
+    s.merge_moments()
+    S, m, K = s.get_f64(diam.F_S, (d, d)), s.get_f64(diam.F_M, (d,)), float(n * P)
+    x = trace[:, 1:].permute(1, 0, 2).reshape(proj.shape[0], -1)
+    q, u = proj.shape[0], {"fp64": U64, "fp32": 2.0 ** -24, "mixed": 2.0 ** -8}[prec]
+    assert torch.equal(S, S.T)
+    y = x - m0[:q, None]
+    err = 2 * (K + 8) * U64 * (x.abs().sum(1) + 40 * m0[:q].abs()) + 2 * u * y.abs().sum(1)
+    assert bool((((40.0 * m0[:q] + x.sum(1)) / (40.0 + K) - m[:q]).abs() * (40.0 + K) <= err).all())
+    ref = (40.0 * S0[:q, :q] + x @ x.T) / (40.0 + K)
+    mag = x.abs() @ x.abs().T + 40 * S0[:q, :q].abs() + K * torch.outer(m0[:q].abs(), m0[:q].abs())
+    acc = U64 if prec == "fp64" else 2.0 ** -24
+    err = 4 * (min(K, 4096) + 8) * acc * mag + 4 * u * (y.abs() @ y.abs().T + y.abs().sum(1)[:, None] * m0[:q].abs() +
+                                                       (y.abs().sum(1)[:, None] * m0[:q].abs()).T)
+    assert bool(((ref - S[:q, :q]).abs() * (40.0 + K) <= err).all())
+
+
 @pytest.mark.parametrize("prec,d", [("fp64", 1), ("fp64", 15), ("fp64", 17), ("fp64", 48), ("fp64", 63), ("fp64", 64),
                                     ("fp64", 66), ("fp64", 127), ("fp64", 129), ("fp64", 320), ("fp64", 451),
                                     ("fp32", 200), ("fp64", 1030)])
