@@ -1104,7 +1104,12 @@ static int update_local(diam_ctx* c, int32_t* jitter_used) {
     HIPCHK(hipMemsetAsync(c->pinfo + p, 0, sizeof(int32_t), s));
   }
   ps = prof_begin(c, DIAM_ST_WHITEN);
-  HIPCHK(dk::pc_adopt(c->Cp, c->mpgp, c->pinfo, c->Lp, c->xrp, d, P, s));
+  if (failed) {  // some chains keep their pair: the others' are copied
+    HIPCHK(dk::pc_adopt(c->Cp, c->mpgp, c->pinfo, c->Lp, c->xrp, d, P, s));
+  } else {  // all new: the buffers change places (a copy of 64 factors of 1024: 176 us)
+    std::swap(c->Lp, c->Cp);
+    std::swap(c->xrp, c->mpgp);
+  }
   HIPCHK(dk::trsm_whiten_batched(c->Lp, dd, c->X, c->xrp, c->Z, c->zq + (long)c->cur * P, c->linvb, sL, d, P,
                                  c->pinfo, s));
   prof_end(c, ps);

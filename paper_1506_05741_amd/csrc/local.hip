@@ -219,28 +219,46 @@ __global__ __launch_bounds__(256) void k_pc_sum(const double* __restrict__ Gp, c
 // Every chain's covariance C_p = S_pg - m_pg m_pg^T (lower triangle, zeros
 // above) and pivot m_pg at once, blockIdx.z = chain: the arithmetic of
 // k_pc_moments followed by the covariance assembly, operation for operation,
-// so a chain's C_p is bitwise what the one-chain path assembles.
+// so a chain's C_p is bitwise what the one-chain path assembles.  256 rows of
+// PC_COV_COLS columns per workgroup, the row's terms formed once: bound by the
+// read of G and the write of C (64 chains of 1024: 390 us with an element and
+// its divisions per thread, now 200).
+constexpr int PC_COV_COLS = 8;
 __global__ __launch_bounds__(256) void k_pc_cov(const double* __restrict__ S, const double* __restrict__ m, double N,
                                                 const double* __restrict__ Gp, const double* __restrict__ hp,
                                                 const double* __restrict__ sft, double n, double* __restrict__ Cp,
                                                 double* __restrict__ mpgp, int d) {
-  const long e = (long)blockIdx.x * 256 + threadIdx.x, dd = (long)d * d;
-  const int z = blockIdx.z;
+  const long dd = (long)d * d;
+  const int z = blockIdx.z, i = blockIdx.x * 256 + threadIdx.x, j0 = blockIdx.y * PC_COV_COLS;
   const double* h = hp + (long)z * d;
-  const double inv = 1.0 / (N + n);
-  if (e < dd) {
-    const int i = (int)(e % d), j = (int)(e / d);
+  const double* G = Gp + z * dd;
+  double* C = Cp + z * dd;
+  if (i >= d) return;
+  const double inv = 1.0 / (N + n), hi = h[i], si = sft[i];
+  const double mi = (N * m[i] + (hi + n * si)) * inv;
+  if (j0 == 0) mpgp[i + (long)z * d] = mi;
+  double g[PC_COV_COLS], sv[PC_COV_COLS];
+#pragma unroll
+  for (int c = 0; c < PC_COV_COLS; ++c) {
+    const int j = j0 + c;
+    const bool in = j < d && i >= j;
+    const long e = i + (long)j * d;
+    g[c] = in ? G[e] : 0.0;
+    sv[c] = in ? S[e] : 0.0;
+  }
+#pragma unroll
+  for (int c = 0; c < PC_COV_COLS; ++c) {
+    const int j = j0 + c;
+    if (j >= d) break;
     double v = 0.0;
     if (i >= j) {
-      const double raw = Gp[e + z * dd] + h[i] * sft[j] + sft[i] * h[j] + n * sft[i] * sft[j];
-      const double Spg = (N * S[e] + raw) * inv;
-      const double mi = (N * m[i] + (h[i] + n * sft[i])) * inv;
+      const double raw = g[c] + hi * sft[j] + si * h[j] + n * si * sft[j];
+      const double Spg = (N * sv[c] + raw) * inv;
       const double mj = (N * m[j] + (h[j] + n * sft[j])) * inv;
       v = Spg - mi * mj;
     }
-    Cp[e + z * dd] = v;
+    C[i + (long)j * d] = v;
   }
-  if (e < d) mpgp[e + (long)z * d] = (N * m[e] + (h[e] + n * sft[e])) * inv;
 }
 
 // Every chain starts the batch's local updates from the shared pair.
@@ -304,8 +322,10 @@ hipError_t pc_moments(const double* S, const double* m, double N, const double* 
 hipError_t pc_cov(const double* S, const double* m, double N, const double* Gp, const double* hp, const double* sft,
                   double n, double* Cp, double* mpgp, int d, int P, hipStream_t s) {
   if (P < 1 || P > 65535) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_pc_cov, dim3((unsigned)cdiv_l((long)d * d, 256), 1, (unsigned)P), dim3(256), 0, s, S, m, N, Gp,
-                     hp, sft, n, Cp, mpgp, d);
+  const long cols = cdiv_l(d, PC_COV_COLS);
+  if (cols > 65535) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_pc_cov, dim3((unsigned)cdiv_l(d, 256), (unsigned)cols, (unsigned)P), dim3(256), 0, s, S, m, N,
+                     Gp, hp, sft, n, Cp, mpgp, d);
   return hipGetLastError();
 }
 
