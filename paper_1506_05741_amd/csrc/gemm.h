@@ -1048,6 +1048,27 @@ DEV uint32_t t_copy_offset(long ld, int nrows, int kv, int blk) {
   return (uint32_t)(e * (long)sizeof(T));
 }
 
+// The same for the narrow copies: quarter u of the block, 4 bytes a lane, so
+// that any row length and stride will do; every element is clamped by itself.
+template <typename T, int ROWS, bool KC>
+DEV uint32_t t_copy_offset_narrow(long ld, int nrows, int kv, int blk, int u) {
+  constexpr int VEC = 16 / (int)sizeof(T), EW = (int)sizeof(T) / 4;
+  const int lane = threadIdx.x & 63;
+  const int q = 16 * u + (lane >> 2), el = (lane & 3) / EW, wb = (lane & 3) % EW * 4;
+  long e;
+  if (KC) {
+    const int r = blk * 8 + (q >> 3);
+    const int k = ((q & 7) ^ tswz(r)) * VEC + el;
+    e = (long)min(r, nrows - 1) * ld + (k < kv ? k : 0);
+  } else {
+    constexpr int LPK = ROWS / VEC;
+    const int k = blk * (64 / LPK) + q / LPK;
+    const int r = ((q % LPK) ^ tkswz<T, ROWS>(k)) * VEC + el;
+    e = min(r, nrows - 1) + (long)(k < kv ? k : 0) * ld;
+  }
+  return (uint32_t)(e * (long)sizeof(T)) + wb;
+}
+
 // LDS index of element (r, k) of an operand slice
 template <typename T, int ROWS, bool KC>
 DEV int t_index(int r, int k) {
@@ -1097,13 +1118,15 @@ __host__ __device__ inline bool t_gemm_ok(const void* A, long lda, int M, const 
 // order, for sums whose order is free.
 // SETS accumulator sets take the slices in turn (slice s to set s mod SETS), as
 // the k-groups of the element engine do; the caller adds them up in order.
+// NARROW: 4 bytes a lane and copy instead of 16, for operands that t_gemm_ok
+// refuses (odd leading dimensions); tiles and order as ever.
 // SPLIT: the sets take consecutive parts of the slices instead, in order (nk a
 // multiple of SETS).
 // GRP slices per stage of the ring and per barrier: for one tile per CU, where
 // a barrier and an LDS round trip per slice would stretch the chain of
 // products, and for GRP = SETS, whose slices are then free to overlap.
 template <typename T, int BM, int BN, int WGM, int WGN, int ST, bool AKC, bool BKC, bool PAIR = false, int SETS = 1,
-          int GRP = 1, bool SPLIT = false>
+          int GRP = 1, bool SPLIT = false, bool NARROW = false>
 DEV void t_gemm(TFrag<T, BM, BN, WGM, WGN> (&fs)[SETS], const T* __restrict__ A, long lda, int M, const T* __restrict__ B,
                 long ldb, int N, int i0, int j0, int kbeg, int kend, T* lds) {
   typedef TFrag<T, BM, BN, WGM, WGN> F;
@@ -1112,7 +1135,8 @@ DEV void t_gemm(TFrag<T, BM, BN, WGM, WGN> (&fs)[SETS], const T* __restrict__ A,
   constexpr int BLK_A = BM / 8, BLK_B = BN / 8, NBLK = BLK_A + BLK_B;
   static_assert(GRP == 1 || SETS == 1 || (SETS == GRP && !SPLIT), "grouped slices: one set, or one per slice");
   static_assert(NBLK % NW == 0, "copy blocks must divide among the waves");
-  constexpr int LPW = NBLK / NW;
+  constexpr int LPW = NBLK / NW, CPB = NARROW ? 4 : 1;  // copies per block
+  static_assert(LPW * CPB * GRP * (ST - 2) < 64, "copies in flight that one wait can count");
   constexpr bool UNROLLED = SPLIT || (SETS > 2 && GRP == 1);  // steps without a loop's end between them
   const int nk = (kend - kbeg) / (GRP * TBK);  // whole stages
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -1122,13 +1146,20 @@ DEV void t_gemm(TFrag<T, BM, BN, WGM, WGN> (&fs)[SETS], const T* __restrict__ A,
   const T* Ab = AKC ? A + (long)i0 * lda + kbeg : A + i0 + (long)kbeg * lda;
   const T* Bb = BKC ? B + (long)j0 * ldb + kbeg : B + j0 + (long)kbeg * ldb;
   const long sa = (AKC ? 1 : lda) * TBK, sb = (BKC ? 1 : ldb) * TBK;
-  uint32_t voff[LPW];
+  uint32_t voff[LPW][CPB];
   auto offsets = [&](int kv) {
 #pragma unroll
     for (int q = 0; q < LPW; ++q) {
       const int blk = w * LPW + q;
-      voff[q] = blk < BLK_A ? t_copy_offset<T, BM, AKC>(lda, M - i0, kv, blk)
-                            : t_copy_offset<T, BN, BKC>(ldb, N - j0, kv, blk - BLK_A);
+#pragma unroll
+      for (int u = 0; u < CPB; ++u) {
+        if constexpr (NARROW)
+          voff[q][u] = blk < BLK_A ? t_copy_offset_narrow<T, BM, AKC>(lda, M - i0, kv, blk, u)
+                                   : t_copy_offset_narrow<T, BN, BKC>(ldb, N - j0, kv, blk - BLK_A, u);
+        else
+          voff[q][u] = blk < BLK_A ? t_copy_offset<T, BM, AKC>(lda, M - i0, kv, blk)
+                                   : t_copy_offset<T, BN, BKC>(ldb, N - j0, kv, blk - BLK_A);
+      }
     }
   };
   auto issue_slice = [&](int sl, int pos) {
@@ -1139,8 +1170,14 @@ DEV void t_gemm(TFrag<T, BM, BN, WGM, WGN> (&fs)[SETS], const T* __restrict__ A,
     for (int q = 0; q < LPW; ++q) {
       const int blk = w * LPW + q;
       const char* src = blk < BLK_A ? pa : pb;
-      __builtin_amdgcn_global_load_lds((const void*)(src + voff[q]),
-                                       (lds_ptr_t)(st + blk * (1024 / (int)sizeof(T))), 16, 0, 0);
+#pragma unroll
+      for (int u = 0; u < CPB; ++u)
+        if constexpr (NARROW)
+          __builtin_amdgcn_global_load_lds((const void*)(src + voff[q][u]),
+                                           (lds_ptr_t)(st + (blk * 4 + u) * (256 / (int)sizeof(T))), 4, 0, 0);
+        else
+          __builtin_amdgcn_global_load_lds((const void*)(src + voff[q][u]),
+                                           (lds_ptr_t)(st + blk * (1024 / (int)sizeof(T))), 16, 0, 0);
     }
   };
   auto issue = [&](int kt, int slot) {
@@ -1238,7 +1275,7 @@ DEV void t_gemm(TFrag<T, BM, BN, WGM, WGN> (&fs)[SETS], const T* __restrict__ A,
     // them the waits for their operands, behind the next barrier, after which
     // the slot they read is refilled: there the reads are waited for here.
     if (UNROLLED) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    if (kt + ST - 2 < nk) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LPW * GRP * (ST - 2)) : "memory");
+    if (kt + ST - 2 < nk) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LPW * CPB * GRP * (ST - 2)) : "memory");
     else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     asm volatile("s_barrier" ::: "memory");
     // the ring slot refilled here was last read before this barrier

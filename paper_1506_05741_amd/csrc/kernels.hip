@@ -585,37 +585,8 @@ hipError_t tgt_gauss(Prec prec, const void* R, const void* V, int d, int P, doub
 // (a) proposal contraction Xi = c L W, L lower triangular: the K range of a
 // row tile stops at its last row.
 // ============================================================================
-template <typename T, int BK>
-DEV void trigemm_tile(const T* __restrict__ L, const T* __restrict__ W, T* __restrict__ Xi, int d, int ncols, double c,
-                      int bx, int by) {
-  constexpr int BM = 64, BN = 64;
-  __shared__ T lds[e_lds_elems<T, BM, BN, BK>()];
-  const int i0 = bx * BM, j0 = by * BN;
-  const int kend = min(d, i0 + BM);
-  EFrag<T, BM, BN> f;
-  f.zero();
-  e_gemm<T, BM, BN, BK, false, true>(f, L, d, d, W, d, ncols, i0, j0, 0, kend, lds);
-#pragma unroll
-  for (int m = 0; m < EFrag<T, BM, BN>::FM; ++m)
-#pragma unroll
-    for (int n = 0; n < EFrag<T, BM, BN>::FN; ++n)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        int ti, tj;
-        frag_coords<BM, BN, T>(m, n, r, ti, tj);
-        const int i = i0 + ti, j = j0 + tj;
-        if (i < d && j < ncols) Xi[i + (long)j * d] = (T)(c * (double)f.c[m][n][r]);
-      }
-}
-
-template <typename T, int BK>
-__global__ __launch_bounds__(256) void k_trigemm_e(const T* __restrict__ L, const T* __restrict__ W, T* __restrict__ Xi,
-                                                   int d, int ncols, double c) {
-  trigemm_tile<T, BK>(L, W, Xi, d, ncols, c, blockIdx.x, blockIdx.y);
-}
-
-// The same on the direct-to-LDS engine, Xi^T = W^T L^T so that lanes run along
-// the rows of Xi (128-byte stores); bitwise the tile above.  BJ columns of W by
+// On the direct-to-LDS engine, Xi^T = W^T L^T so that lanes run along the rows
+// of Xi (128-byte stores).  BJ columns of W by
 // BI rows of L per workgroup.  64 x 64 tiles, three stages, three workgroups
 // per CU measured best at middle sizes (d = 1024, 12800 columns: FP64 565 to
 // 306 us, FP32 276 to 179 us).  With many tiles FP64 runs at the chip's power
@@ -623,7 +594,7 @@ __global__ __launch_bounds__(256) void k_trigemm_e(const T* __restrict__ L, cons
 // are ahead: d = 4096, 65536 columns 29.9 to 17.9 ms against 19.5 ms with 64 x
 // 64 (61 TFLOP/s; a large library product reaches 68 there), but 335 against
 // 314 us at d = 1024.  32 x 32 tiles where 64 x 64 would not give every CU two.
-template <typename T, int BJ, int BI, int ST>
+template <typename T, int BJ, int BI, int ST, bool NARROW = false>
 DEV void trigemm_tile_t(const T* __restrict__ L, const T* __restrict__ W, T* __restrict__ Xi, int d, int ncols, double c,
                         int bi, int bj) {
   typedef TFrag<T, BJ, BI, 2, 2> F;
@@ -631,7 +602,8 @@ DEV void trigemm_tile_t(const T* __restrict__ L, const T* __restrict__ W, T* __r
   const int i0 = bi * BI, j0 = bj * BJ;
   F f;
   f.zero();
-  t_gemm<T, BJ, BI, 2, 2, ST, true, false>(f, W, d, ncols, L, d, d, j0, i0, 0, min(d, i0 + BI), lds);
+  t_gemm<T, BJ, BI, 2, 2, ST, true, false, false, 1, 1, false, NARROW>(*(F(*)[1]) & f, W, d, ncols, L, d, d, j0, i0, 0,
+                                                                       min(d, i0 + BI), lds);
 #pragma unroll
   for (int m = 0; m < F::FM; ++m)
 #pragma unroll
@@ -648,31 +620,37 @@ DEV void trigemm_tile_t(const T* __restrict__ L, const T* __restrict__ W, T* __r
 // Workgroup ids are dealt round-robin to the 8 XCDs: ids xcd + 8 k on one XCD
 // take the row blocks of one column block of W, longest K range first, so that
 // slice of W is fetched into the XCD's L2 once.
-template <typename T, int BJ, int BI, int ST>
+template <typename T, int BJ, int BI, int ST, bool NARROW>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_trigemm_t(
     const T* __restrict__ L, const T* __restrict__ W, T* __restrict__ Xi, int d, int ncols, double c, int nj, int ni) {
   const int xcd = blockIdx.x & 7, k = blockIdx.x >> 3;
   const int jb = (k / ni) * 8 + xcd;
   if (jb >= nj) return;
-  trigemm_tile_t<T, BJ, BI, ST>(L, W, Xi, d, ncols, c, ni - 1 - k % ni, jb);
+  trigemm_tile_t<T, BJ, BI, ST, NARROW>(L, W, Xi, d, ncols, c, ni - 1 - k % ni, jb);
 }
 
-template <typename T, int BJ, int BI, int ST>
+template <typename T, int BJ, int BI, int ST, bool NARROW>
 static void trigemm_t_launch(const void* L, const void* W, void* Xi, int d, long ncols, double c, hipStream_t s) {
   const int nj = cdiv(ncols, BJ), ni = cdiv(d, BI);
-  hipLaunchKernelGGL((k_trigemm_t<T, BJ, BI, ST>), dim3((unsigned)((nj + 7) / 8 * 8) * ni), dim3(256), 0, s,
+  hipLaunchKernelGGL((k_trigemm_t<T, BJ, BI, ST, NARROW>), dim3((unsigned)((nj + 7) / 8 * 8) * ni), dim3(256), 0, s,
                      (const T*)L, (const T*)W, (T*)Xi, d, (int)ncols, c, nj, ni);
 }
 
-// false: operands not aligned for the engine
-template <typename T>
-static bool trigemm_t(const void* L, const void* W, void* Xi, int d, long ncols, double c, hipStream_t s) {
-  if (!t_gemm_ok<T, true, false>(W, d, (int)ncols, L, d, d, d)) return false;
+// Operands without 16-byte rows take the engine's narrow copies (d = 75, 3200
+// columns: 8.3 us on the element engine, 5.3 so).
+template <typename T, bool NARROW>
+static void trigemm_t(const void* L, const void* W, void* Xi, int d, long ncols, double c, hipStream_t s) {
   const long tiles = (long)cdiv(d, 64) * cdiv(ncols, 64);
-  if (tiles < 512) trigemm_t_launch<T, 32, 32, 6>(L, W, Xi, d, ncols, c, s);
-  else if (sizeof(T) == 8 && tiles >= 8192) trigemm_t_launch<T, 128, 64, 3>(L, W, Xi, d, ncols, c, s);
-  else trigemm_t_launch<T, 64, 64, 3>(L, W, Xi, d, ncols, c, s);
-  return true;
+  if (tiles < 512) trigemm_t_launch<T, 32, 32, 6, NARROW>(L, W, Xi, d, ncols, c, s);
+  else if (sizeof(T) == 8 && tiles >= 8192) trigemm_t_launch<T, 128, 64, 3, NARROW>(L, W, Xi, d, ncols, c, s);
+  else trigemm_t_launch<T, 64, 64, 3, NARROW>(L, W, Xi, d, ncols, c, s);
+}
+template <typename T>
+static hipError_t trigemm_e(const void* L, const void* W, void* Xi, int d, long ncols, double c, hipStream_t s) {
+  if (t_gemm_ok<T, true, false>(W, d, (int)ncols, L, d, d, d)) trigemm_t<T, false>(L, W, Xi, d, ncols, c, s);
+  else if (d < 1 << 20) trigemm_t<T, true>(L, W, Xi, d, ncols, c, s);  // 32-bit offsets in a tile's slice
+  else return hipErrorInvalidValue;
+  return hipGetLastError();
 }
 
 // bf16: Xi^T = W~^T L~^T with the roles swapped so that lanes run along the
@@ -757,16 +735,9 @@ constexpr int TW_BM = 256, TW_BN = 128, TW_WGM = 4, TW_WGN = 2;
 hipError_t trigemm(Prec prec, const void* L, const void* W, const void* Wlo, void* Xi, int d, long ncols, double c,
                    hipStream_t s) {
   if (ncols <= 0) return hipSuccess;
-  if (prec == P64 && trigemm_t<double>(L, W, Xi, d, ncols, c, s)) return hipGetLastError();
-  if (prec == P32 && trigemm_t<float>(L, W, Xi, d, ncols, c, s)) return hipGetLastError();
-  dim3 grid(cdiv(d, 64), cdiv(ncols, 64));
-  if (prec == P64)
-    hipLaunchKernelGGL((k_trigemm_e<double, 16>), grid, dim3(256), 0, s, (const double*)L, (const double*)W,
-                       (double*)Xi, d, (int)ncols, c);
-  else if (prec == P32)
-    hipLaunchKernelGGL((k_trigemm_e<float, 32>), grid, dim3(256), 0, s, (const float*)L, (const float*)W, (float*)Xi,
-                       d, (int)ncols, c);
-  else {
+  if (prec == P64) return trigemm_e<double>(L, W, Xi, d, ncols, c, s);
+  if (prec == P32) return trigemm_e<float>(L, W, Xi, d, ncols, c, s);
+  {
     const u16* Lhi = (const u16*)L;
     const long dW = (const u16*)Wlo - (const u16*)W;
     const int vec_ok = (d % 8 == 0) && ((uintptr_t)L % 16 == 0) && ((uintptr_t)W % 16 == 0) && ((uintptr_t)Wlo % 16 == 0);
@@ -805,57 +776,10 @@ DEV void tile_pair(int t, int& bi, int& bj) {
 
 constexpr int FOLD_K = 4096;  // fp32 accumulation span before folding into fp64
 
-// lower tile t (row-by-row enumeration) of the scatter over K split ksp
-template <typename T, int BK>
-DEV void syrk_tile(const T* __restrict__ Xs, int d, int K, int kchunk, int t, int ksp, double* __restrict__ Gpart) {
-  constexpr int BM = 64, BN = 64;
-  __shared__ T lds[e_lds_elems<T, BM, BN, BK>()];
-  int bi, bj;
-  tile_pair(t, bi, bj);
-  const int i0 = bi * BM, j0 = bj * BN;
-  const int kb = ksp * kchunk, ke = min(K, kb + kchunk);
-  double acc[EFrag<T, BM, BN>::FM][EFrag<T, BM, BN>::FN][4];
-#pragma unroll
-  for (int m = 0; m < EFrag<T, BM, BN>::FM; ++m)
-#pragma unroll
-    for (int n = 0; n < EFrag<T, BM, BN>::FN; ++n)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) acc[m][n][r] = 0.0;
-  const int span = (sizeof(T) == 8) ? kchunk : FOLD_K;
-  for (int k0 = kb; k0 < ke; k0 += span) {
-    EFrag<T, BM, BN> f;
-    f.zero();
-    e_gemm<T, BM, BN, BK, false, false>(f, Xs, d, d, Xs, d, d, i0, j0, k0, min(ke, k0 + span), lds);
-#pragma unroll
-    for (int m = 0; m < EFrag<T, BM, BN>::FM; ++m)
-#pragma unroll
-      for (int n = 0; n < EFrag<T, BM, BN>::FN; ++n)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) acc[m][n][r] += (double)f.c[m][n][r];
-  }
-  double* G = Gpart + (long)ksp * d * d;
-#pragma unroll
-  for (int m = 0; m < EFrag<T, BM, BN>::FM; ++m)
-#pragma unroll
-    for (int n = 0; n < EFrag<T, BM, BN>::FN; ++n)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        int ti, tj;
-        frag_coords<BM, BN, T>(m, n, r, ti, tj);
-        const int i = i0 + ti, j = j0 + tj;
-        if (i < d && j < d) G[j + (long)i * d] = acc[m][n][r];  // G(i,j) at (row j, col i): upper
-      }
-}
-
-template <typename T, int BK>
-__global__ __launch_bounds__(256) void k_syrk_e(const T* __restrict__ Xs, int d, int K, int kchunk,
-                                                double* __restrict__ Gpart) {
-  syrk_tile<T, BK>(Xs, d, K, kchunk, blockIdx.x, blockIdx.y, Gpart);
-}
-
-// The same on the direct-to-LDS engine (leading dimension ld), bitwise; lanes
+// Lower tile t (row-by-row enumeration) of the scatter over K split ksp, on the
+// direct-to-LDS engine (leading dimension ld); lanes
 // run along j, so the stores are 128-byte runs of a column of G.
-template <typename T, int BT, int ST>
+template <typename T, int BT, int ST, bool NARROW = false>
 DEV void syrk_tile_t(const T* __restrict__ Xs, int ld, int d, int K, int kchunk, int t, int ksp,
                      double* __restrict__ Gpart, T* lds) {
   typedef TFrag<T, BT, BT, 2, 2> F;
@@ -874,7 +798,8 @@ DEV void syrk_tile_t(const T* __restrict__ Xs, int ld, int d, int K, int kchunk,
   for (int k0 = kb; k0 < ke; k0 += span) {
     F f;
     f.zero();
-    t_gemm<T, BT, BT, 2, 2, ST, false, false>(f, Xs, ld, ld, Xs, ld, ld, i0, j0, k0, min(ke, k0 + span), lds);
+    t_gemm<T, BT, BT, 2, 2, ST, false, false, false, 1, 1, false, NARROW>(*(F(*)[1]) & f, Xs, ld, ld, Xs, ld, ld, i0, j0, k0,
+                                                                       min(ke, k0 + span), lds);
 #pragma unroll
     for (int m = 0; m < F::FM; ++m)
 #pragma unroll
@@ -950,7 +875,7 @@ DEV void rowsum_block(const T* __restrict__ X, int d, long ld, int K, int kchunk
 // its row sums: a chain of loads of its own (26 us at d = 1024), beside the
 // products.  The loads in flight take registers, which FP32 products need for
 // their occupancy (173 + 21 us apart, 231 together, at d = 1024, K = 12800).
-template <typename T, int BT, int ST>
+template <typename T, int BT, int ST, bool NARROW>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_syrk_t(
     const T* __restrict__ Xs, int d, int K, int kchunk, double* __restrict__ Gpart, int nrb, int nh, int hchunk,
     double* __restrict__ hpart) {
@@ -961,26 +886,34 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
       if (blockIdx.y == 0) rowsum_block<T, true>(Xs, d, d, K, hchunk, b % nrb, b / nrb, hpart, (double (*)[64])lds);
       return;
     }
-  syrk_tile_t<T, BT, ST>(Xs, d, d, K, kchunk, b - nrb * nh, blockIdx.y, Gpart, lds);
+  syrk_tile_t<T, BT, ST, NARROW>(Xs, d, d, K, kchunk, b - nrb * nh, blockIdx.y, Gpart, lds);
 }
 
 // 64-row tiles (FP64 d = 4096, K = 65536: 22.5 to 21.1 ms, 2080 tiles being
 // 8.1 per CU; d = 1024, K = 12800: 415 to 320 us, FP32 195 to 168 us), 32-row
 // ones where those would not give every CU one (d = 100, K = 3200: 6 tiles).
-// false: operands not aligned for the engine.
-template <typename T>
-static bool syrk_t(const void* Xs, int d, long K, int ns, int kchunk, double* Gpart, int nh, int hchunk,
+// Columns without 16-byte strides take the engine's narrow copies (d = 75, K =
+// 3200: 66.8 us on the element engine and 12 for the row sums, 24.8 together).
+template <typename T, bool NARROW>
+static void syrk_t(const void* Xs, int d, long K, int ns, int kchunk, double* Gpart, int nh, int hchunk,
                    double* hpart, hipStream_t s) {
-  if (!t_gemm_ok<T, false, false>(Xs, d, d, Xs, d, d, K)) return false;
   const int n64 = cdiv(d, 64), n32 = cdiv(d, 32);
   if (sizeof(T) != 8) nh = 0;
   if ((long)n64 * (n64 + 1) / 2 * ns < 256)
-    hipLaunchKernelGGL((k_syrk_t<T, 32, 6>), dim3(n64 * nh + n32 * (n32 + 1) / 2, ns), dim3(256), 0, s, (const T*)Xs,
+    hipLaunchKernelGGL((k_syrk_t<T, 32, 6, NARROW>), dim3(n64 * nh + n32 * (n32 + 1) / 2, ns), dim3(256), 0, s, (const T*)Xs,
                        d, (int)K, kchunk, Gpart, n64, nh, hchunk, hpart);
   else
-    hipLaunchKernelGGL((k_syrk_t<T, 64, 3>), dim3(n64 * nh + n64 * (n64 + 1) / 2, ns), dim3(256), 0, s, (const T*)Xs,
+    hipLaunchKernelGGL((k_syrk_t<T, 64, 3, NARROW>), dim3(n64 * nh + n64 * (n64 + 1) / 2, ns), dim3(256), 0, s, (const T*)Xs,
                        d, (int)K, kchunk, Gpart, n64, nh, hchunk, hpart);
-  return true;
+}
+
+template <typename T>
+static hipError_t syrk_e(const void* Xs, int d, long K, int ns, int kchunk, double* Gpart, int nh, int hchunk,
+                         double* hpart, hipStream_t s) {
+  if (t_gemm_ok<T, false, false>(Xs, d, d, Xs, d, d, K)) syrk_t<T, false>(Xs, d, K, ns, kchunk, Gpart, nh, hchunk, hpart, s);
+  else if (d < 1 << 20) syrk_t<T, true>(Xs, d, K, ns, kchunk, Gpart, nh, hchunk, hpart, s);
+  else return hipErrorInvalidValue;
+  return hipGetLastError();
 }
 
 // bf16: Xt is the transposed window (d x K row-major, ld = K).  Tiles are
@@ -1252,27 +1185,20 @@ hipError_t syrk_window(Prec prec, const void* Xw, void* Xt, int d, long K, void*
   }
   const int nt = syrk_tiles(prec, d, K);
   dim3 grid(nt, ns);
-  if ((prec == P64 && syrk_t<double>(Xs, d, K, ns, kchunk, Gpart, nh, hchunk, hpart, s)) ||
-      (prec == P32 && syrk_t<float>(Xs, d, K, ns, kchunk, Gpart, nh, hchunk, hpart, s))) {
-    h_done = prec == P64;
-  } else if (syrk_pl(prec, d, K) && (uintptr_t)Xs % 16 == 0)
+  hipError_t e = hipSuccess;
+  if (prec == P64) e = syrk_e<double>(Xs, d, K, ns, kchunk, Gpart, nh, hchunk, hpart, s);
+  else if (prec == P32) e = syrk_e<float>(Xs, d, K, ns, kchunk, Gpart, nh, hchunk, hpart, s);
+  else if (syrk_pl(prec, d, K) && (uintptr_t)Xs % 16 == 0)
     hipLaunchKernelGGL(k_syrk_pl, grid, dim3(512), 0, s, (const u16*)Xs, d, (int)K, kchunk, Gpart);
-  else if (prec == P64)
-    hipLaunchKernelGGL((k_syrk_e<double, 16>), grid, dim3(256), 0, s, (const double*)Xs, d, (int)K, kchunk, Gpart);
-  else if (prec == P32)
-    hipLaunchKernelGGL((k_syrk_e<float, 32>), grid, dim3(256), 0, s, (const float*)Xs, d, (int)K, kchunk, Gpart);
   else {
     const int vec_ok = (K % 8 == 0) && ((uintptr_t)Xs % 16 == 0);
     hipLaunchKernelGGL(k_syrk_bf16, grid, dim3(256), 0, s, (const u16*)Xs, d, (int)K, kchunk, vec_ok, Gpart);
   }
-  if (h_done) {
-  } else if (prec == P64)
-    hipLaunchKernelGGL((k_rowsum<double, true>), dim3(cdiv(d, 64), nh), dim3(256), 0, s, (const double*)Xs, d, (int)K,
-                       hchunk, hpart);
-  else if (prec == P32)
+  if (e != hipSuccess) return e;
+  if (prec == P32)
     hipLaunchKernelGGL((k_rowsum<float, true>), dim3(cdiv(d, 64), nh), dim3(256), 0, s, (const float*)Xs, d, (int)K,
                        hchunk, hpart);
-  else
+  else if (prec == PMIX && !h_done)
     hipLaunchKernelGGL((k_rowsum<u16, false>), dim3(cdiv(d, 4), nh), dim3(256), 0, s, (const u16*)Xs, d, (int)K,
                        hchunk, hpart);
   *out = {Gpart, hpart, ns, nh};

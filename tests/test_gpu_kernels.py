@@ -125,7 +125,11 @@ def test_steps_of_a_call_in_one_launch(d, P, n, nproj, proposal):
                                         ("fp64", 66, 17, 31), ("fp64", 130, 64, 33), ("fp64", 75, 9, 5),
                                         ("fp64", 194, 256, 44), ("fp64", 2050, 128, 128), ("fp32", 4, 3, 2),
                                         ("fp32", 28, 65, 3), ("fp32", 68, 31, 9), ("fp32", 132, 64, 66),
-                                        ("fp32", 300, 100, 90), ("fp32", 70, 9, 5)])
+                                        ("fp32", 300, 100, 90), ("fp32", 70, 9, 5),
+                                        ("fp64", 1, 3, 9), ("fp64", 3, 2, 3), ("fp64", 65, 17, 31),
+                                        ("fp64", 129, 64, 33), ("fp64", 451, 100, 90), ("fp64", 2051, 128, 128),
+                                        ("fp32", 1, 3, 9), ("fp32", 67, 31, 9), ("fp32", 133, 64, 66),
+                                        ("fp32", 602, 100, 90)])
 def test_proposal_and_scatter_products(prec, d, P, n):
     """The proposal contraction and the merged moments at the edges of their
     tiles and sizes of the dispatch, against FP64 products of the same operands
