@@ -1621,12 +1621,10 @@ __global__ __launch_bounds__(256) void k_tri_inv(const double* __restrict__ L, i
 
 // Panel rows below the diagonal block: A(i, j0 + c) <- sum_q A(i, j0 + q)
 // Linv(c, q), 32 rows per workgroup (few rows, so latency counts) on the
-// direct-to-LDS engine with all of K in flight, transposed so that lanes run
-// along the columns of memory: 7.3 us on the element engine, which unaligned d
-// keeps, now 4.8.
+// direct-to-LDS engine (narrow copies for odd d) with all of K in flight, transposed so that lanes run
+// along the columns of memory: 7.3 us on the element engine, now 4.8.
 constexpr int CHOL_ST = 5;  // four slices of 16 in flight: a block column
 constexpr int CHOL_PANEL_LDS = t_lds_elems<double, CHOL_NB, CHOL_PANEL_ROWS, CHOL_ST>();
-static_assert(CHOL_PANEL_LDS >= e_lds_elems<double, 64, 64, 16>(), "one buffer for both engines");
 
 DEV bool chol_aligned(const double* A, int d) { return d % 2 == 0 && (uintptr_t)A % 16 == 0; }
 
@@ -1635,39 +1633,25 @@ DEV void chol_panel_tile(double* __restrict__ A, int d, int j0, int jn, const do
   const int i0 = j0 + jn + bx * CHOL_PANEL_ROWS;
   if (i0 >= d) return;  // uniform: the second half of a block of at most 32 rows
   double* Pc = A + (long)j0 * d;
-  if (chol_aligned(A, d)) {
-    constexpr int BN = CHOL_PANEL_ROWS;
-    typedef TFrag<double, CHOL_NB, BN, 2, 2> F;
-    F f;
-    f.zero();
+  constexpr int BN = CHOL_PANEL_ROWS;
+  typedef TFrag<double, CHOL_NB, BN, 2, 2> F;
+  F f;
+  f.zero();
+  if (chol_aligned(A, d))
     t_gemm<double, CHOL_NB, BN, 2, 2, CHOL_ST, false, false>(f, Linv, CHOL_NB, CHOL_NB, Pc, d, d, 0, i0, 0, CHOL_NB,
                                                              lds);
+  else
+    t_gemm<double, CHOL_NB, BN, 2, 2, CHOL_ST, false, false, false, 1, 1, false, true>(
+        *(F(*)[1]) & f, Linv, CHOL_NB, CHOL_NB, Pc, d, d, 0, i0, 0, CHOL_NB, lds);
 #pragma unroll
-    for (int m = 0; m < F::FM; ++m)
+  for (int m = 0; m < F::FM; ++m)
 #pragma unroll
-      for (int n = 0; n < F::FN; ++n)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          int c, ti;
-          t_coords<double, CHOL_NB, BN, 2, 2>(m, n, r, c, ti);
-          if (i0 + ti < d) Pc[i0 + ti + (long)c * d] = f.c[m][n][r];
-        }
-    return;
-  }
-  if (bx & 1) return;  // 64 rows per tile
-  constexpr int BM = 64, BN = 64, BK = 16;
-  EFrag<double, BM, BN> f;
-  f.zero();
-  e_gemm<double, BM, BN, BK, false, false>(f, Pc, d, d, Linv, CHOL_NB, jn, i0, 0, 0, jn, lds);
-#pragma unroll
-  for (int m = 0; m < 2; ++m)
-#pragma unroll
-    for (int n = 0; n < 2; ++n)
+    for (int n = 0; n < F::FN; ++n)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        int ti, tj;
-        frag_coords<BM, BN, double>(m, n, r, ti, tj);
-        if (i0 + ti < d) Pc[i0 + ti + (long)tj * d] = f.c[m][n][r];
+        int c, ti;
+        t_coords<double, CHOL_NB, BN, 2, 2>(m, n, r, c, ti);
+        if (i0 + ti < d) Pc[i0 + ti + (long)c * d] = f.c[m][n][r];
       }
 }
 
@@ -1690,65 +1674,46 @@ int chol_update_tiles(int nb, int jb) {
   return jb % 2 == 0 ? m + (m >= 2) : m * (m + 1) / 2;
 }
 constexpr int CHOL_UPD_LDS = t_lds_elems<double, 64, 64, CHOL_ST>();  // doubles
-static_assert(CHOL_UPD_LDS >= e_lds_elems<double, 64, 64, 16>(), "one buffer for both engines");
 
 // block columns [c0, c0 + 64 NC) on tile (i0, k0)
 template <int NC>
 DEV void chol_update_part(double* __restrict__ A, int d, int c0, int i0, int k0, double* lds) {
   const double* Pc = A + (long)c0 * d;
-  if (chol_aligned(A, d)) {
-    typedef TFrag<double, 64, 64, 2, 2> F;
-    // the tile itself, on its way during the products
-    double c[F::FM][F::FN][4];
+  typedef TFrag<double, 64, 64, 2, 2> F;
+  // the tile itself, on its way during the products
+  double c[F::FM][F::FN][4];
 #pragma unroll
-    for (int m = 0; m < F::FM; ++m)
+  for (int m = 0; m < F::FM; ++m)
 #pragma unroll
-      for (int n = 0; n < F::FN; ++n)
+    for (int n = 0; n < F::FN; ++n)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          int tk, ti;
-          t_coords<double, 64, 64, 2, 2>(m, n, r, tk, ti);
-          c[m][n][r] = A[min(i0 + ti, d - 1) + (long)min(k0 + tk, d - 1) * d];
-        }
-    F f[NC];
+      for (int r = 0; r < 4; ++r) {
+        int tk, ti;
+        t_coords<double, 64, 64, 2, 2>(m, n, r, tk, ti);
+        c[m][n][r] = A[min(i0 + ti, d - 1) + (long)min(k0 + tk, d - 1) * d];
+      }
+  F f[NC];
 #pragma unroll
-    for (int x = 0; x < NC; ++x) f[x].zero();
+  for (int x = 0; x < NC; ++x) f[x].zero();
+  if (chol_aligned(A, d))
     t_gemm<double, 64, 64, 2, 2, CHOL_ST, false, false, false, NC, 1, true>(f, Pc, d, d, Pc, d, d, k0, i0, 0,
                                                                             CHOL_NB * NC, lds);
+  else
+    t_gemm<double, 64, 64, 2, 2, CHOL_ST, false, false, false, NC, 1, true, true>(f, Pc, d, d, Pc, d, d, k0, i0, 0,
+                                                                                  CHOL_NB * NC, lds);
 #pragma unroll
-    for (int m = 0; m < F::FM; ++m)
+  for (int m = 0; m < F::FM; ++m)
 #pragma unroll
-      for (int n = 0; n < F::FN; ++n)
+    for (int n = 0; n < F::FN; ++n)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          int tk, ti;
-          t_coords<double, 64, 64, 2, 2>(m, n, r, tk, ti);
-          double v = c[m][n][r];
+      for (int r = 0; r < 4; ++r) {
+        int tk, ti;
+        t_coords<double, 64, 64, 2, 2>(m, n, r, tk, ti);
+        double v = c[m][n][r];
 #pragma unroll
-          for (int x = 0; x < NC; ++x) v -= f[x].c[m][n][r];
-          if (i0 + ti < d && k0 + tk < d) A[i0 + ti + (long)(k0 + tk) * d] = v;
-        }
-    return;
-  }
-  constexpr int BM = 64, BN = 64, BK = 16;
-#pragma unroll 1
-  for (int x = 0; x < NC; ++x) {
-    EFrag<double, BM, BN> f;
-    f.zero();
-    e_gemm<double, BM, BN, BK, false, false>(f, Pc, d, d, Pc, d, d, i0, k0, CHOL_NB * x, CHOL_NB * (x + 1), lds);
-#pragma unroll
-    for (int m = 0; m < 2; ++m)
-#pragma unroll
-      for (int n = 0; n < 2; ++n)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          int ti, tj;
-          frag_coords<BM, BN, double>(m, n, r, ti, tj);
-          const int i = i0 + ti, k = k0 + tj;
-          if (i < d && k < d) A[i + (long)k * d] -= f.c[m][n][r];
-        }
-    __syncthreads();
-  }
+        for (int x = 0; x < NC; ++x) v -= f[x].c[m][n][r];
+        if (i0 + ti < d && k0 + tk < d) A[i0 + ti + (long)(k0 + tk) * d] = v;
+      }
 }
 
 // tile t of the update after block column jb
