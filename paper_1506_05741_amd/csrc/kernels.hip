@@ -1326,13 +1326,13 @@ hipError_t cov_assemble(const double* S, const double* m, double eps, double* C,
 }
 
 // ============================================================================
-// (e) blocked right-looking Cholesky, FP64, block 64.  Per block column:
-//   k_chol_diag   one wavefront factors the 64 x 64 diagonal block with its
-//                 rows in registers and forms the block's inverse;
+// (e) blocked right-looking Cholesky, FP64, block 64.
+//   k_chol_diag   four wavefronts factor the first 64 x 64 diagonal block with
+//                 its rows in registers and form the block's inverse;
 //   k_chol_panel  MFMA: A_ij <- A_ij L_jj^-T as a product with that inverse;
-//   k_chol_update_diag MFMA: trailing lower tiles A_ik -= A_ij A_kj^T, and
-//                 the next diagonal block factored by the workgroup that
-//                 updated it.
+//   k_chol_update_diag MFMA: trailing lower tiles A_ik -= A_ij A_kj^T, for up
+//                 to two block columns j in one pass over the tiles, and the
+//                 next diagonal block factored by the workgroup that updated it.
 // ============================================================================
 
 // lane's value v broadcast from lane `src` (a compile-time lane after unrolling)
