@@ -2714,11 +2714,17 @@ __global__ __launch_bounds__(256) void k_decide(StepArgs a, int nch) { decide_bl
 // that waits for the target's terms can load these first.
 struct DecIn {
   double zs, pq, lp, zq, u;
+  int nacc, wacc;  // the chain's counters, for the wavefront that writes them
 };
 
-DEV DecIn decide_inputs(const StepArgs& a, int nch, int p) {
+DEV DecIn decide_inputs(const StepArgs& a, int nch, int p, bool write) {
   const int lane = threadIdx.x & 63;
   DecIn in;
+  in.nacc = in.wacc = 0;
+  if (write) {
+    in.nacc = a.nacc[p];
+    if (a.wacc) in.wacc = a.wacc[p];
+  }
   in.zs = lane < nch ? 0.0 + a.zq_part_cur[(long)p * nch + lane] : 0.0;
   in.pq = (a.prior_w > 0.0 && lane < nch) ? 0.0 + a.pq_part_cur[(long)p * nch + lane] : 0.0;
   in.lp = a.lp_cur[p];
@@ -2727,10 +2733,15 @@ DEV DecIn decide_inputs(const StepArgs& a, int nch, int p) {
   return in;
 }
 
-DEV bool decide_wave(const StepArgs& a, int nch, int p, bool write, const double* parts, const DecIn& in) {
+DEV double lane_part(const StepArgs& a, const double* parts) {
   const int lane = threadIdx.x & 63;
-  double s = lane < a.nrb ? 0.0 + row_block_part(a, parts, lane) : 0.0;
-  s = wave_sum_f64(s);
+  return lane < a.nrb ? 0.0 + row_block_part(a, parts, lane) : 0.0;
+}
+
+DEV bool decide_wave(const StepArgs& a, int p, bool write, double part, const DecIn& in) {
+  const int lane = threadIdx.x & 63;
+  const double lu = log(in.u);
+  double s = wave_sum_f64(part);
   if (a.prior_w > 0.0) {
     const double pq = wave_sum_f64(in.pq);
     s = __fma_rn(-a.prior_w, pq, s);
@@ -2739,12 +2750,12 @@ DEV bool decide_wave(const StepArgs& a, int nch, int p, bool write, const double
   const double zs = wave_sum_f64(in.zs);
   const double lp = in.lp, zq = in.zq;
   const double la = (lpp + zs * a.inv2a2) - (lp + zq * a.inv2a2);
-  const bool acc = log(in.u) < la;  // NaN compares false: rejected
+  const bool acc = lu < la;  // NaN compares false: rejected
   if (write && lane == 0) {
     a.lp_nxt[p] = acc ? lpp : lp;
     a.zq_nxt[p] = acc ? zs : zq;
-    a.nacc[p] += acc ? 1 : 0;
-    if (a.wacc) a.wacc[p] += acc ? 1 : 0;
+    a.nacc[p] = in.nacc + (acc ? 1 : 0);
+    if (a.wacc) a.wacc[p] = in.wacc + (acc ? 1 : 0);
     a.la_out[p] = la;
     a.acc_out[p] = acc ? 1 : 0;
     if (a.trace_lp) a.trace_lp[p] = acc ? lpp : lp;
@@ -2754,7 +2765,7 @@ DEV bool decide_wave(const StepArgs& a, int nch, int p, bool write, const double
 }
 
 DEV bool decide_wave(const StepArgs& a, int nch, int p, bool write, const double* parts) {
-  return decide_wave(a, nch, p, write, parts, decide_inputs(a, nch, p));
+  return decide_wave(a, p, write, lane_part(a, parts), decide_inputs(a, nch, p, write));
 }
 
 // Paired-row loads and stores for the update half (d even, so that every
@@ -2832,6 +2843,7 @@ struct UpdRegs {
   double x0[CPW], x1[CPW], z0[CPW], z1[CPW], r0[CPW], r1[CPW];
   double m0[CPW], m1[CPW];
   Raw2<PR> nw[CPW];  // the next proposal's Xi and W
+  Raw2<PR> cw[CPW];  // the accepted proposal's Xi and W
   float2 sv[CPW];
 };
 
@@ -2867,17 +2879,44 @@ DEV void upd_load(const StepArgs& a, int p, int cb, int nch, UpdRegs<PR, CPW>& g
   }
 }
 
+// The loads of an accepting and proposing step without branches: lanes past d
+// read the chunk's first row, a target without a mean the pivot (neither is
+// used), and both proposals are read whatever the decision will be.
 template <int PR, int CPW>
-DEV void upd_finish(const StepArgs& a, int p, int cb, int nch, bool acc, const UpdRegs<PR, CPW>& g) {
+DEV void upd_load_run(const StepArgs& a, int p, int cb, int nch, UpdRegs<PR, CPW>& g) {
+  const int lane = threadIdx.x & 63;
+  const int d = a.d;
+  const long ldw = a.ldw ? a.ldw : d;
+  const double* mu = a.mu ? a.mu : a.xr;
+#pragma unroll
+  for (int c = 0; c < CPW; ++c) {
+    const int ch = cb * CPW + c;
+    g.ii[c] = ch * STEP_RCH + 2 * lane;
+    g.in[c] = g.ii[c] < d;  // ch < nch in its launch
+    const int i = g.in[c] ? g.ii[c] : ch * STEP_RCH;
+    const long e = i + (long)p * d, ew = i + (long)p * ldw;
+    const double2 xv = *(const double2*)(a.X + e), zv = *(const double2*)(a.Z + e);
+    raw_load(g.cw[c], a.xi_cur, a.w_cur, a.wlo_cur, ew);
+    raw_load(g.nw[c], a.xi_nxt, a.w_nxt, a.wlo_nxt, ew);
+    const double2 rv = *(const double2*)(a.xr + i), mv = *(const double2*)(mu + i);
+    g.x0[c] = xv.x; g.x1[c] = xv.y; g.z0[c] = zv.x; g.z1[c] = zv.y; g.r0[c] = rv.x; g.r1[c] = rv.y;
+    g.m0[c] = mv.x; g.m1[c] = mv.y;
+  }
+}
+
+// RUN: the step accepts and proposes, and g comes from upd_load_run.
+template <int PR, int CPW, bool RUN = false>
+DEV void upd_finish(const StepArgs& a, int p, int cb, int nch, bool acc, UpdRegs<PR, CPW>& g) {
   const int lane = threadIdx.x & 63;
   const int d = a.d, P = a.P;
   const long ldw = a.ldw ? a.ldw : d;
-  Raw2<PR> cw[CPW];  // the accepted proposal's Xi and W
+  const bool do_accept = RUN || a.do_accept, do_propose = RUN || a.do_propose;
+  if (!RUN)
 #pragma unroll
-  for (int c = 0; c < CPW; ++c) {
-    raw_zero(cw[c]);
-    if (g.in[c] && acc) raw_load(cw[c], a.xi_cur, a.w_cur, a.wlo_cur, g.ii[c] + (long)p * ldw);
-  }
+    for (int c = 0; c < CPW; ++c) {
+      raw_zero(g.cw[c]);
+      if (g.in[c] && acc) raw_load(g.cw[c], a.xi_cur, a.w_cur, a.wlo_cur, g.ii[c] + (long)p * ldw);
+    }
 #pragma unroll
   for (int c = 0; c < CPW; ++c) {
     const int ch = cb * CPW + c;
@@ -2889,11 +2928,11 @@ DEV void upd_finish(const StepArgs& a, int p, int cb, int nch, bool acc, const U
     if (g.in[c]) {
       double xa = g.x0[c], xb = g.x1[c], za = g.z0[c], zb = g.z1[c];
       const double ra = g.r0[c], rb = g.r1[c];
-      if (a.do_accept) {
+      if (do_accept) {
         if (acc) {
           double c0, c1, wc0, wc1;
-          raw_xi(cw[c], c0, c1);
-          raw_w(cw[c], wc0, wc1);
+          raw_xi(g.cw[c], c0, c1);
+          raw_w(g.cw[c], wc0, wc1);
           xa = propose1(ra, xa, a.rho, c0);
           xb = propose1(rb, xb, a.rho, c1);
           za = __fma_rn(a.c, wc0, a.rho * za);
@@ -2907,14 +2946,15 @@ DEV void upd_finish(const StepArgs& a, int p, int cb, int nch, bool acc, const U
           pacc[k] = __fma_rn(pv.y, xb, __fma_rn(pv.x, xa, pacc[k]));
         }
       }
-      if (a.do_propose) {
+      if (do_propose) {
         double n0, n1, wn0, wn1;
         raw_xi(g.nw[c], n0, n1);
         raw_w(g.nw[c], wn0, wn1);
         const double xp0 = propose1(ra, xa, a.rho, n0), xp1 = propose1(rb, xb, a.rho, n1);
-        if (a.vh) {
+        const double m0 = RUN && !a.mu ? 0.0 : g.m0[c], m1 = RUN && !a.mu ? 0.0 : g.m1[c];
+        if (!RUN && a.vh) {
           u16 h0, l0, h1, l1;
-          const double s0 = (xp0 - g.m0[c]) * (double)g.sv[c].x, s1 = (xp1 - g.m1[c]) * (double)g.sv[c].y;
+          const double s0 = (xp0 - m0) * (double)g.sv[c].x, s1 = (xp1 - m1) * (double)g.sv[c].y;
           if (fmax(fabs(s0), fabs(s1)) >= H2_RANGE) atomicOr(a.err, 2);
           split_f16(s0, h0, l0);
           split_f16(s1, h1, l1);
@@ -2923,15 +2963,15 @@ DEV void upd_finish(const StepArgs& a, int p, int cb, int nch, bool acc, const U
         } else {
           const long ev = i + (long)p * (a.ldv ? a.ldv : d);
           if (a.v32 || PR != P64)
-            *(float2*)((float*)a.V + ev) = make_float2((float)(xp0 - g.m0[c]), (float)(xp1 - g.m1[c]));
-          else *(double2*)((double*)a.V + ev) = make_double2(xp0 - g.m0[c], xp1 - g.m1[c]);
+            *(float2*)((float*)a.V + ev) = make_float2((float)(xp0 - m0), (float)(xp1 - m1));
+          else *(double2*)((double*)a.V + ev) = make_double2(xp0 - m0, xp1 - m1);
         }
         const double zp0 = __fma_rn(a.c, wn0, a.rho * za), zp1 = __fma_rn(a.c, wn1, a.rho * zb);
         zacc = __fma_rn(zp1, zp1, __fma_rn(zp0, zp0, 0.0));
         xacc = __fma_rn(xp1, xp1, __fma_rn(xp0, xp0, 0.0));
       }
     }
-    if (a.do_propose) {
+    if (do_propose) {
       zacc = wave_sum_f64(zacc);
       if (lane == 0) a.zq_part_nxt[(long)p * nch + ch] = zacc;
       if (a.prior_w > 0.0) {
@@ -2939,7 +2979,7 @@ DEV void upd_finish(const StepArgs& a, int p, int cb, int nch, bool acc, const U
         if (lane == 0) a.pq_part_nxt[(long)p * nch + ch] = xacc;
       }
     }
-    if (a.do_accept && a.nproj > 0) {
+    if (do_accept && a.nproj > 0) {
       for (int k = 0; k < a.nproj; ++k) {
         const double v = wave_sum_f64(pacc[k]);
         if (lane == 0) a.proj_part[((long)ch * a.nproj + k) * P + p] = v;
@@ -3082,11 +3122,11 @@ __global__ __launch_bounds__(1024) void k_step_h2(StepArgs a, int nch, const flo
   const int p = blockIdx.x, v = threadIdx.x >> 6, lane = threadIdx.x & 63;
   UpdRegs<PMIX, 2> g;
   upd_load_h2<PROP>(a, p, v, g);
-  const DecIn din = decide_inputs(a, nch, p);
+  const DecIn din = decide_inputs(a, nch, p, v == 0);
   const double q = h2_reduce_wave(Yp, rsc, a.d, a.P, a.nrb, part, twist, p, v);
   if ((lane & 15) == 0) lpp[v * 4 + (lane >> 4)] = q;
   __syncthreads();
-  const bool acc = decide_wave(a, nch, p, v == 0, lpp, din);
+  const bool acc = decide_wave(a, p, v == 0, lane_part(a, lpp), din);
   upd_finish_h2<PROP>(a, p, v, nch, acc, g);
 }
 
@@ -3099,6 +3139,49 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8 / STEP_CP
   else step_body<PR, MODE>(a, blockIdx.x, nch, blockIdx.y);
 }
 
+// A step that takes its decision and proposes the next one, for the sizes
+// where latency bounds it: one chunk per wavefront, and every load that either
+// verdict may need in flight before the first wait, instead of a wait for the
+// state's loads, one for the decision's and one for the accepted proposal's.
+// d = 1024, P = 64: 5.7 -> 3.9 us (FP64), 5.6 -> 4.2 (FP32); d = 750, P = 50,
+// mixed: 5.7 -> 3.9.
+template <int PR>
+__global__ __launch_bounds__(256) void k_step_run(StepArgs a, int nch) {
+  // a word from each line of the arguments, so that the lines arrive together
+  asm volatile("" ::"s"(a.d), "s"(a.nrb), "s"(a.nproj), "s"(a.v32), "s"(a.ldw));
+  const int lane = threadIdx.x & 63;
+  const int p = blockIdx.y * 4 + (threadIdx.x >> 6), cb = blockIdx.x;
+  if (p >= a.P) return;
+  UpdRegs<PR, 1> g;
+  upd_load_run<PR, 1>(a, p, cb, nch, g);
+  // lanes without a row block or chunk read the chain's first; of a row
+  // block's partials those that it lacks are replaced by its first
+  const double* parts = chain_parts(a, p);
+  const int q = lane < a.nrb ? lane : 0, sub = a.sub > 1 ? a.sub : 1;
+  const bool two = 64 * q + 32 < a.d;
+  const int have = sub > 1 && !two ? sub / 2 : sub;
+  double f[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) f[k] = parts[sub * q + (k < have ? k : 0)];
+  const double zs = a.zq_part_cur[(long)p * nch + (lane < nch ? lane : 0)];
+  DecIn din;
+  din.lp = a.lp_cur[p];
+  din.zq = a.zq_cur[p];
+  din.u = a.u[p];
+  const int* wacc = a.wacc ? a.wacc : a.nacc;
+  din.nacc = din.wacc = 0;
+  if (cb == 0) {
+    din.nacc = a.nacc[p];
+    din.wacc = wacc[p];
+  }
+  din.pq = 0.0;
+  if (a.prior_w > 0.0 && lane < nch) din.pq = 0.0 + a.pq_part_cur[(long)p * nch + lane];
+  din.zs = lane < nch ? 0.0 + zs : 0.0;
+  const double part = sub == 1 ? f[0] : sub == 2 ? f[0] + (two ? f[1] : 0.0) : (f[0] + f[1]) + (two ? f[2] + f[3] : 0.0);
+  const bool acc = decide_wave(a, p, cb == 0, lane < a.nrb ? 0.0 + part : 0.0, din);
+  upd_finish<PR, 1, true>(a, p, cb, nch, acc, g);
+}
+
 // A step with an accept half runs as a decision launch (one wave per chain)
 // followed by the streaming update; the first proposal of a call has no
 // decision.
@@ -3108,6 +3191,17 @@ hipError_t step(const StepArgs& a, hipStream_t s) {
   // the decision moves into the update launch where one wavefront can take it
   StepArgs b = a;
   b.fuse_dec = a.do_accept && !a.da && a.nrb <= 64 && nch <= 64 && (a.d & 1) == 0;
+  // up to 4096 wavefronts; beyond, reading both proposals whatever the verdict
+  // costs more than the waits.  k_step_run against k_step, us: P nch = 2048
+  // 7.0 / 8.2 FP64, 4.8 / 6.9 FP32; 4096 9.8 / 10.4, 8.3 / 9.9; 8192
+  // 16.7 / 15.4, 13.6 / 13.0.
+  if (b.fuse_dec && a.do_propose && !a.vh && (long)a.P * nch <= 4096) {
+    const dim3 grun(nch, cdiv(a.P, 4));
+    if (a.prec == P64) hipLaunchKernelGGL((k_step_run<P64>), grun, dim3(256), 0, s, b, nch);
+    else if (a.prec == P32) hipLaunchKernelGGL((k_step_run<P32>), grun, dim3(256), 0, s, b, nch);
+    else hipLaunchKernelGGL((k_step_run<PMIX>), grun, dim3(256), 0, s, b, nch);
+    return hipGetLastError();
+  }
   if (a.do_accept && !b.fuse_dec) hipLaunchKernelGGL(k_decide, dim3(a.P), dim3(256), 0, s, b, nch);
   if (a.prec == P64) hipLaunchKernelGGL((k_step<P64, 2>), gupd, dim3(256), 0, s, b, nch);
   else if (a.prec == P32) hipLaunchKernelGGL((k_step<P32, 2>), gupd, dim3(256), 0, s, b, nch);

@@ -346,3 +346,42 @@ def test_grouped_target_tiles(tiles):
             y = (xs[k] - mus[k]) @ Rs[k].double().T
             tol = 2 * d * 2.0 ** -24 * (100.0 + 4.0 * (y * y).sum(1))
             assert bool(((la_b[0] - la_s[0]).abs() <= tol).all()), d
+
+
+@pytest.mark.parametrize("proposal", ["diam", "am"])
+@pytest.mark.parametrize("prec,d,P,nproj,n_obs", [("fp64", 194, 5, 0, 0), ("fp64", 256, 3, 4, 0), ("fp64", 770, 66, 1, 0),
+                                                  ("fp32", 2, 1, 1, 0), ("fp32", 34, 7, 4, 0), ("fp32", 130, 64, 0, 0),
+                                                  ("fp32", 1154, 29, 2, 0), ("mixed", 64, 9, 2, 0),
+                                                  ("mixed", 226, 50, 0, 0), ("mixed", 750, 31, 3, 0),
+                                                  ("fp32", 128, 1024 * 4 + 1, 0, 0), ("fp32", 200, 6, 2, 300),
+                                                  ("fp32", 62, 5, 0, 2000)])
+def test_latency_bound_steps(prec, d, P, nproj, n_obs, proposal):
+    """Steps that accept and propose at once (all of a call but its ends) give
+    the bits of calls of one step each, which never do.  From these states the
+    contracting proposals are nearly all accepted, the random walk's about half."""
+    n = 6
+    outs = []
+    for split in (False, True):
+        if n_obs:
+            g = torch.Generator("cuda").manual_seed(d)
+            rn = lambda *sh: torch.randn(*sh, generator=g, dtype=torch.float64, device="cuda")
+            A, y = rn(n_obs, d).float(), (rn(n_obs) > 0).float()
+            s = diam.Sampler(diam.make_config(d, P, n, prec, beta=0.25, seed=3, proposal=proposal), None, None,
+                             (0.1 * rn(P, d)).contiguous(), A=A, y=y, prior_var=2.0)
+        else:
+            s, _, _, rn = sampler(prec, d, P, n, 5 + d, beta=0.25, proposal=proposal)
+        trace = torch.zeros(n, 1 + nproj, P, dtype=torch.float64, device="cuda")
+        s.set_trace(rn(nproj, d) if nproj else None, trace)
+        W = (0.5 / np.sqrt(d) * rn(n, P, d)).contiguous()
+        U = torch.linspace(0.05, 0.95, n * P, dtype=torch.float64, device="cuda").flip(0).reshape(n, P).contiguous()
+        cnt = torch.zeros(P, dtype=torch.int32, device="cuda")
+        la = []
+        for t in range(n) if split else [slice(0, n)]:
+            m = 1 if split else n
+            s.step_batch(m, W[t].clone(), U[t].clone(), cnt)
+            la.append(s.get(diam.F_LA).view(torch.float64)[:m * P].clone())
+        outs.append([torch.cat(la), cnt, trace, s.get_f64(diam.F_X, (P, d)), s.get_f64(diam.F_Z, (P, d)),
+                     s.get_f64(diam.F_LOGP, (P,))])
+    for a, b in zip(*outs):
+        assert torch.equal(a, b)
+    assert proposal == "diam" or P == 1 or 0 < int(outs[0][1].sum()) < n * P
