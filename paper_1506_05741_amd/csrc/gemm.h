@@ -1219,7 +1219,7 @@ DEV void t_gemm(TFrag<T, BM, BN, WGM, WGN> (&fs)[SETS], const T* __restrict__ A,
     }
     if (UNROLLED) {
       // a quarter of the slice's reads ahead of the products, so that none is
-      // pending at the next barrier, which the last products may pass
+      // waited for at the next barrier, which the last products may pass
       constexpr int G = Q / 4;
       T a[4][G][F::FM], b[4][G][F::FN];
       auto read = [&](int h) {
@@ -1265,18 +1265,19 @@ DEV void t_gemm(TFrag<T, BM, BN, WGM, WGN> (&fs)[SETS], const T* __restrict__ A,
     }
   };
   offsets(TBK);
-  // the ring may still be read by other waves from a previous call
-  asm volatile("s_barrier" ::: "memory");
+  // the ring's reads of a previous call are done, this wave's and the others'
+  asm volatile("s_waitcnt lgkmcnt(0)\n s_barrier" ::: "memory");
   for (int p = 0; p < ST - 1 && p < nk; ++p) issue(p, p);
   int slot = 0;
   auto step = [&](int kt, F& f) {
     // Stage kt has landed once at most the later stages' copies are pending.
-    // Without a loop's end between steps the compiler moves products, and with
-    // them the waits for their operands, behind the next barrier, after which
-    // the slot they read is refilled: there the reads are waited for here.
-    if (UNROLLED) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    if (kt + ST - 2 < nk) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LPW * CPB * GRP * (ST - 2)) : "memory");
-    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    // No LDS read may be pending either: after the barrier the slot of the step
+    // before is refilled.  In a loop the compiler has waited for that step's
+    // reads before the loop's end; in steps that it unrolls (SPLIT, or any
+    // constant K) it moves products, and the waits for their operands with
+    // them, behind this barrier.
+    if (kt + ST - 2 < nk) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(LPW * CPB * GRP * (ST - 2)) : "memory");
+    else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
     asm volatile("s_barrier" ::: "memory");
     // the ring slot refilled here was last read before this barrier
     if (kt + ST - 1 < nk) issue(kt + ST - 1, slot == 0 ? ST - 1 : slot - 1);
