@@ -42,6 +42,9 @@
  *     values (the MH ratio stays exact for the kernel actually applied).
  *   - Determinism: with fixed inputs (or a fixed seed) results are bitwise
  *     reproducible run to run; no floating-point atomics are used.
+ *     In FP64 with d <= 192 and more than 64 chains, how a window is cut into
+ *     diam_step_batch calls may change the last bits: short calls sum the
+ *     target's terms in another order than long ones.
  */
 #ifndef DIAM_H
 #define DIAM_H

@@ -661,7 +661,7 @@ extern "C" int diam_step_batch(diam_ctx* c, int32_t n, const double* W, const do
   const int nfun = 1 + c->nproj;
 
   const bool walk = walk_proposal(c->cfg);
-  if (prec == dk::P64 && !c->logreg && !c->da_on && dk::steps_resident_ok(d, P)) {
+  if (prec == dk::P64 && !c->logreg && !c->da_on && dk::steps_resident_ok(d, P, n)) {
     dk::ResidentArgs r{};
     r.d = d;
     r.P = P;

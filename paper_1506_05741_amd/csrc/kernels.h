@@ -201,7 +201,7 @@ hipError_t step_h2(const StepArgs& a, const float* Yp, const double* rsc, double
                    hipStream_t s);
 // All n steps of a call in one launch, one workgroup per chain with the FP64
 // matrix of the Gaussian target in its registers.
-bool steps_resident_ok(int d, int P);
+bool steps_resident_ok(int d, int P, int n);
 struct ResidentArgs {
   int d, P, n;
   double rho, c, inv2a2;         // as StepArgs

@@ -3408,16 +3408,32 @@ __global__ __launch_bounds__(64 * (KS + 1)) void k_steps_resident(ResidentArgs a
   }
 }
 
-// Above d = 192 the columns pass a lane's 256 registers.  Every chain reads R
-// from its own CU's registers, so the CUs' rounds over many chains lose to the
-// tiled target in the end: us a step, proposals included, this loop / the
-// launches per step: 10.8 / 23.3 at d = 64 and 8192 chains, 31.7 / 34.9 at d =
-// 128 and 8192, 10.7 / 18.6 at d = 192 and 1024, 20.9 / 22.6 at 2048, 41.5 /
-// 29.7 at 4096.
-bool steps_resident_ok(int d, int P) { return d <= 64 || (d <= 128 && P <= 8192) || (d <= 192 && P <= 1024); }
+// Above d = 192 the columns pass a lane's 256 registers.  Every chain's CU reads
+// R anew, so a call of many chains begins with P / 256 rounds of that, which
+// its steps have to earn back; long calls of very many chains lose to the tiled
+// target in the end.  us a call of n steps, launches per step / this loop:
+//   d     P      n = 1     n = 4     n = 8     n = 16     n = 64
+//   64    64     20 / 13   40 / 16   69 / 17   126 / 22   468 / 51
+//   64    4096   31 / 48   93 / 68   169 / 87  318 / 124  1284 / 370
+//   64    16384  49 / 165  150 / 211 275 / 277 578 / 497
+//   64    65536  137 / 603 511 / 890 995 / 1278
+//   128   64     19 / 20   43 / 23   74 / 26   135 / 34   504 / 78
+//   128   256    19 / 28   44 / 32   78 / 37   142 / 47   527 / 106
+//   128   1024   22 / 71   55 / 83   99 / 99   183 / 123  695 / 255
+//   128   8192   44 / 511  139 / 552 263 / 616 528 / 771
+//   192   64     21 / 32   48 / 36   77 / 40   139 / 51   523 / 115
+//   192   256    22 / 52   49 / 57   83 / 66   152 / 81   557 / 159
+//   192   1024   29 / 173  78 / 195  140 / 224 258 / 270  1016 / 570
+// Up to 64 chains the loop runs whatever the length, so that a window's bits do
+// not depend on how it is cut into calls; beyond, from the length on at which
+// it is ahead.
+bool steps_resident_ok(int d, int P, int n) {
+  const long per_step = d <= 64 ? 1024 : d <= 128 ? 128 : 43;  // chains that one step earns back
+  return (d <= 64 || (d <= 128 && P <= 8192) || (d <= 192 && P <= 1024)) && (P <= 64 || n * per_step >= P);
+}
 
 hipError_t steps_resident(const ResidentArgs& a, hipStream_t s) {
-  if (a.d < 1 || !steps_resident_ok(a.d, a.P) || a.P < 1 || a.n < 1 || a.nfun - 1 > MAXPROJ)
+  if (a.d < 1 || !steps_resident_ok(a.d, a.P, a.n) || a.P < 1 || a.n < 1 || a.nfun - 1 > MAXPROJ)
     return hipErrorInvalidValue;
   if (a.d <= 64) hipLaunchKernelGGL((k_steps_resident<1, 3, 22>), dim3(a.P), dim3(256), 0, s, a);
   else if (a.d <= 128) hipLaunchKernelGGL((k_steps_resident<2, 7, 20>), dim3(a.P), dim3(512), 0, s, a);
