@@ -525,24 +525,48 @@ hipError_t tgt_gauss_h2(const uint16_t* R2, const uint16_t* V2, const double* rs
   return hipGetLastError();
 }
 
-// Which kernel, by the number n of 64 x 64 tiles (256 CUs), in us:
-//   d, P (n)         tile kernel    split         engine tiles, FP64
-//                    FP64   FP32    FP64   FP32   32 x 32   64 x 32
-//   1024, 192 (48)   40.3   23.0    14.5   11.1   17.8      26.5
-//   2048, 128 (64)   77.4   43.3    35.0   21.4   32.4      50.6
-//   1536, 192 (72)   59.0   33.3    29.4   20.2   32.0      38.4
-//   2048, 256 (128)  78.2   43.7    59.8   33.1   41.8      50.7
-//   3000, 200 (188)  136    111     111    70.2   89.6      106
-//   2048, 512 (256)  78.1   44.1    139    64.3   74.4      72.0
-//   4096, 256 (256)  153    84.8    210    121    150       141
-// The tile kernel takes the time of one tile up to n = 256, the split kernel
-// time in proportion to n.  The engine needs rows of 16-byte multiples; in
-// FP32, whose two chains double its accumulators, it is behind (99.3 us at d =
-// 4096, P = 256).
+// Which kernel, by the split kernel's workgroups w (16 rows x 16 chains, its
+// time in proportion to them beyond one per CU) and the number n of 64 x 64
+// tiles (the tile kernels take the time of one tile up to n = 256, twice that
+// where the tile is not whole).  us, with 6 of launch and clock around a kernel:
+//   d, P           n    w      FP64: split  32 x 32  64 x 32    FP32: split  tile kernel
+//   64, 1024       16   256          6.2    6.2      6.2              6.2    6.3
+//   64, 8192       128  2048         19.2   6.3      6.3              12.4   6.3
+//   128, 1024      32   512          7.0    6.3      7.6              6.4    7.7
+//   256, 512       32   512          8.0    8.2      10.5             7.1    10.0
+//   256, 2048      128  2048         18.2   10.1     10.7             11.1   10.5
+//   512, 384       48   768          11.7   11.9     16.5             10.0   15.5
+//   512, 1024      128  2048         24.1   14.6     16.7             14.0   15.5
+//   700, 384       66   1056         20.4   18.4     21.2             16.2   29.0
+//   700, 1024      176  2816         46.7   25.2     29.9             26.1   29.3
+//   1024, 192      48   768          16.7   19.3     28.1             14.4   25.2
+//   1024, 256      64   1024         22.2   19.5     27.9             15.3   25.0
+//   1024, 768      192  3072         53.2   32.7     39.8             30.6   25.1
+//   2048, 128      64   1024         34.9   33.9     51.4             24.4   44.9
+//   3000, 256      188  3008         140    93.6     111              77.6   112
+//   4096, 16       64   256          31.6   62.1     98.3
+//   4096, 64       64   1024         62.8   63.7     98.3             40.8   84.3
+//   8192, 32       128  1024         162    147      196
+//   4096, 256      256  4096         210    150      141              121    84.8
+//   odd d          n    w      FP64: split, tile kernel
+//   65, 2048       64   768          9.1    9.8
+//   129, 2048      96   1280         15.0   12.7
+//   511, 1024      128  2048         28.2   28.7
+//   1023, 768      192  3072         66.4   52.3
+// The engine (32 x 32, 64 x 32) needs rows of 16-byte multiples; in FP32, whose
+// two chains double its accumulators, it is behind (99.3 us at d = 4096, P =
+// 256).
 int tgt_gauss_sub(Prec prec, int d, int P) {
-  const long n = (long)cdiv(d, TGT_BM) * cdiv(P, 64);
-  if (prec != P64 || d % 2) return n <= 192 ? 4 : 1;
-  return n <= 64 ? 4 : n < 256 ? 2 : 1;
+  const long w = (long)tgt_quarters(d) * cdiv(P, 16), n = (long)cdiv(d, TGT_BM) * cdiv(P, 64);
+  const bool small = d < 384;  // few slices of K: the split has less to share out
+  if (prec == P64 && d % 2 == 0) {
+    if (small ? P <= 1024 && w <= max(256, 2 * d) : w <= (P <= 64 && d <= 4096 ? 1024 : P <= 128 ? 960 : 768)) return 4;
+    return n < 256 ? 2 : 1;
+  }
+  if (prec == P64) return w <= 2048 && (P <= 1024 || w <= 768) ? 4 : 1;
+  if (d % 64 == 0 && P % 64 == 0)  // whole tiles
+    return (small ? P <= 2048 && w <= 1280 : P <= 1024 && w <= 2048) ? 4 : 1;
+  return P <= 2048 && w <= (small ? 2048 : 3072) ? 4 : 1;
 }
 
 // FP64 on the engine's tiles of BM rows; false: rows not aligned for it
@@ -3412,23 +3436,23 @@ __global__ __launch_bounds__(64 * (KS + 1)) void k_steps_resident(ResidentArgs a
 // R anew, so a call of many chains begins with P / 256 rounds of that, which
 // its steps have to earn back; long calls of very many chains lose to the tiled
 // target in the end.  us a call of n steps, launches per step / this loop:
-//   d     P      n = 1     n = 4     n = 8     n = 16     n = 64
-//   64    64     20 / 13   40 / 16   69 / 17   126 / 22   468 / 51
-//   64    4096   31 / 48   93 / 68   169 / 87  318 / 124  1284 / 370
-//   64    16384  49 / 165  150 / 211 275 / 277 578 / 497
-//   64    65536  137 / 603 511 / 890 995 / 1278
-//   128   64     19 / 20   43 / 23   74 / 26   135 / 34   504 / 78
-//   128   256    19 / 28   44 / 32   78 / 37   142 / 47   527 / 106
-//   128   1024   22 / 71   55 / 83   99 / 99   183 / 123  695 / 255
-//   128   8192   44 / 511  139 / 552 263 / 616 528 / 771
-//   192   64     21 / 32   48 / 36   77 / 40   139 / 51   523 / 115
-//   192   256    22 / 52   49 / 57   83 / 66   152 / 81   557 / 159
-//   192   1024   29 / 173  78 / 195  140 / 224 258 / 270  1016 / 570
+//   d     P      n = 1     n = 4      n = 8      n = 16     n = 64
+//   64    64     20 / 15   42 / 16    75 / 18    129 / 23   478 / 50
+//   64    4096   23 / 48   63 / 68    107 / 86   198 / 124  802 / 362
+//   64    16384  48 / 165  148 / 212  274 / 277  578 / 496
+//   64    65536  138 / 601 512 / 890  995 / 1277
+//   128   64     22 / 20   46 / 23    77 / 27    140 / 34   516 / 78
+//   128   256    21 / 28   44 / 32    79 / 37    145 / 48   535 / 106
+//   128   1024   21 / 72   53 / 85    97 / 103   174 / 126  649 / 255
+//   128   8192   44 / 509  140 / 553  264 / 614  530 / 770
+//   192   64     23 / 32   48 / 36    79 / 40    143 / 51   533 / 115
+//   192   256    23 / 52   51 / 58    86 / 67    157 / 82   561 / 157
+//   192   1024   26 / 173  69 / 196   120 / 224  215 / 271  832 / 569
 // Up to 64 chains the loop runs whatever the length, so that a window's bits do
 // not depend on how it is cut into calls; beyond, from the length on at which
 // it is ahead.
 bool steps_resident_ok(int d, int P, int n) {
-  const long per_step = d <= 64 ? 1024 : d <= 128 ? 128 : 43;  // chains that one step earns back
+  const long per_step = d <= 64 ? 700 : d <= 128 ? 100 : 40;  // chains that one step earns back
   return (d <= 64 || (d <= 128 && P <= 8192) || (d <= 192 && P <= 1024)) && (P <= 64 || n * per_step >= P);
 }
 

@@ -30,15 +30,52 @@ def sampler(prec, d, P, n_lag, **kw):
                         rn(P, d).contiguous())
 
 
-@pytest.mark.parametrize("d,P,n,one", [(64, 64, 1, True), (64, 65, 1, True), (64, 2048, 1, False), (64, 2048, 2, True),
-                                       (32, 16384, 8, False), (32, 16384, 16, True), (128, 64, 1, True),
-                                       (128, 256, 1, False), (128, 256, 2, True), (100, 8192, 16, False),
-                                       (100, 8192, 64, True), (100, 8193, 64, False), (192, 64, 1, True),
-                                       (192, 256, 4, False), (192, 256, 6, True), (192, 1024, 16, False),
-                                       (192, 1024, 24, True), (193, 4, 8, False)])
+@pytest.mark.parametrize("d,P,n,one", [(64, 64, 1, True), (64, 700, 1, True), (64, 2048, 2, False), (64, 2048, 3, True),
+                                       (32, 16384, 23, False), (32, 16384, 24, True), (128, 64, 1, True),
+                                       (128, 256, 2, False), (128, 256, 3, True), (100, 8192, 81, False),
+                                       (100, 8192, 82, True), (100, 8193, 82, False), (192, 64, 1, True),
+                                       (192, 256, 6, False), (192, 256, 7, True), (192, 1024, 25, False),
+                                       (192, 1024, 26, True), (193, 4, 8, False)])
 def test_steps_in_one_launch_only_where_a_call_earns_it_back(d, P, n, one):
     """The loop with R in registers reads R once per chain and call: a call of
     few steps of many chains takes the launches per step (d = 128, 8192 chains,
     one step: 511 us in the loop, 44 in launches)."""
     names = kernels(lambda s=sampler("fp64", d, P, 2 * n): s.step_batch(n))
     assert any("k_steps_resident" in k for k in names) == one
+
+
+@pytest.mark.parametrize("prec,d,P,kernel", [("fp64", 64, 8192, "k_tgt_gauss_t<32>"), ("fp64", 200, 300, "k_tgt_split<double>"),
+                                             ("fp64", 1024, 192, "k_tgt_split<double>"),
+                                             ("fp64", 1024, 256, "k_tgt_gauss_t<32>"),
+                                             ("fp64", 2048, 512, "k_tgt_gauss_t<64>"),
+                                             ("fp64", 129, 2048, "k_tgt_gauss<double"),
+                                             ("fp64", 129, 1024, "k_tgt_split<double>"),
+                                             ("fp32", 64, 2048, "k_tgt_split<float>"),
+                                             ("fp32", 64, 8192, "k_tgt_gauss<float"),
+                                             ("fp32", 1024, 512, "k_tgt_split<float>"),
+                                             ("fp32", 1024, 768, "k_tgt_gauss<float"),
+                                             ("fp32", 700, 1024, "k_tgt_split<float>"),
+                                             ("mixed", 64, 8192, "k_tgt_gauss<float")])
+def test_target_kernel_by_size(prec, d, P, kernel):
+    """The split target kernel's time grows with its workgroups, the tile
+    kernels take that of one tile: many chains of a small dimension belong to
+    the latter (d = 64, 8192 chains: FP32 12.4 us split, 6.3 tiled)."""
+    names = kernels(lambda s=sampler(prec, d, P, 4): s.step_batch(2))
+    assert any(kernel in k for k in names) and sum("k_tgt" in k for k in names) == 2
+
+
+@pytest.mark.parametrize("d,P", [(2, 1100), (14, 1041), (34, 1025), (62, 3000), (66, 1500), (130, 607), (254, 531)])
+def test_engine_target_of_few_dimensions_and_many_chains(d, P):
+    """The FP64 engine's 32 x 32 tiles with less than one to a few slices of K,
+    against FP64 products (a sum of d + 8 terms, 8 (d + 8) u)."""
+    g = torch.Generator("cuda").manual_seed(d)
+    rn = lambda *s: torch.randn(*s, generator=g, dtype=torch.float64, device="cuda")
+    R, mu, x0 = torch.eye(d, dtype=torch.float64, device="cuda") + rn(d, d) / np.sqrt(d), rn(d), rn(P, d)
+    s = diam.Sampler(diam.make_config(d, P, 4, "fp64", beta=0.05, seed=5), mu, R, x0)
+    W, U = 0.2 * rn(1, P, d), torch.full((1, P), 0.5 * 2.0 ** -52, dtype=torch.float64, device="cuda")
+    names = kernels(lambda: s.step_batch(1, W, U))
+    assert any("k_tgt_gauss_t<32>" in k for k in names)
+    assert bool(s.get(diam.F_ACC).bool().all())  # accepted unless log alpha < -36
+    y = (s.get_f64(diam.F_X, (P, d)) - mu) @ R.T
+    ref = -0.5 * (y * y).sum(1)
+    assert bool(((s.get_f64(diam.F_LOGP, (P,)) - ref).abs() <= 8 * (d + 8) * 2.0 ** -53 * ref.abs()).all())
