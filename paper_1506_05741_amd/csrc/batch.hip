@@ -66,6 +66,7 @@ struct BLay {
 struct Tiles {
   std::vector<BTile> all;
   Seg tgt[dk::G_TGT_CONFIGS], decide, step, trigemm, syrk, rowsum, dd, d1, colnorm, triinv;
+  bool tgt_engine[dk::G_TGT_CONFIGS];
   Seg cdiag;
   std::vector<Seg> cpanel, cupd, whiten, wupd;
   std::vector<dk::PItem> pitems;  // one step of the persistent loop
@@ -91,7 +92,8 @@ Tiles build_tiles(const std::vector<int>& dims, int P, int n) {
   std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return dims[x] > dims[y]; });
   for (int c = 0; c < dk::G_TGT_CONFIGS; ++c) {
     v.clear();
-    const int bm = dk::g_tgt_rows(c);
+    T.tgt_engine[c] = dk::g_tgt_engine(c, dims.data(), G, P);
+    const int bm = dk::g_tgt_rows(c, T.tgt_engine[c]);
     for (int g : order)
       for (int bx = 0; bx < cdivh(dims[g], bm); ++bx)
         for (int by = 0; by < cdivh(P, 32); ++by) v.push_back({g, bx, by});
@@ -600,7 +602,7 @@ static int enqueue_window(diam_batch* b, hipStream_t s) {
   } else {
     const Seg& tg = T.tgt[b->tgt_cfg];
     for (int t = 0; t < n; ++t) {
-      BCHK(dk::g_tgt(b->tgt_cfg, b->dp, tl(tg), tg.n, P, s));
+      BCHK(dk::g_tgt(b->tgt_cfg, T.tgt_engine[b->tgt_cfg], b->dp, tl(tg), tg.n, P, s));
       st.t = t;
       BCHK(dk::g_step(b->dp, tl(T.decide), T.decide.n, tl(T.step), T.step.n, st, s));
     }
@@ -785,9 +787,9 @@ extern "C" int diam_batch_autotune(diam_batch* b, int32_t reps, int32_t* choice,
     const Seg& tg = b->T.tgt[c];
     const BTile* tl = b->dt + tg.off;
     hipError_t e = hipSuccess;
-    for (int i = 0; i < 2 && e == hipSuccess; ++i) e = dk::g_tgt(c, b->dp, tl, tg.n, b->P, s);
+    for (int i = 0; i < 2 && e == hipSuccess; ++i) e = dk::g_tgt(c, b->T.tgt_engine[c], b->dp, tl, tg.n, b->P, s);
     if (e == hipSuccess) e = hipEventRecord(e0, s);
-    for (int i = 0; i < reps && e == hipSuccess; ++i) e = dk::g_tgt(c, b->dp, tl, tg.n, b->P, s);
+    for (int i = 0; i < reps && e == hipSuccess; ++i) e = dk::g_tgt(c, b->T.tgt_engine[c], b->dp, tl, tg.n, b->P, s);
     if (e == hipSuccess) e = hipEventRecord(e1, s);
     if (e == hipSuccess) e = hipEventSynchronize(e1);
     float ms = 0.f;

@@ -302,8 +302,10 @@ hipError_t g_persist(const BProb* pr, const PItem* items, int nitems, const BSte
 int g_persist_blocks_per_cu();
 constexpr int G_TGT_CONFIGS = 5;    // target tile shapes the autotuner chooses from
 int g_tgt_bm(int cfg);               // rows per partial
-int g_tgt_rows(int cfg);             // rows per tile of the list
-hipError_t g_tgt(int cfg, const BProb* pr, const BTile* tl, int ntiles, int P, hipStream_t s);
+// whether the direct-to-LDS engine serves shape cfg of this problem set
+bool g_tgt_engine(int cfg, const int* dims, int G, int P);
+int g_tgt_rows(int cfg, bool engine);  // rows per tile of the list
+hipError_t g_tgt(int cfg, bool engine, const BProb* pr, const BTile* tl, int ntiles, int P, hipStream_t s);
 hipError_t g_step(const BProb* pr, const BTile* dec_tl, int ndec, const BTile* tl, int ntiles, const BStep& st,
                   hipStream_t s);
 hipError_t g_trigemm(const BProb* pr, const BTile* tl, int ntiles, int ncols, double c, hipStream_t s);

@@ -3596,10 +3596,13 @@ __global__ __launch_bounds__(256 * KG) void gk_tgt(const BProb* __restrict__ pr,
 }
 
 // Shapes 64 x 2 and 32 x 4 on the direct-to-LDS engine, 64-row tiles for both
-// (the latter writes two 32-row partials), bitwise the tiles above.  The 271 MB
-// of R of the 48 problems do not fit the 256 MB Infinity Cache, so R streams
-// from HBM every step: 93 us in either shape as the lists stood, 81 and 77 us
-// with the largest problems first, 67 us (4.0 TB/s) with the engine too.
+// (the latter writes two 32-row partials), bitwise the tiles above.  Four
+// wavefronts take the k-groups one after the other where the tiles above have
+// four wavefronts each, so a tile takes longer and more of them run per CU;
+// g_tgt_engine chooses.  The 271 MB of R of the 48 problems do not fit the 256
+// MB Infinity Cache, so R streams from HBM every step: 93 us in either shape as
+// the lists stood, 81 and 77 us with the largest problems first, 67 us (4.0
+// TB/s) with the engine too.
 template <int WGM, int WGN, int SETS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void gk_tgt_t(const BProb* __restrict__ pr,
                                                                                       const BTile* __restrict__ tl,
@@ -3609,21 +3612,68 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void g
   tgt_tile_t<float, 64, 32, WGM, WGN, 6, SETS>(b.Rp, b.Vp, b.ld, P, t.a, t.b, b.lpp_part, b.nrb);
 }
 
-hipError_t g_tgt(int cfg, const BProb* pr, const BTile* tl, int ntiles, int P, hipStream_t s) {
+// Which kernel serves shapes 64 x 2 and 32 x 4, by the number n of 64 x 32 tiles
+// of the problem set; a tile at an edge takes 1.5 (rows) to 2 times (chains) as
+// long in the tile kernel, no longer on the engine.  us, tile kernel / engine:
+//   d; P                    n      64 x 2         32 x 4
+//   1024; 32                16     15.1 / 21.0    9.2 / 18.6
+//   3072; 32                48     41.1 / 59.0    25.0 / 51.1
+//   8 of 1024; 32           128    15.7 / 21.1    11.3 / 19.4
+//   64 of 256; 32           256    6.0 / 7.3      7.0 / 6.8
+//   8 of 2048; 32           256    30.7 / 40.7    31.0 / 36.6
+//   16 of 2048; 32          512    51.6 / 56.5    58.5 / 54.4
+//   64 of 1024; 32          1024   52.6 / 61.4    62.1 / 59.0
+//   256 of 64; 32           256    3.3 / 3.6      5.0 / 3.5
+//   2048, 65, 33; 32        35     27.9 / 40.0    17.5 / 34.6
+//   2000, 2048; 32          64     37.3 / 39.2    29.5 / 35.4
+//   8 of 1000; 32           128    22.9 / 22.0    13.3 / 20.2
+//   32 of 1000; 32          512    40.8 / 33.4    40.6 / 32.4
+//   48, 64 .. 1091; 32      310    24.4 / 26.8    18.9 / 25.1
+//   48, 64 .. 2708; 32      579    64.0 / 61.5    52.2 / 57.2
+//   8, 64 .. 1038; 24       64     27.1 / 22.2    17.6 / 19.8
+//   32, 64 .. 1134; 24      215    32.2 / 24.3    23.6 / 22.3
+//   48, 64 .. 3039; 16      656    103 / 69.8     93.2 / 64.8
+//   8 of 1024; 20           128    28.1 / 20.9    18.4 / 19.3
+// 64 x 2: the tile kernel where no chain tile has an edge and no problem within
+// a tenth of the largest has one, up to 1.5 tiles a CU, and without any edge at
+// all sizes.  32 x 4: its four k-groups pay where the chip is not full.
+bool g_tgt_engine(int cfg, const int* dims, int G, int P) {
+  if (cfg != 2 && cfg != 4) return false;
+  long n = 0;
+  int dmax = 0;
+  for (int g = 0; g < G; ++g) {
+    n += (long)cdiv(dims[g], 64) * cdiv(P, 32);
+    dmax = max(dmax, dims[g]);
+  }
+  if (cfg == 4) return dmax <= 128 || n > (P % 32 == 0 ? 384 : 192);
+  if (P % 32 != 0) return true;
+  bool edge = false, large_edge = false;
+  for (int g = 0; g < G; ++g)
+    if (dims[g] % 64 != 0) {
+      edge = true;
+      large_edge |= 10L * dims[g] > 9L * dmax;
+    }
+  return large_edge || (edge && n > 384);
+}
+
+hipError_t g_tgt(int cfg, bool engine, const BProb* pr, const BTile* tl, int ntiles, int P, hipStream_t s) {
   if (ntiles <= 0) return hipSuccess;
+  if (engine) {
+    if (cfg == 2) hipLaunchKernelGGL((gk_tgt_t<2, 2, 2>), dim3(ntiles), dim3(256), 0, s, pr, tl, P);
+    else if (cfg == 4) hipLaunchKernelGGL((gk_tgt_t<4, 1, 4>), dim3(ntiles), dim3(256), 0, s, pr, tl, P);
+    else return hipErrorInvalidValue;
+    return hipGetLastError();
+  }
   switch (cfg) {
     case 0: hipLaunchKernelGGL((gk_tgt<32, 2>), dim3(ntiles), dim3(512), 0, s, pr, tl, P); break;
     case 1: hipLaunchKernelGGL((gk_tgt<64, 1>), dim3(ntiles), dim3(256), 0, s, pr, tl, P); break;
-    case 2: hipLaunchKernelGGL((gk_tgt_t<2, 2, 2>), dim3(ntiles), dim3(256), 0, s, pr, tl, P); break;
+    case 2: hipLaunchKernelGGL((gk_tgt<64, 2>), dim3(ntiles), dim3(512), 0, s, pr, tl, P); break;
     case 3: hipLaunchKernelGGL((gk_tgt<128, 2>), dim3(ntiles), dim3(512), 0, s, pr, tl, P); break;
-    default: hipLaunchKernelGGL((gk_tgt_t<4, 1, 4>), dim3(ntiles), dim3(256), 0, s, pr, tl, P); break;
+    default: hipLaunchKernelGGL((gk_tgt<32, 4>), dim3(ntiles), dim3(1024), 0, s, pr, tl, P); break;
   }
   return hipGetLastError();
 }
-int g_tgt_rows(int cfg) {
-  static const int rows[G_TGT_CONFIGS] = {32, 64, 64, 128, 64};
-  return rows[cfg];
-}
+int g_tgt_rows(int cfg, bool engine) { return engine ? 64 : g_tgt_bm(cfg); }
 int g_tgt_bm(int cfg) {
   static const int bm[G_TGT_CONFIGS] = {32, 64, 64, 128, 32};
   return bm[cfg];

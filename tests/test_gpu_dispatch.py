@@ -79,3 +79,45 @@ def test_engine_target_of_few_dimensions_and_many_chains(d, P):
     y = (s.get_f64(diam.F_X, (P, d)) - mu) @ R.T
     ref = -0.5 * (y * y).sum(1)
     assert bool(((s.get_f64(diam.F_LOGP, (P,)) - ref).abs() <= 8 * (d + 8) * 2.0 ** -53 * ref.abs()).all())
+
+
+@pytest.mark.parametrize("tiles", [2, 4])
+@pytest.mark.parametrize("dims,P,engine", [([320, 64, 33], 32, (False, False)), ([256, 230, 7], 64, (False, False)),
+                                           ([300, 310], 32, (True, False)), ([200, 130, 33], 20, (True, False)),
+                                           ([128, 64], 32, (False, True)), ([192] * 132, 32, (False, True)),
+                                           ([192] * 132 + [65], 32, (True, True)), ([190] * 70, 24, (True, True))])
+def test_grouped_target_kernel_by_problem_set(dims, P, engine, tiles):
+    """Few tiles, or none at an edge, belong to the tile kernels (one problem
+    of 1024: 9.2 us against the engine's 18.6 in shape 32 x 4).  Both give the
+    log ratios of a separate FP32 sampler: shape 64 x 2 the same bits, 32 x 4,
+    whose four chains of a sum are added in another order, within 2 d u32 of
+    the squares summed."""
+    n = 2
+    g = torch.Generator("cuda").manual_seed(3)
+    rn = lambda *s: torch.randn(*s, generator=g, dtype=torch.float64, device="cuda")
+    mus, xs = [rn(d) for d in dims], [rn(P, d) for d in dims]
+    Rs = [(torch.eye(d, device="cuda") + rn(d, d) / d).float() for d in dims]
+    b = diam.Batch(diam.make_batch_config(len(dims), P, n, seed=4), mus, Rs, xs)
+    b.set_graph(False)
+    b.set_tiles(tiles)
+    first = [None]
+
+    def window():
+        b.window()
+        if first[0] is None:
+            first[0] = [(b.get(k, diam.F_W).clone(), b.get_f64(k, diam.F_U, (n, P)).clone(),
+                         b.get_f64(k, diam.F_LA, (n, P)).clone()) for k in range(len(dims))]
+
+    names = kernels(window)
+    assert any("gk_tgt_t<" in k for k in names) == engine[tiles == 4]
+    for k in range(len(dims))[-6:]:
+        d, (W, U, la) = dims[k], first[0][k]
+        s = diam.Sampler(diam.make_config(d, P, n, "fp32"), mus[k], Rs[k], xs[k])
+        ld = (d + 3) // 4 * 4
+        s.step_batch(n, W.view(torch.float32).reshape(n, P, ld)[:, :, :d].double().contiguous(), U.contiguous())
+        ref = s.get_f64(diam.F_LA, (n, P))
+        if tiles == 2:
+            assert torch.equal(la, ref), d
+        else:  # the first step: same states on both sides
+            y = (xs[k] - mus[k]) @ Rs[k].double().T
+            assert bool(((la[0] - ref[0]).abs() <= 2 * d * 2.0 ** -24 * (100.0 + 4.0 * (y * y).sum(1))).all()), d
