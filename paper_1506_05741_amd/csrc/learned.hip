@@ -127,11 +127,21 @@ int logreg_row_blocks(long n_obs) { return (int)((n_obs + 63) / 64); }
 // Column tiles of 64 chains; under delayed acceptance (nact set) the tiles
 // past the survivor count exit at once.  (32-chain tiles were measured 1.5x
 // less efficient per chain, more than their finer granularity saves.)
+// The engine's two stages need the other workgroups of a CU to cover a slice's
+// latency, and it reads an edge at full speed; up to two tiles a CU and without
+// an edge the tile kernel's eight wavefronts are ahead.  us a step, tile kernel /
+// engine, by n_obs, d, P (tiles): 4096, 512, 64 (64) 22.8 / 24.6; 16000, 512, 64
+// (250) 29.0 / 30.6; 12800, 512, 128 (400) 39.3 / 41.0; 32768, 1024, 64 (512)
+// 59.7 / 62.9; 16000, 4096, 64 (250) 115 / 135; 51200, 512, 64 (800) 63.4 / 63.8;
+// 38400, 1024, 64 (600) 92.4 / 82.8; with an edge 16001, 1024, 64 (251) 42.7 / 44.1,
+// 20000, 512, 64 (313) 42.1 / 40.8, 12800, 512, 50 (200) 35.6 / 30.5; with few
+// slices of K 12800, 200, 64 (200) 23.5 / 23.5.
 hipError_t tgt_logreg(const float* A, const float* y, long n_obs, const float* V, int d, int P, const int* nact,
                       double* part, hipStream_t s) {
   const int nrb = logreg_row_blocks(n_obs), groups = (nrb + 7) / 8;
   const int nct = cdiv(P, 64);
-  if (t_gemm_ok<float, true, true>(A, d, (int)n_obs, V, d, P, d)) {
+  const bool few_whole = n_obs % 64 == 0 && P % 64 == 0 && d >= 256 && (long)nrb * nct <= 512;
+  if (!few_whole && t_gemm_ok<float, true, true>(A, d, (int)n_obs, V, d, P, d)) {
     hipLaunchKernelGGL(k_tgt_logreg_t, dim3(groups * 8 * nct), dim3(256), 0, s, A, y, (int)n_obs, V, d, P, nact, nrb,
                        nct, part);
     return hipGetLastError();

@@ -121,3 +121,29 @@ def test_grouped_target_kernel_by_problem_set(dims, P, engine, tiles):
         else:  # the first step: same states on both sides
             y = (xs[k] - mus[k]) @ Rs[k].double().T
             assert bool(((la[0] - ref[0]).abs() <= 2 * d * 2.0 ** -24 * (100.0 + 4.0 * (y * y).sum(1))).all()), d
+
+
+@pytest.mark.parametrize("n_obs,d,P,engine", [(64, 256, 64, False), (128, 300, 128, False), (16384, 256, 128, False),
+                                              (16448, 256, 128, True), (63, 256, 64, True), (128, 256, 63, True),
+                                              (128, 252, 64, True), (128, 301, 64, False), (129, 301, 63, False)])
+def test_logistic_kernel_by_size(n_obs, d, P, engine):
+    """Few whole tiles belong to the tile kernel (2048 dimensions, 16000
+    observations, 64 chains: 65 us a step, 74 on the engine), unaligned rows
+    too.  Against FP64 at the accepted states: an FP32 dot product of d terms
+    errs by (d + 4) u32 sum |a x|, a term's evaluation by 6 u32 (|t| + 1)."""
+    g = torch.Generator("cuda").manual_seed(n_obs + d)
+    rn = lambda *s: torch.randn(*s, generator=g, dtype=torch.float64, device="cuda")
+    A, y = (rn(n_obs, d) / np.sqrt(d)).float(), (rn(n_obs) > 0).float()
+    s = diam.Sampler(diam.make_config(d, P, 8, "fp32", beta=0.05, seed=3), None, None, rn(P, d).contiguous(), A=A, y=y,
+                     prior_var=10.0)
+    W, U = 0.2 * rn(1, P, d), torch.full((1, P), 0.5 * 2.0 ** -52, dtype=torch.float64, device="cuda")
+    names = kernels(lambda: s.step_batch(1, W, U))
+    assert any("k_tgt_logreg_t" in k for k in names) == engine
+    assert bool(s.get(diam.F_ACC).bool().all())  # accepted unless log alpha < -36
+    x = s.get_f64(diam.F_X, (P, d))
+    xf = x.float().double()
+    t = A.double() @ xf.T
+    ref = (y.double()[:, None] * t - torch.nn.functional.softplus(t)).sum(0) - 0.05 * (x * x).sum(1)
+    u32 = 2.0 ** -24
+    tol = ((d + 4) * u32 * (A.double().abs() @ xf.abs().T) + 6 * u32 * (t.abs() + 1)).sum(0) + 1e-12 * ref.abs()
+    assert bool(((s.get_f64(diam.F_LOGP, (P,)) - ref).abs() <= tol).all())
