@@ -3,6 +3,7 @@
 #include <math.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "gemm.h"
 #include "kernels.h"
@@ -1251,9 +1252,9 @@ DEV void fold_S_elem(const double* __restrict__ G, const double* __restrict__ h,
 // its mirror image).  The scatter's upper-storage tile is read along its
 // columns into LDS, so the tile below the diagonal does not read it at a
 // stride of d; each element's arithmetic is fold_S_elem's.  One launch and one
-// trip through the splits in place of three (d = 1024: 20 + 10 + 3 us, now 16).
+// trip through the splits in place of three (d = 1024: 20 + 7 + 4 us, now 13).
 constexpr int MERGE_TY = 16;
-__global__ __launch_bounds__(64 * MERGE_TY) void k_merge(Scatter g, const double* __restrict__ sft, double N, double n,
+__global__ __launch_bounds__(64 * MERGE_TY) __attribute__((amdgpu_waves_per_eu(8))) void k_merge(Scatter g, const double* __restrict__ sft, double N, double n,
                                                          double* __restrict__ S, double* __restrict__ m, int d) {
   __shared__ double T[64][65], hs[2][64];
   int bi, bj;
@@ -1264,19 +1265,46 @@ __global__ __launch_bounds__(64 * MERGE_TY) void k_merge(Scatter g, const double
   if (ty < 2) {
     const int i = (ty ? c0 : r0) + tx;
     double s = 0.0;
-    if (i < d)
+    if (i < d) {
+#pragma unroll 8
       for (int q = 0; q < g.nh; ++q) s += g.h[(long)q * d + i];
+    }
     hs[ty][tx] = s;
     if (ty == 0 && bi == bj && i < d) m[i] = (N * m[i] + (s + n * sft[i])) / (N + n);
   }
+  // The thread's columns side by side and four splits at a time: a load at a
+  // time, column after column, was a chain of 64 / MERGE_TY x ns of them (d =
+  // 64, 64 splits, one workgroup: 89 us, now 39; d = 256 47 and 24).  64
+  // registers, for two workgroups a CU: with one, d = 4096 takes 82 us in place
+  // of 69.
+  constexpr int MC = 64 / MERGE_TY;
+  double v[MC];
 #pragma unroll
-  for (int c = ty; c < 64; c += MERGE_TY) {
-    const int r = r0 + tx, cc = c0 + c;
-    double v = 0.0;
-    if (r < d && cc < d)
-      for (int q = 0; q < g.ns; ++q) v += g.G[q * dd + r + (long)cc * d];
-    T[tx][c] = v;
-  }
+  for (int c = 0; c < MC; ++c) v[c] = 0.0;
+  // bytes from the tile's first element; past the edge the last row or column
+  uint32_t o[MC];
+#pragma unroll
+  for (int c = 0; c < MC; ++c)
+    o[c] = (uint32_t)(8 * (min(tx, d - 1 - r0) + (long)min(ty + c * MERGE_TY, d - 1 - c0) * d));
+  const char* part = (const char*)(g.G + r0 + (long)c0 * d);
+  auto add = [&](auto count) {
+    constexpr int NQ = decltype(count)::value;
+    double x[NQ][MC];
+#pragma unroll
+    for (int q = 0; q < NQ; ++q)
+#pragma unroll
+      for (int c = 0; c < MC; ++c) x[q][c] = *(const double*)(part + 8 * q * dd + o[c]);
+#pragma unroll
+    for (int q = 0; q < NQ; ++q)
+#pragma unroll
+      for (int c = 0; c < MC; ++c) v[c] += x[q][c];
+    part += 8 * NQ * dd;
+  };
+  int q = 0;
+  for (; q + 4 <= g.ns; q += 4) add(std::integral_constant<int, 4>());
+  for (; q < g.ns; ++q) add(std::integral_constant<int, 1>());
+#pragma unroll
+  for (int c = 0; c < MC; ++c) T[tx][ty + c * MERGE_TY] = v[c];
   __syncthreads();
   auto fold = [&](int i, int j, double v, int a, double ha, int b, double hb) {
     const long e = i + (long)j * d;

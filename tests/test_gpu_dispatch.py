@@ -147,3 +147,23 @@ def test_logistic_kernel_by_size(n_obs, d, P, engine):
     u32 = 2.0 ** -24
     tol = ((d + 4) * u32 * (A.double().abs() @ xf.abs().T) + 6 * u32 * (t.abs() + 1)).sum(0) + 1e-12 * ref.abs()
     assert bool(((s.get_f64(diam.F_LOGP, (P,)) - ref).abs() <= tol).all())
+
+
+def test_merge_of_one_tile_and_many_splits():
+    """The sum over the splits of the scatter has its loads in flight together
+    (d = 64, 64 splits on one workgroup: 39 us, 89 with one load at a time,
+    beside a scatter of 37)."""
+    s = sampler("mixed", 64, 8192, 16)
+
+    def window():
+        s.step_batch(16)
+        s.merge_moments()
+
+    window()
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CUDA]) as p:
+        for _ in range(5):
+            window()
+        torch.cuda.synchronize()
+    us = lambda name: min(e.device_time for e in p.events() if name in e.name)
+    assert us("k_merge") < 1.6 * us("k_syrk")
