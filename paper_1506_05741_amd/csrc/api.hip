@@ -48,7 +48,7 @@ struct Layout {
       h, syrk, status, proj_part, linv;
   // learned-part form
   size_t mlp_master, mlp_eff, mlp_grad, mlp_m, mlp_in_mean, mlp_in_scale, mlp_stats, mlp_Xs, mlp_ts, mlp_xb, mlp_tb,
-      mlp_a1, mlp_h1, mlp_a2, mlp_h2, mlp_ga1, mlp_ga2, mlp_out, mlp_gout, mlp_loss, mlp_bidx, s_cur, s_new, pass1,
+      mlp_a1, mlp_h1, mlp_a2, mlp_h2, mlp_ga1, mlp_ga2, mlp_out, mlp_loss, mlp_bidx, s_cur, s_new, pass1,
       slot, idx, nsurv, npass, Vs, t64, Zs;
   // two-part half target (mixed form, Gaussian)
   size_t R2, V2, vsc, rsc, Yp;
@@ -160,7 +160,6 @@ Layout make_layout(const diam_config& c, const diam_target& tg) {
     L.mlp_ga1 = take(H * nmax * 4);
     L.mlp_ga2 = take(H * nmax * 4);
     L.mlp_out = take(nmax * 4);
-    L.mlp_gout = take(nmax * 4);
     L.mlp_loss = take(LOSS_HIST * 4);
     L.mlp_bidx = take(nmax * 4);
     L.s_cur = take(2 * P * 8);
@@ -319,12 +318,11 @@ __global__ void k_fill_i32(int32_t* p, long n) {
   if (e < n) p[e] = 0;
 }
 
-// Clears the Cholesky words; the target error word only when clear_err.
-__global__ void k_clear_status(Status* s, int clear_err) {
+__global__ void k_clear_status(Status* s) {
   if (threadIdx.x == 0) {
     s->info = 0;
     s->trace = 0.0;
-    if (clear_err) s->err = 0;
+    s->err = 0;
   }
 }
 
@@ -477,7 +475,6 @@ extern "C" int diam_init(diam_ctx** out, const diam_config* cfg, const diam_targ
     b.ga1 = fp(lay.mlp_ga1);
     b.ga2 = fp(lay.mlp_ga2);
     b.out = fp(lay.mlp_out);
-    b.gout = fp(lay.mlp_gout);
     b.loss = fp(lay.mlp_loss);
     b.bidx = (int*)(c->ws + lay.mlp_bidx);
     c->s_cur = dptr(c, lay.s_cur);
@@ -581,7 +578,7 @@ extern "C" int diam_init(diam_ctx** out, const diam_config* cfg, const diam_targ
   if (cfg->M > 1) reset_local(c);
   hipLaunchKernelGGL(k_fill_i32, dim3(nblk(P)), dim3(256), 0, s, c->nacc, (long)P);
   hipLaunchKernelGGL(k_fill_i32, dim3(nblk(P)), dim3(256), 0, s, c->wacc, (long)P);
-  hipLaunchKernelGGL(k_clear_status, dim3(1), dim3(64), 0, s, c->status, 1);
+  hipLaunchKernelGGL(k_clear_status, dim3(1), dim3(64), 0, s, c->status);
   HIPCHK_INIT(hipGetLastError());
   HIPCHK_INIT(dk::round_factor(c->prec, c->L, c->Llow, d, s));
   // log pi(x0) and z0 = x0 (A = I, x_ref = 0)
@@ -1005,7 +1002,7 @@ static int read_status(diam_ctx* c, Status* st) {
 // from the target mean, where the spread is the larger of the states' largest
 // deviation and the proposal scale at the last update).  Cleared once reported.
 static int status_error(diam_ctx* c, int err) {
-  hipLaunchKernelGGL(k_clear_status, dim3(1), dim3(64), 0, c->stream, c->status, 1);
+  hipLaunchKernelGGL(k_clear_status, dim3(1), dim3(64), 0, c->stream, c->status);
   if (err & 1) return fail(DIAM_E_TARGET, "the target log density returned +inf");
   return fail(DIAM_E_TARGET, "a proposal left the range of the mixed-form target's scaled half operands");
 }

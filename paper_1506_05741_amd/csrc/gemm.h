@@ -1122,9 +1122,9 @@ __host__ __device__ inline bool t_gemm_ok(const void* A, long lda, int M, const 
 // refuses (odd leading dimensions); tiles and order as ever.
 // SPLIT: the sets take consecutive parts of the slices instead, in order (nk a
 // multiple of SETS).
-// GRP slices per stage of the ring and per barrier: for one tile per CU, where
+// GRP slices per stage of the ring and per barrier, for one tile per CU, where
 // a barrier and an LDS round trip per slice would stretch the chain of
-// products, and for GRP = SETS, whose slices are then free to overlap.
+// products; one set, and K whole stages.
 template <typename T, int BM, int BN, int WGM, int WGN, int ST, bool AKC, bool BKC, bool PAIR = false, int SETS = 1,
           int GRP = 1, bool SPLIT = false, bool NARROW = false>
 DEV void t_gemm(TFrag<T, BM, BN, WGM, WGN> (&fs)[SETS], const T* __restrict__ A, long lda, int M, const T* __restrict__ B,
@@ -1133,7 +1133,7 @@ DEV void t_gemm(TFrag<T, BM, BN, WGM, WGN> (&fs)[SETS], const T* __restrict__ A,
   constexpr int NW = WGM * WGN, TBK = tbk<T>(), Q = TBK / 4;
   constexpr int SA = BM * TBK, SS = (BM + BN) * TBK;
   constexpr int BLK_A = BM / 8, BLK_B = BN / 8, NBLK = BLK_A + BLK_B;
-  static_assert(GRP == 1 || SETS == 1 || (SETS == GRP && !SPLIT), "grouped slices: one set, or one per slice");
+  static_assert(GRP == 1 || (SETS == 1 && !SPLIT), "grouped slices: one set");
   static_assert(NBLK % NW == 0, "copy blocks must divide among the waves");
   constexpr int LPW = NBLK / NW, CPB = NARROW ? 4 : 1;  // copies per block
   static_assert(LPW * CPB * GRP * (ST - 2) < 64, "copies in flight that one wait can count");
@@ -1282,7 +1282,7 @@ DEV void t_gemm(TFrag<T, BM, BN, WGM, WGN> (&fs)[SETS], const T* __restrict__ A,
     // the ring slot refilled here was last read before this barrier
     if (kt + ST - 1 < nk) issue(kt + ST - 1, slot == 0 ? ST - 1 : slot - 1);
 #pragma unroll
-    for (int g = 0; g < GRP; ++g) compute(lds + (slot * GRP + g) * SS, SETS == GRP ? fs[SETS == GRP ? g : 0] : f);
+    for (int g = 0; g < GRP; ++g) compute(lds + (slot * GRP + g) * SS, f);
     slot = slot == ST - 1 ? 0 : slot + 1;
   };
   if (SPLIT) {
@@ -1316,26 +1316,21 @@ DEV void t_gemm(TFrag<T, BM, BN, WGM, WGN> (&fs)[SETS], const T* __restrict__ A,
     }
   }
   const int kv = (kend - kbeg) - nk * GRP * TBK;
-  if (SPLIT || kv <= 0) return;
+  if (SPLIT || GRP > 1 || kv <= 0) return;
+  // the last slice, cleared beyond kend
+  asm volatile("s_waitcnt lgkmcnt(0)\n s_barrier" ::: "memory");
+  offsets(kv);
+  issue_slice(nk, 0);
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  for (int e = threadIdx.x; e < BM * (TBK - kv); e += 64 * NW)
+    lds[t_index<T, BM, AKC>(e % BM, kv + e / BM)] = T(0);
+  for (int e = threadIdx.x; e < BN * (TBK - kv); e += 64 * NW)
+    lds[SA + t_index<T, BN, BKC>(e % BN, kv + e / BN)] = T(0);
+  __syncthreads();
 #pragma unroll
-  for (int g = 0; g < GRP; ++g) {  // the last slices, the partial one cleared beyond kend
-    const int kg = min(kv - g * TBK, TBK);
-    if (kg <= 0) break;
-    asm volatile("s_waitcnt lgkmcnt(0)\n s_barrier" ::: "memory");
-    offsets(kg);
-    issue_slice(nk * GRP + g, 0);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    for (int e = threadIdx.x; e < BM * (TBK - kg); e += 64 * NW)
-      lds[t_index<T, BM, AKC>(e % BM, kg + e / BM)] = T(0);
-    for (int e = threadIdx.x; e < BN * (TBK - kg); e += 64 * NW)
-      lds[SA + t_index<T, BN, BKC>(e % BN, kg + e / BN)] = T(0);
-    __syncthreads();
-#pragma unroll
-    for (int x = 0; x < SETS; ++x)
-      if ((GRP > 1 ? g % SETS : nk % SETS) == x) compute(lds, fs[x]);
-    if (GRP > 1) __syncthreads();
-  }
+  for (int x = 0; x < SETS; ++x)
+    if (nk % SETS == x) compute(lds, fs[x]);
 }
 
 template <typename T, int BM, int BN, int WGM, int WGN, int ST, bool AKC, bool BKC, bool PAIR = false>

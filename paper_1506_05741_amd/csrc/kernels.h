@@ -66,7 +66,7 @@ struct MlpBufs {
   float *Xs, *ts;                         // standardised training pairs (D x ntrain, ntrain)
   float *xb, *tb;                         // minibatch / evaluation input (D x nmax, nmax)
   float *a1, *h1, *a2, *h2, *ga1, *ga2;   // H x nmax
-  float *out, *gout, *loss;               // nmax, nmax, 1
+  float *out, *loss;                      // nmax, 1
   int* bidx;                              // nmax (minibatch indices)
 };
 size_t mlp_nparam(int D, int H);
