@@ -10,7 +10,8 @@ random orthogonal Q), chains started from exact draws with the global moments
 seeded at the target's (warm-start protocol), all random numbers drawn on the
 GPU by Philox.  Everything is resident in HBM before timing starts.
 
-Prints ONE JSON line.  ``--gpus N`` with N > 1 is refused: this build runs on
+Prints ONE JSON line, the figures beside the headline shortened; ``--details
+FILE`` writes all of them in full.  ``--gpus N`` with N > 1 is refused: this build runs on
 one GPU.
 """
 from __future__ import annotations
@@ -715,6 +716,35 @@ def cpu_baseline(tgt, args):
     }
 
 
+EXACT = {"value", "ms_per_step"}  # written as measured
+# explanations and breakdowns that stand in the details only
+DETAILS = {"note", "host", "work", "run", "surrogate", "library_reference", "seconds", "regions", "ess_per_step", "tol",
+           "method_bytes", "bytes_per_window", "stage2_accept_rate", "ess_per_exact_eval_gain_at_setting"}
+
+
+def short(v, key="", top=True):
+    """A document for the printed line: four significant digits, no
+    explanations, of traced moments the worst scores, of the experiments beside
+    the timed workload the rates.  (At full length the line passed 20 kB, and
+    readers that keep a run's last 10 kB, its log
+    included, lost its head.)"""
+    if isinstance(v, dict):
+        if key == "config":
+            return v
+        if "worst_abs_z" in v:
+            v = {k: v[k] for k in ("worst_abs_z", "worst_abs_z_chains", "windows") if k in v}
+        elif set(v) == {"ms_per_window", "regions"}:
+            return short(v["ms_per_window"])
+        elif key in ("diam", "am", "pcn", "rw"):
+            v = {k: v[k] for k in ("ess_per_s", "beta") if k in v}
+        return {k: short(x, k, top and k in ("stage_ms_per_window", "fp64")) for k, x in v.items()
+                if k not in DETAILS and k != "workload" and (top or k != "stage_ms_per_window")
+                and not (k == "ess" and isinstance(x, dict))}
+    if isinstance(v, (list, tuple)):
+        return [short(x, "", False) for x in v]
+    return float(f"{v:.4g}") if isinstance(v, float) and key not in EXACT else v
+
+
 def library_gemm_reference(d, P, torch):
     """The vendor GEMM (torch.matmul on hipBLASLt) at the target's shape, for
     context beside the roofline: one f16 product R V (d x d by d x P, FP32
@@ -784,6 +814,7 @@ def main():
     ap.add_argument("--no-d1024", action="store_true", help="skip the d = 1024 precision comparison")
     ap.add_argument("--d1024-only", action="store_true", help="run only the d = 1024 precision comparison")
     ap.add_argument("--c2-windows", dest="c2_windows", type=int, default=20)
+    ap.add_argument("--details", default=None, help="file for every figure at full length; the line has them shortened")
     args = ap.parse_args()
     if args.gpus != 1:
         print(f"bench.py runs on one GPU only; --gpus {args.gpus} is not supported by this build", file=sys.stderr)
@@ -941,7 +972,10 @@ def main():
     if not args.no_cpu:
         log("cpu baseline (oracle) ...")
         out["cpu_baseline"] = cpu_baseline(tgt, args)
-    print(json.dumps(out), flush=True)
+    if args.details:
+        with open(args.details, "w") as f:
+            json.dump(out, f, indent=1)
+    print(json.dumps(short(out), separators=(",", ":")), flush=True)
 
 
 if __name__ == "__main__":
