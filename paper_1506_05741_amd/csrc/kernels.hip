@@ -529,7 +529,7 @@ hipError_t tgt_gauss_h2(const uint16_t* R2, const uint16_t* V2, const double* rs
 // Which kernel, by the split kernel's workgroups w (16 rows x 16 chains, its
 // time in proportion to them beyond one per CU) and the number n of 64 x 64
 // tiles (the tile kernels take the time of one tile up to n = 256, twice that
-// where the tile is not whole).  us, with 6 of launch and clock around a kernel:
+// where the tile is not whole).  us between events, about 2 more than a kernel:
 //   d, P           n    w      FP64: split  32 x 32  64 x 32    FP32: split  tile kernel
 //   64, 1024       16   256          6.2    6.2      6.2              6.2    6.3
 //   64, 8192       128  2048         19.2   6.3      6.3              12.4   6.3
@@ -616,9 +616,13 @@ hipError_t tgt_gauss(Prec prec, const void* R, const void* V, int d, int P, doub
 // per CU measured best at middle sizes (d = 1024, 12800 columns: FP64 565 to
 // 306 us, FP32 276 to 179 us).  With many tiles FP64 runs at the chip's power
 // limit (about 1.95 GHz), where 128 x 64 tiles, which move less per product,
-// are ahead: d = 4096, 65536 columns 29.9 to 17.9 ms against 19.5 ms with 64 x
-// 64 (61 TFLOP/s; a large library product reaches 68 there), but 335 against
-// 314 us at d = 1024.  32 x 32 tiles where 64 x 64 would not give every CU two.
+// are ahead at large d: d = 4096, 65536 columns 29.9 to 17.4 ms against 17.7
+// with 64 x 64 (62 TFLOP/s; a large library product reaches 68 there), 32768
+// columns 8.7 against 9.2.  At 8192 tiles, where the rule changes over, the two
+// differ by -4 to +3 % (64 x 64 / 128 x 64, ms: d = 451 0.44 / 0.46, 1024 0.68 /
+// 0.69, 2048 1.21 / 1.23, 4096 2.26 / 2.19), at 4096 tiles by -7 to +7 % (d =
+// 512 0.22 / 0.23, 1024 0.35 / 0.37, 4096 1.18 / 1.10), below that 64 x 64 is
+// ahead by 10 % at d = 1024.  32 x 32 tiles where 64 x 64 would not give every CU two.
 template <typename T, int BJ, int BI, int ST, bool NARROW = false>
 DEV void trigemm_tile_t(const T* __restrict__ L, const T* __restrict__ W, T* __restrict__ Xi, int d, int ncols, double c,
                         int bi, int bj) {
@@ -1155,8 +1159,10 @@ static int syrk_tiles(int prec, int d, long K) {
   return n;
 }
 
-// K is split so that at least ~512 workgroups run; chunks are whole
-// multiples of 64 columns (keeps the bf16 vector loads 16-byte aligned).
+// K is split until about 512 workgroups run, but into parts of no less than
+// 2048 columns (so a small window's scatter runs on few of them: 20 at d = 100, K
+// = 3200); chunks are whole multiples of 64 columns (keeps the bf16 vector loads
+// 16-byte aligned).
 // FP32 chunks are whole multiples of the FP32 span FOLD_K: a window of at
 // most FOLD_K samples is then one chunk, accumulated exactly as the grouped
 // scatter of the batched form accumulates it (same FP32 sums, same FP64 fold).
@@ -1645,7 +1651,7 @@ __global__ __launch_bounds__(CHOL_DIAG_THREADS) void k_chol_diag(double* __restr
 }
 
 // Inverses of all (already factored) diagonal blocks of L, one workgroup per
-// block: the block is read once and inverted as in the factorisation (16 us,
+// block: the block is read once and inverted as in the factorisation (7 us,
 // a serial chain in code that is cold once a window; 20 to 34 us when each
 // lane of one wavefront substituted for a whole column).  Only for a factor
 // rounded since; the factorisation leaves the unrounded blocks' inverses.

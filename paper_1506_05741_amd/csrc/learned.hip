@@ -168,8 +168,8 @@ DEV float gelu_grad_f(float a) {
 // 256 outputs, K = 256 or 512, at the default minibatch), so a product is one
 // chain of K / 4 matrix instructions and the time to fill it.  MLP_T32: 32 x 32
 // tiles of the direct-to-LDS engine, one 16 x 16 block and one chain per
-// wavefront; MLP_CHAIN: the same with four slices of K per barrier and 128 KB
-// in flight, where no CU gets a second tile and K is whole stages (a forward
+// wavefront; MLP_CHAIN: the same with four slices of K per barrier and 96 KB
+// in flight (of a ring of 128), where no CU gets a second tile and K is whole stages (a forward
 // layer 6.6 us against 7.9); MLP_T64: its 64 x 64 tiles, where those give every
 // CU two; MLP_E: the element engine for unaligned operands.  All take k in the
 // same order, so the results are bitwise the same (64 x 64 tiles of the element

@@ -167,3 +167,49 @@ def test_merge_of_one_tile_and_many_splits():
         torch.cuda.synchronize()
     us = lambda name: min(e.device_time for e in p.events() if name in e.name)
     assert us("k_merge") < 1.6 * us("k_syrk")
+
+
+@pytest.mark.parametrize("proposal", ["diam", "am"])
+@pytest.mark.parametrize("d,P,cuts", [(64, 2048, (8, 1, 4, 2, 2, 3)), (101, 300, (2, 9, 1, 5)), (192, 256, (7, 3, 8))])
+def test_window_cut_into_calls_of_both_kinds(d, P, cuts, proposal):
+    """Calls that run in one launch and calls that launch per step take over
+    from each other: decisions, states, log densities and the window's mean
+    against the recursion in FP64 on the directions each call drew (t steps err
+    by at most t times a step's 4 u, log pi by 8 (d + n) u of its terms)."""
+    n, beta, U64 = sum(cuts), 0.25, 2.0 ** -53
+    g = torch.Generator("cuda").manual_seed(d)
+    rn = lambda *sh: torch.randn(*sh, generator=g, dtype=torch.float64, device="cuda")
+    R, mu = torch.eye(d, dtype=torch.float64, device="cuda") + rn(d, d) / np.sqrt(d), rn(d)
+    s = diam.Sampler(diam.make_config(d, P, n, "fp64", seed=1, beta=beta, proposal=proposal), mu, R.contiguous(),
+                     rn(P, d).contiguous())
+    rho = 1.0 if proposal == "am" else np.sqrt(1 - beta * beta)
+    x, z, xr = s.get_f64(diam.F_X, (P, d)).clone(), s.get_f64(diam.F_Z, (P, d)).clone(), s.get_f64(diam.F_XREF, (d,))
+    lp, tot, cnt = s.get_f64(diam.F_LOGP, (P,)).clone(), 0.0, torch.zeros(P, dtype=torch.int32, device="cuda")
+    taken, kinds = torch.zeros_like(cnt), set()
+    for m in cuts:
+        W = (0.4 / np.sqrt(d) * rn(m, P, d)).contiguous()
+        U = torch.rand(m, P, generator=g, dtype=torch.float64, device="cuda").clamp_(1e-12)
+        with profile(activities=[ProfilerActivity.CUDA]) as p:
+            s.step_batch(m, W, U, cnt)
+            torch.cuda.synchronize()
+        kinds.add(any("k_steps_resident" in e.name for e in p.events()))
+        Xi = s.get(diam.F_XI).view(torch.float64)[:m * P * d].reshape(m, P, d)
+        Acc = s.get(diam.F_ACC)[:m * P].reshape(m, P).bool()
+        mag = torch.maximum(x.abs(), z.abs()).amax() + Xi.abs().amax() * m + mu.abs().amax()
+        for t in range(m):
+            xp, zp = xr + rho * (x - xr) + Xi[t], rho * z + beta * W[t]
+            y = (xp - mu) @ R.T
+            lpp = -0.5 * (y * y).sum(1)
+            la = lpp - lp + (0.0 if proposal == "am" else 0.5 * ((zp * zp).sum(1) - (z * z).sum(1)))
+            assert torch.equal(Acc[t], torch.log(U[t]) < la)
+            x, z = torch.where(Acc[t][:, None], xp, x), torch.where(Acc[t][:, None], zp, z)
+            lp, tot = torch.where(Acc[t], lpp, lp), tot + x.sum(0)
+        taken += Acc.sum(0, dtype=torch.int32)
+        assert bool(((s.get_f64(diam.F_X, (P, d)) - x).abs() <= 4 * n * U64 * mag).all())
+        assert bool(((s.get_f64(diam.F_Z, (P, d)) - z).abs() <= 4 * n * U64 * mag).all())
+        ya = mu.abs() @ R.abs().T + x.abs() @ R.abs().T
+        assert bool(((s.get_f64(diam.F_LOGP, (P,)) - lp).abs() <= 8 * (d + n) * U64 * (ya * ya).sum(1)).all())
+    assert kinds == {True, False} and torch.equal(cnt, taken)
+    assert proposal == "diam" or 0 < int(taken.sum()) < n * P  # contracting proposals may all be accepted
+    s.merge_moments()
+    assert bool(((s.get_f64(diam.F_M, (d,)) - tot / (n * P)).abs() <= 4 * (n * P + n) * U64 * mag).all())
